@@ -205,7 +205,7 @@ __device__ __forceinline__ void moddown_cols_pass(uint64_t *lds, const NttJob &J
     pro.r64 = pc.r64;
     pro.r64_p = pc.r64_p;
     pro.one_p = pc.one_p;
-    ntt_cols_unit_pro<A, B, true>(lds, out, tw, pc, tile, pro);
+    ntt_cols_unit_pro<A, B, true>(lds, out, tw, pc, pc.q < kFpPrimeBound, tile, pro);
 }
 
 // One pass of a batched (I)NTT over the items of one ring degree 2^(A+B) (the
@@ -231,12 +231,13 @@ __device__ __forceinline__ void ntt_batched_unit(uint64_t *lds, const NttJob &J,
     const uint64_t *in = base_in + (size_t)poly * in_stride + ((size_t)li << LOGN);
     uint64_t *out = J.b.out + (size_t)poly * J.b.out_poly_stride + ((size_t)li << LOGN);
     const PrimeConst pc = J.pcs[g];
+    const bool fp = pc.q < kFpPrimeBound;
     const TwPair *tw = (COLS ? J.tw_all : J.tw_rows) + ((size_t)g << LOGN);
     if constexpr (PRO == 1) {
         // first pass of INTT(d2): d2 = a1 b1 of limb li
         const size_t poly1 = ((size_t)J.nl + li) << LOGN;
         const TensorPro pro{J.ct_a + poly1, J.ct_b + poly1, pc.q, pc.r64, pc.r64_p, pc.one_p};
-        ntt_rows_unit_pe<A, B, false>(lds, pro, tw, pc, tile, StoreEpi{out});
+        ntt_rows_unit_pe<A, B, false>(lds, pro, tw, pc, fp, tile, RawEpi{out});
     } else if constexpr (PRO == 2 || PRO == 3) {
         // first pass of NTT(conv): ModDown conversion of target li of polynomial
         // poly (2: 4 special primes; 3: any K <= 8).  One variant per kernel: both
@@ -247,11 +248,11 @@ __device__ __forceinline__ void ntt_batched_unit(uint64_t *lds, const NttJob &J,
         const size_t lo = ((size_t)poly * (J.nl + J.K) + li) << LOGN;
         const size_t oo = ((size_t)poly * J.nl + li) << LOGN;
         const ModdownFoldEpi epi{J.ip + lo, J.out + oo, J.pinv[2 * li], J.pinv[2 * li + 1], pc.q};
-        ntt_rows_unit_epi<A, B, true>(lds, in, tw, pc, tile, epi);
+        ntt_rows_unit_epi<A, B>(lds, in, tw, pc, fp, tile, epi);
     } else if constexpr (COLS) {
-        ntt_cols_unit<A, B, FWD>(lds, in, out, tw, pc, tile);
+        ntt_cols_unit<A, B, FWD>(lds, in, out, tw, pc, fp, tile);
     } else {
-        ntt_rows_unit<A, B, FWD>(lds, in, out, tw, pc, tile);
+        ntt_rows_unit<A, B, FWD>(lds, in, out, tw, pc, fp, tile);
     }
 }
 
@@ -266,7 +267,7 @@ __device__ __forceinline__ void ntt_batched_unit(uint64_t *lds, const NttJob &J,
 // ring degree, whose unit_begin values are absolute.  LOOP: workgroups walk
 // per_wg consecutive units; otherwise each takes one unit (per_wg == 1).
 template <int A, int B, bool FWD, bool FIRST, bool TAIL, int PRO, bool LOOP>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kNttWavesCols))) void ntt_batched_kernel(
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(PRO == 3 ? 3 : ntt_waves(FWD == FIRST ? A : B)))) void ntt_batched_kernel(
     const NttJob *__restrict__ jobs, uint32_t njobs, uint32_t unit0, uint32_t total, uint32_t per_wg) {
     constexpr bool COLS = FWD == FIRST;
     __shared__ uint64_t lds[COLS ? (1 << A) * (kTile / (1 << A) + 1) : (1 << B) * (kTile / (1 << B) + 1)];

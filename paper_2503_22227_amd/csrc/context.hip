@@ -63,6 +63,14 @@ uint64_t shoup_companion(uint64_t w, uint64_t q) { return (uint64_t)(((u128h)w <
 // companion of the NTT twiddles, scaled by 2^62 (shoup62_lazy)
 uint64_t shoup_companion62(uint64_t w, uint64_t q) { return (uint64_t)(((u128h)w << 62) / q); }
 
+// Rewrite a prime's N twiddle pairs as N doubles in [-q/2, q/2], at the start of
+// the same memory.
+void twiddles_to_fp(rf::TwPair *tw, uint32_t n, uint64_t q) {
+    std::vector<double> d(n);
+    for (uint32_t k = 0; k < n; ++k) d[k] = tw[k].w > q / 2 ? -(double)(q - tw[k].w) : (double)tw[k].w;
+    std::memcpy((void *)tw, d.data(), n * sizeof(double));
+}
+
 uint32_t bitrev_h(uint32_t x, int bits) {
     uint32_t r = 0;
     for (int i = 0; i < bits; ++i) r |= ((x >> i) & 1u) << (bits - 1 - i);
@@ -178,6 +186,7 @@ extern "C" int rf_ctx_create(const rf_params *p, int device, rf_ctx **out) {
                 delete c;
                 return fail(RF_EINVAL, "primes must be distinct");
             }
+        if (q < kFpPrimeBound) c->fp_mask.m[g >> 6] |= 1ull << (g & 63);
         uint64_t psi_max = root_2n(q, nmax);
         c->psi.push_back(powmod_h(psi_max, nmax / N, q));
     }
@@ -223,6 +232,8 @@ extern "C" int rf_ctx_create(const rf_params *p, int device, rf_ctx **out) {
         pc[g].r64 = (uint64_t)(((u128h)1 << 64) % q);
         pc[g].r64_p = shoup_companion(pc[g].r64, q);
         pc[g].one_p = shoup_companion(1, q);
+        pc[g].qd = (double)q;
+        pc[g].qinv = 1.0 / (double)q;
         uint64_t psi = c->psi[g], psi_inv = inv_h(psi, q);
         pw[0] = pwi[0] = 1;
         for (uint32_t e = 1; e < N; ++e) {
@@ -250,6 +261,9 @@ extern "C" int rf_ctx_create(const rf_params *p, int device, rf_ctx **out) {
                     }
         }
         uint64_t wl = mulmod_h(twi[(size_t)g * N + 1].w, ninv, q);
+        if (q < kFpPrimeBound)
+            for (std::vector<TwPair> *t : {&twf, &twi, &twrf, &twri})
+                if (!t->empty()) twiddles_to_fp(t->data() + (size_t)g * N, N, q);
         pc[g].wlast = wl;
         pc[g].wlast_p = shoup_companion(wl, q);
         pc[g].tmod = pc[g].tmod_p = pc[g].tinv = pc[g].tinv_p = 0;

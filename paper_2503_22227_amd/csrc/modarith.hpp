@@ -12,7 +12,11 @@
 //     by two Shoup products into [0, 4q);
 //   * Harvey's lazy butterflies keep NTT values in [0, 4q), so every prime must
 //     be below 2^62; the library accepts primes below 2^60, which the split
-//     multiply-accumulate below relies on.
+//     multiply-accumulate below relies on;
+//   * primes below 2^46 are computed in FP64 instead (FpMod): the vector FP64
+//     unit issues a fused multiply-add at the rate of one 32-bit multiply, and a
+//     modular product of exact integers held in doubles takes 6 operations
+//     against about 15.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -210,5 +214,51 @@ __device__ __forceinline__ uint64_t addmod(uint64_t a, uint64_t b, uint64_t q) {
 __device__ __forceinline__ uint64_t submod(uint64_t a, uint64_t b, uint64_t q) {
     return a >= b ? a - b : a + q - b;
 }
+
+// Residues of a prime below this bound are transformed in FP64 (FpMod).
+constexpr uint64_t kFpPrimeBound = 1ull << 46;
+
+// Exact modular arithmetic on integers held in doubles, for primes q < 2^46.
+//
+// mul(x, w) = x w - c q with c = rint(RN(x w) / q): h = RN(x w) and
+// l = x w - h are exact (l by the fused multiply-add), h - c q is an integer
+// below 2^53 and so exact, and so is its sum with l: the result is the exact
+// integer x w - c q.  For integers |x| <= 2^51 and |w| <= q / 2 the rounding of
+// h and of 1 / q moves the quotient by at most |x| 2^-53 <= 1/4, so |mul| <=
+// 0.75 q; |w| < q with |x| < 2^50 gives the same.  c is rounded to an integer
+// by adding and subtracting 1.5 2^52 (|c| < 2^51): one full-rate fma and one add.
+// Every bound is on |x| itself, so an input need not be reduced mod q first.
+struct FpMod {
+    double q, qinv;  // qinv = RN(1 / q)
+    static constexpr double kMagic = 6755399441055744.0;  // 1.5 * 2^52
+
+    // |r| <= 0.5 q (1 + 2^-5) for |x| < 2^51
+    __device__ __forceinline__ double red(double x) const {
+#pragma clang fp contract(off)
+        const double c = __builtin_fma(x, qinv, kMagic) - kMagic;
+        return __builtin_fma(-c, q, x);
+    }
+    __device__ __forceinline__ double mul(double x, double w) const {
+#pragma clang fp contract(off)
+        const double h = x * w;
+        const double l = __builtin_fma(x, w, -h);
+        const double c = __builtin_fma(h, qinv, kMagic) - kMagic;
+        return __builtin_fma(-c, q, h) + l;
+    }
+    // an integer |x| < q as a residue in [0, q)
+    __device__ __forceinline__ uint64_t canon(double x) const {
+        const double y = x + (x < 0.0 ? q : 0.0) + 4503599627370496.0;  // [0, q) + 2^52
+        return (uint64_t)__double_as_longlong(y) & 0xfffffffffffffull;
+    }
+    // a constant w in [0, q) as its representative in [-q/2, q/2]
+    __device__ __forceinline__ double centre(uint64_t w) const {
+        const double d = from_u52(w);
+        return d + d > q ? d - q : d;
+    }
+    // an integer below 2^52 (exact)
+    __device__ __forceinline__ static double from_u52(uint64_t x) {
+        return __longlong_as_double((long long)(x | 0x4330000000000000ull)) - 4503599627370496.0;
+    }
+};
 
 }  // namespace rf

@@ -30,24 +30,24 @@ __device__ __forceinline__ LimbView limb_view(const NttBatch &b, int log_n, uint
     return v;
 }
 
-template <int A, int B, bool FWD>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kNttWavesCols))) void ntt_cols_kernel(NttBatch b, const TwPair *__restrict__ tw_all,
+template <int A, int B, bool FWD, typename Fp>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ntt_waves(A)))) void ntt_cols_kernel(NttBatch b, Fp fpm, const TwPair *__restrict__ tw_all,
                                                             const PrimeConst *__restrict__ pcs) {
     __shared__ uint64_t lds[(1 << A) * (kTile / (1 << A) + 1)];
     const uint32_t tile = blockIdx.x;
     const LimbView v = limb_view(b, A + B, blockIdx.y);
     const PrimeConst pc = pcs[v.g];
-    ntt_cols_unit<A, B, FWD>(lds, v.in, v.out, tw_all + ((size_t)v.g << (A + B)), pc, tile);
+    ntt_cols_unit<A, B, FWD>(lds, v.in, v.out, tw_all + ((size_t)v.g << (A + B)), pc, fpm.has(v.g), tile);
 }
 
-template <int A, int B, bool FWD>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kNttWavesRows))) void ntt_rows_kernel(NttBatch b, const TwPair *__restrict__ tw_all,
+template <int A, int B, bool FWD, typename Fp>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ntt_waves(B)))) void ntt_rows_kernel(NttBatch b, Fp fpm, const TwPair *__restrict__ tw_all,
                                                             const PrimeConst *__restrict__ pcs) {
     __shared__ uint64_t lds[(1 << B) * (kTile / (1 << B) + 1)];
     const uint32_t tile = blockIdx.x;
     const LimbView v = limb_view(b, A + B, blockIdx.y);
     const PrimeConst pc = pcs[v.g];
-    ntt_rows_unit<A, B, FWD>(lds, v.in, v.out, tw_all + ((size_t)v.g << (A + B)), pc, tile);
+    ntt_rows_unit<A, B, FWD>(lds, v.in, v.out, tw_all + ((size_t)v.g << (A + B)), pc, fpm.has(v.g), tile);
 }
 
 // Prologue of the first pass of NTT(conv): the ModDown conversion of target i
@@ -88,6 +88,7 @@ __device__ __forceinline__ LiftPro<KEEP_T> lift_pro(const uint64_t *last, const 
     pro.ql_half = pl.q >> 1;
     pro.tinv = pl.tinv;
     pro.tinv_p = pl.tinv_p;
+    pro.qld = pl.qd;
     pro.q = pc.q;
     pro.one_p = pc.one_p;
     pro.corr = tab[((size_t)l * L + i) * 3 + 2];
@@ -98,9 +99,9 @@ __device__ __forceinline__ LiftPro<KEEP_T> lift_pro(const uint64_t *last, const 
 
 // First forward pass of NTT(conv) with the ModDown base conversion as its
 // prologue: limb (c, i) of conv [2][nl][N] from the K P-limbs of ip[c].
-template <int A, int B, int KP>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(KP == 8 ? kNttWavesCols : kNttWavesFused))) void ntt_cols_moddown_kernel(
-    const uint64_t *ip, uint64_t *conv, const TwPair *__restrict__ tw_all, const PrimeConst *__restrict__ pcs,
+template <int A, int B, int KP, typename Fp>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(KP == 8 ? 3 : kNttWavesFused))) void ntt_cols_moddown_kernel(
+    Fp fpm, const uint64_t *ip, uint64_t *conv, const TwPair *__restrict__ tw_all, const PrimeConst *__restrict__ pcs,
     const uint64_t *__restrict__ cross, const uint64_t *__restrict__ negp, uint32_t nl, uint32_t L, uint32_t K) {
     __shared__ uint64_t lds[(1 << A) * (kTile / (1 << A) + 1)];
     constexpr int LOGN = A + B;
@@ -108,15 +109,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(KP == 
     const uint32_t c = blockIdx.y & 1, i = blockIdx.y >> 1;  // polynomials interleaved
     const PrimeConst pc = pcs[i];
     const ModdownPro<KP> pro = moddown_pro<KP, LOGN>(ip, pcs, pc, cross, negp, c, i, nl, L, K);
-    ntt_cols_unit_pro<A, B, true, B == 8>(lds, conv + (((size_t)c * nl + i) << LOGN), tw_all + ((size_t)i << LOGN), pc,
-                                  tile, pro);
+    ntt_cols_unit_pro<A, B, true>(lds, conv + (((size_t)c * nl + i) << LOGN), tw_all + ((size_t)i << LOGN), pc,
+                                  fpm.has(i), tile, pro);
 }
 
 // First forward pass of NTT(lift) with the rescale lift as its prologue: limb
 // (c, i) of lift [2][l][N], l = nl - 1, from the last limb last[c].
-template <int A, int B, bool KEEP_T>
+template <int A, int B, bool KEEP_T, typename Fp>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kNttWavesFused))) void ntt_cols_lift_kernel(
-    const uint64_t *last, uint64_t *lift, const TwPair *__restrict__ tw_all, const PrimeConst *__restrict__ pcs,
+    Fp fpm, const uint64_t *last, uint64_t *lift, const TwPair *__restrict__ tw_all, const PrimeConst *__restrict__ pcs,
     const uint64_t *__restrict__ tab, uint32_t nl, uint32_t L) {
     __shared__ uint64_t lds[(1 << A) * (kTile / (1 << A) + 1)];
     constexpr int LOGN = A + B;
@@ -125,15 +126,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kNttWa
     const uint32_t c = blockIdx.y & 1, i = blockIdx.y >> 1;  // polynomials interleaved
     const PrimeConst pc = pcs[i];
     const LiftPro<KEEP_T> pro = lift_pro<KEEP_T, LOGN>(last, pcs, pc, tab, c, i, nl, L);
-    ntt_cols_unit_pro<A, B, true, B == 8>(lds, lift + (((size_t)c * l + i) << LOGN), tw_all + ((size_t)i << LOGN), pc,
-                                  tile, pro);
+    ntt_cols_unit_pro<A, B, true>(lds, lift + (((size_t)c * l + i) << LOGN), tw_all + ((size_t)i << LOGN), pc,
+                                  fpm.has(i), tile, pro);
 }
 
 // Last forward pass of NTT(conv) with the ModDown tail: limb (c, i) of conv
 // [2][nl][N] -> out[c][i] = (ip[c][i] - NTT(conv)[c][i]) P^-1 (+ add_c[i]).
-template <int A, int B>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(B == 8 ? kNttWavesFused : kNttWavesCols))) void ntt_rows_moddown_kernel(
-    const uint64_t *conv, const TwPair *__restrict__ tw_all, const PrimeConst *__restrict__ pcs, const uint64_t *ip,
+template <int A, int B, typename Fp>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ntt_waves(B)))) void ntt_rows_moddown_kernel(
+    Fp fpm, const uint64_t *conv, const TwPair *__restrict__ tw_all, const PrimeConst *__restrict__ pcs, const uint64_t *ip,
     uint64_t *out, const uint64_t *__restrict__ pinv, uint32_t nl, uint32_t K) {
     __shared__ uint64_t lds[(1 << B) * (kTile / (1 << B) + 1)];
     constexpr int LOGN = A + B;
@@ -142,15 +143,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(B == 8
     const PrimeConst pc = pcs[i];
     const ModdownFoldEpi epi{ip + (((size_t)c * (nl + K) + i) << LOGN), out + (((size_t)c * nl + i) << LOGN),
                              pinv[2 * i], pinv[2 * i + 1], pc.q};
-    ntt_rows_unit_epi<A, B, true, B == 8>(lds, conv + (((size_t)c * nl + i) << LOGN), tw_all + ((size_t)i << LOGN), pc,
-                                  tile, epi);
+    ntt_rows_unit_epi<A, B>(lds, conv + (((size_t)c * nl + i) << LOGN), tw_all + ((size_t)i << LOGN), pc,
+                                  fpm.has(i), tile, epi);
 }
 
 // First inverse pass of INTT(d2) with d2 = a1 b1 as its prologue: limb i of a, b
 // ([2][nl][N], NTT domain); the row pass goes to dc [nl][N].
-template <int A, int B>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kNttWavesRows))) void ntt_inv_rows_tensor_kernel(
-    const uint64_t *a, const uint64_t *b, uint64_t *dc, const TwPair *__restrict__ tw_all,
+template <int A, int B, typename Fp>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ntt_waves(B)))) void ntt_inv_rows_tensor_kernel(
+    Fp fpm, const uint64_t *a, const uint64_t *b, uint64_t *dc, const TwPair *__restrict__ tw_all,
     const PrimeConst *__restrict__ pcs, uint32_t nl) {
     __shared__ uint64_t lds[(1 << B) * (kTile / (1 << B) + 1)];
     constexpr int LOGN = A + B;
@@ -158,14 +159,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kNttWa
     const PrimeConst pc = pcs[i];
     const size_t li = (size_t)i << LOGN, poly = (size_t)nl << LOGN;
     const TensorPro pro{a + poly + li, b + poly + li, pc.q, pc.r64, pc.r64_p, pc.one_p};
-    ntt_rows_unit_pe<A, B, false>(lds, pro, tw_all + li, pc, tile, StoreEpi{dc + li});
+    ntt_rows_unit_pe<A, B, false>(lds, pro, tw_all + li, pc, fpm.has(i), tile, RawEpi{dc + li});
 }
 
 // First inverse pass of INTT(sigma_g(a1)) with the automorphism as its
 // prologue: limb i of a1 ([nl][N], NTT domain) permuted, row pass into dc.
-template <int A, int B>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kNttWavesRows))) void ntt_inv_rows_gather_kernel(
-    const uint64_t *a1, uint64_t *dc, uint32_t galois, const TwPair *__restrict__ tw_all,
+template <int A, int B, typename Fp>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ntt_waves(B)))) void ntt_inv_rows_gather_kernel(
+    Fp fpm, const uint64_t *a1, uint64_t *dc, uint32_t galois, const TwPair *__restrict__ tw_all,
     const PrimeConst *__restrict__ pcs) {
     __shared__ uint64_t lds[(1 << B) * (kTile / (1 << B) + 1)];
     constexpr int LOGN = A + B;
@@ -173,14 +174,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kNttWa
     const PrimeConst pc = pcs[i];
     const size_t li = (size_t)i << LOGN;
     const GatherPro pro{a1 + li, galois, (uint32_t)LOGN};
-    ntt_rows_unit_pe<A, B, false>(lds, pro, tw_all + li, pc, tile, StoreEpi{dc + li});
+    ntt_rows_unit_pe<A, B, false>(lds, pro, tw_all + li, pc, fpm.has(i), tile, RawEpi{dc + li});
 }
 
 // Last forward pass of NTT(lift) with the rescale tail: limb (c, i) of lift
 // [2][l][N] -> out[c][i] = (in[c][i] - NTT(lift)[c][i]) q_l^-1, l = nl - 1.
-template <int A, int B>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(B == 8 ? kNttWavesFused : kNttWavesCols))) void ntt_rows_rescale_kernel(
-    const uint64_t *lift, const TwPair *__restrict__ tw_all, const PrimeConst *__restrict__ pcs, const uint64_t *in,
+template <int A, int B, typename Fp>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ntt_waves(B)))) void ntt_rows_rescale_kernel(
+    Fp fpm, const uint64_t *lift, const TwPair *__restrict__ tw_all, const PrimeConst *__restrict__ pcs, const uint64_t *in,
     uint64_t *out, const uint64_t *__restrict__ tab, uint32_t nl, uint32_t L) {
     __shared__ uint64_t lds[(1 << B) * (kTile / (1 << B) + 1)];
     constexpr int LOGN = A + B;
@@ -190,35 +191,46 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(B == 8
     const PrimeConst pc = pcs[i];
     const uint64_t *t = tab + ((size_t)l * L + i) * 3;
     RescaleTailEpi epi{in + (((size_t)c * nl + i) << LOGN), out + (((size_t)c * l + i) << LOGN), t[0], t[1], pc.q};
-    ntt_rows_unit_epi<A, B, true, B == 8>(lds, lift + (((size_t)c * l + i) << LOGN), tw_all + ((size_t)i << LOGN), pc,
-                                  tile, epi);
+    ntt_rows_unit_epi<A, B>(lds, lift + (((size_t)c * l + i) << LOGN), tw_all + ((size_t)i << LOGN), pc,
+                                  fpm.has(i), tile, epi);
 }
 
 // Whole limb in one workgroup (N = 2^LOGN <= 4096).
-template <int LOGN, bool FWD>
-__global__ __launch_bounds__(kThreads) void ntt_single_kernel(NttBatch b, const TwPair *__restrict__ tw_all,
-                                                              const PrimeConst *__restrict__ pcs) {
+template <typename Ar, int LOGN, bool FWD>
+__device__ __forceinline__ void ntt_single(uint64_t *lds, const LimbView &v, const TwPair *__restrict__ tw,
+                                           const Ar &ar) {
     constexpr int S = 1 << LOGN;
     constexpr int NT = S / kElems;
-    __shared__ uint64_t lds[S];
+    if (threadIdx.x < NT) {
+        const LoadPro pro{v.in};
+#pragma unroll
+        for (int r = 0; r < kElems; ++r) lds[threadIdx.x + r * NT] = Ar::bits(pass_in(pro, threadIdx.x + r * NT, ar));
+    }
+    __syncthreads();
+    ntt_rounds<Ar, LOGN, FWD, !FWD>(lds, 1, 0, threadIdx.x < NT ? threadIdx.x : 0, 1u, twiddles<Ar>(tw), ar);
+    if (threadIdx.x < NT) {
+#pragma unroll
+        for (int r = 0; r < kElems; ++r) {
+            typename Ar::V x = Ar::raw(lds[threadIdx.x + r * NT]);
+            if constexpr (!FWD) {
+                v.out[threadIdx.x + r * NT] = ar.canon_last(x);
+            } else {
+                if constexpr (!Ar::kFp) x = csub(csub(x, ar.q2), ar.q);
+                pass_out(StoreEpi{v.out}, threadIdx.x + r * NT, x, ar);
+            }
+        }
+    }
+}
+
+template <int LOGN, bool FWD, typename Fp>
+__global__ __launch_bounds__(kThreads) void ntt_single_kernel(NttBatch b, Fp fpm, const TwPair *__restrict__ tw_all,
+                                                              const PrimeConst *__restrict__ pcs) {
+    __shared__ uint64_t lds[1 << LOGN];
     const LimbView v = limb_view(b, LOGN, blockIdx.y);
     const PrimeConst pc = pcs[v.g];
     const TwPair *tw = tw_all + ((size_t)v.g << LOGN);
-    if (threadIdx.x < NT) {
-#pragma unroll
-        for (int r = 0; r < kElems; ++r) lds[threadIdx.x + r * NT] = v.in[threadIdx.x + r * NT];
-    }
-    __syncthreads();
-    ntt_rounds<LOGN, FWD, !FWD>(lds, 1, 0, threadIdx.x < NT ? threadIdx.x : 0, 1u, tw, pc);
-    if (threadIdx.x < NT) {
-        const uint64_t q2 = 2 * pc.q;
-#pragma unroll
-        for (int r = 0; r < kElems; ++r) {
-            uint64_t x = lds[threadIdx.x + r * NT];
-            x = FWD ? csub(csub(x, q2), pc.q) : csub(x, pc.q);
-            v.out[threadIdx.x + r * NT] = x;
-        }
-    }
+    if (fpm.has(v.g)) ntt_single<ArFp, LOGN, FWD>(lds, v, tw, ArFp(pc));
+    else ntt_single<ArInt, LOGN, FWD>(lds, v, tw, ArInt(pc));
 }
 
 // A pass of a launch with few limbs (ntt_cols_small / ntt_rows_small): one
@@ -238,16 +250,16 @@ __device__ __forceinline__ int xcd_grouped_tile() {
     return ((r / G) * 8 + x) * G + r % G;
 }
 
-template <int A, int B, bool FWD, bool COLS, int TILE, int E>
-__global__ __launch_bounds__(TILE / E) void ntt_small_kernel(NttBatch b, const TwPair *__restrict__ tw_all,
+template <int A, int B, bool FWD, bool COLS, int TILE, int E, typename Fp>
+__global__ __launch_bounds__(TILE / E) void ntt_small_kernel(NttBatch b, Fp fpm, const TwPair *__restrict__ tw_all,
                                                              const PrimeConst *__restrict__ pcs) {
     constexpr int S = COLS ? (1 << A) : (1 << B);
     __shared__ uint64_t lds[S * (TILE / S + 1)];
     const LimbView v = limb_view(b, A + B, blockIdx.y);
     const PrimeConst pc = pcs[v.g];
     const TwPair *tw = tw_all + ((size_t)v.g << (A + B));
-    if constexpr (COLS) ntt_cols_small<A, B, FWD, TILE, E>(lds, v.in, v.out, tw, pc, xcd_grouped_tile<TILE, A>());
-    else ntt_rows_small<A, B, FWD, TILE, E>(lds, v.in, v.out, tw, pc, blockIdx.x);
+    if constexpr (COLS) ntt_cols_small<A, B, FWD, TILE, E>(lds, v.in, v.out, tw, pc, fpm.has(v.g), xcd_grouped_tile<TILE, A>());
+    else ntt_rows_small<A, B, FWD, TILE, E>(lds, v.in, v.out, tw, pc, fpm.has(v.g), blockIdx.x);
 }
 
 // Default residues per thread of the few-limb passes (4 measured faster than 8:
@@ -258,9 +270,9 @@ constexpr int kSmallE = 4;
 // The passes of the fused ModDown, rescale and first-INTT launches on small
 // tiles (the same prologues and epilogues as their 4096-tile kernels; natural
 // twiddle tables, strict butterflies in both passes of a limb).
-template <int A, int B, int TILE, int KP>
+template <int A, int B, int TILE, int KP, typename Fp>
 __global__ __launch_bounds__(TILE / kSmallE) void ntt_small_cols_moddown_kernel(
-    const uint64_t *ip, uint64_t *conv, const TwPair *__restrict__ tw_all, const PrimeConst *__restrict__ pcs,
+    Fp fpm, const uint64_t *ip, uint64_t *conv, const TwPair *__restrict__ tw_all, const PrimeConst *__restrict__ pcs,
     const uint64_t *__restrict__ cross, const uint64_t *__restrict__ negp, uint32_t nl, uint32_t L, uint32_t K) {
     __shared__ uint64_t lds[(1 << A) * (TILE / (1 << A) + 1)];
     constexpr int LOGN = A + B;
@@ -268,12 +280,12 @@ __global__ __launch_bounds__(TILE / kSmallE) void ntt_small_cols_moddown_kernel(
     const PrimeConst pc = pcs[i];
     const ModdownPro<KP> pro = moddown_pro<KP, LOGN>(ip, pcs, pc, cross, negp, c, i, nl, L, K);
     ntt_cols_small_pro<A, B, true, TILE, kSmallE>(lds, pro, conv + (((size_t)c * nl + i) << LOGN),
-                                                  tw_all + ((size_t)i << LOGN), pc, xcd_grouped_tile<TILE, A>());
+                                                  tw_all + ((size_t)i << LOGN), pc, fpm.has(i), xcd_grouped_tile<TILE, A>());
 }
 
-template <int A, int B, int TILE>
+template <int A, int B, int TILE, typename Fp>
 __global__ __launch_bounds__(TILE / kSmallE) void ntt_small_rows_moddown_kernel(
-    const uint64_t *conv, const TwPair *__restrict__ tw_all, const PrimeConst *__restrict__ pcs, const uint64_t *ip,
+    Fp fpm, const uint64_t *conv, const TwPair *__restrict__ tw_all, const PrimeConst *__restrict__ pcs, const uint64_t *ip,
     uint64_t *out, const uint64_t *__restrict__ pinv, uint32_t nl, uint32_t K) {
     __shared__ uint64_t lds[(1 << B) * (TILE / (1 << B) + 1)];
     constexpr int LOGN = A + B;
@@ -281,13 +293,13 @@ __global__ __launch_bounds__(TILE / kSmallE) void ntt_small_rows_moddown_kernel(
     const PrimeConst pc = pcs[i];
     const ModdownFoldEpi epi{ip + (((size_t)c * (nl + K) + i) << LOGN), out + (((size_t)c * nl + i) << LOGN),
                              pinv[2 * i], pinv[2 * i + 1], pc.q};
-    ntt_rows_small_pe<A, B, true, TILE, kSmallE>(lds, LoadPro{conv + (((size_t)c * nl + i) << LOGN)},
-                                                 tw_all + ((size_t)i << LOGN), pc, blockIdx.x, epi);
+    ntt_rows_small_pe<A, B, true, TILE, kSmallE>(lds, RawPro{conv + (((size_t)c * nl + i) << LOGN)},
+                                                 tw_all + ((size_t)i << LOGN), pc, fpm.has(i), blockIdx.x, epi);
 }
 
-template <int A, int B, int TILE, bool KEEP_T>
+template <int A, int B, int TILE, bool KEEP_T, typename Fp>
 __global__ __launch_bounds__(TILE / kSmallE) void ntt_small_cols_lift_kernel(
-    const uint64_t *last, uint64_t *lift, const TwPair *__restrict__ tw_all, const PrimeConst *__restrict__ pcs,
+    Fp fpm, const uint64_t *last, uint64_t *lift, const TwPair *__restrict__ tw_all, const PrimeConst *__restrict__ pcs,
     const uint64_t *__restrict__ tab, uint32_t nl, uint32_t L) {
     __shared__ uint64_t lds[(1 << A) * (TILE / (1 << A) + 1)];
     constexpr int LOGN = A + B;
@@ -296,12 +308,12 @@ __global__ __launch_bounds__(TILE / kSmallE) void ntt_small_cols_lift_kernel(
     const PrimeConst pc = pcs[i];
     const LiftPro<KEEP_T> pro = lift_pro<KEEP_T, LOGN>(last, pcs, pc, tab, c, i, nl, L);
     ntt_cols_small_pro<A, B, true, TILE, kSmallE>(lds, pro, lift + (((size_t)c * l + i) << LOGN),
-                                                  tw_all + ((size_t)i << LOGN), pc, xcd_grouped_tile<TILE, A>());
+                                                  tw_all + ((size_t)i << LOGN), pc, fpm.has(i), xcd_grouped_tile<TILE, A>());
 }
 
-template <int A, int B, int TILE>
+template <int A, int B, int TILE, typename Fp>
 __global__ __launch_bounds__(TILE / kSmallE) void ntt_small_rows_rescale_kernel(
-    const uint64_t *lift, const TwPair *__restrict__ tw_all, const PrimeConst *__restrict__ pcs, const uint64_t *in,
+    Fp fpm, const uint64_t *lift, const TwPair *__restrict__ tw_all, const PrimeConst *__restrict__ pcs, const uint64_t *in,
     uint64_t *out, const uint64_t *__restrict__ tab, uint32_t nl, uint32_t L) {
     __shared__ uint64_t lds[(1 << B) * (TILE / (1 << B) + 1)];
     constexpr int LOGN = A + B;
@@ -311,15 +323,15 @@ __global__ __launch_bounds__(TILE / kSmallE) void ntt_small_rows_rescale_kernel(
     const uint64_t *t = tab + ((size_t)l * L + i) * 3;
     const RescaleTailEpi epi{in + (((size_t)c * nl + i) << LOGN), out + (((size_t)c * l + i) << LOGN), t[0], t[1],
                              pc.q};
-    ntt_rows_small_pe<A, B, true, TILE, kSmallE>(lds, LoadPro{lift + (((size_t)c * l + i) << LOGN)},
-                                                 tw_all + ((size_t)i << LOGN), pc, blockIdx.x, epi);
+    ntt_rows_small_pe<A, B, true, TILE, kSmallE>(lds, RawPro{lift + (((size_t)c * l + i) << LOGN)},
+                                                 tw_all + ((size_t)i << LOGN), pc, fpm.has(i), blockIdx.x, epi);
 }
 
 // First pass of INTT(d2) (galois == 0: d2 = a1 b1 of a, b) or of INTT(sigma_g(a1))
 // on small tiles, into dc [nl][N].
-template <int A, int B, int TILE>
+template <int A, int B, int TILE, typename Fp>
 __global__ __launch_bounds__(TILE / kSmallE) void ntt_small_inv_rows_first_kernel(
-    const uint64_t *a, const uint64_t *b, uint64_t *dc, uint32_t galois, const TwPair *__restrict__ tw_all,
+    Fp fpm, const uint64_t *a, const uint64_t *b, uint64_t *dc, uint32_t galois, const TwPair *__restrict__ tw_all,
     const PrimeConst *__restrict__ pcs, uint32_t nl) {
     __shared__ uint64_t lds[(1 << B) * (TILE / (1 << B) + 1)];
     constexpr int LOGN = A + B;
@@ -328,16 +340,17 @@ __global__ __launch_bounds__(TILE / kSmallE) void ntt_small_inv_rows_first_kerne
     const size_t li = (size_t)i << LOGN, poly = (size_t)nl << LOGN;
     if (galois) {
         const GatherPro pro{a + poly + li, galois, (uint32_t)LOGN};
-        ntt_rows_small_pe<A, B, false, TILE, kSmallE>(lds, pro, tw_all + li, pc, blockIdx.x, StoreEpi{dc + li});
+        ntt_rows_small_pe<A, B, false, TILE, kSmallE>(lds, pro, tw_all + li, pc, fpm.has(i), blockIdx.x, RawEpi{dc + li});
     } else {
         const TensorPro pro{a + poly + li, b + poly + li, pc.q, pc.r64, pc.r64_p, pc.one_p};
-        ntt_rows_small_pe<A, B, false, TILE, kSmallE>(lds, pro, tw_all + li, pc, blockIdx.x, StoreEpi{dc + li});
+        ntt_rows_small_pe<A, B, false, TILE, kSmallE>(lds, pro, tw_all + li, pc, fpm.has(i), blockIdx.x, RawEpi{dc + li});
     }
 }
 
 
-template <int A, int B, int TILE, int E>
-static void launch_two_pass_small(const rf_ctx *c, const NttBatch &b, bool forward, hipStream_t s,
+// Launchers: fpm is the context's FpMask, or NoFp.
+template <int A, int B, int TILE, int E, typename Fp>
+static void launch_two_pass_small(const rf_ctx *c, Fp fpm, const NttBatch &b, bool forward, hipStream_t s,
                                   const PrimeConst *pcs) {
     const uint32_t limbs = b.per_poly * b.n_polys;
     const dim3 grid((1u << (A + B)) / TILE, limbs), block(TILE / E);
@@ -347,34 +360,34 @@ static void launch_two_pass_small(const rf_ctx *c, const NttBatch &b, bool forwa
     if (forward) {
         {
             ProfScope p("ntt_fwd_cols_small", s);
-            hipLaunchKernelGGL((ntt_small_kernel<A, B, true, true, TILE, E>), grid, block, 0, s, b, c->d_tw_fwd, pcs);
+            hipLaunchKernelGGL((ntt_small_kernel<A, B, true, true, TILE, E>), grid, block, 0, s, b, fpm, c->d_tw_fwd, pcs);
         }
         ProfScope p("ntt_fwd_rows_small", s);
-        hipLaunchKernelGGL((ntt_small_kernel<A, B, true, false, TILE, E>), grid, block, 0, s, b2, c->d_tw_fwd, pcs);
+        hipLaunchKernelGGL((ntt_small_kernel<A, B, true, false, TILE, E>), grid, block, 0, s, b2, fpm, c->d_tw_fwd, pcs);
     } else {
         {
             ProfScope p("ntt_inv_rows_small", s);
-            hipLaunchKernelGGL((ntt_small_kernel<A, B, false, false, TILE, E>), grid, block, 0, s, b, c->d_tw_inv,
+            hipLaunchKernelGGL((ntt_small_kernel<A, B, false, false, TILE, E>), grid, block, 0, s, b, fpm, c->d_tw_inv,
                                pcs);
         }
         ProfScope p("ntt_inv_cols_small", s);
-        hipLaunchKernelGGL((ntt_small_kernel<A, B, false, true, TILE, E>), grid, block, 0, s, b2, c->d_tw_inv, pcs);
+        hipLaunchKernelGGL((ntt_small_kernel<A, B, false, true, TILE, E>), grid, block, 0, s, b2, fpm, c->d_tw_inv, pcs);
     }
 }
 
-template <int A, int B>
-static void launch_two_pass(const rf_ctx *c, const NttBatch &b, bool forward, hipStream_t s,
+template <int A, int B, typename Fp>
+static void launch_two_pass(const rf_ctx *c, Fp fpm, const NttBatch &b, bool forward, hipStream_t s,
                             const PrimeConst *pcs, const rf_tuning &tn) {
     const uint32_t limbs = b.per_poly * b.n_polys;
     const uint32_t tiles = limbs << (A + B - 12);
     if (tiles < tn.ntt_small_below) {
         const bool big = tn.ntt_small_tile == 2048 || (tn.ntt_small_tile == 0 && tiles * 2 >= tn.ntt_small_below);
         if (tn.ntt_small_radix == 8) {
-            if (big) launch_two_pass_small<A, B, 2048, 8>(c, b, forward, s, pcs);
-            else launch_two_pass_small<A, B, 1024, 8>(c, b, forward, s, pcs);
+            if (big) launch_two_pass_small<A, B, 2048, 8>(c, fpm, b, forward, s, pcs);
+            else launch_two_pass_small<A, B, 1024, 8>(c, fpm, b, forward, s, pcs);
         } else {
-            if (big) launch_two_pass_small<A, B, 2048, kSmallE>(c, b, forward, s, pcs);
-            else launch_two_pass_small<A, B, 1024, kSmallE>(c, b, forward, s, pcs);
+            if (big) launch_two_pass_small<A, B, 2048, kSmallE>(c, fpm, b, forward, s, pcs);
+            else launch_two_pass_small<A, B, 1024, kSmallE>(c, fpm, b, forward, s, pcs);
         }
         return;
     }
@@ -387,17 +400,17 @@ static void launch_two_pass(const rf_ctx *c, const NttBatch &b, bool forward, hi
     if (forward) {
         {
             ProfScope p("ntt_fwd_cols", s);
-            hipLaunchKernelGGL((ntt_cols_kernel<A, B, true>), grid_cols, block, 0, s, b, c->d_tw_fwd, pcs);
+            hipLaunchKernelGGL((ntt_cols_kernel<A, B, true>), grid_cols, block, 0, s, b, fpm, c->d_tw_fwd, pcs);
         }
         ProfScope p("ntt_fwd_rows", s);
-        hipLaunchKernelGGL((ntt_rows_kernel<A, B, true>), grid_rows, block, 0, s, b2, c->d_tw_fwd_rows, pcs);
+        hipLaunchKernelGGL((ntt_rows_kernel<A, B, true>), grid_rows, block, 0, s, b2, fpm, c->d_tw_fwd_rows, pcs);
     } else {
         {
             ProfScope p("ntt_inv_rows", s);
-            hipLaunchKernelGGL((ntt_rows_kernel<A, B, false>), grid_rows, block, 0, s, b, c->d_tw_inv_rows, pcs);
+            hipLaunchKernelGGL((ntt_rows_kernel<A, B, false>), grid_rows, block, 0, s, b, fpm, c->d_tw_inv_rows, pcs);
         }
         ProfScope p("ntt_inv_cols", s);
-        hipLaunchKernelGGL((ntt_cols_kernel<A, B, false>), grid_cols, block, 0, s, b2, c->d_tw_inv, pcs);
+        hipLaunchKernelGGL((ntt_cols_kernel<A, B, false>), grid_cols, block, 0, s, b2, fpm, c->d_tw_inv, pcs);
     }
 }
 
@@ -410,7 +423,8 @@ static int small_tile_of(const rf_ctx *c, uint32_t limbs, const rf_tuning *tn) {
     return t.ntt_small_tile == 2048 || (t.ntt_small_tile == 0 && tiles * 2 >= t.ntt_fused_small_below) ? 2048 : 1024;
 }
 
-int launch_ntt_fwd_moddown(const rf_ctx *c, uint64_t *conv, const uint64_t *ip, uint64_t *out, uint32_t nl,
+template <typename Fp>
+static int launch_ntt_fwd_moddown_t(const rf_ctx *c, Fp fpm, uint64_t *conv, const uint64_t *ip, uint64_t *out, uint32_t nl,
                            hipStream_t s, const rf_tuning *tn) {
     const uint64_t *tab = c->scheme == RF_BGV ? c->d_moddown_t : c->d_moddown;
     const uint64_t *cross = tab + moddown_cross_off(c), *negp = tab + moddown_negp_off(c);
@@ -420,7 +434,7 @@ int launch_ntt_fwd_moddown(const rf_ctx *c, uint64_t *conv, const uint64_t *ip, 
     if (st) {
 #define RF_SMDK(A, B, T, KP)                                                                                     \
     hipLaunchKernelGGL((ntt_small_cols_moddown_kernel<A, B, T, KP>), dim3(c->n / T, 2 * nl), dim3(T / kSmallE), 0, s, \
-                       ip, conv, c->d_tw_fwd, c->d_pc, cross, negp, nl, c->L, c->K)
+                       fpm, ip, conv, c->d_tw_fwd, c->d_pc, cross, negp, nl, c->L, c->K)
 #define RF_SMD(A, B, T)                                                                                          \
     {                                                                                                            \
         {                                                                                                        \
@@ -435,9 +449,9 @@ int launch_ntt_fwd_moddown(const rf_ctx *c, uint64_t *conv, const uint64_t *ip, 
         }                                                                                                        \
         ProfScope p("ntt_fwd_rows_moddown_small", s);                                                            \
         hipLaunchKernelGGL((ntt_small_rows_moddown_kernel<A, B, T>), dim3(c->n / T, 2 * nl), dim3(T / kSmallE), 0, s, \
-                           conv, c->d_tw_fwd, c->d_pc, ip, out, pinv, nl, c->K);                                 \
+                           fpm, conv, c->d_tw_fwd, c->d_pc, ip, out, pinv, nl, c->K);                     \
     }
-#define RF_SMDT(A, B) \
+#define RF_SMDT(A, B)                                                                                            \
     if (st == 2048) RF_SMD(A, B, 2048) else RF_SMD(A, B, 1024)
         switch (c->log_n) {
             case 13: RF_SMDT(7, 6) break;
@@ -454,7 +468,7 @@ int launch_ntt_fwd_moddown(const rf_ctx *c, uint64_t *conv, const uint64_t *ip, 
     }
 #define RF_MDK(A, B, KP)                                                                                         \
     hipLaunchKernelGGL((ntt_cols_moddown_kernel<A, B, KP>), dim3((1u << B) / (kTile >> A), 2 * nl), dim3(kThreads), \
-                       0, s, ip, conv, c->d_tw_fwd, c->d_pc, cross, negp, nl, c->L, c->K)
+                       0, s, fpm, ip, conv, c->d_tw_fwd, c->d_pc, cross, negp, nl, c->L, c->K)
 #define RF_MD(A, B)                                                                                              \
     {                                                                                                            \
         {                                                                                                        \
@@ -468,7 +482,7 @@ int launch_ntt_fwd_moddown(const rf_ctx *c, uint64_t *conv, const uint64_t *ip, 
             }                                                                                                    \
         }                                                                                                        \
         ProfScope p("ntt_fwd_rows_moddown", s);                                                                  \
-        hipLaunchKernelGGL((ntt_rows_moddown_kernel<A, B>), g, dim3(kThreads), 0, s, conv, c->d_tw_fwd_rows, c->d_pc, ip, \
+        hipLaunchKernelGGL((ntt_rows_moddown_kernel<A, B>), g, dim3(kThreads), 0, s, fpm, conv, c->d_tw_fwd_rows, c->d_pc, ip, \
                            out, pinv, nl, c->K);                                                                 \
     }
     switch (c->log_n) {
@@ -485,7 +499,14 @@ int launch_ntt_fwd_moddown(const rf_ctx *c, uint64_t *conv, const uint64_t *ip, 
     return RF_OK;
 }
 
-int launch_ntt_fwd_rescale(const rf_ctx *c, const uint64_t *last, uint64_t *lift, const uint64_t *in,
+int launch_ntt_fwd_moddown(const rf_ctx *c, uint64_t *conv, const uint64_t *ip, uint64_t *out, uint32_t nl,
+                           hipStream_t s, const rf_tuning *tn) {
+    return c->fp_mask.any() ? launch_ntt_fwd_moddown_t(c, c->fp_mask, conv, ip, out, nl, s, tn)
+                            : launch_ntt_fwd_moddown_t(c, NoFp{}, conv, ip, out, nl, s, tn);
+}
+
+template <typename Fp>
+static int launch_ntt_fwd_rescale_t(const rf_ctx *c, Fp fpm, const uint64_t *last, uint64_t *lift, const uint64_t *in,
                            uint64_t *out, uint32_t nl, bool keep_t, hipStream_t s, const rf_tuning *tn) {
     const uint32_t l = nl - 1;
     const dim3 g(c->n / kTile, 2 * l);
@@ -497,17 +518,17 @@ int launch_ntt_fwd_rescale(const rf_ctx *c, const uint64_t *last, uint64_t *lift
         {                                                                                                        \
             ProfScope p("ntt_fwd_cols_lift_small", s);                                                           \
             if (keep_t)                                                                                          \
-                hipLaunchKernelGGL((ntt_small_cols_lift_kernel<A, B, T, true>), gs, bs, 0, s, last, lift,        \
+                hipLaunchKernelGGL((ntt_small_cols_lift_kernel<A, B, T, true>), gs, bs, 0, s, fpm, last, lift, \
                                    c->d_tw_fwd, c->d_pc, c->d_rescale, nl, c->L);                                \
             else                                                                                                 \
-                hipLaunchKernelGGL((ntt_small_cols_lift_kernel<A, B, T, false>), gs, bs, 0, s, last, lift,       \
+                hipLaunchKernelGGL((ntt_small_cols_lift_kernel<A, B, T, false>), gs, bs, 0, s, fpm, last, lift, \
                                    c->d_tw_fwd, c->d_pc, c->d_rescale, nl, c->L);                                \
         }                                                                                                        \
         ProfScope p("ntt_fwd_rows_rescale_small", s);                                                            \
-        hipLaunchKernelGGL((ntt_small_rows_rescale_kernel<A, B, T>), gs, bs, 0, s, lift, c->d_tw_fwd, c->d_pc, in, \
+        hipLaunchKernelGGL((ntt_small_rows_rescale_kernel<A, B, T>), gs, bs, 0, s, fpm, lift, c->d_tw_fwd, c->d_pc, in, \
                            out, c->d_rescale, nl, c->L);                                                         \
     }
-#define RF_SRST(A, B) \
+#define RF_SRST(A, B)                                                                                            \
     if (st == 2048) RF_SRS(A, B, 2048) else RF_SRS(A, B, 1024)
         switch (c->log_n) {
             case 13: RF_SRST(7, 6) break;
@@ -527,14 +548,14 @@ int launch_ntt_fwd_rescale(const rf_ctx *c, const uint64_t *last, uint64_t *lift
             ProfScope p("ntt_fwd_cols_lift", s);                                                                 \
             const dim3 gc((1u << B) / (kTile >> A), 2 * l);                                                      \
             if (keep_t)                                                                                          \
-                hipLaunchKernelGGL((ntt_cols_lift_kernel<A, B, true>), gc, dim3(kThreads), 0, s, last, lift,     \
+                hipLaunchKernelGGL((ntt_cols_lift_kernel<A, B, true>), gc, dim3(kThreads), 0, s, fpm, last, lift, \
                                    c->d_tw_fwd, c->d_pc, c->d_rescale, nl, c->L);                                \
             else                                                                                                 \
-                hipLaunchKernelGGL((ntt_cols_lift_kernel<A, B, false>), gc, dim3(kThreads), 0, s, last, lift,    \
+                hipLaunchKernelGGL((ntt_cols_lift_kernel<A, B, false>), gc, dim3(kThreads), 0, s, fpm, last, lift, \
                                    c->d_tw_fwd, c->d_pc, c->d_rescale, nl, c->L);                                \
         }                                                                                                        \
         ProfScope p("ntt_fwd_rows_rescale", s);                                                                  \
-        hipLaunchKernelGGL((ntt_rows_rescale_kernel<A, B>), g, dim3(kThreads), 0, s, lift, c->d_tw_fwd_rows, c->d_pc, in, \
+        hipLaunchKernelGGL((ntt_rows_rescale_kernel<A, B>), g, dim3(kThreads), 0, s, fpm, lift, c->d_tw_fwd_rows, c->d_pc, in, \
                            out, c->d_rescale, nl, c->L);                                                         \
     }
     switch (c->log_n) {
@@ -550,7 +571,14 @@ int launch_ntt_fwd_rescale(const rf_ctx *c, const uint64_t *last, uint64_t *lift
     return RF_OK;
 }
 
-int launch_intt_first(const rf_ctx *c, const uint64_t *a, const uint64_t *b, uint64_t *dc, uint32_t galois,
+int launch_ntt_fwd_rescale(const rf_ctx *c, const uint64_t *last, uint64_t *lift, const uint64_t *in,
+                           uint64_t *out, uint32_t nl, bool keep_t, hipStream_t s, const rf_tuning *tn) {
+    return c->fp_mask.any() ? launch_ntt_fwd_rescale_t(c, c->fp_mask, last, lift, in, out, nl, keep_t, s, tn)
+                            : launch_ntt_fwd_rescale_t(c, NoFp{}, last, lift, in, out, nl, keep_t, s, tn);
+}
+
+template <typename Fp>
+static int launch_intt_first_t(const rf_ctx *c, Fp fpm, const uint64_t *a, const uint64_t *b, uint64_t *dc, uint32_t galois,
                       uint32_t nl, hipStream_t s, const rf_tuning *tn) {
     const uint64_t N = c->n;
     const int st = small_tile_of(c, nl, tn);
@@ -560,15 +588,15 @@ int launch_intt_first(const rf_ctx *c, const uint64_t *a, const uint64_t *b, uin
         const dim3 gs(c->n / T, nl), bs(T / kSmallE);                                                            \
         {                                                                                                        \
             ProfScope p(galois ? "ntt_inv_rows_gather_small" : "ntt_inv_rows_tensor_small", s);                  \
-            hipLaunchKernelGGL((ntt_small_inv_rows_first_kernel<A, B, T>), gs, bs, 0, s, a, b, dc, galois,      \
+            hipLaunchKernelGGL((ntt_small_inv_rows_first_kernel<A, B, T>), gs, bs, 0, s, fpm, a, b, dc, galois, \
                                c->d_tw_inv, c->d_pc, nl);                                                        \
         }                                                                                                        \
         NttBatch bc{dc, dc, 0, 0, nl, 1, 0, nullptr};                                                            \
         ProfScope p("ntt_inv_cols_small", s);                                                                    \
-        hipLaunchKernelGGL((ntt_small_kernel<A, B, false, true, T, kSmallE>), gs, bs, 0, s, bc, c->d_tw_inv,     \
+        hipLaunchKernelGGL((ntt_small_kernel<A, B, false, true, T, kSmallE>), gs, bs, 0, s, bc, fpm, c->d_tw_inv, \
                            pc_modup(c, nl));                                                                     \
     }
-#define RF_SIFT(A, B) \
+#define RF_SIFT(A, B)                                                                                            \
     if (st == 2048) RF_SIF(A, B, 2048) else RF_SIF(A, B, 1024)
         switch (c->log_n) {
             case 13: RF_SIFT(7, 6) break;
@@ -587,17 +615,17 @@ int launch_intt_first(const rf_ctx *c, const uint64_t *a, const uint64_t *b, uin
         const dim3 gr((1u << A) / (kTile >> B), nl);                                                             \
         if (galois) {                                                                                            \
             ProfScope p("ntt_inv_rows_gather", s);                                                               \
-            hipLaunchKernelGGL((ntt_inv_rows_gather_kernel<A, B>), gr, dim3(kThreads), 0, s, a + (size_t)nl * N, dc, \
-                               galois, c->d_tw_inv_rows, c->d_pc);                                                    \
+            hipLaunchKernelGGL((ntt_inv_rows_gather_kernel<A, B>), gr, dim3(kThreads), 0, s, fpm, a + (size_t)nl * N, dc, \
+                               galois, c->d_tw_inv_rows, c->d_pc);                                               \
         } else {                                                                                                 \
             ProfScope p("ntt_inv_rows_tensor", s);                                                               \
-            hipLaunchKernelGGL((ntt_inv_rows_tensor_kernel<A, B>), gr, dim3(kThreads), 0, s, a, b, dc,           \
-                               c->d_tw_inv_rows, c->d_pc, nl);                                                        \
+            hipLaunchKernelGGL((ntt_inv_rows_tensor_kernel<A, B>), gr, dim3(kThreads), 0, s, fpm, a, b, dc, \
+                               c->d_tw_inv_rows, c->d_pc, nl);                                                   \
         }                                                                                                        \
         NttBatch bc{dc, dc, 0, 0, nl, 1, 0, nullptr};                                                            \
         ProfScope p("ntt_inv_cols", s);                                                                          \
         hipLaunchKernelGGL((ntt_cols_kernel<A, B, false>), dim3((1u << B) / (kTile >> A), nl), dim3(kThreads), 0, \
-                           s, bc, c->d_tw_inv, pc_modup(c, nl));                                                 \
+                           s, bc, fpm, c->d_tw_inv, pc_modup(c, nl));                                     \
     }
     switch (c->log_n) {
         case 13: RF_IF(7, 6) break;
@@ -612,7 +640,14 @@ int launch_intt_first(const rf_ctx *c, const uint64_t *a, const uint64_t *b, uin
     return RF_OK;
 }
 
-int launch_ntt(const rf_ctx *c, const NttBatch &b, bool forward, hipStream_t s, const PrimeConst *pcs,
+int launch_intt_first(const rf_ctx *c, const uint64_t *a, const uint64_t *b, uint64_t *dc, uint32_t galois,
+                      uint32_t nl, hipStream_t s, const rf_tuning *tn) {
+    return c->fp_mask.any() ? launch_intt_first_t(c, c->fp_mask, a, b, dc, galois, nl, s, tn)
+                            : launch_intt_first_t(c, NoFp{}, a, b, dc, galois, nl, s, tn);
+}
+
+template <typename Fp>
+static int launch_ntt_t(const rf_ctx *c, Fp fpm, const NttBatch &b, bool forward, hipStream_t s, const PrimeConst *pcs,
                const rf_tuning *tn) {
     const uint32_t limbs = b.per_poly * b.n_polys;
     if (!pcs) pcs = c->d_pc;
@@ -624,21 +659,27 @@ int launch_ntt(const rf_ctx *c, const NttBatch &b, bool forward, hipStream_t s, 
             ProfScope p(forward ? "ntt_fwd_single" : "ntt_inv_single", s);
             if (forward)
                 hipLaunchKernelGGL((ntt_single_kernel<12, true>), dim3(1, limbs), dim3(kThreads), 0, s, b,
-                                   c->d_tw_fwd, pcs);
+                                   fpm, c->d_tw_fwd, pcs);
             else
                 hipLaunchKernelGGL((ntt_single_kernel<12, false>), dim3(1, limbs), dim3(kThreads), 0, s, b,
-                                   c->d_tw_inv, pcs);
+                                   fpm, c->d_tw_inv, pcs);
             break;
         }
-        case 13: launch_two_pass<7, 6>(c, b, forward, s, pcs, t); break;
-        case 14: launch_two_pass<7, 7>(c, b, forward, s, pcs, t); break;
-        case 15: launch_two_pass<8, 7>(c, b, forward, s, pcs, t); break;
-        case 16: launch_two_pass<8, 8>(c, b, forward, s, pcs, t); break;
+        case 13: launch_two_pass<7, 6>(c, fpm, b, forward, s, pcs, t); break;
+        case 14: launch_two_pass<7, 7>(c, fpm, b, forward, s, pcs, t); break;
+        case 15: launch_two_pass<8, 7>(c, fpm, b, forward, s, pcs, t); break;
+        case 16: launch_two_pass<8, 8>(c, fpm, b, forward, s, pcs, t); break;
         default: return fail(RF_EUNSUPPORTED, "ring degree");
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(RF_EHIP, std::string("NTT launch: ") + hipGetErrorString(e));
     return RF_OK;
+}
+
+int launch_ntt(const rf_ctx *c, const NttBatch &b, bool forward, hipStream_t s, const PrimeConst *pcs,
+               const rf_tuning *tn) {
+    return c->fp_mask.any() ? launch_ntt_t(c, c->fp_mask, b, forward, s, pcs, tn)
+                            : launch_ntt_t(c, NoFp{}, b, forward, s, pcs, tn);
 }
 
 }  // namespace rf

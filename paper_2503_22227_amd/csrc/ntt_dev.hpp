@@ -22,11 +22,15 @@
 //     tile is exchanged through LDS for the next round, so a pass of up to 8
 //     stages takes two rounds (256-thread workgroups; 8 residues per thread
 //     with radix-8 rounds was measured no faster on MI355X);
-//   * values stay in Harvey's lazy ranges ([0, 4q) forward, [0, 2q) inverse)
-//     between stages and passes and are reduced to [0, q) at the last store.
+//   * primes below 2^46 are transformed in FP64 (ArFp), the others in 64-bit
+//     integers that stay in Harvey's lazy ranges ([0, 4q) forward, [0, 2q)
+//     inverse) between stages and passes; both are reduced to [0, q) at the
+//     last store.
 // N <= 4096 is done in one pass by one workgroup per limb.
 #pragma once
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "modarith.hpp"
 #include "rf_internal.hpp"
@@ -65,45 +69,83 @@ __host__ __device__ inline uint32_t row_tw_index(int A, int B, bool fwd, uint32_
     return (1u << (A + s)) + ((r_hi * R + k) * T + t) * U + u;
 }
 
-// Butterflies with twiddle w and its 2^62-scaled companion wp (shoup62_lazy);
-// nq = 2^64 - q.
+// Arithmetic of a transform: the register form V of a residue, the twiddles Tw
+// and the butterflies.  Between the passes of one transform a residue is kept
+// as bits(V) (raw inverts it).
 //
-// LZ (primes below kLazyPrimeBound): no correction of the sum.  Forward
-// (Cooley-Tukey), x grows by less than 2q per stage, so after all stages of
-// both passes of N <= 2^16 every value stays below 36q < 2^56; inverse
-// (Gentleman-Sande), values at most double per stage, so at local stage k of a
-// pass (inputs below 2^(k+1) q) the difference is formed as x - y + off with
-// off = 2^(k+1) q, and each pass starts from inputs below 2q (the row pass
-// reduces its output once, see ntt_rows_compute).  Strict: Harvey's ranges,
-// inputs and outputs below 4q (forward) or 2q (inverse), off = 2q.
-template <bool LZ>
-__device__ __forceinline__ void ct_bfly(uint64_t &x, uint64_t &y, uint64_t w, uint64_t wp, uint64_t nq,
-                                        uint64_t q2) {
-    uint64_t xr = LZ ? x : (x >= q2 ? x - q2 : x);  // strict: [0, 2q)
-    uint64_t t = shoup62_lazy(y, w, wp, nq);         // [0, 2q); y < 2^62
-    x = xr + t;
-    y = xr - t + q2;
-}
+// ArInt: 64-bit integers, butterflies with a twiddle w and its 2^62-scaled
+// companion wp (shoup62_lazy), nq = 2^64 - q, in Harvey's ranges: inputs and
+// outputs below 4q (forward) or 2q (inverse).
+struct ArInt {
+    using V = uint64_t;
+    using Tw = TwPair;
+    static constexpr bool kFp = false;
+    uint64_t q, q2, nq, ninv, ninv_p, wlast, wlast_p;
+    __device__ __forceinline__ explicit ArInt(const PrimeConst &pc)
+        : q(pc.q), q2(2 * pc.q), nq(0 - pc.q), ninv(pc.ninv), ninv_p(pc.ninv_p), wlast(pc.wlast),
+          wlast_p(pc.wlast_p) {}
+    __device__ __forceinline__ static uint64_t bits(V x) { return x; }
+    __device__ __forceinline__ static V raw(uint64_t b) { return b; }
+    __device__ __forceinline__ void ct(V &x, V &y, const TwPair &w) const {
+        uint64_t xr = x >= q2 ? x - q2 : x;               // [0, 2q)
+        uint64_t t = shoup62_lazy(y, w.w, w.wp, nq);       // [0, 2q); y < 2^62
+        x = xr + t;
+        y = xr - t + q2;
+    }
+    __device__ __forceinline__ void gs(V &x, V &y, const TwPair &w) const {
+        uint64_t s = x + y;
+        s = s >= q2 ? s - q2 : s;
+        uint64_t d = x - y + q2;
+        x = s;
+        y = shoup62_lazy(d, w.w, w.wp, nq);       // [0, 2q)
+    }
+    __device__ __forceinline__ void gs_last(V &x, V &y) const {
+        uint64_t s = x + y;
+        uint64_t d = x - y + q2;
+        x = shoup_lazy(s, ninv, ninv_p, q);
+        y = shoup_lazy(d, wlast, wlast_p, q);
+    }
+    // the last inverse stage's output as a residue in [0, q)
+    __device__ __forceinline__ uint64_t canon_last(V x) const { return csub(x, q); }
+};
 
-template <bool LZ>
-__device__ __forceinline__ void gs_bfly(uint64_t &x, uint64_t &y, uint64_t w, uint64_t wp, uint64_t nq,
-                                        uint64_t q2, uint64_t off) {
-    uint64_t s = x + y;
-    if (!LZ) s = s >= q2 ? s - q2 : s;
-    uint64_t d = x - y + off;                 // off >= any y of this stage
-    x = s;
-    y = shoup62_lazy(d, w, wp, nq);           // [0, 2q)
-}
-
-__device__ __forceinline__ void gs_bfly_last(uint64_t &x, uint64_t &y, const PrimeConst &pc, uint64_t off) {
-    uint64_t s = x + y;
-    uint64_t d = x - y + off;
-    x = shoup_lazy(s, pc.ninv, pc.ninv_p, pc.q);
-    y = shoup_lazy(d, pc.wlast, pc.wlast_p, pc.q);
-}
-
-// Transforms of primes below this bound skip the sum corrections (LZ above).
-constexpr uint64_t kLazyPrimeBound = 1ull << 50;
+// ArFp (primes below kFpPrimeBound): whole numbers in doubles (FpMod), 8 FP64
+// operations per butterfly against about 30 integer ones.  Forward, x grows by
+// at most 0.75q per stage, so from inputs below 4q every value of both passes
+// stays below 16q < 2^50.  Inverse, the sums double per stage; a round of C
+// stages ends by reducing the values that were sums in its last two stages (a
+// quarter of them, red()), so that every round starts below 1.5q and its
+// sums stay below 24q < 2^51.
+struct ArFp {
+    using V = double;
+    using Tw = double;
+    static constexpr bool kFp = true;
+    FpMod f;
+    double ninv, wlast;
+    __device__ __forceinline__ explicit ArFp(const PrimeConst &pc) : f{pc.qd, pc.qinv} {
+        ninv = f.centre(pc.ninv);
+        wlast = f.centre(pc.wlast);
+    }
+    __device__ __forceinline__ static uint64_t bits(V x) { return (uint64_t)__double_as_longlong(x); }
+    __device__ __forceinline__ static V raw(uint64_t b) { return __longlong_as_double((long long)b); }
+    __device__ __forceinline__ void ct(V &x, V &y, double w) const {
+        const double t = f.mul(y, w);
+        y = x - t;
+        x = x + t;
+    }
+    __device__ __forceinline__ void gs(V &x, V &y, double w) const {
+        const double d = x - y;
+        x = x + y;
+        y = f.mul(d, w);
+    }
+    __device__ __forceinline__ void gs_last(V &x, V &y) const {
+        const double d = x - y;
+        x = f.mul(x + y, ninv);
+        y = f.mul(d, wlast);
+    }
+    __device__ __forceinline__ V red(V x) const { return f.red(x); }
+    __device__ __forceinline__ uint64_t canon_last(V x) const { return f.canon(x); }
+};
 
 // Table index of twiddle j of local stage s: the natural index (tw_base << s) + j
 // (column passes, ROW_A == 0) or the row-pass layout above, with tw_base = 2^A + r
@@ -139,28 +181,29 @@ constexpr int kTwLoad = 0, kTwPrefetch = 1, kTwCached = 2;
 __host__ __device__ constexpr int tw_slots(int S_LOG, int E) { return E * S_LOG; }
 
 // One round of C butterfly stages of a size-2^S_LOG sub-transform held in LDS
-// (element p of sub-transform u at lds[p * ldu + u]).  Thread t of the
-// sub-transform owns E residues (kElems unless stated): E / 2^C groups of 2^C
-// residues spaced by the round's smallest distance 2^DL.
+// (element p of sub-transform u at lds[p * ldu + u], as Ar::bits).  Thread t of
+// the sub-transform owns E residues (kElems unless stated): E / 2^C groups of
+// 2^C residues spaced by the round's smallest distance 2^DL.
 //
 // IN_REGS / OUT_REGS: the round takes its residues from regs / leaves them in
 // regs (group gi, element e at regs[gi * 2^C + e]) instead of LDS.  TW, SLOT0,
 // cache: the twiddle source above.
-template <int S_LOG, int ST0, int C, bool FWD, bool SCALE_LAST, int ROW_A, bool IN_REGS = false,
-          bool OUT_REGS = false, bool LZ = false, int E = kElems, int TW = kTwLoad, int SLOT0 = 0>
+template <typename Ar, int S_LOG, int ST0, int C, bool FWD, bool SCALE_LAST, int ROW_A, bool IN_REGS = false,
+          bool OUT_REGS = false, int E = kElems, int TW = kTwLoad, int SLOT0 = 0>
 __device__ __forceinline__ void ntt_round(uint64_t *lds, int ldu, int u, int t, uint32_t tw_base,
-                                          const TwPair *__restrict__ tw, const PrimeConst &pc,
-                                          uint64_t *regs = nullptr, TwPair *cache = nullptr) {
+                                          const typename Ar::Tw *__restrict__ tw, const Ar &ar,
+                                          typename Ar::V *regs = nullptr, typename Ar::Tw *cache = nullptr) {
+    using V = typename Ar::V;
+    using Tw = typename Ar::Tw;
     constexpr int G = 1 << C;
     constexpr int NG = E / G;
     constexpr int DL = FWD ? (S_LOG - ST0 - C) : ST0;
     constexpr bool RUN = TW != kTwPrefetch;
-    const uint64_t q = pc.q, q2 = 2 * q, nq = 0 - q;
     // twiddle (slot, table index): fetched, loaded or taken from the cache
-    auto twiddle = [&](int slot, uint32_t idx) -> TwPair {
+    auto twiddle = [&](int slot, uint32_t idx) -> Tw {
         if constexpr (TW == kTwPrefetch) {
             cache[slot] = tw[idx];
-            return TwPair{};
+            return Tw{};
         } else if constexpr (TW == kTwCached) {
             return cache[slot];
         } else {
@@ -173,10 +216,13 @@ __device__ __forceinline__ void ntt_round(uint64_t *lds, int ldu, int u, int t, 
         const int lo = grp & ((1 << DL) - 1);
         const int hi = grp >> DL;
         const int base = (hi << (DL + C)) + lo;
-        uint64_t v[G];
+        V v[G];
         if constexpr (RUN) {
 #pragma unroll
-            for (int e = 0; e < G; ++e) v[e] = IN_REGS ? regs[gi * G + e] : lds[(base + (e << DL)) * ldu + u];
+            for (int e = 0; e < G; ++e) {
+                if constexpr (IN_REGS) v[e] = regs[gi * G + e];
+                else v[e] = Ar::raw(lds[(base + (e << DL)) * ldu + u]);
+            }
         }
         if constexpr (FWD) {
 #pragma unroll
@@ -190,9 +236,9 @@ __device__ __forceinline__ void ntt_round(uint64_t *lds, int ldu, int u, int t, 
                     // index depends on e only (uniform across the sub-transform)
                     const uint32_t j = ST0 == 0 ? (uint32_t)(e >> (C - c))
                                                 : (uint32_t)((base + (e << DL)) >> (S_LOG - st));
-                    const TwPair w = twiddle(SLOT0 + (gi * C + c) * G + e,
-                                             row_or_natural<S_LOG, ROW_A, true>(tw_base, st, t, j));
-                    if constexpr (RUN) ct_bfly<LZ>(v[e], v[e + h], w.w, w.wp, nq, q2);
+                    const Tw w = twiddle(SLOT0 + (gi * C + c) * G + e,
+                                         row_or_natural<S_LOG, ROW_A, true>(tw_base, st, t, j));
+                    if constexpr (RUN) ar.ct(v[e], v[e + h], w);
                 }
             }
         } else {
@@ -200,29 +246,33 @@ __device__ __forceinline__ void ntt_round(uint64_t *lds, int ldu, int u, int t, 
             for (int c = 0; c < C; ++c) {
                 const int us = ST0 + c;
                 const int h = 1 << c;
-                const uint64_t off = LZ ? q << (us + 1) : q2;
 #pragma unroll
                 for (int e = 0; e < G; ++e) {
                     if (e & h) continue;
                     if (SCALE_LAST && us == S_LOG - 1) {
-                        if constexpr (RUN) gs_bfly_last(v[e], v[e + h], pc, off);
+                        if constexpr (RUN) ar.gs_last(v[e], v[e + h]);
                     } else {
                         // in the last round every group starts below 2^DL: index from e only
                         const uint32_t lo_part = ST0 + C == S_LOG ? (uint32_t)(e >> (c + 1))
                                                                   : (uint32_t)((base + (e << DL)) >> (us + 1));
-                        const TwPair w = twiddle(SLOT0 + (gi * C + c) * G + e,
-                                                 row_or_natural<S_LOG, ROW_A, false>(tw_base, S_LOG - us - 1, t,
-                                                                                     lo_part));
-                        if constexpr (RUN) gs_bfly<LZ>(v[e], v[e + h], w.w, w.wp, nq, q2, off);
+                        const Tw w = twiddle(SLOT0 + (gi * C + c) * G + e,
+                                             row_or_natural<S_LOG, ROW_A, false>(tw_base, S_LOG - us - 1, t,
+                                                                                 lo_part));
+                        if constexpr (RUN) ar.gs(v[e], v[e + h], w);
                     }
                 }
+            }
+            // the sums of the round's last two stages (none where it scaled its outputs)
+            if constexpr (RUN && Ar::kFp && !(SCALE_LAST && ST0 + C == S_LOG)) {
+#pragma unroll
+                for (int e = 0; 4 * e < G; ++e) v[e] = ar.red(v[e]);
             }
         }
         if constexpr (RUN) {
 #pragma unroll
             for (int e = 0; e < G; ++e) {
                 if constexpr (OUT_REGS) regs[gi * G + e] = v[e];
-                else lds[(base + (e << DL)) * ldu + u] = v[e];
+                else lds[(base + (e << DL)) * ldu + u] = Ar::bits(v[e]);
             }
         }
     }
@@ -231,48 +281,93 @@ __device__ __forceinline__ void ntt_round(uint64_t *lds, int ldu, int u, int t, 
 // Rounds of a size-2^S_LOG sub-transform from stage ST0 on: radix-E rounds,
 // the last one shorter when log2(E) does not divide S_LOG.  With kTwPrefetch
 // only the twiddle loads run (no barriers).
-template <int S_LOG, int ST0, bool FWD, bool SCALE_LAST, int ROW_A, bool LZ = false, int E = kElems,
-          int TW = kTwLoad, int SLOT0 = 0>
+template <typename Ar, int S_LOG, int ST0, bool FWD, bool SCALE_LAST, int ROW_A, int E = kElems, int TW = kTwLoad,
+          int SLOT0 = 0>
 __device__ __forceinline__ void ntt_rounds_from(uint64_t *lds, int ldu, int u, int t, uint32_t tw_base,
-                                                const TwPair *__restrict__ tw, const PrimeConst &pc,
-                                                TwPair *cache = nullptr) {
+                                                const typename Ar::Tw *__restrict__ tw, const Ar &ar,
+                                                typename Ar::Tw *cache = nullptr) {
     constexpr int CL = ilog2(E);
     constexpr int C = (S_LOG - ST0) < CL ? (S_LOG - ST0) : CL;
     constexpr bool LAST = ST0 + C == S_LOG;
-    ntt_round<S_LOG, ST0, C, FWD, SCALE_LAST && LAST, ROW_A, false, false, LZ, E, TW, SLOT0>(
-        lds, ldu, u, t, tw_base, tw, pc, nullptr, cache);
+    ntt_round<Ar, S_LOG, ST0, C, FWD, SCALE_LAST && LAST, ROW_A, false, false, E, TW, SLOT0>(
+        lds, ldu, u, t, tw_base, tw, ar, nullptr, cache);
     if constexpr (TW != kTwPrefetch) __syncthreads();
     if constexpr (!LAST)
-        ntt_rounds_from<S_LOG, ST0 + C, FWD, SCALE_LAST, ROW_A, LZ, E, TW, SLOT0 + E * C>(lds, ldu, u, t, tw_base,
-                                                                                        tw, pc, cache);
+        ntt_rounds_from<Ar, S_LOG, ST0 + C, FWD, SCALE_LAST, ROW_A, E, TW, SLOT0 + E * C>(lds, ldu, u, t, tw_base, tw,
+                                                                                         ar, cache);
 }
 
 // ROW_A: 0 for the natural twiddle table; A for a row pass reading the row table
 // (which needs exactly two rounds of kElems residues: S_LOG in (kElemsLog, 2 kElemsLog]).
-template <int S_LOG, bool FWD, bool SCALE_LAST, int ROW_A = 0, bool LZ = false, int E = kElems, int TW = kTwLoad>
+template <typename Ar, int S_LOG, bool FWD, bool SCALE_LAST, int ROW_A = 0, int E = kElems, int TW = kTwLoad>
 __device__ __forceinline__ void ntt_rounds(uint64_t *lds, int ldu, int u, int t, uint32_t tw_base,
-                                           const TwPair *__restrict__ tw, const PrimeConst &pc,
-                                           TwPair *cache = nullptr) {
+                                           const typename Ar::Tw *__restrict__ tw, const Ar &ar,
+                                           typename Ar::Tw *cache = nullptr) {
     static_assert(S_LOG >= 5 && S_LOG <= 12, "sub-transform size");
     static_assert(ROW_A == 0 || (E == kElems && S_LOG > kElemsLog && S_LOG <= 2 * kElemsLog),
                   "row table: two rounds of kElems residues");
-    ntt_rounds_from<S_LOG, 0, FWD, SCALE_LAST, ROW_A, LZ, E, TW, 0>(lds, ldu, u, t, tw_base, tw, pc, cache);
+    ntt_rounds_from<Ar, S_LOG, 0, FWD, SCALE_LAST, ROW_A, E, TW, 0>(lds, ldu, u, t, tw_base, tw, ar, cache);
 }
 
-// Plain load of a pass (no prologue).
+// A prime's twiddles in the form its arithmetic takes.
+template <typename Ar>
+__device__ __forceinline__ const typename Ar::Tw *twiddles(const TwPair *__restrict__ tw) {
+    return reinterpret_cast<const typename Ar::Tw *>(tw);
+}
+
+// Inputs and outputs of a pass.  A prologue gives the input residue of limb
+// index idx, pro(idx) for integer arithmetic and pro.fp(idx, f) (a whole number
+// below 2^50 in magnitude) for FP64; an epilogue takes the result, epi(idx, x)
+// and epi.fp(idx, x, f).  An element-wise step before or after the transform
+// (the ModDown or rescale conversion and tail) runs there instead of in
+// another kernel.
+template <typename Ar, typename Pro>
+__device__ __forceinline__ typename Ar::V pass_in(const Pro &pro, size_t idx, const Ar &ar) {
+    if constexpr (Ar::kFp) return pro.fp(idx, ar.f);
+    else return pro(idx);
+}
+
+template <typename Ar, typename Epi>
+__device__ __forceinline__ void pass_out(const Epi &epi, size_t idx, typename Ar::V x, const Ar &ar) {
+    if constexpr (Ar::kFp) epi.fp(idx, x, ar.f);
+    else epi(idx, x);
+}
+
+// Residues in [0, 4q) (no prologue).
 struct LoadPro {
     const uint64_t *in;
     __device__ __forceinline__ uint64_t operator()(size_t idx) const { return in[idx]; }
+    __device__ __forceinline__ double fp(size_t idx, const FpMod &) const { return FpMod::from_u52(in[idx]); }
 };
 
-// Final store of a pass: out[idx] = x.  Passes take the store as a functor, so
-// an element-wise step that follows the transform (the ModDown or rescale
-// tail) runs in the pass's epilogue instead of another kernel.
+// What the transform's other pass left (the register form's bits).
+struct RawPro {
+    const uint64_t *in;
+    __device__ __forceinline__ uint64_t operator()(size_t idx) const { return in[idx]; }
+    __device__ __forceinline__ double fp(size_t idx, const FpMod &) const { return ArFp::raw(in[idx]); }
+};
+
+// Results in [0, q) (the forward transform's last pass).
 struct StoreEpi {
     static constexpr bool kPrefetch = false;
     uint64_t *out;
     __device__ __forceinline__ void operator()(size_t idx, uint64_t x) const { out[idx] = x; }
+    __device__ __forceinline__ void fp(size_t idx, double x, const FpMod &f) const { out[idx] = f.canon(f.red(x)); }
 };
+
+// The register form's bits, for the transform's other pass.
+struct RawEpi {
+    static constexpr bool kPrefetch = false;
+    uint64_t *out;
+    __device__ __forceinline__ void operator()(size_t idx, uint64_t x) const { out[idx] = x; }
+    __device__ __forceinline__ void fp(size_t idx, double x, const FpMod &) const { out[idx] = ArFp::bits(x); }
+};
+
+// The prologue of a pass and the epilogue of a row pass that are plain loads and stores.
+template <bool FIRST>
+using PlainPro = std::conditional_t<FIRST, LoadPro, RawPro>;
+template <bool FWD>
+using RowStore = std::conditional_t<FWD, StoreEpi, RawEpi>;
 
 // Passes of launches with few limbs (the INTT of the special-prime limbs before
 // ModDown, the INTT of the dropped limb before a rescale): a tile of TILE
@@ -283,56 +378,67 @@ struct StoreEpi {
 // ranges as the kTile passes (forward columns lazy below 4q, forward rows in
 // [0, q); inverse rows lazy below 2q, inverse columns in [0, q)).  Ends with a
 // barrier.
-template <int A, int B, bool FWD, int TILE, int E, typename Pro>
-__device__ __forceinline__ void ntt_cols_small_pro(uint64_t *lds, const Pro &pro, uint64_t *out,
-                                                   const TwPair *__restrict__ tw, const PrimeConst &pc, int tile) {
+template <typename Ar, int A, int B, bool FWD, int TILE, int E, typename Pro>
+__device__ __forceinline__ void ntt_cols_small_t(uint64_t *lds, const Pro &pro, uint64_t *out,
+                                                 const TwPair *__restrict__ tw_all, const Ar &ar, int tile) {
+    using V = typename Ar::V;
     constexpr int U = TILE >> A, LDU = U + 1, NT = TILE / E;
     static_assert(U >= 1 && NT >= 64, "small column tile");
     const int col0 = tile * U;
-    uint64_t vin[E];
+    const auto *tw = twiddles<Ar>(tw_all);
+    V vin[E];
 #pragma unroll
     for (int r = 0; r < E; ++r) {
         const int idx = threadIdx.x + r * NT;
-        vin[r] = pro(((size_t)(idx / U) << B) + col0 + idx % U);
+        vin[r] = pass_in(pro, ((size_t)(idx / U) << B) + col0 + idx % U, ar);
     }
-    TwPair twc[tw_slots(A, E)];
-    ntt_rounds<A, FWD, !FWD, 0, false, E, kTwPrefetch>(lds, LDU, threadIdx.x % U, threadIdx.x / U, 1u, tw, pc, twc);
+    typename Ar::Tw twc[tw_slots(A, E)];
+    ntt_rounds<Ar, A, FWD, !FWD, 0, E, kTwPrefetch>(lds, LDU, threadIdx.x % U, threadIdx.x / U, 1u, tw, ar, twc);
 #pragma unroll
     for (int r = 0; r < E; ++r) {
         const int idx = threadIdx.x + r * NT;
-        lds[(idx / U) * LDU + idx % U] = vin[r];
+        lds[(idx / U) * LDU + idx % U] = Ar::bits(vin[r]);
     }
     __syncthreads();
-    ntt_rounds<A, FWD, !FWD, 0, false, E, kTwCached>(lds, LDU, threadIdx.x % U, threadIdx.x / U, 1u, tw, pc, twc);
+    ntt_rounds<Ar, A, FWD, !FWD, 0, E, kTwCached>(lds, LDU, threadIdx.x % U, threadIdx.x / U, 1u, tw, ar, twc);
 #pragma unroll
     for (int r = 0; r < E; ++r) {
         const int idx = threadIdx.x + r * NT;
         const uint64_t x = lds[(idx / U) * LDU + idx % U];
-        out[((size_t)(idx / U) << B) + col0 + idx % U] = FWD ? x : csub(x, pc.q);
+        out[((size_t)(idx / U) << B) + col0 + idx % U] = FWD ? x : ar.canon_last(Ar::raw(x));
     }
     __syncthreads();
 }
 
-template <int A, int B, bool FWD, int TILE, int E>
-__device__ __forceinline__ void ntt_cols_small(uint64_t *lds, const uint64_t *in, uint64_t *out,
-                                               const TwPair *__restrict__ tw, const PrimeConst &pc, int tile) {
-    ntt_cols_small_pro<A, B, FWD, TILE, E>(lds, LoadPro{in}, out, tw, pc, tile);
+template <int A, int B, bool FWD, int TILE, int E, typename Pro>
+__device__ __forceinline__ void ntt_cols_small_pro(uint64_t *lds, const Pro &pro, uint64_t *out,
+                                                   const TwPair *__restrict__ tw, const PrimeConst &pc, bool fp, int tile) {
+    if (fp) ntt_cols_small_t<ArFp, A, B, FWD, TILE, E>(lds, pro, out, tw, ArFp(pc), tile);
+    else ntt_cols_small_t<ArInt, A, B, FWD, TILE, E>(lds, pro, out, tw, ArInt(pc), tile);
 }
 
-// The result for limb index idx (forward: in [0, q); inverse: lazy in [0, 2q))
-// goes through epi(idx, value), or, when Epi::kPrefetch, through
+template <int A, int B, bool FWD, int TILE, int E>
+__device__ __forceinline__ void ntt_cols_small(uint64_t *lds, const uint64_t *in, uint64_t *out,
+                                               const TwPair *__restrict__ tw, const PrimeConst &pc, bool fp, int tile) {
+    ntt_cols_small_pro<A, B, FWD, TILE, E>(lds, PlainPro<FWD>{in}, out, tw, pc, fp, tile);
+}
+
+// The result for limb index idx goes through epi (integer: in [0, q) forward,
+// lazy in [0, 2q) inverse), or, when Epi::kPrefetch, through
 // epi.finish(idx, value, epi.operand(idx)) with the operand loaded at the start.
-template <int A, int B, bool FWD, int TILE, int E, typename Pro, typename Epi>
-__device__ __forceinline__ void ntt_rows_small_pe(uint64_t *lds, const Pro &pro, const TwPair *__restrict__ tw,
-                                                  const PrimeConst &pc, int tile, const Epi &epi) {
+template <typename Ar, int A, int B, bool FWD, int TILE, int E, typename Pro, typename Epi>
+__device__ __forceinline__ void ntt_rows_small_t(uint64_t *lds, const Pro &pro, const TwPair *__restrict__ tw_all,
+                                                 const Ar &ar, int tile, const Epi &epi) {
+    using V = typename Ar::V;
     constexpr int S = 1 << B, U = TILE >> B, LDU = U + 1, NT = TILE / E;
     static_assert(U >= 1 && NT >= 64, "small row tile");
     const int row0 = tile * U;
-    uint64_t vin[E];
+    const auto *tw = twiddles<Ar>(tw_all);
+    V vin[E];
 #pragma unroll
     for (int r = 0; r < E; ++r) {
         const int idx = threadIdx.x + r * NT;
-        vin[r] = pro(((size_t)(row0 + (idx >> B)) << B) + (idx & (S - 1)));
+        vin[r] = pass_in(pro, ((size_t)(row0 + (idx >> B)) << B) + (idx & (S - 1)), ar);
     }
     // an epilogue that reads an operand of its own (the ModDown and rescale
     // tails) has it loaded here, with the tile, instead of after the last
@@ -346,34 +452,42 @@ __device__ __forceinline__ void ntt_rows_small_pe(uint64_t *lds, const Pro &pro,
         }
     }
     const int u = threadIdx.x % U;
-    TwPair twc[tw_slots(B, E)];
-    ntt_rounds<B, FWD, false, 0, false, E, kTwPrefetch>(lds, LDU, u, threadIdx.x / U, (1u << A) + row0 + u, tw, pc,
-                                                        twc);
+    typename Ar::Tw twc[tw_slots(B, E)];
+    ntt_rounds<Ar, B, FWD, false, 0, E, kTwPrefetch>(lds, LDU, u, threadIdx.x / U, (1u << A) + row0 + u, tw, ar, twc);
 #pragma unroll
     for (int r = 0; r < E; ++r) {
         const int idx = threadIdx.x + r * NT;
-        lds[(idx & (S - 1)) * LDU + (idx >> B)] = vin[r];
+        lds[(idx & (S - 1)) * LDU + (idx >> B)] = Ar::bits(vin[r]);
     }
     __syncthreads();
-    ntt_rounds<B, FWD, false, 0, false, E, kTwCached>(lds, LDU, u, threadIdx.x / U, (1u << A) + row0 + u, tw, pc,
-                                                      twc);
-    const uint64_t q2 = 2 * pc.q;
+    ntt_rounds<Ar, B, FWD, false, 0, E, kTwCached>(lds, LDU, u, threadIdx.x / U, (1u << A) + row0 + u, tw, ar, twc);
 #pragma unroll
     for (int r = 0; r < E; ++r) {
         const int idx = threadIdx.x + r * NT;
-        const uint64_t x = lds[(idx & (S - 1)) * LDU + (idx >> B)];
+        V v = Ar::raw(lds[(idx & (S - 1)) * LDU + (idx >> B)]);
         const size_t gi = ((size_t)(row0 + (idx >> B)) << B) + (idx & (S - 1));
-        const uint64_t v = FWD ? csub(csub(x, q2), pc.q) : x;
-        if constexpr (Epi::kPrefetch) epi.finish(gi, v, opnd[r]);
-        else epi(gi, v);
+        if constexpr (!Ar::kFp && FWD) v = csub(csub(v, ar.q2), ar.q);
+        if constexpr (Epi::kPrefetch) {
+            if constexpr (Ar::kFp) epi.finish_fp(gi, v, opnd[r], ar.f);
+            else epi.finish(gi, v, opnd[r]);
+        } else {
+            pass_out(epi, gi, v, ar);
+        }
     }
     __syncthreads();
 }
 
+template <int A, int B, bool FWD, int TILE, int E, typename Pro, typename Epi>
+__device__ __forceinline__ void ntt_rows_small_pe(uint64_t *lds, const Pro &pro, const TwPair *__restrict__ tw,
+                                                  const PrimeConst &pc, bool fp, int tile, const Epi &epi) {
+    if (fp) ntt_rows_small_t<ArFp, A, B, FWD, TILE, E>(lds, pro, tw, ArFp(pc), tile, epi);
+    else ntt_rows_small_t<ArInt, A, B, FWD, TILE, E>(lds, pro, tw, ArInt(pc), tile, epi);
+}
+
 template <int A, int B, bool FWD, int TILE, int E>
 __device__ __forceinline__ void ntt_rows_small(uint64_t *lds, const uint64_t *in, uint64_t *out,
-                                               const TwPair *__restrict__ tw, const PrimeConst &pc, int tile) {
-    ntt_rows_small_pe<A, B, FWD, TILE, E>(lds, LoadPro{in}, tw, pc, tile, StoreEpi{out});
+                                               const TwPair *__restrict__ tw, const PrimeConst &pc, bool fp, int tile) {
+    ntt_rows_small_pe<A, B, FWD, TILE, E>(lds, PlainPro<!FWD>{in}, tw, pc, fp, tile, RowStore<FWD>{out});
 }
 
 // Column pass: sub-transforms are columns (2^A rows, stride 2^B), tile
@@ -388,8 +502,8 @@ __device__ __forceinline__ void ntt_rows_small(uint64_t *lds, const uint64_t *in
 // (ntt_cols_compute): the prologue's temporaries are dead before the transform
 // starts, which keeps the multi-pass batched kernels within their register
 // budget.
-template <int A, int B, bool FWD, typename Pro>
-__device__ __forceinline__ void ntt_cols_load(uint64_t (&regs)[kElems], int tile, const Pro &pro) {
+template <typename Ar, int A, int B, bool FWD, typename Pro>
+__device__ __forceinline__ void ntt_cols_load(typename Ar::V (&regs)[kElems], int tile, const Pro &pro, const Ar &ar) {
     static_assert(A > kElemsLog && A <= 2 * kElemsLog, "two rounds");
     constexpr int U = kTile >> A;
     constexpr int C2 = A - kElemsLog;  // stages of the second round
@@ -399,31 +513,32 @@ __device__ __forceinline__ void ntt_cols_load(uint64_t (&regs)[kElems], int tile
         // The first forward round works on rows t + e 2^(A-4) of column u, the
         // order in which the tile arrives: it starts from registers.
 #pragma unroll
-        for (int e = 0; e < kElems; ++e) regs[e] = pro(((size_t)(t + (e << C2)) << B) + col0 + u);
+        for (int e = 0; e < kElems; ++e) regs[e] = pass_in(pro, ((size_t)(t + (e << C2)) << B) + col0 + u, ar);
     } else {
 #pragma unroll
         for (int r = 0; r < kTile / kThreads; ++r) {
             const int idx = threadIdx.x + r * kThreads;
-            regs[r] = pro(((size_t)(idx / U) << B) + col0 + idx % U);
+            regs[r] = pass_in(pro, ((size_t)(idx / U) << B) + col0 + idx % U, ar);
         }
     }
 }
 
-// Ends with a barrier, so lds may be reused at once.  LZ: see ct_bfly; the
-// forward output is then lazy below (4 + 2A) q.
-template <int A, int B, bool FWD, bool LZ>
-__device__ __forceinline__ void ntt_cols_compute_t(uint64_t *lds, uint64_t *out, const TwPair *__restrict__ tw,
-                                                   const PrimeConst &pc, int tile, uint64_t (&regs)[kElems]) {
+// Ends with a barrier, so lds may be reused at once.  The forward output is
+// left as Ar's bits (integer: lazy below 4q).
+template <typename Ar, int A, int B, bool FWD>
+__device__ __forceinline__ void ntt_cols_compute(uint64_t *lds, uint64_t *out, const TwPair *__restrict__ tw_all,
+                                                 const Ar &ar, int tile, typename Ar::V (&regs)[kElems]) {
     constexpr int S = 1 << A;
     constexpr int U = kTile / S;
     constexpr int LDU = U + 1;
     constexpr int C2 = A - kElemsLog;
     const int col0 = tile * U;
     const int u = threadIdx.x % U, t = threadIdx.x / U;
+    const auto *tw = twiddles<Ar>(tw_all);
     if constexpr (FWD) {
-        ntt_round<A, 0, kElemsLog, true, false, 0, true, false, LZ>(lds, LDU, u, t, 1u, tw, pc, regs);
+        ntt_round<Ar, A, 0, kElemsLog, true, false, 0, true, false>(lds, LDU, u, t, 1u, tw, ar, regs);
         __syncthreads();
-        ntt_round<A, kElemsLog, C2, true, false, 0, false, false, LZ>(lds, LDU, u, t, 1u, tw, pc);
+        ntt_round<Ar, A, kElemsLog, C2, true, false, 0, false, false>(lds, LDU, u, t, 1u, tw, ar);
         __syncthreads();
 #pragma unroll
         for (int r = 0; r < kTile / kThreads; ++r) {
@@ -435,61 +550,60 @@ __device__ __forceinline__ void ntt_cols_compute_t(uint64_t *lds, uint64_t *out,
 #pragma unroll
         for (int r = 0; r < kTile / kThreads; ++r) {
             const int idx = threadIdx.x + r * kThreads;
-            lds[(idx / U) * LDU + idx % U] = regs[r];
+            lds[(idx / U) * LDU + idx % U] = Ar::bits(regs[r]);
         }
         __syncthreads();
-        ntt_round<A, 0, kElemsLog, false, false, 0, false, false, LZ>(lds, LDU, u, t, 1u, tw, pc);
+        ntt_round<Ar, A, 0, kElemsLog, false, false, 0, false, false>(lds, LDU, u, t, 1u, tw, ar);
         __syncthreads();
         // The last inverse round leaves rows grp + 16 e (grp = t NG + gi) of
         // column u in registers, the order of a coalesced store.
-        ntt_round<A, kElemsLog, C2, false, true, 0, false, true, LZ>(lds, LDU, u, t, 1u, tw, pc, regs);
+        ntt_round<Ar, A, kElemsLog, C2, false, true, 0, false, true>(lds, LDU, u, t, 1u, tw, ar, regs);
         constexpr int G = 1 << C2, NG = kElems / G;
 #pragma unroll
         for (int gi = 0; gi < NG; ++gi)
 #pragma unroll
             for (int e = 0; e < G; ++e) {
                 const int row = t * NG + gi + (e << kElemsLog);
-                out[((size_t)row << B) + col0 + u] = csub(regs[gi * G + e], pc.q);
+                out[((size_t)row << B) + col0 + u] = ar.canon_last(regs[gi * G + e]);
             }
     }
     __syncthreads();
 }
 
-// LZOK: the butterflies skip the sum corrections for primes below
-// kLazyPrimeBound (the prime is uniform across the workgroup: a scalar
-// branch).  Worth it only in passes whose prologue or epilogue adds ALU work
-// (the two code paths cost registers, so occupancy); the forward column and
-// row passes of a limb must agree on it (the column output range differs).
-template <int A, int B, bool FWD, bool LZOK = false>
-__device__ __forceinline__ void ntt_cols_compute(uint64_t *lds, uint64_t *out, const TwPair *__restrict__ tw,
-                                                 const PrimeConst &pc, int tile, uint64_t (&regs)[kElems]) {
-    if (LZOK && pc.q < kLazyPrimeBound) ntt_cols_compute_t<A, B, FWD, true>(lds, out, tw, pc, tile, regs);
-    else ntt_cols_compute_t<A, B, FWD, false>(lds, out, tw, pc, tile, regs);
+template <typename Ar, int A, int B, bool FWD, typename Pro>
+__device__ __forceinline__ void ntt_cols_unit_t(uint64_t *lds, uint64_t *out, const TwPair *__restrict__ tw,
+                                                const Ar &ar, int tile, const Pro &pro) {
+    typename Ar::V regs[kElems];
+    ntt_cols_load<Ar, A, B, FWD>(regs, tile, pro, ar);
+    ntt_cols_compute<Ar, A, B, FWD>(lds, out, tw, ar, tile, regs);
 }
 
-template <int A, int B, bool FWD, bool LZOK = false, typename Pro>
+// The prime decides the arithmetic (fp: it is below kFpPrimeBound; uniform
+// across the workgroup, a scalar branch).
+template <int A, int B, bool FWD, typename Pro>
 __device__ __forceinline__ void ntt_cols_unit_pro(uint64_t *lds, uint64_t *out, const TwPair *__restrict__ tw,
-                                                  const PrimeConst &pc, int tile, const Pro &pro) {
-    uint64_t regs[kElems];
-    ntt_cols_load<A, B, FWD>(regs, tile, pro);
-    ntt_cols_compute<A, B, FWD, LZOK>(lds, out, tw, pc, tile, regs);
+                                                  const PrimeConst &pc, bool fp, int tile, const Pro &pro) {
+    if (fp) ntt_cols_unit_t<ArFp, A, B, FWD>(lds, out, tw, ArFp(pc), tile, pro);
+    else ntt_cols_unit_t<ArInt, A, B, FWD>(lds, out, tw, ArInt(pc), tile, pro);
 }
 
 template <int A, int B, bool FWD>
 __device__ __forceinline__ void ntt_cols_unit(uint64_t *lds, const uint64_t *in, uint64_t *out,
-                                              const TwPair *__restrict__ tw, const PrimeConst &pc, int tile) {
-    ntt_cols_unit_pro<A, B, FWD>(lds, out, tw, pc, tile, LoadPro{in});
+                                              const TwPair *__restrict__ tw, const PrimeConst &pc, bool fp, int tile) {
+    ntt_cols_unit_pro<A, B, FWD>(lds, out, tw, pc, fp, tile, PlainPro<FWD>{in});
 }
 
 // Rescale / modulus-switch lift as the prologue of the NTT of the lifted limb:
 // the last limb x (coefficient domain, in [0, q_l)) taken from its centred
 // representative into prime q: [x]_q, + (q - [q_l]_q) when x > q_l / 2, lazy in
 // [0, 3q).  KEEP_T (BGV): x is first replaced by [x t^-1]_{q_l} and the result
-// multiplied by t (lazy in [0, 2q)), so the lift is 0 mod t as well.
+// multiplied by t (lazy in [0, 2q)), so the lift is 0 mod t as well.  In FP64
+// the centred representative of a q_l below kFpPrimeBound is an input as it is.
 template <bool KEEP_T>
 struct LiftPro {
     const uint64_t *last;
     uint64_t ql, ql_half, tinv, tinv_p;  // dropped prime q_l, t^-1 mod q_l
+    double qld;                          // q_l in FP64
     uint64_t q, one_p, corr, tmod, tmod_p;
     __device__ __forceinline__ uint64_t operator()(size_t idx) const {
         uint64_t x = last[idx];
@@ -498,6 +612,12 @@ struct LiftPro {
         if (x > ql_half) r += corr;
         if (KEEP_T) r = shoup_lazy(r, tmod, tmod_p, q);
         return r;
+    }
+    __device__ __forceinline__ double fp(size_t idx, const FpMod &) const {
+        if (KEEP_T || ql >= kFpPrimeBound) return FpMod::from_u52((*this)(idx));
+        const uint64_t x = last[idx];
+        const double d = FpMod::from_u52(x);
+        return x > ql_half ? d - qld : d;
     }
 };
 
@@ -527,6 +647,7 @@ struct ModdownPro {
         acc.add(cnt * negp);
         return reduce128_lazy(acc.value(), q, r64, r64_p, one_p);
     }
+    __device__ __forceinline__ double fp(size_t idx, const FpMod &) const { return FpMod::from_u52((*this)(idx)); }
 };
 
 // Row pass: sub-transforms are rows (2^B contiguous residues), tile `tile`
@@ -534,73 +655,73 @@ struct ModdownPro {
 // [0, q)); inverse: the first B stages (output lazy in [0, 2q)).  The result
 // for limb index idx goes through epi(idx, value).  Split into loads and the
 // rest like the column pass.
-template <int A, int B, typename Pro>
-__device__ __forceinline__ void ntt_rows_load(uint64_t (&regs)[kElems], int tile, const Pro &pro) {
+template <typename Ar, int A, int B, typename Pro>
+__device__ __forceinline__ void ntt_rows_load(typename Ar::V (&regs)[kElems], int tile, const Pro &pro, const Ar &ar) {
     constexpr int S = 1 << B;
     constexpr int U = kTile / S;
     const int row0 = tile * U;
 #pragma unroll
     for (int r = 0; r < kTile / kThreads; ++r) {
         const int idx = threadIdx.x + r * kThreads;
-        regs[r] = pro(((size_t)(row0 + (idx >> B)) << B) + (idx & (S - 1)));
+        regs[r] = pass_in(pro, ((size_t)(row0 + (idx >> B)) << B) + (idx & (S - 1)), ar);
     }
 }
 
-template <int A, int B, bool FWD, bool LZ, typename Epi>
-__device__ __forceinline__ void ntt_rows_compute_t(uint64_t *lds, const TwPair *__restrict__ tw, const PrimeConst &pc,
-                                                   int tile, const Epi &epi, uint64_t (&regs)[kElems]) {
+template <typename Ar, int A, int B, bool FWD, typename Epi>
+__device__ __forceinline__ void ntt_rows_compute(uint64_t *lds, const TwPair *__restrict__ tw_all, const Ar &ar,
+                                                 int tile, const Epi &epi, typename Ar::V (&regs)[kElems]) {
     constexpr int S = 1 << B;
     constexpr int U = kTile / S;
     constexpr int LDU = U + 1;
     const int row0 = tile * U;
+    const auto *tw = twiddles<Ar>(tw_all);
 #pragma unroll
     for (int r = 0; r < kTile / kThreads; ++r) {
         const int idx = threadIdx.x + r * kThreads;
-        lds[(idx & (S - 1)) * LDU + (idx >> B)] = regs[r];
+        lds[(idx & (S - 1)) * LDU + (idx >> B)] = Ar::bits(regs[r]);
     }
     __syncthreads();
     const int u = threadIdx.x % U, t = threadIdx.x / U;
-    ntt_rounds<B, FWD, false, A, LZ>(lds, LDU, u, t, (1u << A) + row0 + u, tw, pc);
-    const uint64_t q2 = 2 * pc.q;
+    ntt_rounds<Ar, B, FWD, false, A>(lds, LDU, u, t, (1u << A) + row0 + u, tw, ar);
 #pragma unroll
     for (int r = 0; r < kTile / kThreads; ++r) {
         const int idx = threadIdx.x + r * kThreads;
         const int row = idx >> B, p = idx & (S - 1);
-        uint64_t x = lds[p * LDU + row];
-        // LZ values lie below 2^59: one Shoup reduction by 1 brings them to [0, 2q)
-        if (LZ) x -= mulhi64(x, pc.one_p) * pc.q;
-        if (FWD) x = csub(LZ ? x : csub(x, q2), pc.q);
-        epi(((size_t)(row0 + row) << B) + p, x);
+        typename Ar::V x = Ar::raw(lds[p * LDU + row]);
+        if constexpr (!Ar::kFp) {
+            if (FWD) x = csub(csub(x, ar.q2), ar.q);
+        }
+        pass_out(epi, ((size_t)(row0 + row) << B) + p, x, ar);
     }
     __syncthreads();
 }
 
-// LZOK: as for ntt_cols_compute.
-template <int A, int B, bool FWD, typename Epi, bool LZOK = false>
-__device__ __forceinline__ void ntt_rows_compute(uint64_t *lds, const TwPair *__restrict__ tw, const PrimeConst &pc,
-                                                 int tile, const Epi &epi, uint64_t (&regs)[kElems]) {
-    if (LZOK && pc.q < kLazyPrimeBound) ntt_rows_compute_t<A, B, FWD, true>(lds, tw, pc, tile, epi, regs);
-    else ntt_rows_compute_t<A, B, FWD, false>(lds, tw, pc, tile, epi, regs);
+template <typename Ar, int A, int B, bool FWD, typename Pro, typename Epi>
+__device__ __forceinline__ void ntt_rows_unit_t(uint64_t *lds, const Pro &pro, const TwPair *__restrict__ tw,
+                                                const Ar &ar, int tile, const Epi &epi) {
+    typename Ar::V regs[kElems];
+    ntt_rows_load<Ar, A, B>(regs, tile, pro, ar);
+    ntt_rows_compute<Ar, A, B, FWD>(lds, tw, ar, tile, epi, regs);
 }
 
-template <int A, int B, bool FWD, bool LZOK = false, typename Pro, typename Epi>
+template <int A, int B, bool FWD, typename Pro, typename Epi>
 __device__ __forceinline__ void ntt_rows_unit_pe(uint64_t *lds, const Pro &pro, const TwPair *__restrict__ tw,
-                                                 const PrimeConst &pc, int tile, const Epi &epi) {
-    uint64_t regs[kElems];
-    ntt_rows_load<A, B>(regs, tile, pro);
-    ntt_rows_compute<A, B, FWD, Epi, LZOK>(lds, tw, pc, tile, epi, regs);
+                                                 const PrimeConst &pc, bool fp, int tile, const Epi &epi) {
+    if (fp) ntt_rows_unit_t<ArFp, A, B, FWD>(lds, pro, tw, ArFp(pc), tile, epi);
+    else ntt_rows_unit_t<ArInt, A, B, FWD>(lds, pro, tw, ArInt(pc), tile, epi);
 }
 
-template <int A, int B, bool FWD, bool LZOK = false, typename Epi>
+// The last forward pass with an epilogue of its own, on what the column pass left.
+template <int A, int B, typename Epi>
 __device__ __forceinline__ void ntt_rows_unit_epi(uint64_t *lds, const uint64_t *in, const TwPair *__restrict__ tw,
-                                                  const PrimeConst &pc, int tile, const Epi &epi) {
-    ntt_rows_unit_pe<A, B, FWD, LZOK>(lds, LoadPro{in}, tw, pc, tile, epi);
+                                                  const PrimeConst &pc, bool fp, int tile, const Epi &epi) {
+    ntt_rows_unit_pe<A, B, true>(lds, RawPro{in}, tw, pc, fp, tile, epi);
 }
 
 template <int A, int B, bool FWD>
 __device__ __forceinline__ void ntt_rows_unit(uint64_t *lds, const uint64_t *in, uint64_t *out,
-                                              const TwPair *__restrict__ tw, const PrimeConst &pc, int tile) {
-    ntt_rows_unit_epi<A, B, FWD>(lds, in, tw, pc, tile, StoreEpi{out});
+                                              const TwPair *__restrict__ tw, const PrimeConst &pc, bool fp, int tile) {
+    ntt_rows_unit_pe<A, B, FWD>(lds, PlainPro<!FWD>{in}, tw, pc, fp, tile, RowStore<FWD>{out});
 }
 
 // HMult: d2 = a1 b1 mod q as the prologue of the INTT of d2 (the inner product
@@ -614,6 +735,9 @@ struct TensorPro {
         s2.mac(a1[idx], b1[idx]);
         return csub(reduce128_lazy(s2.value(), q, r64, r64_p, one_p), 2 * q);
     }
+    __device__ __forceinline__ double fp(size_t idx, const FpMod &f) const {
+        return f.mul(FpMod::from_u52(a1[idx]), FpMod::from_u52(b1[idx]));
+    }
 };
 
 // HRotate: sigma_g(a1) as the prologue of its INTT.
@@ -623,25 +747,11 @@ struct GatherPro {
     __device__ __forceinline__ uint64_t operator()(size_t idx) const {
         return in[galois_src((uint32_t)idx, galois, log_n)];
     }
+    __device__ __forceinline__ double fp(size_t idx, const FpMod &) const { return FpMod::from_u52((*this)(idx)); }
 };
 
-// ModDown tail as the epilogue of the last forward pass of NTT(conv):
-// out = (ip - NTT(conv)) * P^-1 mod q (+ add).  add may alias out.
-struct ModdownTailEpi {
-    static constexpr bool kPrefetch = false;
-    const uint64_t *ip;
-    const uint64_t *add;
-    uint64_t *out;
-    uint64_t pinv, pinv_p, q;
-    __device__ __forceinline__ void operator()(size_t idx, uint64_t conv) const {
-        uint64_t r = shoup(submod(ip[idx], conv, q), pinv, pinv_p, q);
-        if (add) r = addmod(r, add[idx], q);
-        out[idx] = r;
-    }
-};
-
-// The same tail when the inner product already left ip' = ip P^-1 + add:
-// out = ip' - NTT(conv) P^-1 mod q (one stream read besides the transform).
+// ModDown tail as the epilogue of the last forward pass of NTT(conv), the inner
+// product having left ip' = ip P^-1 + add: out = ip' - NTT(conv) P^-1 mod q.
 struct ModdownFoldEpi {
     // the small-tile row pass loads ip with its tile (operand), then finish
     static constexpr bool kPrefetch = true;
@@ -652,6 +762,10 @@ struct ModdownFoldEpi {
     __device__ __forceinline__ uint64_t operand(size_t idx) const { return ip[idx]; }
     __device__ __forceinline__ void finish(size_t idx, uint64_t conv, uint64_t ipv) const {
         out[idx] = submod(ipv, shoup(conv, pinv, pinv_p, q), q);
+    }
+    __device__ __forceinline__ void fp(size_t idx, double conv, const FpMod &f) const { finish_fp(idx, conv, ip[idx], f); }
+    __device__ __forceinline__ void finish_fp(size_t idx, double conv, uint64_t ipv, const FpMod &f) const {
+        out[idx] = f.canon(f.red(FpMod::from_u52(ipv) - f.mul(conv, f.centre(pinv))));
     }
 };
 
@@ -667,26 +781,22 @@ struct RescaleTailEpi {
     __device__ __forceinline__ void finish(size_t idx, uint64_t lift, uint64_t inv) const {
         out[idx] = shoup(submod(inv, lift, q), qlinv, qlinv_p, q);
     }
+    __device__ __forceinline__ void fp(size_t idx, double lift, const FpMod &f) const { finish_fp(idx, lift, in[idx], f); }
+    __device__ __forceinline__ void finish_fp(size_t idx, double lift, uint64_t inv, const FpMod &f) const {
+        out[idx] = f.canon(f.mul(FpMod::from_u52(inv) - lift, f.centre(qlinv)));
+    }
 };
 
-// Waves per SIMD the NTT kernels are compiled for.  Measured on MI355X at
-// N = 2^16: 4 (a 128-VGPR cap, four workgroups per CU) gains nothing on the row
-// pass and makes the column pass spill, so the passes are built for 3.
-#ifndef RF_NTT_WAVES_COLS
-#define RF_NTT_WAVES_COLS 3
-#endif
-#ifndef RF_NTT_WAVES_ROWS
-#define RF_NTT_WAVES_ROWS 3
-#endif
-constexpr int kNttWavesCols = RF_NTT_WAVES_COLS;
-constexpr int kNttWavesRows = RF_NTT_WAVES_ROWS;
-// The forward passes with the ModDown conversion / tail and the rescale lift /
-// tail (the lazy butterflies, two code paths): held to 4 waves per SIMD so
-// that they share the CUs with a concurrent stream as the other passes do.
-#ifndef RF_NTT_WAVES_FUSED
-#define RF_NTT_WAVES_FUSED 4
-#endif
-constexpr int kNttWavesFused = RF_NTT_WAVES_FUSED;
+// Waves per SIMD the 4096-tile passes are compiled for.  The sub-transforms of
+// 2^8 are held to 128 VGPRs, four workgroups per CU: a 60-limb launch at N =
+// 2^16 (960 workgroups) is then resident at once.  Measured there, 3 against 4
+// waves (130 and 128 VGPRs): forward columns 21.3 against 18.5 us, forward rows
+// 22.6 against 19.6 us.  The shorter row transforms would spill 13 to 43
+// registers, so they are built for 3.
+__host__ __device__ constexpr int ntt_waves(int sub_log) { return sub_log == 8 ? 4 : 3; }
+// The lift pass, and the ModDown pass of up to 4 special primes, fit 4 waves at
+// every size.
+constexpr int kNttWavesFused = 4;
 
 // LDS words a column or row unit needs (the largest tile: 2^8 x 17 padded).
 constexpr int kNttLdsWords = 256 * 17;

@@ -24,10 +24,33 @@ struct PrimeConst {
     uint64_t tinv, tinv_p;   // t^-1 mod q and companion
     uint64_t r64, r64_p;     // 2^64 mod q and companion
     uint64_t one_p;          // floor(2^64 / q): Shoup companion of 1
+    double qd, qinv;         // q and 1 / q in FP64 (primes below kFpPrimeBound; see FpMod)
 };
 
+// Twiddles.  A prime's table takes N pairs of memory; a prime below
+// kFpPrimeBound keeps N doubles (the twiddles in [-q/2, q/2]) at its start
+// instead: FP64 products need no companion, so a pass reads half the bytes.
 struct __align__(16) TwPair {
     uint64_t w, wp;  // twiddle and floor(w 2^62 / q) (the companion of shoup62_lazy)
+};
+
+// Which primes are below kFpPrimeBound, one bit per prime index, passed to the
+// kernels by value: the arithmetic of a limb is then known from the kernel
+// arguments, so its loads need not wait for the prime's constants to arrive.
+struct FpMask {
+    uint64_t m[4];
+    __host__ __device__ __forceinline__ bool has(uint32_t g) const {
+        const uint64_t w = g < 128 ? (g < 64 ? m[0] : m[1]) : (g < 192 ? m[2] : m[3]);
+        return (w >> (g & 63)) & 1;
+    }
+    bool any() const { return (m[0] | m[1] | m[2] | m[3]) != 0; }
+};
+// The mask of a context with no such prime (the exact schemes' 55-bit chain):
+// its kernels hold the integer code alone.  With both forms in every kernel the
+// few-limb passes of that chain took 2.5 % longer (HMult+Relin of 9 limbs at
+// N = 2^15, 115.6 against 112.4 us).
+struct NoFp {
+    __host__ __device__ __forceinline__ static constexpr bool has(uint32_t) { return false; }
 };
 
 // Launch description of a batched (I)NTT over limbs laid out as
@@ -83,6 +106,7 @@ struct rf_ctx {
     uint64_t t;
     std::vector<uint64_t> primes;  // L + K: q_0..q_{L-1}, p_0..p_{k-1}
     std::vector<uint64_t> psi;     // primitive 2N-th roots
+    rf::FpMask fp_mask{};          // primes below rf::kFpPrimeBound
     std::vector<rf::ModupLevel> modup_levels;  // index nl in [1, L]
     std::vector<rf_tuning> tuning;             // kernel variants per level nl in [1, L] (index 0 unused)
 
