@@ -129,8 +129,9 @@ static void free_tables(rf_ctx *c) {
     (void)hipFree(c->d_pmap_qb);
     (void)hipFree(c->d_client);
     (void)hipFree(c->d_garner);
+    (void)hipFree(c->d_garner_fp);
     (void)hipFree(c->d_zeta);
-    (void)hipFree(c->d_slot_idx);
+    (void)hipFree(c->d_slot_of);
 }
 
 extern "C" int rf_ctx_create(const rf_params *p, int device, rf_ctx **out) {
@@ -552,17 +553,24 @@ extern "C" int rf_ctx_create(const rf_params *p, int device, rf_ctx **out) {
     }
     // q_i^-1 mod q_j (i < j): balanced mixed-radix digits of the CRT composition
     std::vector<uint64_t> gar((size_t)c->L * c->L * 2, 0);
+    const size_t gstride = (size_t)c->L + kMaxCrtLimbs;
+    std::vector<double> gar_fp((2 + c->L) * gstride, 0.0);
+    for (size_t j = 0; j < gstride; ++j) {
+        gar_fp[2 * j] = j < c->L ? pc[j].qd : 1.0;
+        gar_fp[2 * j + 1] = j < c->L ? pc[j].qinv : 1.0;
+    }
     for (uint32_t i = 0; i < c->L; ++i)
         for (uint32_t j = i + 1; j < c->L; ++j) {
             const uint64_t qj = c->primes[j];
             const uint64_t v = inv_h(c->primes[i] % qj, qj);
             gar[((size_t)i * c->L + j) * 2] = v;
             gar[((size_t)i * c->L + j) * 2 + 1] = shoup_companion(v, qj);
+            if (qj < kFpPrimeBound) gar_fp[(2 + i) * gstride + j] = v > qj / 2 ? -(double)(qj - v) : (double)v;
         }
     // CKKS: zeta^k = exp(i pi k / N) for k < 2N and the slot positions of the
     // canonical embedding: slot j is the evaluation at zeta^(5^j)
     std::vector<double> zeta;
-    std::vector<uint32_t> slot_idx;
+    std::vector<uint32_t> slot_of;
     if (c->scheme == RF_CKKS) {
         zeta.resize(4 * (size_t)N);
         const long double pi = 3.141592653589793238462643383279502884L;
@@ -571,17 +579,19 @@ extern "C" int rf_ctx_create(const rf_params *p, int device, rf_ctx **out) {
             zeta[2 * k] = (double)cosl(ang);
             zeta[2 * k + 1] = (double)sinl(ang);
         }
-        slot_idx.resize(N / 2);
+        slot_of.resize(N);
         uint64_t x = 1;
         for (uint32_t j = 0; j < N / 2; ++j) {
-            slot_idx[j] = (uint32_t)((x - 1) / 2);
+            const uint32_t t = (uint32_t)((x - 1) / 2);
+            slot_of[t] = j;
+            slot_of[N - 1 - t] = j | 0x80000000u;
             x = x * 5 % (2 * (uint64_t)N);
         }
     }
 
     int rc = RF_OK;
-    if ((rc = upload(&c->d_client, cl)) || (rc = upload(&c->d_garner, gar)) ||
-        (!zeta.empty() && ((rc = upload(&c->d_zeta, zeta)) || (rc = upload(&c->d_slot_idx, slot_idx))))) {
+    if ((rc = upload(&c->d_client, cl)) || (rc = upload(&c->d_garner, gar)) || (rc = upload(&c->d_garner_fp, gar_fp)) ||
+        (!zeta.empty() && ((rc = upload(&c->d_zeta, zeta)) || (rc = upload(&c->d_slot_of, slot_of))))) {
         free_tables(c);
         delete c;
         return rc;

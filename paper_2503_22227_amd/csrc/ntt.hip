@@ -682,4 +682,33 @@ int launch_ntt(const rf_ctx *c, const NttBatch &b, bool forward, hipStream_t s, 
                             : launch_ntt_t(c, NoFp{}, b, forward, s, pcs, tn);
 }
 
+template <typename Fp>
+static int launch_intt_cols_t(const rf_ctx *c, Fp fpm, uint64_t *data, uint32_t nl, hipStream_t s) {
+    const NttBatch b{data, data, 0, 0, nl, 1, 0, nullptr};
+    const bool small = nl * (c->n / kTile) < kDefaultTuning.ntt_small_below;
+    ProfScope p(small ? "ntt_inv_cols_small" : "ntt_inv_cols", s);
+#define RF_IC(A, B)                                                                                              \
+    if (small)                                                                                                   \
+        hipLaunchKernelGGL((ntt_small_kernel<A, B, false, true, 1024, kSmallE, Fp>), dim3(c->n / 1024, nl),       \
+                           dim3(1024 / kSmallE), 0, s, b, fpm, c->d_tw_inv, c->d_pc);                            \
+    else                                                                                                         \
+        hipLaunchKernelGGL((ntt_cols_kernel<A, B, false, Fp>), dim3(c->n / kTile, nl), dim3(kThreads), 0, s, b,   \
+                           fpm, c->d_tw_inv, c->d_pc)
+    switch (c->log_n) {
+        case 13: RF_IC(7, 6); break;
+        case 14: RF_IC(7, 7); break;
+        case 15: RF_IC(8, 7); break;
+        case 16: RF_IC(8, 8); break;
+        default: return fail(RF_EUNSUPPORTED, "INTT column pass: ring degree");
+    }
+#undef RF_IC
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return fail(RF_EHIP, std::string("NTT launch: ") + hipGetErrorString(e));
+    return RF_OK;
+}
+
+int launch_intt_cols(const rf_ctx *c, uint64_t *data, uint32_t nl, hipStream_t s) {
+    return c->fp_mask.any() ? launch_intt_cols_t(c, c->fp_mask, data, nl, s) : launch_intt_cols_t(c, NoFp{}, data, nl, s);
+}
+
 }  // namespace rf

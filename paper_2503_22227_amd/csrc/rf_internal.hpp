@@ -12,6 +12,7 @@ namespace rf {
 
 constexpr int kMaxAlpha = 8;
 constexpr int kMaxBfvLimbs = 24;  // BFV: Q-primes and auxiliary primes the BEHZ kernels hold in registers
+constexpr uint32_t kMaxCrtLimbs = 32;  // limbs of a CRT composition
 constexpr int kMaxPrimes = 250;  // L + k, prime indices fit in a byte
 
 // Per-prime constants, device resident.  Prime index g < L is q_g, g >= L is p_{g-L}.
@@ -135,8 +136,10 @@ struct rf_ctx {
     // client side (key generation, encryption, decryption, encode / decode)
     uint64_t *d_client = nullptr;          // [L+K][4]: [P]_{p_g}, companion, [floor(Q_L / t)]_{p_g} (BFV), companion
     uint64_t *d_garner = nullptr;          // [L][L][2]: (q_i^-1 mod q_j, companion) for i < j
+    double *d_garner_fp = nullptr;         // [L + 32] pairs (q_j, 1 / q_j), then [L][L + 32]: q_i^-1 mod q_j in
+                                           // (-q_j/2, q_j/2), q_j below kFpPrimeBound; the last 32 columns padding
     double *d_zeta = nullptr;              // CKKS: [2N][2] (cos, sin)(pi k / N)
-    uint32_t *d_slot_idx = nullptr;        // CKKS: [N/2] (5^j mod 2N - 1) / 2
+    uint32_t *d_slot_of = nullptr;         // CKKS: [N] the slot j with 5^j = 2t + 1 mod 2N, or j | 2^31 with -5^j = 2t + 1
 };
 
 namespace rf {
@@ -214,6 +217,8 @@ int fail(int code, const std::string &msg);
 // tn: the level's kernel variants (null: the defaults).
 int launch_ntt(const rf_ctx *c, const NttBatch &b, bool forward, hipStream_t s, const PrimeConst *pcs = nullptr,
                const rf_tuning *tn = nullptr);
+// Second pass alone of the INTT of data [nl][N] over q_0.. (two-pass ring degrees, default variants).
+int launch_intt_cols(const rf_ctx *c, uint64_t *data, uint32_t nl, hipStream_t s);
 // ModDown after the inner product, two-pass ring degrees only: ip = [2][nl + K][N]
 // whose K P-limbs hold the INTT with d_pc_md (so already scaled by the input
 // factor).  The first forward pass computes the base conversion of each Q
