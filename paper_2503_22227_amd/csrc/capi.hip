@@ -70,9 +70,9 @@ NttBatch batch(const uint64_t *in, uint64_t *out, uint64_t in_stride, uint64_t o
 }
 
 // (KS_0(d), KS_1(d)) into out [2][nl][N]; add0/add1 (nullable) are added.
-// fused (two-pass ring degrees only): d is not materialised; the workspace's
-// d_coeff region already holds INTT(d) (launch_intt_first) and the inner
-// product takes d's residues and the addends from fused's sources.
+// fused: d is not materialised, d's residues and the addends come from fused's
+// sources; at two-pass ring degrees the workspace's d_coeff region already holds
+// INTT(d) (launch_intt_first).
 // d_coeff_in (nullable): d in the coefficient domain, given by the caller
 // (BFV's fast floor produces it), which replaces the INTT of d.
 int keyswitch_core(const rf_ctx *c, const uint64_t *d, const uint64_t *evk, uint64_t *out, uint32_t nl,
@@ -83,44 +83,32 @@ int keyswitch_core(const rf_ctx *c, const uint64_t *d, const uint64_t *evk, uint
     const ModupLevel &lv = c->modup_levels[nl];
     uint64_t *d_coeff = ws + l.d_coeff, *ext = ws + l.ext, *ip = ws + l.ip, *conv = ws + l.conv;
     int rc;
+    IpFold f;
+    if (fused) {
+        f = *fused;
+    } else {
+        f.add0 = add0;
+        f.add1 = add1;
+    }
+    if (c->log_n == 12) return launch_keyswitch_single(c, f, d, d_coeff_in, evk, d_coeff, ext, ip, out, nl, s);
     // ModUp: INTT of d, base conversion of each digit, NTT of the new limbs.
-    // Two-pass ring degrees: the INTT folds in the conversion's input factor
-    // (pc_modup; launch_intt_first does the same for the fused callers).
+    // The INTT folds in the conversion's input factor (pc_modup;
+    // launch_intt_first does the same for the fused callers).
     const rf_tuning &tn = level_tuning(c, nl);
-    const bool scaled = c->log_n > 12 && !d_coeff_in;
     if (!fused && !d_coeff_in &&
-        (rc = launch_ntt(c, batch(d, d_coeff, 0, 0, nl, 1, 0, nullptr), false, s, scaled ? pc_modup(c, nl) : nullptr,
-                         &tn)))
+        (rc = launch_ntt(c, batch(d, d_coeff, 0, 0, nl, 1, 0, nullptr), false, s, pc_modup(c, nl), &tn)))
         return rc;
-    if ((rc = launch_modup_bconv(c, d_coeff_in ? d_coeff_in : d_coeff, ext, nl, s, scaled, tn.modup_chunk))) return rc;
+    if ((rc = launch_modup_bconv(c, d_coeff_in ? d_coeff_in : d_coeff, ext, nl, s, !d_coeff_in, tn.modup_chunk))) return rc;
     if ((rc = launch_ntt(c, batch(ext, ext, 0, 0, lv.ext_limbs, 1, 0, c->d_pmaps + lv.pmap_off), true, s, nullptr, &tn)))
         return rc;
-    // ModDown: INTT of the P-limbs, base conversion to Q_l, NTT, subtract and scale by P^-1
+    // ModDown: the inner product applies P^-1 and the addends to its Q-limbs; the
+    // INTT of the P-limbs folds in the conversion's input factor; the conversion
+    // runs in the first pass of the NTT and the tail in its last pass
     const uint64_t ip_stride = (uint64_t)(nl + c->K) * N;
     const NttBatch pl = batch(ip + (size_t)nl * N, ip + (size_t)nl * N, ip_stride, ip_stride, c->K, 2, c->L, nullptr);
-    if (c->log_n > 12) {
-        // the inner product applies P^-1 and the addends to its Q-limbs; the INTT
-        // of the P-limbs folds in the conversion's input factor; the conversion
-        // runs in the first pass of the NTT and the tail in its last pass
-        IpFold f;
-        if (fused) {
-            f = *fused;
-        } else {
-            f.add0 = add0;
-            f.add1 = add1;
-        }
-        if ((rc = launch_inner_product(c, d, ext, evk, ip, nl, s, &f))) return rc;
-        if ((rc = launch_ntt(c, pl, false, s, c->d_pc_md, &tn))) return rc;
-        return launch_ntt_fwd_moddown(c, conv, ip, out, nl, s, &tn);
-    }
-    // inner product with the key over Q_l u P
-    if ((rc = launch_inner_product(c, d, ext, evk, ip, nl, s))) return rc;
-    if ((rc = launch_ntt(c, pl, false, s, nullptr, &tn))) return rc;
-    if ((rc = launch_moddown_bconv(c, ip, conv, nl, s))) return rc;
-    if ((rc = launch_ntt(c, batch(conv, conv, (uint64_t)nl * N, (uint64_t)nl * N, nl, 2, 0, nullptr), true, s, nullptr,
-                         &tn)))
-        return rc;
-    return launch_moddown_tail(c, ip, conv, add0, add1, out, nl, s);
+    if ((rc = launch_inner_product(c, d, ext, evk, ip, nl, s, &f))) return rc;
+    if ((rc = launch_ntt(c, pl, false, s, c->d_pc_md, &tn))) return rc;
+    return launch_ntt_fwd_moddown(c, conv, ip, out, nl, s, &tn);
 }
 
 }  // namespace
@@ -231,47 +219,34 @@ extern "C" int rf_hmult_relin(const rf_ctx *c, const uint64_t *a, const uint64_t
         if (nl != c->L) return fail(RF_ELEVEL, "rf_hmult_relin: BFV ciphertexts carry all L limbs");
         return bfv_hmult_relin(c, a, b, rlk, out, (uint64_t *)ws, s);
     }
-    const size_t poly = (size_t)nl * c->n;
-    uint64_t *d2 = (uint64_t *)ws;
-    uint64_t *ks_ws = d2 + poly;
-    if (c->log_n > 12) {
-        // d2 = a1 b1 is formed by the first pass of its INTT and, with d0 and d1,
-        // by the inner product
-        if ((rc = launch_intt_first(c, a, b, ks_ws + ks_layout(c, nl).d_coeff, 0, nl, s, &level_tuning(c, nl))))
-            return rc;
-        IpFold f;
-        f.mode = 1;
-        f.a = a;
-        f.b = b;
-        return keyswitch_core(c, nullptr, rlk, out, nl, nullptr, nullptr, ks_ws, s, &f);
-    }
-    if ((rc = launch_tensor(c, a, b, out, d2, nl, s))) return rc;
-    return keyswitch_core(c, d2, rlk, out, nl, out, out + poly, ks_ws, s);
+    // d2 = a1 b1 is formed by the first pass of its INTT and, with d0 and d1, by
+    // the inner product
+    uint64_t *ks_ws = (uint64_t *)ws + (size_t)nl * c->n;
+    if (c->log_n > 12 && (rc = launch_intt_first(c, a, b, ks_ws + ks_layout(c, nl).d_coeff, 0, nl, s,
+                                                 &level_tuning(c, nl))))
+        return rc;
+    IpFold f;
+    f.mode = 1;
+    f.a = a;
+    f.b = b;
+    return keyswitch_core(c, nullptr, rlk, out, nl, nullptr, nullptr, ks_ws, s, &f);
 }
 
-// HRotate of an NTT-domain ciphertext (CKKS, BGV) into out; ws holds the
-// automorphism of polynomial 1 and the key-switch workspace.
+// HRotate of an NTT-domain ciphertext (CKKS, BGV) into out.
 static int rotate_ntt(const rf_ctx *c, const uint64_t *in, uint32_t galois, const uint64_t *gk, uint64_t *out,
                       uint32_t nl, uint64_t *ws, hipStream_t s) {
     int rc;
-    const size_t poly = (size_t)nl * c->n;
-    uint64_t *d = ws;
-    uint64_t *ks_ws = d + poly;
-    if (c->log_n > 12) {
-        // sigma_g(a1) is gathered by the first pass of its INTT and, with sigma_g(a0),
-        // by the inner product
-        if ((rc = launch_intt_first(c, in, nullptr, ks_ws + ks_layout(c, nl).d_coeff, galois, nl, s,
-                                    &level_tuning(c, nl))))
-            return rc;
-        IpFold f;
-        f.mode = 2;
-        f.a = in;
-        f.galois = galois;
-        return keyswitch_core(c, nullptr, gk, out, nl, nullptr, nullptr, ks_ws, s, &f);
-    }
-    if ((rc = launch_automorphism(c, in, out, galois, nl, 1, s))) return rc;
-    if ((rc = launch_automorphism(c, in + poly, d, galois, nl, 1, s))) return rc;
-    return keyswitch_core(c, d, gk, out, nl, out, nullptr, ks_ws, s);
+    // sigma_g(a1) is gathered by the first pass of its INTT and, with sigma_g(a0),
+    // by the inner product
+    uint64_t *ks_ws = ws + (size_t)nl * c->n;
+    if (c->log_n > 12 && (rc = launch_intt_first(c, in, nullptr, ks_ws + ks_layout(c, nl).d_coeff, galois, nl, s,
+                                                 &level_tuning(c, nl))))
+        return rc;
+    IpFold f;
+    f.mode = 2;
+    f.a = in;
+    f.galois = galois;
+    return keyswitch_core(c, nullptr, gk, out, nl, nullptr, nullptr, ks_ws, s, &f);
 }
 
 extern "C" int rf_rotate(const rf_ctx *c, const uint64_t *in, uint32_t galois, const uint64_t *gk, uint64_t *out,
@@ -333,26 +308,22 @@ static int divide_last(const rf_ctx *c, const uint64_t *in, uint64_t *out, uint3
     uint64_t *last = (uint64_t *)ws;         // [2][N]
     uint64_t *lift = last + 2 * N;           // [2][nl-1][N]
     const uint64_t in_stride = (uint64_t)nl * N;
-    const rf_tuning &tn = level_tuning(c, nl);
-    if ((rc = launch_ntt(c, batch(in + (size_t)(nl - 1) * N, last, in_stride, N, 1, 2, nl - 1, nullptr), false, s,
-                         nullptr, &tn)))
-        return rc;
     // out has a smaller polynomial stride than in: when they overlap, compute in
     // the workspace and copy the result over.
     const bool overlap = (const void *)out < (const void *)(in + 2 * (size_t)nl * N) &&
                          (const void *)in < (const void *)(out + 2 * (size_t)(nl - 1) * N);
-    if (c->log_n > 12) {
-        // the lift runs in the first pass of the NTT and the tail in its last pass
-        if (!overlap) return launch_ntt_fwd_rescale(c, last, lift, in, out, nl, keep_t, s, &tn);
-        if ((rc = launch_ntt_fwd_rescale(c, last, lift, in, lift, nl, keep_t, s, &tn))) return rc;
+    uint64_t *to = overlap ? lift : out;
+    if (c->log_n == 12) {
+        rc = launch_divide_single(c, in, to, nl, keep_t, s);
     } else {
-        if ((rc = launch_rescale_lift(c, last, lift, nl, keep_t, s))) return rc;
-        if ((rc = launch_ntt(c, batch(lift, lift, (uint64_t)(nl - 1) * N, (uint64_t)(nl - 1) * N, nl - 1, 2, 0,
-                                      nullptr), true, s, nullptr, &tn)))
+        const rf_tuning &tn = level_tuning(c, nl);
+        if ((rc = launch_ntt(c, batch(in + (size_t)(nl - 1) * N, last, in_stride, N, 1, 2, nl - 1, nullptr), false, s,
+                             nullptr, &tn)))
             return rc;
-        if (!overlap) return launch_rescale_tail(c, in, lift, out, nl, s);
-        if ((rc = launch_rescale_tail(c, in, lift, lift, nl, s))) return rc;
+        // the lift runs in the first pass of the NTT and the tail in its last pass
+        rc = launch_ntt_fwd_rescale(c, last, lift, in, to, nl, keep_t, s, &tn);
     }
+    if (rc || !overlap) return rc;
     if (hipMemcpyAsync(out, lift, 2 * (size_t)(nl - 1) * N * 8, hipMemcpyDeviceToDevice, s) != hipSuccess)
         return fail(RF_EHIP, "copy of the divided ciphertext");
     return RF_OK;

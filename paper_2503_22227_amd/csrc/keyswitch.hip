@@ -68,37 +68,6 @@ __global__ __launch_bounds__(kEw) void inner_product_kernel(const uint64_t *__re
     inner_product_unit<V>(d, ext, evk, ip, pcs, log_n, nl, L, K, alpha, blockIdx.x, blockIdx.y, fold);
 }
 
-__global__ __launch_bounds__(kEw) void moddown_bconv_kernel(const uint64_t *__restrict__ ip, uint64_t *__restrict__ conv,
-                                                            const PrimeConst *__restrict__ pcs,
-                                                            const uint64_t *__restrict__ tab, uint32_t log_n,
-                                                            uint32_t nl, uint32_t L, uint32_t K) {
-    moddown_bconv_unit(ip, conv, pcs, tab, log_n, nl, L, K, blockIdx.x, blockIdx.y);
-}
-
-__global__ __launch_bounds__(kEw) void moddown_tail_kernel(const uint64_t *__restrict__ ip,
-                                                           const uint64_t *__restrict__ conv, const uint64_t *add0,
-                                                           const uint64_t *add1, uint64_t *out,
-                                                           const PrimeConst *__restrict__ pcs,
-                                                           const uint64_t *__restrict__ pinv, uint32_t log_n,
-                                                           uint32_t nl, uint32_t K) {
-    moddown_tail_unit(ip, conv, add0, add1, out, pcs, pinv, log_n, nl, K, blockIdx.x, blockIdx.y);
-}
-
-template <bool KEEP_T>
-__global__ __launch_bounds__(kEw) void rescale_lift_kernel(const uint64_t *__restrict__ last, uint64_t *__restrict__ lift,
-                                                           const PrimeConst *__restrict__ pcs,
-                                                           const uint64_t *__restrict__ tab, uint32_t log_n,
-                                                           uint32_t nl, uint32_t L) {
-    rescale_lift_unit<KEEP_T>(last, lift, pcs, tab, log_n, nl, L, blockIdx.x, blockIdx.y);
-}
-
-__global__ __launch_bounds__(kEw) void rescale_tail_kernel(const uint64_t *__restrict__ in, const uint64_t *lift,
-                                                           uint64_t *out, const PrimeConst *__restrict__ pcs,
-                                                           const uint64_t *__restrict__ tab, uint32_t log_n,
-                                                           uint32_t nl, uint32_t L) {
-    rescale_tail_unit(in, lift, out, pcs, tab, log_n, nl, L, blockIdx.x, blockIdx.y);
-}
-
 __global__ __launch_bounds__(kEw) void automorphism_kernel(const uint64_t *__restrict__ in, uint64_t *__restrict__ out,
                                                            uint32_t galois, uint32_t log_n) {
     automorphism_unit(in, out, galois, log_n, blockIdx.x, blockIdx.y);
@@ -188,42 +157,6 @@ int launch_inner_product(const rf_ctx *c, const uint64_t *d, const uint64_t *ext
     hipLaunchKernelGGL(inner_product_kernel<kIpVec>, dim3(c->n / (kEw * kIpVec), nl + c->K), dim3(kEw), 0, s, d, ext,
                        evk, ip, c->d_pc, c->log_n, nl, c->L, c->K, c->alpha, f);
     return check_launch("inner_product");
-}
-
-int launch_moddown_bconv(const rf_ctx *c, const uint64_t *ip, uint64_t *conv, uint32_t nl, hipStream_t s) {
-    ProfScope prof("moddown_bconv", s);
-    const uint64_t *tab = c->scheme == RF_BGV ? c->d_moddown_t : c->d_moddown;
-    hipLaunchKernelGGL(moddown_bconv_kernel, ew_grid(c, 2 * moddown_chunks(nl)), dim3(kEw), 0, s, ip, conv, c->d_pc, tab,
-                       c->log_n, nl, c->L, c->K);
-    return check_launch("moddown_bconv");
-}
-
-int launch_moddown_tail(const rf_ctx *c, const uint64_t *ip, const uint64_t *conv, const uint64_t *add0,
-                        const uint64_t *add1, uint64_t *out, uint32_t nl, hipStream_t s) {
-    ProfScope prof("moddown_tail", s);
-    hipLaunchKernelGGL(moddown_tail_kernel, ew_grid(c, 2 * nl), dim3(kEw), 0, s, ip, conv, add0, add1, out, c->d_pc,
-                       c->d_moddown + moddown_pinv_off(c), c->log_n, nl, c->K);
-    return check_launch("moddown_tail");
-}
-
-int launch_rescale_lift(const rf_ctx *c, const uint64_t *last, uint64_t *lift, uint32_t nl, bool keep_t,
-                        hipStream_t s) {
-    ProfScope prof("rescale_lift", s);
-    if (keep_t)
-        hipLaunchKernelGGL(rescale_lift_kernel<true>, ew_grid(c, 2 * (nl - 1)), dim3(kEw), 0, s, last, lift, c->d_pc,
-                           c->d_rescale, c->log_n, nl, c->L);
-    else
-        hipLaunchKernelGGL(rescale_lift_kernel<false>, ew_grid(c, 2 * (nl - 1)), dim3(kEw), 0, s, last, lift,
-                           c->d_pc, c->d_rescale, c->log_n, nl, c->L);
-    return check_launch("rescale_lift");
-}
-
-int launch_rescale_tail(const rf_ctx *c, const uint64_t *in, const uint64_t *lift, uint64_t *out, uint32_t nl,
-                        hipStream_t s) {
-    ProfScope prof("rescale_tail", s);
-    hipLaunchKernelGGL(rescale_tail_kernel, ew_grid(c, 2 * (nl - 1)), dim3(kEw), 0, s, in, lift, out, c->d_pc,
-                       c->d_rescale, c->log_n, nl, c->L);
-    return check_launch("rescale_tail");
 }
 
 int launch_automorphism(const rf_ctx *c, const uint64_t *in, uint64_t *out, uint32_t galois, uint32_t nl,

@@ -351,44 +351,6 @@ __device__ __forceinline__ void moddown_tail_unit(const uint64_t *__restrict__ i
     out[off] = r;
 }
 
-// Rescale / modulus switch, step 1: the last limb (coefficient domain, [2][N])
-// lifted from its centred representative into every remaining prime:
-// lift = [2][nl-1][N].  KEEP_T (BGV): the lifted value is t [x t^-1]_{q_l}, so
-// that the difference is 0 mod t as well as mod q_l.
-template <bool KEEP_T>
-__device__ __forceinline__ void rescale_lift_unit(const uint64_t *__restrict__ last, uint64_t *__restrict__ lift,
-                                                           const PrimeConst *__restrict__ pcs,
-                                                           const uint64_t *__restrict__ tab, uint32_t log_n,
-                                                           uint32_t nl, uint32_t L, uint32_t gx, uint32_t gy) {
-    const uint32_t l = nl - 1;
-    const uint32_t c = gy / l, i = gy - c * l;
-    const size_t n = (size_t)gx * kEw + threadIdx.x;
-    const PrimeConst pl = pcs[l];
-    const PrimeConst pc = pcs[i];
-    uint64_t x = last[((size_t)c << log_n) + n];
-    if (KEEP_T) x = shoup(x, pl.tinv, pl.tinv_p, pl.q);
-    uint64_t r = barrett64(x, pc.mu1, pc.mu0, pc.q);
-    if (x > (pl.q >> 1)) r = addmod(r, tab[((size_t)l * L + i) * 3 + 2], pc.q);
-    if (KEEP_T) r = shoup(r, pc.tmod, pc.tmod_p, pc.q);
-    lift[(((size_t)c * l + i) << log_n) + n] = r;
-}
-
-// Rescale, step 2: out[c][i] = (in[c][i] - lift[c][i]) * q_l^-1 mod q_i.  grid.y = c * (nl-1) + i.
-// out may equal lift.
-__device__ __forceinline__ void rescale_tail_unit(const uint64_t *__restrict__ in, const uint64_t *lift,
-                                                           uint64_t *out, const PrimeConst *__restrict__ pcs,
-                                                           const uint64_t *__restrict__ tab, uint32_t log_n,
-                                                           uint32_t nl, uint32_t L, uint32_t gx, uint32_t gy) {
-    const uint32_t l = nl - 1;
-    const uint32_t c = gy / l, i = gy - c * l;
-    const size_t n = (size_t)gx * kEw + threadIdx.x;
-    const PrimeConst pc = pcs[i];
-    const uint64_t *t = tab + ((size_t)l * L + i) * 3;
-    const size_t off = (((size_t)c * l + i) << log_n) + n;
-    const uint64_t x = in[(((size_t)c * nl + i) << log_n) + n];
-    out[off] = shoup(submod(x, lift[off], pc.q), t[0], t[1], pc.q);
-}
-
 // sigma_g in the NTT domain: out[k] = in[k'] with 2 brv(k') + 1 = (2 brv(k) + 1) g mod 2N.
 // grid.y = polynomial * nl + limb (the permutation is the same on every limb).
 __device__ __forceinline__ void automorphism_unit(const uint64_t *__restrict__ in, uint64_t *__restrict__ out,

@@ -195,44 +195,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ntt_wa
                                   fpm.has(i), tile, epi);
 }
 
-// Whole limb in one workgroup (N = 2^LOGN <= 4096).
-template <typename Ar, int LOGN, bool FWD>
-__device__ __forceinline__ void ntt_single(uint64_t *lds, const LimbView &v, const TwPair *__restrict__ tw,
-                                           const Ar &ar) {
-    constexpr int S = 1 << LOGN;
-    constexpr int NT = S / kElems;
-    if (threadIdx.x < NT) {
-        const LoadPro pro{v.in};
-#pragma unroll
-        for (int r = 0; r < kElems; ++r) lds[threadIdx.x + r * NT] = Ar::bits(pass_in(pro, threadIdx.x + r * NT, ar));
-    }
-    __syncthreads();
-    ntt_rounds<Ar, LOGN, FWD, !FWD>(lds, 1, 0, threadIdx.x < NT ? threadIdx.x : 0, 1u, twiddles<Ar>(tw), ar);
-    if (threadIdx.x < NT) {
-#pragma unroll
-        for (int r = 0; r < kElems; ++r) {
-            typename Ar::V x = Ar::raw(lds[threadIdx.x + r * NT]);
-            if constexpr (!FWD) {
-                v.out[threadIdx.x + r * NT] = ar.canon_last(x);
-            } else {
-                if constexpr (!Ar::kFp) x = csub(csub(x, ar.q2), ar.q);
-                pass_out(StoreEpi{v.out}, threadIdx.x + r * NT, x, ar);
-            }
-        }
-    }
-}
-
-template <int LOGN, bool FWD, typename Fp>
-__global__ __launch_bounds__(kThreads) void ntt_single_kernel(NttBatch b, Fp fpm, const TwPair *__restrict__ tw_all,
-                                                              const PrimeConst *__restrict__ pcs) {
-    __shared__ uint64_t lds[1 << LOGN];
-    const LimbView v = limb_view(b, LOGN, blockIdx.y);
-    const PrimeConst pc = pcs[v.g];
-    const TwPair *tw = tw_all + ((size_t)v.g << LOGN);
-    if (fpm.has(v.g)) ntt_single<ArFp, LOGN, FWD>(lds, v, tw, ArFp(pc));
-    else ntt_single<ArInt, LOGN, FWD>(lds, v, tw, ArInt(pc));
-}
-
 // A pass of a launch with few limbs (ntt_cols_small / ntt_rows_small): one
 // workgroup per TILE residues of a limb, E residues per thread.
 // Tile of a small column pass.  Its U = TILE / 2^A columns are narrower than
@@ -655,16 +617,7 @@ static int launch_ntt_t(const rf_ctx *c, Fp fpm, const NttBatch &b, bool forward
     if (limbs == 0) return RF_OK;
     if (limbs > 65535) return fail(RF_EUNSUPPORTED, "too many limbs in one NTT launch");
     switch (c->log_n) {
-        case 12: {
-            ProfScope p(forward ? "ntt_fwd_single" : "ntt_inv_single", s);
-            if (forward)
-                hipLaunchKernelGGL((ntt_single_kernel<12, true>), dim3(1, limbs), dim3(kThreads), 0, s, b,
-                                   fpm, c->d_tw_fwd, pcs);
-            else
-                hipLaunchKernelGGL((ntt_single_kernel<12, false>), dim3(1, limbs), dim3(kThreads), 0, s, b,
-                                   fpm, c->d_tw_inv, pcs);
-            break;
-        }
+        case 12: return launch_ntt_single(c, b, forward, s, pcs);
         case 13: launch_two_pass<7, 6>(c, fpm, b, forward, s, pcs, t); break;
         case 14: launch_two_pass<7, 7>(c, fpm, b, forward, s, pcs, t); break;
         case 15: launch_two_pass<8, 7>(c, fpm, b, forward, s, pcs, t); break;

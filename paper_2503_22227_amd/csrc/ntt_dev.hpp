@@ -180,8 +180,21 @@ constexpr int kTwLoad = 0, kTwPrefetch = 1, kTwCached = 2;
 // does not use are never written or read.
 __host__ __device__ constexpr int tw_slots(int S_LOG, int E) { return E * S_LOG; }
 
+// Where element p of a thread's sub-transform lies in LDS.  A workgroup tile:
+// p ldu + u for sub-transform u.
+struct TileLds {
+    uint64_t *l;
+    int ldu, u;
+    __device__ __forceinline__ uint64_t &operator()(int p) const { return l[p * ldu + u]; }
+};
+// A whole limb, a word of padding after every 16.
+struct LimbLds {
+    uint64_t *l;
+    __device__ __forceinline__ uint64_t &operator()(int p) const { return l[p + (p >> 4)]; }
+};
+
 // One round of C butterfly stages of a size-2^S_LOG sub-transform held in LDS
-// (element p of sub-transform u at lds[p * ldu + u], as Ar::bits).  Thread t of
+// (element p of the thread's sub-transform at lds(p), as Ar::bits).  Thread t of
 // the sub-transform owns E residues (kElems unless stated): E / 2^C groups of
 // 2^C residues spaced by the round's smallest distance 2^DL.
 //
@@ -189,8 +202,8 @@ __host__ __device__ constexpr int tw_slots(int S_LOG, int E) { return E * S_LOG;
 // regs (group gi, element e at regs[gi * 2^C + e]) instead of LDS.  TW, SLOT0,
 // cache: the twiddle source above.
 template <typename Ar, int S_LOG, int ST0, int C, bool FWD, bool SCALE_LAST, int ROW_A, bool IN_REGS = false,
-          bool OUT_REGS = false, int E = kElems, int TW = kTwLoad, int SLOT0 = 0>
-__device__ __forceinline__ void ntt_round(uint64_t *lds, int ldu, int u, int t, uint32_t tw_base,
+          bool OUT_REGS = false, int E = kElems, int TW = kTwLoad, int SLOT0 = 0, typename Lds>
+__device__ __forceinline__ void ntt_round(const Lds &lds, int t, uint32_t tw_base,
                                           const typename Ar::Tw *__restrict__ tw, const Ar &ar,
                                           typename Ar::V *regs = nullptr, typename Ar::Tw *cache = nullptr) {
     using V = typename Ar::V;
@@ -221,7 +234,7 @@ __device__ __forceinline__ void ntt_round(uint64_t *lds, int ldu, int u, int t, 
 #pragma unroll
             for (int e = 0; e < G; ++e) {
                 if constexpr (IN_REGS) v[e] = regs[gi * G + e];
-                else v[e] = Ar::raw(lds[(base + (e << DL)) * ldu + u]);
+                else v[e] = Ar::raw(lds(base + (e << DL)));
             }
         }
         if constexpr (FWD) {
@@ -272,7 +285,7 @@ __device__ __forceinline__ void ntt_round(uint64_t *lds, int ldu, int u, int t, 
 #pragma unroll
             for (int e = 0; e < G; ++e) {
                 if constexpr (OUT_REGS) regs[gi * G + e] = v[e];
-                else lds[(base + (e << DL)) * ldu + u] = Ar::bits(v[e]);
+                else lds(base + (e << DL)) = Ar::bits(v[e]);
             }
         }
     }
@@ -282,31 +295,32 @@ __device__ __forceinline__ void ntt_round(uint64_t *lds, int ldu, int u, int t, 
 // the last one shorter when log2(E) does not divide S_LOG.  With kTwPrefetch
 // only the twiddle loads run (no barriers).
 template <typename Ar, int S_LOG, int ST0, bool FWD, bool SCALE_LAST, int ROW_A, int E = kElems, int TW = kTwLoad,
-          int SLOT0 = 0>
-__device__ __forceinline__ void ntt_rounds_from(uint64_t *lds, int ldu, int u, int t, uint32_t tw_base,
+          int SLOT0 = 0, typename Lds>
+__device__ __forceinline__ void ntt_rounds_from(const Lds &lds, int t, uint32_t tw_base,
                                                 const typename Ar::Tw *__restrict__ tw, const Ar &ar,
                                                 typename Ar::Tw *cache = nullptr) {
     constexpr int CL = ilog2(E);
     constexpr int C = (S_LOG - ST0) < CL ? (S_LOG - ST0) : CL;
     constexpr bool LAST = ST0 + C == S_LOG;
     ntt_round<Ar, S_LOG, ST0, C, FWD, SCALE_LAST && LAST, ROW_A, false, false, E, TW, SLOT0>(
-        lds, ldu, u, t, tw_base, tw, ar, nullptr, cache);
+        lds, t, tw_base, tw, ar, nullptr, cache);
     if constexpr (TW != kTwPrefetch) __syncthreads();
     if constexpr (!LAST)
-        ntt_rounds_from<Ar, S_LOG, ST0 + C, FWD, SCALE_LAST, ROW_A, E, TW, SLOT0 + E * C>(lds, ldu, u, t, tw_base, tw,
-                                                                                         ar, cache);
+        ntt_rounds_from<Ar, S_LOG, ST0 + C, FWD, SCALE_LAST, ROW_A, E, TW, SLOT0 + E * C>(lds, t, tw_base, tw, ar,
+                                                                                         cache);
 }
 
 // ROW_A: 0 for the natural twiddle table; A for a row pass reading the row table
 // (which needs exactly two rounds of kElems residues: S_LOG in (kElemsLog, 2 kElemsLog]).
-template <typename Ar, int S_LOG, bool FWD, bool SCALE_LAST, int ROW_A = 0, int E = kElems, int TW = kTwLoad>
-__device__ __forceinline__ void ntt_rounds(uint64_t *lds, int ldu, int u, int t, uint32_t tw_base,
+template <typename Ar, int S_LOG, bool FWD, bool SCALE_LAST, int ROW_A = 0, int E = kElems, int TW = kTwLoad,
+          typename Lds>
+__device__ __forceinline__ void ntt_rounds(const Lds &lds, int t, uint32_t tw_base,
                                            const typename Ar::Tw *__restrict__ tw, const Ar &ar,
                                            typename Ar::Tw *cache = nullptr) {
     static_assert(S_LOG >= 5 && S_LOG <= 12, "sub-transform size");
     static_assert(ROW_A == 0 || (E == kElems && S_LOG > kElemsLog && S_LOG <= 2 * kElemsLog),
                   "row table: two rounds of kElems residues");
-    ntt_rounds_from<Ar, S_LOG, 0, FWD, SCALE_LAST, ROW_A, E, TW, 0>(lds, ldu, u, t, tw_base, tw, ar, cache);
+    ntt_rounds_from<Ar, S_LOG, 0, FWD, SCALE_LAST, ROW_A, E, TW, 0>(lds, t, tw_base, tw, ar, cache);
 }
 
 // A prime's twiddles in the form its arithmetic takes.
@@ -393,14 +407,14 @@ __device__ __forceinline__ void ntt_cols_small_t(uint64_t *lds, const Pro &pro, 
         vin[r] = pass_in(pro, ((size_t)(idx / U) << B) + col0 + idx % U, ar);
     }
     typename Ar::Tw twc[tw_slots(A, E)];
-    ntt_rounds<Ar, A, FWD, !FWD, 0, E, kTwPrefetch>(lds, LDU, threadIdx.x % U, threadIdx.x / U, 1u, tw, ar, twc);
+    ntt_rounds<Ar, A, FWD, !FWD, 0, E, kTwPrefetch>(TileLds{lds, LDU, (int)(threadIdx.x % U)}, threadIdx.x / U, 1u, tw, ar, twc);
 #pragma unroll
     for (int r = 0; r < E; ++r) {
         const int idx = threadIdx.x + r * NT;
         lds[(idx / U) * LDU + idx % U] = Ar::bits(vin[r]);
     }
     __syncthreads();
-    ntt_rounds<Ar, A, FWD, !FWD, 0, E, kTwCached>(lds, LDU, threadIdx.x % U, threadIdx.x / U, 1u, tw, ar, twc);
+    ntt_rounds<Ar, A, FWD, !FWD, 0, E, kTwCached>(TileLds{lds, LDU, (int)(threadIdx.x % U)}, threadIdx.x / U, 1u, tw, ar, twc);
 #pragma unroll
     for (int r = 0; r < E; ++r) {
         const int idx = threadIdx.x + r * NT;
@@ -453,14 +467,14 @@ __device__ __forceinline__ void ntt_rows_small_t(uint64_t *lds, const Pro &pro, 
     }
     const int u = threadIdx.x % U;
     typename Ar::Tw twc[tw_slots(B, E)];
-    ntt_rounds<Ar, B, FWD, false, 0, E, kTwPrefetch>(lds, LDU, u, threadIdx.x / U, (1u << A) + row0 + u, tw, ar, twc);
+    ntt_rounds<Ar, B, FWD, false, 0, E, kTwPrefetch>(TileLds{lds, LDU, u}, threadIdx.x / U, (1u << A) + row0 + u, tw, ar, twc);
 #pragma unroll
     for (int r = 0; r < E; ++r) {
         const int idx = threadIdx.x + r * NT;
         lds[(idx & (S - 1)) * LDU + (idx >> B)] = Ar::bits(vin[r]);
     }
     __syncthreads();
-    ntt_rounds<Ar, B, FWD, false, 0, E, kTwCached>(lds, LDU, u, threadIdx.x / U, (1u << A) + row0 + u, tw, ar, twc);
+    ntt_rounds<Ar, B, FWD, false, 0, E, kTwCached>(TileLds{lds, LDU, u}, threadIdx.x / U, (1u << A) + row0 + u, tw, ar, twc);
 #pragma unroll
     for (int r = 0; r < E; ++r) {
         const int idx = threadIdx.x + r * NT;
@@ -536,9 +550,9 @@ __device__ __forceinline__ void ntt_cols_compute(uint64_t *lds, uint64_t *out, c
     const int u = threadIdx.x % U, t = threadIdx.x / U;
     const auto *tw = twiddles<Ar>(tw_all);
     if constexpr (FWD) {
-        ntt_round<Ar, A, 0, kElemsLog, true, false, 0, true, false>(lds, LDU, u, t, 1u, tw, ar, regs);
+        ntt_round<Ar, A, 0, kElemsLog, true, false, 0, true, false>(TileLds{lds, LDU, u}, t, 1u, tw, ar, regs);
         __syncthreads();
-        ntt_round<Ar, A, kElemsLog, C2, true, false, 0, false, false>(lds, LDU, u, t, 1u, tw, ar);
+        ntt_round<Ar, A, kElemsLog, C2, true, false, 0, false, false>(TileLds{lds, LDU, u}, t, 1u, tw, ar);
         __syncthreads();
 #pragma unroll
         for (int r = 0; r < kTile / kThreads; ++r) {
@@ -553,11 +567,11 @@ __device__ __forceinline__ void ntt_cols_compute(uint64_t *lds, uint64_t *out, c
             lds[(idx / U) * LDU + idx % U] = Ar::bits(regs[r]);
         }
         __syncthreads();
-        ntt_round<Ar, A, 0, kElemsLog, false, false, 0, false, false>(lds, LDU, u, t, 1u, tw, ar);
+        ntt_round<Ar, A, 0, kElemsLog, false, false, 0, false, false>(TileLds{lds, LDU, u}, t, 1u, tw, ar);
         __syncthreads();
         // The last inverse round leaves rows grp + 16 e (grp = t NG + gi) of
         // column u in registers, the order of a coalesced store.
-        ntt_round<Ar, A, kElemsLog, C2, false, true, 0, false, true>(lds, LDU, u, t, 1u, tw, ar, regs);
+        ntt_round<Ar, A, kElemsLog, C2, false, true, 0, false, true>(TileLds{lds, LDU, u}, t, 1u, tw, ar, regs);
         constexpr int G = 1 << C2, NG = kElems / G;
 #pragma unroll
         for (int gi = 0; gi < NG; ++gi)
@@ -682,7 +696,7 @@ __device__ __forceinline__ void ntt_rows_compute(uint64_t *lds, const TwPair *__
     }
     __syncthreads();
     const int u = threadIdx.x % U, t = threadIdx.x / U;
-    ntt_rounds<Ar, B, FWD, false, A>(lds, LDU, u, t, (1u << A) + row0 + u, tw, ar);
+    ntt_rounds<Ar, B, FWD, false, A>(TileLds{lds, LDU, u}, t, (1u << A) + row0 + u, tw, ar);
 #pragma unroll
     for (int r = 0; r < kTile / kThreads; ++r) {
         const int idx = threadIdx.x + r * kThreads;

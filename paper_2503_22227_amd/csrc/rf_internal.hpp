@@ -253,15 +253,20 @@ int launch_modup_bconv(const rf_ctx *c, const uint64_t *x, uint64_t *ext, uint32
 int launch_inner_product(const rf_ctx *c, const uint64_t *d_ntt, const uint64_t *ext,
                          const uint64_t *evk, uint64_t *ip, uint32_t nl, hipStream_t s,
                          const IpFold *fold = nullptr);
-int launch_moddown_bconv(const rf_ctx *c, const uint64_t *ip, uint64_t *conv, uint32_t nl,
-                         hipStream_t s);  // uses the t-preserving table for BGV contexts
-int launch_moddown_tail(const rf_ctx *c, const uint64_t *ip, const uint64_t *conv,
-                        const uint64_t *add0, const uint64_t *add1, uint64_t *out, uint32_t nl,
-                        hipStream_t s);
-int launch_rescale_lift(const rf_ctx *c, const uint64_t *last, uint64_t *lift, uint32_t nl,
-                        bool keep_t, hipStream_t s);
-int launch_rescale_tail(const rf_ctx *c, const uint64_t *in, const uint64_t *lift, uint64_t *out,
-                        uint32_t nl, hipStream_t s);
+
+// N = 2^12: a workgroup holds a whole limb, so a step that precedes or follows
+// a transform needs no launch of its own (single.hip).
+int launch_ntt_single(const rf_ctx *c, const NttBatch &b, bool forward, hipStream_t s, const PrimeConst *pcs);
+// A key switch after fold's sources (its pinv is filled in here): INTT of the
+// polynomial to switch (coef non-null: its coefficients instead), ModUp with
+// the NTT of the extension, inner product with the INTT of the special limbs,
+// ModDown, into out [2][nl][N].  Scratch: dc [nl], ext, ip [2][nl + K] limbs.
+int launch_keyswitch_single(const rf_ctx *c, const IpFold &fold, const uint64_t *d, const uint64_t *coef,
+                            const uint64_t *evk, uint64_t *dc, uint64_t *ext, uint64_t *ip, uint64_t *out,
+                            uint32_t nl, hipStream_t s);
+// Rescale / modulus switch (keep_t: BGV) of in [2][nl][N] into out [2][nl-1][N].
+int launch_divide_single(const rf_ctx *c, const uint64_t *in, uint64_t *out, uint32_t nl, bool keep_t, hipStream_t s);
+
 int launch_ewise(const rf_ctx *c, int op, const uint64_t *a, const uint64_t *b, int64_t k, uint64_t *out,
                  uint32_t nl, uint32_t n_polys, hipStream_t s);
 int launch_behz_extend(const rf_ctx *c, const uint64_t *a, const uint64_t *b, uint64_t *ext, hipStream_t s);
