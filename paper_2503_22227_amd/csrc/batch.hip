@@ -509,10 +509,10 @@ void build_tables(rf_batch *p, std::vector<KsJob> &jobs, std::vector<NttJob> (&n
             acc[st] += stage_units(c, nl, st, p->modup_chunk);
         }
         const uint64_t ipstride = (uint64_t)(nl + c->K) * N;
-        NttBatch bd{J.d2, J.d_coeff, 0, 0, nl, 1, 0, nullptr};
-        NttBatch be{J.ext, J.ext, 0, 0, lv.ext_limbs, 1, 0, c->d_pmaps + lv.pmap_off};
-        NttBatch bp{J.ip + (size_t)nl * N, J.ip + (size_t)nl * N, ipstride, ipstride, c->K, 2, c->L, nullptr};
-        NttBatch bc{J.conv, J.conv, (uint64_t)nl * N, (uint64_t)nl * N, nl, 2, 0, nullptr};
+        NttBatch bd{J.d2, J.d_coeff, 0, 0, nl, 1, 0, nullptr, {}};
+        NttBatch be{J.ext, J.ext, 0, 0, lv.ext_limbs, 1, 0, c->d_pmaps + lv.pmap_off, {}};
+        NttBatch bp{J.ip + (size_t)nl * N, J.ip + (size_t)nl * N, ipstride, ipstride, c->K, 2, c->L, nullptr, {}};
+        NttBatch bc{J.conv, J.conv, (uint64_t)nl * N, (uint64_t)nl * N, nl, 2, 0, nullptr, {}};
         const NttBatch bs[4] = {bd, be, bp, bc};
         const int first_stage[4] = {kInttD0, kNttExt0, kInttP0, kNttConv0};
         for (int k = 0; k < 4; ++k) {

@@ -8,6 +8,14 @@ using namespace rf;
 
 namespace {
 
+// Launch order of limbs first .. first + n of the chain, where the context holds one.
+LimbOrder window_order(const rf_ctx *c, uint32_t first, uint32_t n) {
+    if (first == 0 && n <= c->L) return c->order(c->q_order[n]);
+    if (first == 0 && n == c->L + c->K) return c->order(c->all_order);
+    if (first == c->L && n == c->K) return c->order(c->p_order);
+    return LimbOrder();
+}
+
 // Key-switching workspace at level nl, in limbs of N residues:
 //   d_coeff [nl] | ext [ext_limbs] | ip [2][nl+K] | conv [2][nl]
 struct KsLayout {
@@ -56,7 +64,7 @@ struct DeviceGuard {
 };
 
 NttBatch batch(const uint64_t *in, uint64_t *out, uint64_t in_stride, uint64_t out_stride, uint32_t per_poly,
-               uint32_t n_polys, uint32_t prime_base, const uint32_t *pmap) {
+               uint32_t n_polys, uint32_t prime_base, const uint32_t *pmap, const LimbOrder &order = LimbOrder()) {
     NttBatch b;
     b.in = in;
     b.out = out;
@@ -66,6 +74,7 @@ NttBatch batch(const uint64_t *in, uint64_t *out, uint64_t in_stride, uint64_t o
     b.n_polys = n_polys;
     b.prime_base = prime_base;
     b.pmap = pmap;
+    b.order = order;
     return b;
 }
 
@@ -96,16 +105,18 @@ int keyswitch_core(const rf_ctx *c, const uint64_t *d, const uint64_t *evk, uint
     // launch_intt_first does the same for the fused callers).
     const rf_tuning &tn = level_tuning(c, nl);
     if (!fused && !d_coeff_in &&
-        (rc = launch_ntt(c, batch(d, d_coeff, 0, 0, nl, 1, 0, nullptr), false, s, pc_modup(c, nl), &tn)))
+        (rc = launch_ntt(c, batch(d, d_coeff, 0, 0, nl, 1, 0, nullptr, c->order(c->q_order[nl])), false, s, pc_modup(c, nl), &tn)))
         return rc;
     if ((rc = launch_modup_bconv(c, d_coeff_in ? d_coeff_in : d_coeff, ext, nl, s, !d_coeff_in, tn.modup_chunk))) return rc;
-    if ((rc = launch_ntt(c, batch(ext, ext, 0, 0, lv.ext_limbs, 1, 0, c->d_pmaps + lv.pmap_off), true, s, nullptr, &tn)))
+    if ((rc = launch_ntt(c, batch(ext, ext, 0, 0, lv.ext_limbs, 1, 0, c->d_pmaps + lv.pmap_off,
+                               c->order(c->ext_order[nl])), true, s, nullptr, &tn)))
         return rc;
     // ModDown: the inner product applies P^-1 and the addends to its Q-limbs; the
     // INTT of the P-limbs folds in the conversion's input factor; the conversion
     // runs in the first pass of the NTT and the tail in its last pass
     const uint64_t ip_stride = (uint64_t)(nl + c->K) * N;
-    const NttBatch pl = batch(ip + (size_t)nl * N, ip + (size_t)nl * N, ip_stride, ip_stride, c->K, 2, c->L, nullptr);
+    const NttBatch pl = batch(ip + (size_t)nl * N, ip + (size_t)nl * N, ip_stride, ip_stride, c->K, 2, c->L, nullptr,
+                              c->order(c->p_order));
     if ((rc = launch_inner_product(c, d, ext, evk, ip, nl, s, &f))) return rc;
     if ((rc = launch_ntt(c, pl, false, s, c->d_pc_md, &tn))) return rc;
     return launch_ntt_fwd_moddown(c, conv, ip, out, nl, s, &tn);
@@ -142,7 +153,7 @@ extern "C" int rf_ntt(const rf_ctx *c, uint64_t *data, uint32_t first, uint32_t 
     if (nl == 0 || np == 0 || first + nl > c->L + c->K) return fail(RF_ELEVEL, "rf_ntt: limb range");
     DeviceGuard g(c->device);
     const uint64_t stride = (uint64_t)nl * c->n;
-    return launch_ntt(c, batch(data, data, stride, stride, nl, np, first, nullptr), true, (hipStream_t)stream, nullptr,
+    return launch_ntt(c, batch(data, data, stride, stride, nl, np, first, nullptr, window_order(c, first, nl)), true, (hipStream_t)stream, nullptr,
                       &level_tuning(c, nl));
 }
 
@@ -151,7 +162,7 @@ extern "C" int rf_intt(const rf_ctx *c, uint64_t *data, uint32_t first, uint32_t
     if (nl == 0 || np == 0 || first + nl > c->L + c->K) return fail(RF_ELEVEL, "rf_intt: limb range");
     DeviceGuard g(c->device);
     const uint64_t stride = (uint64_t)nl * c->n;
-    return launch_ntt(c, batch(data, data, stride, stride, nl, np, first, nullptr), false, (hipStream_t)stream, nullptr,
+    return launch_ntt(c, batch(data, data, stride, stride, nl, np, first, nullptr, window_order(c, first, nl)), false, (hipStream_t)stream, nullptr,
                       &level_tuning(c, nl));
 }
 
@@ -190,17 +201,17 @@ static int bfv_hmult_relin(const rf_ctx *c, const uint64_t *a, const uint64_t *b
     const uint64_t wstride = (uint64_t)W * N;
     const rf_tuning &tn = level_tuning(c, c->L);
     if ((rc = launch_behz_extend(c, a, b, ext, s))) return rc;
-    if ((rc = launch_ntt(c, batch(ext, ext, wstride, wstride, W, 4, 0, c->d_pmap_qb), true, s, nullptr, &tn))) return rc;
+    if ((rc = launch_ntt(c, batch(ext, ext, wstride, wstride, W, 4, 0, c->d_pmap_qb, c->order(c->qb_order)), true, s, nullptr, &tn))) return rc;
     if ((rc = launch_tensor_map(c, ext, ext + 2 * wstride, tens, tens + 2 * wstride, W, c->d_pmap_qb, s))) return rc;
-    if ((rc = launch_ntt(c, batch(tens, tens, wstride, wstride, W, 3, 0, c->d_pmap_qb), false, s, nullptr, &tn))) return rc;
+    if ((rc = launch_ntt(c, batch(tens, tens, wstride, wstride, W, 3, 0, c->d_pmap_qb, c->order(c->qb_order)), false, s, nullptr, &tn))) return rc;
     // the fast floor's B_sk residues go through the extension region, free after the tensor
     if ((rc = launch_behz_floor_sk(c, tens, ext, out, d2, s))) return rc;
     // the key switch takes d2 in both domains: the NTT (into the free tensor
     // region) for its inner product, the coefficients for its ModUp
     uint64_t *d2n = tens;
-    if ((rc = launch_ntt(c, batch(d2, d2n, 0, 0, c->L, 1, 0, nullptr), true, s, nullptr, &tn))) return rc;
+    if ((rc = launch_ntt(c, batch(d2, d2n, 0, 0, c->L, 1, 0, nullptr, c->order(c->q_order[c->L])), true, s, nullptr, &tn))) return rc;
     if ((rc = keyswitch_core(c, d2n, rlk, ks, c->L, nullptr, nullptr, ks_ws, s, nullptr, d2))) return rc;
-    if ((rc = launch_ntt(c, batch(ks, ks, L * N, L * N, c->L, 2, 0, nullptr), false, s, nullptr, &tn))) return rc;
+    if ((rc = launch_ntt(c, batch(ks, ks, L * N, L * N, c->L, 2, 0, nullptr, c->order(c->q_order[c->L])), false, s, nullptr, &tn))) return rc;
     return launch_ewise(c, 0, out, ks, 0, out, c->L, 2, s);
 }
 
@@ -267,9 +278,9 @@ extern "C" int rf_rotate(const rf_ctx *c, const uint64_t *in, uint32_t galois, c
     // the result back applies sigma_g (and the key switch) to the coefficients.
     const size_t poly = (size_t)nl * c->n;
     uint64_t *x = (uint64_t *)ws;
-    if ((rc = launch_ntt(c, batch(in, x, poly, poly, nl, 2, 0, nullptr), true, s, nullptr, &level_tuning(c, nl)))) return rc;
+    if ((rc = launch_ntt(c, batch(in, x, poly, poly, nl, 2, 0, nullptr, c->order(c->q_order[nl])), true, s, nullptr, &level_tuning(c, nl)))) return rc;
     if ((rc = rotate_ntt(c, x, galois, gk, out, nl, x + 2 * poly, s))) return rc;
-    return launch_ntt(c, batch(out, out, poly, poly, nl, 2, 0, nullptr), false, s, nullptr, &level_tuning(c, nl));
+    return launch_ntt(c, batch(out, out, poly, poly, nl, 2, 0, nullptr, c->order(c->q_order[nl])), false, s, nullptr, &level_tuning(c, nl));
 }
 
 extern "C" int rf_galois_element(const rf_ctx *c, int64_t r, int conjugate, uint32_t *out) {

@@ -451,7 +451,7 @@ struct Dev {
     }
 };
 
-NttBatch plain_batch(uint64_t *d, uint64_t stride, uint32_t per_poly, uint32_t n_polys) {
+NttBatch plain_batch(const rf_ctx *c, uint64_t *d, uint64_t stride, uint32_t per_poly, uint32_t n_polys) {
     NttBatch b;
     b.in = d;
     b.out = d;
@@ -461,6 +461,7 @@ NttBatch plain_batch(uint64_t *d, uint64_t stride, uint32_t per_poly, uint32_t n
     b.n_polys = n_polys;
     b.prime_base = 0;
     b.pmap = nullptr;
+    b.order = c->order(per_poly <= c->L ? c->q_order[per_poly] : c->all_order);
     return b;
 }
 
@@ -533,7 +534,7 @@ extern "C" int rf_key_ntt(const rf_ctx *c, const int64_t *x, uint64_t *out, void
     const uint32_t all = c->L + c->K;
     int rc;
     if ((rc = lift(c, x, nullptr, 0, out, 0, 0, all, 1, 0, s))) return rc;
-    return launch_ntt(c, plain_batch(out, 0, all, 1), true, s);
+    return launch_ntt(c, plain_batch(c, out, 0, all, 1), true, s);
 }
 
 extern "C" int rf_keygen_switch(const rf_ctx *c, const uint64_t *s_ntt, uint32_t galois, const uint64_t *a,
@@ -552,7 +553,7 @@ extern "C" int rf_keygen_switch(const rf_ctx *c, const uint64_t *s_ntt, uint32_t
     // NTT(err e_j) into polynomial 0 of every digit
     if ((rc = lift(c, e, nullptr, c->n, evk, 2 * limbs, 0, all, c->dnum, c->scheme == RF_BGV ? kLiftXT : 0, s)))
         return rc;
-    if ((rc = launch_ntt(c, plain_batch(evk, 2 * limbs, all, c->dnum), true, s))) return rc;
+    if ((rc = launch_ntt(c, plain_batch(c, evk, 2 * limbs, all, c->dnum), true, s))) return rc;
     {
         ProfScope prof("client_keygen", s);
         hipLaunchKernelGGL(keygen_kernel, dim3(c->n / kCl, all, c->dnum), dim3(kCl), 0, s, evk, a, s_ntt, c->d_pc,
@@ -580,9 +581,9 @@ extern "C" int rf_encrypt_sk(const rf_ctx *c, const int64_t *m, const int64_t *e
         if ((rc = lift(c, m, e, 0, c1, 0, 0, nl, 1, kLiftXDelta, s))) return rc;
         if (hipMemcpyAsync(c0, a, poly * 8, hipMemcpyDeviceToDevice, s) != hipSuccess)
             return fail(RF_EHIP, "rf_encrypt_sk: copy");
-        if ((rc = launch_ntt(c, plain_batch(c0, 0, nl, 1), true, s))) return rc;
+        if ((rc = launch_ntt(c, plain_batch(c, c0, 0, nl, 1), true, s))) return rc;
         if ((rc = launch_ewise(c, 4, c0, s_ntt, 0, c0, nl, 1, s))) return rc;
-        if ((rc = launch_ntt(c, plain_batch(c0, 0, nl, 1), false, s))) return rc;
+        if ((rc = launch_ntt(c, plain_batch(c, c0, 0, nl, 1), false, s))) return rc;
         if ((rc = launch_ewise(c, 1, c1, c0, 0, c0, nl, 1, s))) return rc;
     } else if (c->log_n > 12) {
         // (NTT(m + err e) - a s, a) in the transform's two passes
@@ -592,7 +593,7 @@ extern "C" int rf_encrypt_sk(const rf_ctx *c, const int64_t *m, const int64_t *e
     } else {
         // c0 <- NTT(m + err e) - a s
         if ((rc = lift(c, m, e, 0, c0, 0, 0, nl, 1, c->scheme == RF_BGV ? kLiftYT : 0, s))) return rc;
-        if ((rc = launch_ntt(c, plain_batch(c0, 0, nl, 1), true, s))) return rc;
+        if ((rc = launch_ntt(c, plain_batch(c, c0, 0, nl, 1), true, s))) return rc;
         {
             ProfScope prof("client_encrypt", s);
             hipLaunchKernelGGL(fma_s_kernel<true>, dim3(c->n / kCl, nl), dim3(kCl), 0, s, c0, a, s_ntt, c0, c->d_pc,
@@ -619,9 +620,9 @@ extern "C" int rf_decrypt(const rf_ctx *c, const uint64_t *ct, const uint64_t *s
         // c0 + INTT(NTT(c1) s)
         if (hipMemcpyAsync(out, ct + poly, poly * 8, hipMemcpyDeviceToDevice, s) != hipSuccess)
             return fail(RF_EHIP, "rf_decrypt: copy");
-        if ((rc = launch_ntt(c, plain_batch(out, 0, nl, 1), true, s))) return rc;
+        if ((rc = launch_ntt(c, plain_batch(c, out, 0, nl, 1), true, s))) return rc;
         if ((rc = launch_ewise(c, 4, out, s_ntt, 0, out, nl, 1, s))) return rc;
-        if ((rc = launch_ntt(c, plain_batch(out, 0, nl, 1), false, s))) return rc;
+        if ((rc = launch_ntt(c, plain_batch(c, out, 0, nl, 1), false, s))) return rc;
         return launch_ewise(c, 0, out, ct, 0, out, nl, 1, s);
     }
     if (c->log_n > 12) {
@@ -636,7 +637,7 @@ extern "C" int rf_decrypt(const rf_ctx *c, const uint64_t *ct, const uint64_t *s
                            c->d_pc, c->log_n);
     }
     if ((rc = check_launch("decrypt"))) return rc;
-    return launch_ntt(c, plain_batch(out, 0, nl, 1), false, s);
+    return launch_ntt(c, plain_batch(c, out, 0, nl, 1), false, s);
 }
 
 extern "C" int rf_crt_centered(const rf_ctx *c, const uint64_t *x, double *out, uint32_t nl, double scale,

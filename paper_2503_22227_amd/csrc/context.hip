@@ -125,6 +125,7 @@ static void free_tables(rf_ctx *c) {
     (void)hipFree(c->d_moddown_t);
     (void)hipFree(c->d_rescale);
     (void)hipFree(c->d_pmaps);
+    (void)hipFree(c->d_order);
     (void)hipFree(c->d_behz);
     (void)hipFree(c->d_pmap_qb);
     (void)hipFree(c->d_client);
@@ -527,6 +528,30 @@ extern "C" int rf_ctx_create(const rf_params *p, int device, rf_ctx **out) {
         for (uint32_t m = 0; m <= nb; ++m) pmqb.push_back(KB + m);
     }
 
+    // launch orders: the limbs of wide primes first
+    std::vector<uint32_t> ord;
+    auto order_of = [&](uint32_t n, auto prime) {
+        rf_ctx::OrderRef r;
+        r.off = (uint32_t)ord.size();
+        for (int fp = 0; fp < 2; ++fp)
+            for (uint32_t i = 0; i < n; ++i)
+                if (c->fp_mask.has(prime(i)) == (fp == 1)) {
+                    ord.push_back(i | prime(i) << 16);
+                    r.n_wide += fp == 0;
+                }
+        return r;
+    };
+    c->q_order.resize(c->L + 1);
+    c->ext_order.resize(c->L + 1);
+    for (uint32_t nl = 1; nl <= c->L; ++nl) {
+        c->q_order[nl] = order_of(nl, [](uint32_t i) { return i; });
+        const ModupLevel &lv = c->modup_levels[nl];
+        c->ext_order[nl] = order_of(lv.ext_limbs, [&](uint32_t i) { return pm[lv.pmap_off + i]; });
+    }
+    c->p_order = order_of(c->K, [&](uint32_t i) { return c->L + i; });
+    c->all_order = order_of(c->L + c->K, [](uint32_t i) { return i; });
+    c->qb_order = order_of((uint32_t)pmqb.size(), [&](uint32_t i) { return pmqb[i]; });
+
     // Client-side tables.  [P]_{p_g} for the P [i in D_j] s' term of key
     // generation (0 on the special primes); floor(Q_L / t) mod p_g for BFV
     // encryption, = -[Q_L]_t t^-1 mod q_g since q_g divides Q_L.
@@ -601,7 +626,7 @@ extern "C" int rf_ctx_create(const rf_params *p, int device, rf_ctx **out) {
         (!twrf.empty() && ((rc = upload(&c->d_tw_fwd_rows, twrf)) || (rc = upload(&c->d_tw_inv_rows, twri)))) || (rc = upload(&c->d_tw_fwd, twf)) || (rc = upload(&c->d_tw_inv, twi)) ||
         (rc = upload(&c->d_modup, mu)) || (rc = upload(&c->d_moddown, md)) ||
         (!mdt.empty() && (rc = upload(&c->d_moddown_t, mdt))) || (rc = upload(&c->d_rescale, rs)) ||
-        (rc = upload(&c->d_pmaps, pm))) {
+        (rc = upload(&c->d_pmaps, pm)) || (rc = upload(&c->d_order, ord))) {
         free_tables(c);
         delete c;
         return rc;

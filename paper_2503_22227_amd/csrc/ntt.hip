@@ -30,24 +30,94 @@ __device__ __forceinline__ LimbView limb_view(const NttBatch &b, int log_n, uint
     return v;
 }
 
-template <int A, int B, bool FWD, typename Fp>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ntt_waves(A)))) void ntt_cols_kernel(NttBatch b, Fp fpm, const TwPair *__restrict__ tw_all,
-                                                            const PrimeConst *__restrict__ pcs) {
-    __shared__ uint64_t lds[(1 << A) * (kTile / (1 << A) + 1)];
-    const uint32_t tile = blockIdx.x;
-    const LimbView v = limb_view(b, A + B, blockIdx.y);
-    const PrimeConst pc = pcs[v.g];
-    ntt_cols_unit<A, B, FWD>(lds, v.in, v.out, tw_all + ((size_t)v.g << (A + B)), pc, fpm.has(v.g), tile);
+// A pass of a launch with few limbs (ntt_cols_small / ntt_rows_small): one
+// workgroup per TILE residues of a limb, E residues per thread.
+// Tile of a small column pass.  Its U = TILE / 2^A columns are narrower than
+// a 128-byte line (G = 16 / U tiles share each line of a row), and workgroups
+// are dealt to the 8 XCDs in turn, each with its own L2: dispatch order
+// w = blockIdx.x is mapped so that the G tiles of one line group go to the
+// same XCD one after another (w, w + 8, ...), and the line is read from HBM
+// once instead of G times.  Identity when the grid is not a multiple of 8 G.
+template <int TILE, int A>
+__device__ __forceinline__ int xcd_grouped_tile(int w, int tiles) {
+    constexpr int U = TILE >> A, G = U >= 16 ? 1 : 16 / U;
+    if (G == 1 || tiles % (8 * G) != 0) return w;
+    const int x = w & 7, r = w >> 3;
+    return ((r / G) * 8 + x) * G + r % G;
+}
+
+// The limbs of a launch on tiles by class (ntt_cols_mixed): the wide ones first,
+// since their workgroups take longest, N / 1024 workgroups each, then the narrow
+// ones, N / 4096 each; polynomials interleaved.
+struct MixGrid {
+    const uint32_t *ent;
+    uint32_t n_wide, np, base;
+};
+struct MixUnit {
+    uint32_t li, poly, g;
+    int tile;
+    bool fp;
+};
+
+template <int A, int B, bool COLS, typename Fp>
+__device__ __forceinline__ MixUnit mix_unit(const MixGrid &m) {
+    constexpr int LOGN = A + B, TW = LOGN - 10, TN = LOGN - 12;
+    MixUnit u;
+    const uint32_t wide = m.n_wide * m.np;
+    uint32_t w = blockIdx.x, e;
+    u.fp = !std::is_same_v<Fp, NoFp> && w >= wide << TW;
+    if (u.fp) {
+        w -= wide << TW;
+        e = wide + (w >> TN);
+        u.tile = w & ((1 << TN) - 1);
+    } else {
+        e = w >> TW;
+        u.tile = w & ((1 << TW) - 1);
+        if (COLS) u.tile = xcd_grouped_tile<kMixTile, A>(u.tile, 1 << TW);
+    }
+    const uint32_t k = __builtin_amdgcn_readfirstlane(m.np == 1 ? e : m.np == 2 ? e >> 1 : e / m.np);
+    u.poly = e - k * m.np;
+    const uint32_t x = m.ent ? m.ent[k] : k | (m.base + k) << 16;
+    u.li = x & 0xffffu;
+    u.g = x >> 16;
+    return u;
+}
+
+// The first `limbs` Q-limbs of np polynomials.
+static MixGrid q_mix(const rf_ctx *c, uint32_t limbs, uint32_t np) {
+    const LimbOrder o = c->order(c->q_order[limbs]);
+    return MixGrid{o.ent, o.n_wide, np, 0};
+}
+
+// Grid of a launch of `limbs` limbs of each of np polynomials.
+static dim3 mix_grid(const rf_ctx *c, uint32_t n_wide, uint32_t limbs, uint32_t np) {
+    return dim3(np * (n_wide * (c->n / kMixTile) + (limbs - n_wide) * (c->n / kTile)));
 }
 
 template <int A, int B, bool FWD, typename Fp>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ntt_waves(B)))) void ntt_rows_kernel(NttBatch b, Fp fpm, const TwPair *__restrict__ tw_all,
-                                                            const PrimeConst *__restrict__ pcs) {
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ntt_waves(A)))) void ntt_cols_kernel(
+    NttBatch b, Fp, MixGrid m, const TwPair *__restrict__ tw_all, const PrimeConst *__restrict__ pcs) {
+    __shared__ uint64_t lds[(1 << A) * (kTile / (1 << A) + 1)];
+    constexpr int LOGN = A + B;
+    const MixUnit u = mix_unit<A, B, true, Fp>(m);
+    const PrimeConst pc = pcs[u.g];
+    ntt_cols_mixed<A, B, FWD>(lds, b.out + (size_t)u.poly * b.out_poly_stride + ((size_t)u.li << LOGN),
+                              tw_all + ((size_t)u.g << LOGN), pc, u.fp, u.tile,
+                              PlainPro<FWD>{b.in + (size_t)u.poly * b.in_poly_stride + ((size_t)u.li << LOGN)});
+}
+
+template <int A, int B, bool FWD, typename Fp>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ntt_waves(B)))) void ntt_rows_kernel(
+    NttBatch b, Fp, MixGrid m, const TwPair *__restrict__ tw_rows, const TwPair *__restrict__ tw_all,
+    const PrimeConst *__restrict__ pcs) {
     __shared__ uint64_t lds[(1 << B) * (kTile / (1 << B) + 1)];
-    const uint32_t tile = blockIdx.x;
-    const LimbView v = limb_view(b, A + B, blockIdx.y);
-    const PrimeConst pc = pcs[v.g];
-    ntt_rows_unit<A, B, FWD>(lds, v.in, v.out, tw_all + ((size_t)v.g << (A + B)), pc, fpm.has(v.g), tile);
+    constexpr int LOGN = A + B;
+    const MixUnit u = mix_unit<A, B, false, Fp>(m);
+    const PrimeConst pc = pcs[u.g];
+    const size_t tl = (size_t)u.g << LOGN;
+    ntt_rows_mixed<A, B, FWD>(lds, PlainPro<!FWD>{b.in + (size_t)u.poly * b.in_poly_stride + ((size_t)u.li << LOGN)},
+                              tw_rows + tl, tw_all + tl, pc, u.fp, u.tile,
+                              RowStore<FWD>{b.out + (size_t)u.poly * b.out_poly_stride + ((size_t)u.li << LOGN)});
 }
 
 // Prologue of the first pass of NTT(conv): the ModDown conversion of target i
@@ -101,115 +171,100 @@ __device__ __forceinline__ LiftPro<KEEP_T> lift_pro(const uint64_t *last, const 
 // prologue: limb (c, i) of conv [2][nl][N] from the K P-limbs of ip[c].
 template <int A, int B, int KP, typename Fp>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(KP == 8 ? 3 : kNttWavesFused))) void ntt_cols_moddown_kernel(
-    Fp fpm, const uint64_t *ip, uint64_t *conv, const TwPair *__restrict__ tw_all, const PrimeConst *__restrict__ pcs,
+    Fp, MixGrid m, const uint64_t *ip, uint64_t *conv, const TwPair *__restrict__ tw_all, const PrimeConst *__restrict__ pcs,
     const uint64_t *__restrict__ cross, const uint64_t *__restrict__ negp, uint32_t nl, uint32_t L, uint32_t K) {
     __shared__ uint64_t lds[(1 << A) * (kTile / (1 << A) + 1)];
     constexpr int LOGN = A + B;
-    const uint32_t tile = blockIdx.x;
-    const uint32_t c = blockIdx.y & 1, i = blockIdx.y >> 1;  // polynomials interleaved
+    const MixUnit u = mix_unit<A, B, true, Fp>(m);
+    const uint32_t c = u.poly, i = u.li;
     const PrimeConst pc = pcs[i];
     const ModdownPro<KP> pro = moddown_pro<KP, LOGN>(ip, pcs, pc, cross, negp, c, i, nl, L, K);
-    ntt_cols_unit_pro<A, B, true>(lds, conv + (((size_t)c * nl + i) << LOGN), tw_all + ((size_t)i << LOGN), pc,
-                                  fpm.has(i), tile, pro);
+    ntt_cols_mixed<A, B, true>(lds, conv + (((size_t)c * nl + i) << LOGN), tw_all + ((size_t)i << LOGN), pc, u.fp,
+                               u.tile, pro);
 }
 
 // First forward pass of NTT(lift) with the rescale lift as its prologue: limb
 // (c, i) of lift [2][l][N], l = nl - 1, from the last limb last[c].
 template <int A, int B, bool KEEP_T, typename Fp>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kNttWavesFused))) void ntt_cols_lift_kernel(
-    Fp fpm, const uint64_t *last, uint64_t *lift, const TwPair *__restrict__ tw_all, const PrimeConst *__restrict__ pcs,
+    Fp, MixGrid m, const uint64_t *last, uint64_t *lift, const TwPair *__restrict__ tw_all, const PrimeConst *__restrict__ pcs,
     const uint64_t *__restrict__ tab, uint32_t nl, uint32_t L) {
     __shared__ uint64_t lds[(1 << A) * (kTile / (1 << A) + 1)];
     constexpr int LOGN = A + B;
     const uint32_t l = nl - 1;
-    const uint32_t tile = blockIdx.x;
-    const uint32_t c = blockIdx.y & 1, i = blockIdx.y >> 1;  // polynomials interleaved
+    const MixUnit u = mix_unit<A, B, true, Fp>(m);
+    const uint32_t c = u.poly, i = u.li;
     const PrimeConst pc = pcs[i];
     const LiftPro<KEEP_T> pro = lift_pro<KEEP_T, LOGN>(last, pcs, pc, tab, c, i, nl, L);
-    ntt_cols_unit_pro<A, B, true>(lds, lift + (((size_t)c * l + i) << LOGN), tw_all + ((size_t)i << LOGN), pc,
-                                  fpm.has(i), tile, pro);
+    ntt_cols_mixed<A, B, true>(lds, lift + (((size_t)c * l + i) << LOGN), tw_all + ((size_t)i << LOGN), pc, u.fp,
+                               u.tile, pro);
 }
 
 // Last forward pass of NTT(conv) with the ModDown tail: limb (c, i) of conv
 // [2][nl][N] -> out[c][i] = (ip[c][i] - NTT(conv)[c][i]) P^-1 (+ add_c[i]).
 template <int A, int B, typename Fp>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ntt_waves(B)))) void ntt_rows_moddown_kernel(
-    Fp fpm, const uint64_t *conv, const TwPair *__restrict__ tw_all, const PrimeConst *__restrict__ pcs, const uint64_t *ip,
+    Fp, MixGrid m, const uint64_t *conv, const TwPair *__restrict__ tw_rows, const TwPair *__restrict__ tw_all, const PrimeConst *__restrict__ pcs, const uint64_t *ip,
     uint64_t *out, const uint64_t *__restrict__ pinv, uint32_t nl, uint32_t K) {
     __shared__ uint64_t lds[(1 << B) * (kTile / (1 << B) + 1)];
     constexpr int LOGN = A + B;
-    const uint32_t tile = blockIdx.x;
-    const uint32_t c = blockIdx.y & 1, i = blockIdx.y >> 1;  // polynomials interleaved
+    const MixUnit u = mix_unit<A, B, false, Fp>(m);
+    const uint32_t c = u.poly, i = u.li;
     const PrimeConst pc = pcs[i];
     const ModdownFoldEpi epi{ip + (((size_t)c * (nl + K) + i) << LOGN), out + (((size_t)c * nl + i) << LOGN),
                              pinv[2 * i], pinv[2 * i + 1], pc.q};
-    ntt_rows_unit_epi<A, B>(lds, conv + (((size_t)c * nl + i) << LOGN), tw_all + ((size_t)i << LOGN), pc,
-                                  fpm.has(i), tile, epi);
+    ntt_rows_mixed<A, B, true>(lds, RawPro{conv + (((size_t)c * nl + i) << LOGN)}, tw_rows + ((size_t)i << LOGN),
+                               tw_all + ((size_t)i << LOGN), pc, u.fp, u.tile, epi);
 }
 
 // First inverse pass of INTT(d2) with d2 = a1 b1 as its prologue: limb i of a, b
 // ([2][nl][N], NTT domain); the row pass goes to dc [nl][N].
 template <int A, int B, typename Fp>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ntt_waves(B)))) void ntt_inv_rows_tensor_kernel(
-    Fp fpm, const uint64_t *a, const uint64_t *b, uint64_t *dc, const TwPair *__restrict__ tw_all,
+    Fp, MixGrid m, const uint64_t *a, const uint64_t *b, uint64_t *dc, const TwPair *__restrict__ tw_rows, const TwPair *__restrict__ tw_all,
     const PrimeConst *__restrict__ pcs, uint32_t nl) {
     __shared__ uint64_t lds[(1 << B) * (kTile / (1 << B) + 1)];
     constexpr int LOGN = A + B;
-    const uint32_t tile = blockIdx.x, i = blockIdx.y;
+    const MixUnit u = mix_unit<A, B, false, Fp>(m);
+    const uint32_t i = u.li;
     const PrimeConst pc = pcs[i];
     const size_t li = (size_t)i << LOGN, poly = (size_t)nl << LOGN;
     const TensorPro pro{a + poly + li, b + poly + li, pc.q, pc.r64, pc.r64_p, pc.one_p};
-    ntt_rows_unit_pe<A, B, false>(lds, pro, tw_all + li, pc, fpm.has(i), tile, RawEpi{dc + li});
+    ntt_rows_mixed<A, B, false>(lds, pro, tw_rows + li, tw_all + li, pc, u.fp, u.tile, RawEpi{dc + li});
 }
 
 // First inverse pass of INTT(sigma_g(a1)) with the automorphism as its
 // prologue: limb i of a1 ([nl][N], NTT domain) permuted, row pass into dc.
 template <int A, int B, typename Fp>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ntt_waves(B)))) void ntt_inv_rows_gather_kernel(
-    Fp fpm, const uint64_t *a1, uint64_t *dc, uint32_t galois, const TwPair *__restrict__ tw_all,
+    Fp, MixGrid m, const uint64_t *a1, uint64_t *dc, uint32_t galois, const TwPair *__restrict__ tw_rows, const TwPair *__restrict__ tw_all,
     const PrimeConst *__restrict__ pcs) {
     __shared__ uint64_t lds[(1 << B) * (kTile / (1 << B) + 1)];
     constexpr int LOGN = A + B;
-    const uint32_t tile = blockIdx.x, i = blockIdx.y;
+    const MixUnit u = mix_unit<A, B, false, Fp>(m);
+    const uint32_t i = u.li;
     const PrimeConst pc = pcs[i];
     const size_t li = (size_t)i << LOGN;
     const GatherPro pro{a1 + li, galois, (uint32_t)LOGN};
-    ntt_rows_unit_pe<A, B, false>(lds, pro, tw_all + li, pc, fpm.has(i), tile, RawEpi{dc + li});
+    ntt_rows_mixed<A, B, false>(lds, pro, tw_rows + li, tw_all + li, pc, u.fp, u.tile, RawEpi{dc + li});
 }
 
 // Last forward pass of NTT(lift) with the rescale tail: limb (c, i) of lift
 // [2][l][N] -> out[c][i] = (in[c][i] - NTT(lift)[c][i]) q_l^-1, l = nl - 1.
 template <int A, int B, typename Fp>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ntt_waves(B)))) void ntt_rows_rescale_kernel(
-    Fp fpm, const uint64_t *lift, const TwPair *__restrict__ tw_all, const PrimeConst *__restrict__ pcs, const uint64_t *in,
+    Fp, MixGrid m, const uint64_t *lift, const TwPair *__restrict__ tw_rows, const TwPair *__restrict__ tw_all, const PrimeConst *__restrict__ pcs, const uint64_t *in,
     uint64_t *out, const uint64_t *__restrict__ tab, uint32_t nl, uint32_t L) {
     __shared__ uint64_t lds[(1 << B) * (kTile / (1 << B) + 1)];
     constexpr int LOGN = A + B;
     const uint32_t l = nl - 1;
-    const uint32_t tile = blockIdx.x;
-    const uint32_t c = blockIdx.y & 1, i = blockIdx.y >> 1;  // polynomials interleaved
+    const MixUnit u = mix_unit<A, B, false, Fp>(m);
+    const uint32_t c = u.poly, i = u.li;
     const PrimeConst pc = pcs[i];
     const uint64_t *t = tab + ((size_t)l * L + i) * 3;
     RescaleTailEpi epi{in + (((size_t)c * nl + i) << LOGN), out + (((size_t)c * l + i) << LOGN), t[0], t[1], pc.q};
-    ntt_rows_unit_epi<A, B>(lds, lift + (((size_t)c * l + i) << LOGN), tw_all + ((size_t)i << LOGN), pc,
-                                  fpm.has(i), tile, epi);
-}
-
-// A pass of a launch with few limbs (ntt_cols_small / ntt_rows_small): one
-// workgroup per TILE residues of a limb, E residues per thread.
-// Tile of a small column pass.  Its U = TILE / 2^A columns are narrower than
-// a 128-byte line (G = 16 / U tiles share each line of a row), and workgroups
-// are dealt to the 8 XCDs in turn, each with its own L2: dispatch order
-// w = blockIdx.x is mapped so that the G tiles of one line group go to the
-// same XCD one after another (w, w + 8, ...), and the line is read from HBM
-// once instead of G times.  Identity when the grid is not a multiple of 8 G.
-template <int TILE, int A>
-__device__ __forceinline__ int xcd_grouped_tile() {
-    constexpr int U = TILE >> A, G = U >= 16 ? 1 : 16 / U;
-    const int w = blockIdx.x;
-    if (G == 1 || gridDim.x % (8 * G) != 0) return w;
-    const int x = w & 7, r = w >> 3;
-    return ((r / G) * 8 + x) * G + r % G;
+    ntt_rows_mixed<A, B, true>(lds, RawPro{lift + (((size_t)c * l + i) << LOGN)}, tw_rows + ((size_t)i << LOGN),
+                               tw_all + ((size_t)i << LOGN), pc, u.fp, u.tile, epi);
 }
 
 template <int A, int B, bool FWD, bool COLS, int TILE, int E, typename Fp>
@@ -220,7 +275,7 @@ __global__ __launch_bounds__(TILE / E) void ntt_small_kernel(NttBatch b, Fp fpm,
     const LimbView v = limb_view(b, A + B, blockIdx.y);
     const PrimeConst pc = pcs[v.g];
     const TwPair *tw = tw_all + ((size_t)v.g << (A + B));
-    if constexpr (COLS) ntt_cols_small<A, B, FWD, TILE, E>(lds, v.in, v.out, tw, pc, fpm.has(v.g), xcd_grouped_tile<TILE, A>());
+    if constexpr (COLS) ntt_cols_small<A, B, FWD, TILE, E>(lds, v.in, v.out, tw, pc, fpm.has(v.g), xcd_grouped_tile<TILE, A>(blockIdx.x, gridDim.x));
     else ntt_rows_small<A, B, FWD, TILE, E>(lds, v.in, v.out, tw, pc, fpm.has(v.g), blockIdx.x);
 }
 
@@ -242,7 +297,7 @@ __global__ __launch_bounds__(TILE / kSmallE) void ntt_small_cols_moddown_kernel(
     const PrimeConst pc = pcs[i];
     const ModdownPro<KP> pro = moddown_pro<KP, LOGN>(ip, pcs, pc, cross, negp, c, i, nl, L, K);
     ntt_cols_small_pro<A, B, true, TILE, kSmallE>(lds, pro, conv + (((size_t)c * nl + i) << LOGN),
-                                                  tw_all + ((size_t)i << LOGN), pc, fpm.has(i), xcd_grouped_tile<TILE, A>());
+                                                  tw_all + ((size_t)i << LOGN), pc, fpm.has(i), xcd_grouped_tile<TILE, A>(blockIdx.x, gridDim.x));
 }
 
 template <int A, int B, int TILE, typename Fp>
@@ -270,7 +325,7 @@ __global__ __launch_bounds__(TILE / kSmallE) void ntt_small_cols_lift_kernel(
     const PrimeConst pc = pcs[i];
     const LiftPro<KEEP_T> pro = lift_pro<KEEP_T, LOGN>(last, pcs, pc, tab, c, i, nl, L);
     ntt_cols_small_pro<A, B, true, TILE, kSmallE>(lds, pro, lift + (((size_t)c * l + i) << LOGN),
-                                                  tw_all + ((size_t)i << LOGN), pc, fpm.has(i), xcd_grouped_tile<TILE, A>());
+                                                  tw_all + ((size_t)i << LOGN), pc, fpm.has(i), xcd_grouped_tile<TILE, A>(blockIdx.x, gridDim.x));
 }
 
 template <int A, int B, int TILE, typename Fp>
@@ -338,6 +393,31 @@ static void launch_two_pass_small(const rf_ctx *c, Fp fpm, const NttBatch &b, bo
 }
 
 template <int A, int B, typename Fp>
+static void launch_mixed(const rf_ctx *c, Fp fpm, const NttBatch &b, const MixGrid &m, bool forward, hipStream_t s,
+                         const PrimeConst *pcs) {
+    const dim3 block(kThreads), grid = mix_grid(c, m.n_wide, b.per_poly, b.n_polys);
+    NttBatch b2 = b;
+    b2.in = b.out;
+    b2.in_poly_stride = b.out_poly_stride;
+    if (forward) {
+        {
+            ProfScope p("ntt_fwd_cols", s);
+            hipLaunchKernelGGL((ntt_cols_kernel<A, B, true>), grid, block, 0, s, b, fpm, m, c->d_tw_fwd, pcs);
+        }
+        ProfScope p("ntt_fwd_rows", s);
+        hipLaunchKernelGGL((ntt_rows_kernel<A, B, true>), grid, block, 0, s, b2, fpm, m, c->d_tw_fwd_rows, c->d_tw_fwd, pcs);
+    } else {
+        {
+            ProfScope p("ntt_inv_rows", s);
+            hipLaunchKernelGGL((ntt_rows_kernel<A, B, false>), grid, block, 0, s, b, fpm, m, c->d_tw_inv_rows, c->d_tw_inv,
+                               pcs);
+        }
+        ProfScope p("ntt_inv_cols", s);
+        hipLaunchKernelGGL((ntt_cols_kernel<A, B, false>), grid, block, 0, s, b2, fpm, m, c->d_tw_inv, pcs);
+    }
+}
+
+template <int A, int B, typename Fp>
 static void launch_two_pass(const rf_ctx *c, Fp fpm, const NttBatch &b, bool forward, hipStream_t s,
                             const PrimeConst *pcs, const rf_tuning &tn) {
     const uint32_t limbs = b.per_poly * b.n_polys;
@@ -353,27 +433,20 @@ static void launch_two_pass(const rf_ctx *c, Fp fpm, const NttBatch &b, bool for
         }
         return;
     }
-    const dim3 block(kThreads);
-    const dim3 grid_cols((1u << B) / (kTile >> A), limbs);
-    const dim3 grid_rows((1u << A) / (kTile >> B), limbs);
-    NttBatch b2 = b;
-    b2.in = b.out;
-    b2.in_poly_stride = b.out_poly_stride;
-    if (forward) {
-        {
-            ProfScope p("ntt_fwd_cols", s);
-            hipLaunchKernelGGL((ntt_cols_kernel<A, B, true>), grid_cols, block, 0, s, b, fpm, c->d_tw_fwd, pcs);
+    // limbs without an order of their own: a launch per run of one class
+    if (!b.order.ent && !b.pmap) {
+        for (uint32_t i = 0, j; i < b.per_poly; i = j) {
+            const bool wide = !fpm.has(b.prime_base + i);
+            for (j = i + 1; j < b.per_poly && wide == !fpm.has(b.prime_base + j);) ++j;
+            NttBatch r = b;
+            r.in += (size_t)i * c->n;
+            r.out += (size_t)i * c->n;
+            r.per_poly = j - i;
+            launch_mixed<A, B>(c, fpm, r, MixGrid{nullptr, wide ? j - i : 0, b.n_polys, b.prime_base + i}, forward, s, pcs);
         }
-        ProfScope p("ntt_fwd_rows", s);
-        hipLaunchKernelGGL((ntt_rows_kernel<A, B, true>), grid_rows, block, 0, s, b2, fpm, c->d_tw_fwd_rows, pcs);
-    } else {
-        {
-            ProfScope p("ntt_inv_rows", s);
-            hipLaunchKernelGGL((ntt_rows_kernel<A, B, false>), grid_rows, block, 0, s, b, fpm, c->d_tw_inv_rows, pcs);
-        }
-        ProfScope p("ntt_inv_cols", s);
-        hipLaunchKernelGGL((ntt_cols_kernel<A, B, false>), grid_cols, block, 0, s, b2, fpm, c->d_tw_inv, pcs);
+        return;
     }
+    launch_mixed<A, B>(c, fpm, b, MixGrid{b.order.ent, b.order.n_wide, b.n_polys, 0}, forward, s, pcs);
 }
 
 // Small-tile size of a fused launch of `limbs` limbs, or 0 for the 4096-residue
@@ -391,7 +464,8 @@ static int launch_ntt_fwd_moddown_t(const rf_ctx *c, Fp fpm, uint64_t *conv, con
     const uint64_t *tab = c->scheme == RF_BGV ? c->d_moddown_t : c->d_moddown;
     const uint64_t *cross = tab + moddown_cross_off(c), *negp = tab + moddown_negp_off(c);
     const uint64_t *pinv = c->d_moddown + moddown_pinv_off(c);
-    const dim3 g(c->n / kTile, 2 * nl);
+    const MixGrid mg = q_mix(c, nl, 2);
+    const dim3 g = mix_grid(c, mg.n_wide, nl, 2);
     const int st = small_tile_of(c, 2 * nl, tn);
     if (st) {
 #define RF_SMDK(A, B, T, KP)                                                                                     \
@@ -411,7 +485,7 @@ static int launch_ntt_fwd_moddown_t(const rf_ctx *c, Fp fpm, uint64_t *conv, con
         }                                                                                                        \
         ProfScope p("ntt_fwd_rows_moddown_small", s);                                                            \
         hipLaunchKernelGGL((ntt_small_rows_moddown_kernel<A, B, T>), dim3(c->n / T, 2 * nl), dim3(T / kSmallE), 0, s, \
-                           fpm, conv, c->d_tw_fwd, c->d_pc, ip, out, pinv, nl, c->K);                     \
+                           fpm, conv, c->d_tw_fwd, c->d_pc, ip, out, pinv, nl, c->K);                            \
     }
 #define RF_SMDT(A, B)                                                                                            \
     if (st == 2048) RF_SMD(A, B, 2048) else RF_SMD(A, B, 1024)
@@ -429,8 +503,8 @@ static int launch_ntt_fwd_moddown_t(const rf_ctx *c, Fp fpm, uint64_t *conv, con
         return RF_OK;
     }
 #define RF_MDK(A, B, KP)                                                                                         \
-    hipLaunchKernelGGL((ntt_cols_moddown_kernel<A, B, KP>), dim3((1u << B) / (kTile >> A), 2 * nl), dim3(kThreads), \
-                       0, s, fpm, ip, conv, c->d_tw_fwd, c->d_pc, cross, negp, nl, c->L, c->K)
+    hipLaunchKernelGGL((ntt_cols_moddown_kernel<A, B, KP>), g, dim3(kThreads),                                   \
+                       0, s, fpm, mg, ip, conv, c->d_tw_fwd, c->d_pc, cross, negp, nl, c->L, c->K)
 #define RF_MD(A, B)                                                                                              \
     {                                                                                                            \
         {                                                                                                        \
@@ -444,7 +518,7 @@ static int launch_ntt_fwd_moddown_t(const rf_ctx *c, Fp fpm, uint64_t *conv, con
             }                                                                                                    \
         }                                                                                                        \
         ProfScope p("ntt_fwd_rows_moddown", s);                                                                  \
-        hipLaunchKernelGGL((ntt_rows_moddown_kernel<A, B>), g, dim3(kThreads), 0, s, fpm, conv, c->d_tw_fwd_rows, c->d_pc, ip, \
+        hipLaunchKernelGGL((ntt_rows_moddown_kernel<A, B>), g, dim3(kThreads), 0, s, fpm, mg, conv, c->d_tw_fwd_rows, c->d_tw_fwd, c->d_pc, ip, \
                            out, pinv, nl, c->K);                                                                 \
     }
     switch (c->log_n) {
@@ -471,7 +545,8 @@ template <typename Fp>
 static int launch_ntt_fwd_rescale_t(const rf_ctx *c, Fp fpm, const uint64_t *last, uint64_t *lift, const uint64_t *in,
                            uint64_t *out, uint32_t nl, bool keep_t, hipStream_t s, const rf_tuning *tn) {
     const uint32_t l = nl - 1;
-    const dim3 g(c->n / kTile, 2 * l);
+    const MixGrid mg = q_mix(c, l, 2);
+    const dim3 g = mix_grid(c, mg.n_wide, l, 2);
     const int st = small_tile_of(c, 2 * l, tn);
     if (st) {
 #define RF_SRS(A, B, T)                                                                                          \
@@ -480,10 +555,10 @@ static int launch_ntt_fwd_rescale_t(const rf_ctx *c, Fp fpm, const uint64_t *las
         {                                                                                                        \
             ProfScope p("ntt_fwd_cols_lift_small", s);                                                           \
             if (keep_t)                                                                                          \
-                hipLaunchKernelGGL((ntt_small_cols_lift_kernel<A, B, T, true>), gs, bs, 0, s, fpm, last, lift, \
+                hipLaunchKernelGGL((ntt_small_cols_lift_kernel<A, B, T, true>), gs, bs, 0, s, fpm, last, lift,   \
                                    c->d_tw_fwd, c->d_pc, c->d_rescale, nl, c->L);                                \
             else                                                                                                 \
-                hipLaunchKernelGGL((ntt_small_cols_lift_kernel<A, B, T, false>), gs, bs, 0, s, fpm, last, lift, \
+                hipLaunchKernelGGL((ntt_small_cols_lift_kernel<A, B, T, false>), gs, bs, 0, s, fpm, last, lift,  \
                                    c->d_tw_fwd, c->d_pc, c->d_rescale, nl, c->L);                                \
         }                                                                                                        \
         ProfScope p("ntt_fwd_rows_rescale_small", s);                                                            \
@@ -508,16 +583,15 @@ static int launch_ntt_fwd_rescale_t(const rf_ctx *c, Fp fpm, const uint64_t *las
     {                                                                                                            \
         {                                                                                                        \
             ProfScope p("ntt_fwd_cols_lift", s);                                                                 \
-            const dim3 gc((1u << B) / (kTile >> A), 2 * l);                                                      \
             if (keep_t)                                                                                          \
-                hipLaunchKernelGGL((ntt_cols_lift_kernel<A, B, true>), gc, dim3(kThreads), 0, s, fpm, last, lift, \
+                hipLaunchKernelGGL((ntt_cols_lift_kernel<A, B, true>), g, dim3(kThreads), 0, s, fpm, mg, last, lift, \
                                    c->d_tw_fwd, c->d_pc, c->d_rescale, nl, c->L);                                \
             else                                                                                                 \
-                hipLaunchKernelGGL((ntt_cols_lift_kernel<A, B, false>), gc, dim3(kThreads), 0, s, fpm, last, lift, \
+                hipLaunchKernelGGL((ntt_cols_lift_kernel<A, B, false>), g, dim3(kThreads), 0, s, fpm, mg, last, lift, \
                                    c->d_tw_fwd, c->d_pc, c->d_rescale, nl, c->L);                                \
         }                                                                                                        \
         ProfScope p("ntt_fwd_rows_rescale", s);                                                                  \
-        hipLaunchKernelGGL((ntt_rows_rescale_kernel<A, B>), g, dim3(kThreads), 0, s, fpm, lift, c->d_tw_fwd_rows, c->d_pc, in, \
+        hipLaunchKernelGGL((ntt_rows_rescale_kernel<A, B>), g, dim3(kThreads), 0, s, fpm, mg, lift, c->d_tw_fwd_rows, c->d_tw_fwd, c->d_pc, in, \
                            out, c->d_rescale, nl, c->L);                                                         \
     }
     switch (c->log_n) {
@@ -550,10 +624,10 @@ static int launch_intt_first_t(const rf_ctx *c, Fp fpm, const uint64_t *a, const
         const dim3 gs(c->n / T, nl), bs(T / kSmallE);                                                            \
         {                                                                                                        \
             ProfScope p(galois ? "ntt_inv_rows_gather_small" : "ntt_inv_rows_tensor_small", s);                  \
-            hipLaunchKernelGGL((ntt_small_inv_rows_first_kernel<A, B, T>), gs, bs, 0, s, fpm, a, b, dc, galois, \
+            hipLaunchKernelGGL((ntt_small_inv_rows_first_kernel<A, B, T>), gs, bs, 0, s, fpm, a, b, dc, galois,  \
                                c->d_tw_inv, c->d_pc, nl);                                                        \
         }                                                                                                        \
-        NttBatch bc{dc, dc, 0, 0, nl, 1, 0, nullptr};                                                            \
+        NttBatch bc{dc, dc, 0, 0, nl, 1, 0, nullptr, {}};                                                        \
         ProfScope p("ntt_inv_cols_small", s);                                                                    \
         hipLaunchKernelGGL((ntt_small_kernel<A, B, false, true, T, kSmallE>), gs, bs, 0, s, bc, fpm, c->d_tw_inv, \
                            pc_modup(c, nl));                                                                     \
@@ -574,20 +648,20 @@ static int launch_intt_first_t(const rf_ctx *c, Fp fpm, const uint64_t *a, const
     }
 #define RF_IF(A, B)                                                                                              \
     {                                                                                                            \
-        const dim3 gr((1u << A) / (kTile >> B), nl);                                                             \
+        const MixGrid mg = q_mix(c, nl, 1);                                                                      \
+        const dim3 gr = mix_grid(c, mg.n_wide, nl, 1);                                                           \
         if (galois) {                                                                                            \
             ProfScope p("ntt_inv_rows_gather", s);                                                               \
-            hipLaunchKernelGGL((ntt_inv_rows_gather_kernel<A, B>), gr, dim3(kThreads), 0, s, fpm, a + (size_t)nl * N, dc, \
-                               galois, c->d_tw_inv_rows, c->d_pc);                                               \
+            hipLaunchKernelGGL((ntt_inv_rows_gather_kernel<A, B>), gr, dim3(kThreads), 0, s, fpm, mg, a + (size_t)nl * N, dc, \
+                               galois, c->d_tw_inv_rows, c->d_tw_inv, c->d_pc);                                  \
         } else {                                                                                                 \
             ProfScope p("ntt_inv_rows_tensor", s);                                                               \
-            hipLaunchKernelGGL((ntt_inv_rows_tensor_kernel<A, B>), gr, dim3(kThreads), 0, s, fpm, a, b, dc, \
-                               c->d_tw_inv_rows, c->d_pc, nl);                                                   \
+            hipLaunchKernelGGL((ntt_inv_rows_tensor_kernel<A, B>), gr, dim3(kThreads), 0, s, fpm, mg, a, b, dc,  \
+                               c->d_tw_inv_rows, c->d_tw_inv, c->d_pc, nl);                                      \
         }                                                                                                        \
-        NttBatch bc{dc, dc, 0, 0, nl, 1, 0, nullptr};                                                            \
+        NttBatch bc{dc, dc, 0, 0, nl, 1, 0, nullptr, {}};                                                        \
         ProfScope p("ntt_inv_cols", s);                                                                          \
-        hipLaunchKernelGGL((ntt_cols_kernel<A, B, false>), dim3((1u << B) / (kTile >> A), nl), dim3(kThreads), 0, \
-                           s, bc, fpm, c->d_tw_inv, pc_modup(c, nl));                                     \
+        hipLaunchKernelGGL((ntt_cols_kernel<A, B, false>), gr, dim3(kThreads), 0, s, bc, fpm, mg, c->d_tw_inv, pc_modup(c, nl)); \
     }
     switch (c->log_n) {
         case 13: RF_IF(7, 6) break;
@@ -637,16 +711,17 @@ int launch_ntt(const rf_ctx *c, const NttBatch &b, bool forward, hipStream_t s, 
 
 template <typename Fp>
 static int launch_intt_cols_t(const rf_ctx *c, Fp fpm, uint64_t *data, uint32_t nl, hipStream_t s) {
-    const NttBatch b{data, data, 0, 0, nl, 1, 0, nullptr};
+    const NttBatch b{data, data, 0, 0, nl, 1, 0, nullptr, {}};
+    const MixGrid mg = q_mix(c, nl, 1);
     const bool small = nl * (c->n / kTile) < kDefaultTuning.ntt_small_below;
     ProfScope p(small ? "ntt_inv_cols_small" : "ntt_inv_cols", s);
 #define RF_IC(A, B)                                                                                              \
     if (small)                                                                                                   \
-        hipLaunchKernelGGL((ntt_small_kernel<A, B, false, true, 1024, kSmallE, Fp>), dim3(c->n / 1024, nl),       \
+        hipLaunchKernelGGL((ntt_small_kernel<A, B, false, true, 1024, kSmallE, Fp>), dim3(c->n / 1024, nl),      \
                            dim3(1024 / kSmallE), 0, s, b, fpm, c->d_tw_inv, c->d_pc);                            \
     else                                                                                                         \
-        hipLaunchKernelGGL((ntt_cols_kernel<A, B, false, Fp>), dim3(c->n / kTile, nl), dim3(kThreads), 0, s, b,   \
-                           fpm, c->d_tw_inv, c->d_pc)
+        hipLaunchKernelGGL((ntt_cols_kernel<A, B, false, Fp>), mix_grid(c, mg.n_wide, nl, 1), dim3(kThreads),    \
+                           0, s, b, fpm, mg, c->d_tw_inv, c->d_pc)
     switch (c->log_n) {
         case 13: RF_IC(7, 6); break;
         case 14: RF_IC(7, 7); break;

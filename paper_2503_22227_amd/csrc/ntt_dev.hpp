@@ -516,6 +516,15 @@ __device__ __forceinline__ void ntt_rows_small(uint64_t *lds, const uint64_t *in
 // (ntt_cols_compute): the prologue's temporaries are dead before the transform
 // starts, which keeps the multi-pass batched kernels within their register
 // budget.
+// A thread of a 4096-residue tile fetches all its twiddles with its residues
+// where they fit the registers: 30 doubles in FP64 (60 pairs of integers do
+// not).  Fetched stage by stage, each stage waits for the table: the passes of 24
+// to 60 limbs at N = 2^16 take 2 to 9 % longer.
+template <typename Ar>
+__device__ __forceinline__ constexpr int tile_tw() {
+    return Ar::kFp ? kTwCached : kTwLoad;
+}
+
 template <typename Ar, int A, int B, bool FWD, typename Pro>
 __device__ __forceinline__ void ntt_cols_load(typename Ar::V (&regs)[kElems], int tile, const Pro &pro, const Ar &ar) {
     static_assert(A > kElemsLog && A <= 2 * kElemsLog, "two rounds");
@@ -541,18 +550,21 @@ __device__ __forceinline__ void ntt_cols_load(typename Ar::V (&regs)[kElems], in
 // left as Ar's bits (integer: lazy below 4q).
 template <typename Ar, int A, int B, bool FWD>
 __device__ __forceinline__ void ntt_cols_compute(uint64_t *lds, uint64_t *out, const TwPair *__restrict__ tw_all,
-                                                 const Ar &ar, int tile, typename Ar::V (&regs)[kElems]) {
+                                                 const Ar &ar, int tile, typename Ar::V (&regs)[kElems],
+                                                 typename Ar::Tw *twc) {
     constexpr int S = 1 << A;
     constexpr int U = kTile / S;
     constexpr int LDU = U + 1;
-    constexpr int C2 = A - kElemsLog;
+    constexpr int C2 = A - kElemsLog, TW = tile_tw<Ar>(), SLOT1 = kElems * kElemsLog;
     const int col0 = tile * U;
     const int u = threadIdx.x % U, t = threadIdx.x / U;
     const auto *tw = twiddles<Ar>(tw_all);
     if constexpr (FWD) {
-        ntt_round<Ar, A, 0, kElemsLog, true, false, 0, true, false>(TileLds{lds, LDU, u}, t, 1u, tw, ar, regs);
+        ntt_round<Ar, A, 0, kElemsLog, true, false, 0, true, false, kElems, TW>(TileLds{lds, LDU, u}, t, 1u, tw, ar,
+                                                                                regs, twc);
         __syncthreads();
-        ntt_round<Ar, A, kElemsLog, C2, true, false, 0, false, false>(TileLds{lds, LDU, u}, t, 1u, tw, ar);
+        ntt_round<Ar, A, kElemsLog, C2, true, false, 0, false, false, kElems, TW, SLOT1>(TileLds{lds, LDU, u}, t, 1u,
+                                                                                         tw, ar, nullptr, twc);
         __syncthreads();
 #pragma unroll
         for (int r = 0; r < kTile / kThreads; ++r) {
@@ -567,11 +579,13 @@ __device__ __forceinline__ void ntt_cols_compute(uint64_t *lds, uint64_t *out, c
             lds[(idx / U) * LDU + idx % U] = Ar::bits(regs[r]);
         }
         __syncthreads();
-        ntt_round<Ar, A, 0, kElemsLog, false, false, 0, false, false>(TileLds{lds, LDU, u}, t, 1u, tw, ar);
+        ntt_round<Ar, A, 0, kElemsLog, false, false, 0, false, false, kElems, TW>(TileLds{lds, LDU, u}, t, 1u, tw, ar,
+                                                                                  nullptr, twc);
         __syncthreads();
         // The last inverse round leaves rows grp + 16 e (grp = t NG + gi) of
         // column u in registers, the order of a coalesced store.
-        ntt_round<Ar, A, kElemsLog, C2, false, true, 0, false, true>(TileLds{lds, LDU, u}, t, 1u, tw, ar, regs);
+        ntt_round<Ar, A, kElemsLog, C2, false, true, 0, false, true, kElems, TW, SLOT1>(TileLds{lds, LDU, u}, t, 1u, tw,
+                                                                                        ar, regs, twc);
         constexpr int G = 1 << C2, NG = kElems / G;
 #pragma unroll
         for (int gi = 0; gi < NG; ++gi)
@@ -588,8 +602,12 @@ template <typename Ar, int A, int B, bool FWD, typename Pro>
 __device__ __forceinline__ void ntt_cols_unit_t(uint64_t *lds, uint64_t *out, const TwPair *__restrict__ tw,
                                                 const Ar &ar, int tile, const Pro &pro) {
     typename Ar::V regs[kElems];
+    typename Ar::Tw twc[tile_tw<Ar>() == kTwCached ? tw_slots(A, kElems) : 1];
     ntt_cols_load<Ar, A, B, FWD>(regs, tile, pro, ar);
-    ntt_cols_compute<Ar, A, B, FWD>(lds, out, tw, ar, tile, regs);
+    if constexpr (tile_tw<Ar>() == kTwCached)
+        ntt_rounds<Ar, A, FWD, !FWD, 0, kElems, kTwPrefetch>(TileLds{}, threadIdx.x / (kTile >> A), 1u, twiddles<Ar>(tw),
+                                                             ar, twc);
+    ntt_cols_compute<Ar, A, B, FWD>(lds, out, tw, ar, tile, regs, twc);
 }
 
 // The prime decides the arithmetic (fp: it is below kFpPrimeBound; uniform
@@ -599,6 +617,22 @@ __device__ __forceinline__ void ntt_cols_unit_pro(uint64_t *lds, uint64_t *out, 
                                                   const PrimeConst &pc, bool fp, int tile, const Pro &pro) {
     if (fp) ntt_cols_unit_t<ArFp, A, B, FWD>(lds, out, tw, ArFp(pc), tile, pro);
     else ntt_cols_unit_t<ArInt, A, B, FWD>(lds, out, tw, ArInt(pc), tile, pro);
+}
+
+// Launches that hold limbs of both classes give each its own tile: a wide prime's
+// is 1024 residues, 4 per thread with every twiddle fetched up front (kMixTile),
+// a narrow one's 4096, 16 per thread.  On 4096-residue tiles a wide limb's
+// workgroup runs 64 integer butterflies a thread, 3 us of issue and eight waits
+// for its twiddles, long after the narrow ones are done: the 13-limb passes at N
+// = 2^15 took 9.6 to 15.7 us and take 6.2 to 14.6, the 24 to 60-limb ones at N =
+// 2^16 13.4 to 22.0 and now 12.9 to 21.7.
+constexpr int kMixTile = 1024, kMixE = kMixTile / kThreads;
+
+template <int A, int B, bool FWD, typename Pro>
+__device__ __forceinline__ void ntt_cols_mixed(uint64_t *lds, uint64_t *out, const TwPair *__restrict__ tw,
+                                               const PrimeConst &pc, bool fp, int tile, const Pro &pro) {
+    if (fp) ntt_cols_unit_t<ArFp, A, B, FWD>(lds, out, tw, ArFp(pc), tile, pro);
+    else ntt_cols_small_t<ArInt, A, B, FWD, kMixTile, kMixE>(lds, pro, out, tw, ArInt(pc), tile);
 }
 
 template <int A, int B, bool FWD>
@@ -683,7 +717,8 @@ __device__ __forceinline__ void ntt_rows_load(typename Ar::V (&regs)[kElems], in
 
 template <typename Ar, int A, int B, bool FWD, typename Epi>
 __device__ __forceinline__ void ntt_rows_compute(uint64_t *lds, const TwPair *__restrict__ tw_all, const Ar &ar,
-                                                 int tile, const Epi &epi, typename Ar::V (&regs)[kElems]) {
+                                                 int tile, const Epi &epi, typename Ar::V (&regs)[kElems],
+                                                 typename Ar::Tw *twc) {
     constexpr int S = 1 << B;
     constexpr int U = kTile / S;
     constexpr int LDU = U + 1;
@@ -696,7 +731,7 @@ __device__ __forceinline__ void ntt_rows_compute(uint64_t *lds, const TwPair *__
     }
     __syncthreads();
     const int u = threadIdx.x % U, t = threadIdx.x / U;
-    ntt_rounds<Ar, B, FWD, false, A>(TileLds{lds, LDU, u}, t, (1u << A) + row0 + u, tw, ar);
+    ntt_rounds<Ar, B, FWD, false, A, kElems, tile_tw<Ar>()>(TileLds{lds, LDU, u}, t, (1u << A) + row0 + u, tw, ar, twc);
 #pragma unroll
     for (int r = 0; r < kTile / kThreads; ++r) {
         const int idx = threadIdx.x + r * kThreads;
@@ -714,8 +749,15 @@ template <typename Ar, int A, int B, bool FWD, typename Pro, typename Epi>
 __device__ __forceinline__ void ntt_rows_unit_t(uint64_t *lds, const Pro &pro, const TwPair *__restrict__ tw,
                                                 const Ar &ar, int tile, const Epi &epi) {
     typename Ar::V regs[kElems];
+    typename Ar::Tw twc[tile_tw<Ar>() == kTwCached ? tw_slots(B, kElems) : 1];
     ntt_rows_load<Ar, A, B>(regs, tile, pro, ar);
-    ntt_rows_compute<Ar, A, B, FWD>(lds, tw, ar, tile, epi, regs);
+    if constexpr (tile_tw<Ar>() == kTwCached) {
+        constexpr int U = kTile >> B;
+        ntt_rounds<Ar, B, FWD, false, A, kElems, kTwPrefetch>(TileLds{}, threadIdx.x / U,
+                                                              (1u << A) + tile * U + threadIdx.x % U, twiddles<Ar>(tw),
+                                                              ar, twc);
+    }
+    ntt_rows_compute<Ar, A, B, FWD>(lds, tw, ar, tile, epi, regs, twc);
 }
 
 template <int A, int B, bool FWD, typename Pro, typename Epi>
@@ -723,6 +765,15 @@ __device__ __forceinline__ void ntt_rows_unit_pe(uint64_t *lds, const Pro &pro, 
                                                  const PrimeConst &pc, bool fp, int tile, const Epi &epi) {
     if (fp) ntt_rows_unit_t<ArFp, A, B, FWD>(lds, pro, tw, ArFp(pc), tile, epi);
     else ntt_rows_unit_t<ArInt, A, B, FWD>(lds, pro, tw, ArInt(pc), tile, epi);
+}
+
+// As ntt_cols_mixed; tw_rows: the row-pass layout (narrow primes), tw: the natural one.
+template <int A, int B, bool FWD, typename Pro, typename Epi>
+__device__ __forceinline__ void ntt_rows_mixed(uint64_t *lds, const Pro &pro, const TwPair *__restrict__ tw_rows,
+                                               const TwPair *__restrict__ tw, const PrimeConst &pc, bool fp, int tile,
+                                               const Epi &epi) {
+    if (fp) ntt_rows_unit_t<ArFp, A, B, FWD>(lds, pro, tw_rows, ArFp(pc), tile, epi);
+    else ntt_rows_small_t<ArInt, A, B, FWD, kMixTile, kMixE>(lds, pro, tw, ArInt(pc), tile, epi);
 }
 
 // The last forward pass with an epilogue of its own, on what the column pass left.

@@ -54,6 +54,14 @@ struct NoFp {
     __host__ __device__ __forceinline__ static constexpr bool has(uint32_t) { return false; }
 };
 
+// The limbs of a launch with those of wide primes first: device entries limb |
+// prime << 16, n_wide of them wide.  ent null: the limbs in order, all of one
+// class (n_wide = 0 or their number).
+struct LimbOrder {
+    const uint32_t *ent = nullptr;
+    uint32_t n_wide = 0;
+};
+
 // Launch description of a batched (I)NTT over limbs laid out as
 // [n_polys][per_poly][N]; limb i of a polynomial uses prime pmap[i] (or prime_base + i).
 struct NttBatch {
@@ -65,6 +73,7 @@ struct NttBatch {
     uint32_t n_polys;
     uint32_t prime_base;
     const uint32_t *pmap;      // device array [per_poly] or nullptr
+    LimbOrder order;           // the same limbs in launch order (ent null: made from prime_base)
 };
 
 // Offsets (uint64 entries) of the BEHZ tables of a BFV context (L Q-primes,
@@ -127,6 +136,13 @@ struct rf_ctx {
     uint64_t *d_moddown_t = nullptr;       // ModDown constants keeping the message mod t (BGV)
     uint64_t *d_rescale = nullptr;         // rescale constants
     uint32_t *d_pmaps = nullptr;           // ModUp extension prime maps for every level
+    uint32_t *d_order = nullptr;           // rf::LimbOrder entries of the windows below
+    struct OrderRef {
+        uint32_t off = 0, n_wide = 0;
+    };
+    std::vector<OrderRef> q_order, ext_order;  // index nl: q_0..q_{nl-1}; the ModUp extension
+    OrderRef p_order, all_order, qb_order;     // the special primes; Q u P; q u B_sk (BFV)
+    rf::LimbOrder order(const OrderRef &r) const { return rf::LimbOrder{d_order + r.off, r.n_wide}; }
     // BFV: auxiliary base B and m_sk follow the special primes in `primes`
     uint32_t nb = 0;
     uint64_t *d_behz = nullptr;            // BEHZ tables (rf::BehzLayout)
