@@ -9,7 +9,7 @@ from concurrent.futures import ThreadPoolExecutor
 PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "librnsfhe.so")
-SOURCES = ["ntt.hip", "batch.hip", "context.hip", "single.hip", "keyswitch.hip", "capi.hip", "profile.hip", "noalloc.hip",
+SOURCES = ["ntt.hip", "batch.hip", "context.hip", "single.hip", "convert.hip", "keyswitch.hip", "capi.hip", "profile.hip", "noalloc.hip",
            "client.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 

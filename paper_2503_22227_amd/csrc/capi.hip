@@ -64,7 +64,8 @@ struct DeviceGuard {
 };
 
 NttBatch batch(const uint64_t *in, uint64_t *out, uint64_t in_stride, uint64_t out_stride, uint32_t per_poly,
-               uint32_t n_polys, uint32_t prime_base, const uint32_t *pmap, const LimbOrder &order = LimbOrder()) {
+               uint32_t n_polys, uint32_t prime_base, const uint32_t *pmap, const LimbOrder &order = LimbOrder(),
+               bool blocked = false) {
     NttBatch b;
     b.in = in;
     b.out = out;
@@ -75,6 +76,7 @@ NttBatch batch(const uint64_t *in, uint64_t *out, uint64_t in_stride, uint64_t o
     b.prime_base = prime_base;
     b.pmap = pmap;
     b.order = order;
+    b.blocked = blocked;
     return b;
 }
 
@@ -105,18 +107,25 @@ int keyswitch_core(const rf_ctx *c, const uint64_t *d, const uint64_t *evk, uint
     // launch_intt_first does the same for the fused callers).
     const rf_tuning &tn = level_tuning(c, nl);
     if (!fused && !d_coeff_in &&
-        (rc = launch_ntt(c, batch(d, d_coeff, 0, 0, nl, 1, 0, nullptr, c->order(c->q_order[nl])), false, s, pc_modup(c, nl), &tn)))
+        (rc = launch_ntt(c, batch(d, d_coeff, 0, 0, nl, 1, 0, nullptr, c->order(c->q_order[nl]), true), false, s,
+                         pc_modup(c, nl), &tn)))
         return rc;
-    if ((rc = launch_modup_bconv(c, d_coeff_in ? d_coeff_in : d_coeff, ext, nl, s, !d_coeff_in, tn.modup_chunk))) return rc;
-    if ((rc = launch_ntt(c, batch(ext, ext, 0, 0, lv.ext_limbs, 1, 0, c->d_pmaps + lv.pmap_off,
-                               c->order(c->ext_order[nl])), true, s, nullptr, &tn)))
-        return rc;
+    const uint64_t *x = d_coeff_in ? d_coeff_in : d_coeff;
+    const bool blocked = !d_coeff_in;  // the layout of the coefficients, the conversion's and its NTT's
+    const NttBatch eb = batch(ext, ext, 0, 0, lv.ext_limbs, 1, 0, c->d_pmaps + lv.pmap_off, c->order(c->ext_order[nl]), blocked);
+    if (modup_fused(c, !d_coeff_in)) {
+        if ((rc = launch_modup_cols(c, x, ext, nl, blocked, s))) return rc;
+        if ((rc = launch_ntt_fwd_rows(c, eb, s, &tn))) return rc;
+    } else {
+        if ((rc = launch_modup_bconv(c, x, ext, nl, s, !d_coeff_in, tn.modup_chunk))) return rc;
+        if ((rc = launch_ntt(c, eb, true, s, nullptr, &tn))) return rc;
+    }
     // ModDown: the inner product applies P^-1 and the addends to its Q-limbs; the
     // INTT of the P-limbs folds in the conversion's input factor; the conversion
     // runs in the first pass of the NTT and the tail in its last pass
     const uint64_t ip_stride = (uint64_t)(nl + c->K) * N;
     const NttBatch pl = batch(ip + (size_t)nl * N, ip + (size_t)nl * N, ip_stride, ip_stride, c->K, 2, c->L, nullptr,
-                              c->order(c->p_order));
+                              c->order(c->p_order), true);
     if ((rc = launch_inner_product(c, d, ext, evk, ip, nl, s, &f))) return rc;
     if ((rc = launch_ntt(c, pl, false, s, c->d_pc_md, &tn))) return rc;
     return launch_ntt_fwd_moddown(c, conv, ip, out, nl, s, &tn);
@@ -328,7 +337,7 @@ static int divide_last(const rf_ctx *c, const uint64_t *in, uint64_t *out, uint3
         rc = launch_divide_single(c, in, to, nl, keep_t, s);
     } else {
         const rf_tuning &tn = level_tuning(c, nl);
-        if ((rc = launch_ntt(c, batch(in + (size_t)(nl - 1) * N, last, in_stride, N, 1, 2, nl - 1, nullptr), false, s,
+        if ((rc = launch_ntt(c, batch(in + (size_t)(nl - 1) * N, last, in_stride, N, 1, 2, nl - 1, nullptr, LimbOrder(), true), false, s,
                              nullptr, &tn)))
             return rc;
         // the lift runs in the first pass of the NTT and the tail in its last pass

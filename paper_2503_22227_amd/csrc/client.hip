@@ -53,6 +53,7 @@ __global__ __launch_bounds__(kCl) void lift_kernel(const int64_t *__restrict__ x
 // As launches of their own the lift, the product and the copy of a moved another
 // 76 MB: 24 limbs at N = 2^16 took 55 us and the copy, now 40 us (HIP events).
 struct EncryptPro {
+    static constexpr bool kBlocked = false;
     const int64_t *m, *e;
     const PrimeConst *pc;
     bool err_t;  // BGV: err = t
@@ -73,7 +74,7 @@ struct EncryptPro {
 };
 
 struct EncryptEpi {
-    static constexpr bool kPrefetch = false;
+    static constexpr bool kPrefetch = false, kBlocked = false;
     const uint64_t *a, *s;
     uint64_t *c0, *c1;
     uint64_t mu1, mu0, q;
@@ -91,6 +92,7 @@ struct EncryptEpi {
 
 // Decryption (CKKS, BGV): c0 + c1 s as the prologue of the first pass of its INTT.
 struct DecryptPro {
+    static constexpr bool kBlocked = false;
     const uint64_t *c0, *c1, *s;
     uint64_t mu1, mu0, q;
     __device__ __forceinline__ uint64_t operator()(size_t n) const {

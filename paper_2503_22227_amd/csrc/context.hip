@@ -126,6 +126,11 @@ static void free_tables(rf_ctx *c) {
     (void)hipFree(c->d_rescale);
     (void)hipFree(c->d_pmaps);
     (void)hipFree(c->d_order);
+    (void)hipFree(c->d_units);
+    (void)hipFree(c->d_conv_mu);
+    (void)hipFree(c->d_conv_md);
+    (void)hipFree(c->d_conv_mu_off);
+    (void)hipFree(c->d_conv_md_off);
     (void)hipFree(c->d_behz);
     (void)hipFree(c->d_pmap_qb);
     (void)hipFree(c->d_client);
@@ -552,6 +557,84 @@ extern "C" int rf_ctx_create(const rf_params *p, int device, rf_ctx **out) {
     c->all_order = order_of(c->L + c->K, [](uint32_t i) { return i; });
     c->qb_order = order_of((uint32_t)pmqb.size(), [&](uint32_t i) { return pmqb[i]; });
 
+    // fused conversions: units per level, and the narrow targets' constants
+    std::vector<ConvUnit> units;
+    c->modup_units.resize(c->L + 1);
+    c->moddown_units.resize(c->L + 1);
+    // units of n targets (limb i of prime prime(i)) of one class
+    auto units_of = [&](uint32_t digit, uint32_t size, bool narrow, uint32_t n, auto prime) {
+        ConvUnit u{digit, size, 0, narrow ? 0u : 1u, {}};
+        for (uint32_t i = 0; i < n; ++i) {
+            if (c->fp_mask.has(prime(i)) != narrow) continue;
+            for (uint32_t k = u.count; k < 4; ++k) u.e[k] = i | prime(i) << 16;
+            if (++u.count == (narrow ? 4u : 1u)) {
+                units.push_back(u);
+                u.count = 0;
+            }
+        }
+        if (u.count) units.push_back(u);
+    };
+    for (uint32_t nl = 1; nl <= c->L; ++nl) {
+        const ModupLevel &lv = c->modup_levels[nl];
+        c->modup_units[nl].off = (uint32_t)units.size();
+        for (int narrow = 0; narrow < 2; ++narrow) {
+            uint32_t at = lv.pmap_off;
+            for (uint32_t j = 0; j < lv.dnum; ++j) {
+                const uint32_t sz = std::min(A, nl - j * A), n = nl - sz + c->K;
+                units_of(j, sz, narrow != 0, n, [&](uint32_t i) { return pm[at + i]; });
+                at += n;
+            }
+        }
+        c->modup_units[nl].n = (uint32_t)units.size() - c->modup_units[nl].off;
+        c->moddown_units[nl].off = (uint32_t)units.size();
+        for (int narrow = 0; narrow < 2; ++narrow)
+            units_of(0, c->K, narrow != 0, nl, [](uint32_t i) { return i; });
+        c->moddown_units[nl].n = (uint32_t)units.size() - c->moddown_units[nl].off;
+    }
+    // One target's constants c_k mod q, k < n: the bytes of [2^(8d) c_k]_q taken in
+    // (-q/2, q/2], d < 8, as six signed digits to base 256, and what the sources'
+    // bytes less 128 leave out, sum_k sum_{d<7} 2^(8d+7) c_k, in the same range.
+    auto conv_frag = [](const uint64_t *ck, uint32_t n, uint32_t kp, uint64_t q, int8_t *frag, double *off) {
+        uint64_t miss = 0;
+        for (uint32_t k = 0; k < n; ++k) {
+            uint64_t v = ck[k];
+            for (uint32_t d = 0; d < 8; ++d) {
+                if (d < 7) miss = (miss + mulmod_h(128 % q, v, q)) % q;
+                int64_t x = v > q / 2 ? (int64_t)v - (int64_t)q : (int64_t)v;
+                for (uint32_t e = 0; e < 6; ++e) {
+                    const int64_t digit = ((x + 128) & 255) - 128;
+                    frag[((size_t)e * kp + k) * 8 + d] = (int8_t)digit;
+                    x = (x - digit) / 256;
+                }
+                v = mulmod_h(v, 256 % q, q);
+            }
+        }
+        *off = miss > q / 2 ? -(double)(q - miss) : (double)miss;
+    };
+    std::vector<int8_t> conv_mu, conv_md;
+    std::vector<double> conv_mu_off, conv_md_off;
+    if (c->fp_mask.any()) {
+        const uint32_t kpu = conv_kp(A), kpd = conv_kp(c->K);
+        const size_t blocks = (size_t)c->dnum * A;
+        conv_mu.assign(blocks * NQP * conv_bytes(kpu), 0);
+        conv_mu_off.assign(blocks * NQP, 0.0);
+        for (uint32_t j = 0; j < c->dnum; ++j)
+            for (uint32_t sz = 1; sz <= A && j * A + sz <= c->L; ++sz)
+                for (uint32_t g = 0; g < NQP; ++g) {
+                    if (!c->fp_mask.has(g)) continue;
+                    const size_t at = ((size_t)j * A + sz - 1) * NQP + g;
+                    conv_frag(mu.data() + modup_block(c, j, sz) + 2 * A + (size_t)g * A, sz, kpu, c->primes[g],
+                              conv_mu.data() + at * conv_bytes(kpu), &conv_mu_off[at]);
+                }
+        const std::vector<uint64_t> &m = c->scheme == RF_BGV ? mdt : md;
+        conv_md.assign(c->L * conv_bytes(kpd), 0);
+        conv_md_off.assign(c->L, 0.0);
+        for (uint32_t i = 0; i < c->L; ++i)
+            if (c->fp_mask.has(i))
+                conv_frag(m.data() + moddown_cross_off(c) + (size_t)i * c->K, c->K, kpd, c->primes[i],
+                          conv_md.data() + i * conv_bytes(kpd), &conv_md_off[i]);
+    }
+
     // Client-side tables.  [P]_{p_g} for the P [i in D_j] s' term of key
     // generation (0 on the special primes); floor(Q_L / t) mod p_g for BFV
     // encryption, = -[Q_L]_t t^-1 mod q_g since q_g divides Q_L.
@@ -626,7 +709,11 @@ extern "C" int rf_ctx_create(const rf_params *p, int device, rf_ctx **out) {
         (!twrf.empty() && ((rc = upload(&c->d_tw_fwd_rows, twrf)) || (rc = upload(&c->d_tw_inv_rows, twri)))) || (rc = upload(&c->d_tw_fwd, twf)) || (rc = upload(&c->d_tw_inv, twi)) ||
         (rc = upload(&c->d_modup, mu)) || (rc = upload(&c->d_moddown, md)) ||
         (!mdt.empty() && (rc = upload(&c->d_moddown_t, mdt))) || (rc = upload(&c->d_rescale, rs)) ||
-        (rc = upload(&c->d_pmaps, pm)) || (rc = upload(&c->d_order, ord))) {
+        (rc = upload(&c->d_pmaps, pm)) || (rc = upload(&c->d_order, ord)) ||
+        (rc = upload(&c->d_units, units)) ||
+        (!conv_mu.empty() && ((rc = upload(&c->d_conv_mu, conv_mu)) || (rc = upload(&c->d_conv_md, conv_md)) ||
+                              (rc = upload(&c->d_conv_mu_off, conv_mu_off)) ||
+                              (rc = upload(&c->d_conv_md_off, conv_md_off))))) {
         free_tables(c);
         delete c;
         return rc;

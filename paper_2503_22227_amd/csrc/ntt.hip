@@ -30,22 +30,6 @@ __device__ __forceinline__ LimbView limb_view(const NttBatch &b, int log_n, uint
     return v;
 }
 
-// A pass of a launch with few limbs (ntt_cols_small / ntt_rows_small): one
-// workgroup per TILE residues of a limb, E residues per thread.
-// Tile of a small column pass.  Its U = TILE / 2^A columns are narrower than
-// a 128-byte line (G = 16 / U tiles share each line of a row), and workgroups
-// are dealt to the 8 XCDs in turn, each with its own L2: dispatch order
-// w = blockIdx.x is mapped so that the G tiles of one line group go to the
-// same XCD one after another (w, w + 8, ...), and the line is read from HBM
-// once instead of G times.  Identity when the grid is not a multiple of 8 G.
-template <int TILE, int A>
-__device__ __forceinline__ int xcd_grouped_tile(int w, int tiles) {
-    constexpr int U = TILE >> A, G = U >= 16 ? 1 : 16 / U;
-    if (G == 1 || tiles % (8 * G) != 0) return w;
-    const int x = w & 7, r = w >> 3;
-    return ((r / G) * 8 + x) * G + r % G;
-}
-
 // The limbs of a launch on tiles by class (ntt_cols_mixed): the wide ones first,
 // since their workgroups take longest, N / 1024 workgroups each, then the narrow
 // ones, N / 4096 each; polynomials interleaved.
@@ -94,19 +78,19 @@ static dim3 mix_grid(const rf_ctx *c, uint32_t n_wide, uint32_t limbs, uint32_t 
     return dim3(np * (n_wide * (c->n / kMixTile) + (limbs - n_wide) * (c->n / kTile)));
 }
 
-template <int A, int B, bool FWD, typename Fp>
+template <int A, int B, bool FWD, bool BLK, typename Fp>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ntt_waves(A)))) void ntt_cols_kernel(
     NttBatch b, Fp, MixGrid m, const TwPair *__restrict__ tw_all, const PrimeConst *__restrict__ pcs) {
     __shared__ uint64_t lds[(1 << A) * (kTile / (1 << A) + 1)];
     constexpr int LOGN = A + B;
     const MixUnit u = mix_unit<A, B, true, Fp>(m);
     const PrimeConst pc = pcs[u.g];
-    ntt_cols_mixed<A, B, FWD>(lds, b.out + (size_t)u.poly * b.out_poly_stride + ((size_t)u.li << LOGN),
+    ntt_cols_mixed<A, B, FWD, BLK>(lds, b.out + (size_t)u.poly * b.out_poly_stride + ((size_t)u.li << LOGN),
                               tw_all + ((size_t)u.g << LOGN), pc, u.fp, u.tile,
                               PlainPro<FWD>{b.in + (size_t)u.poly * b.in_poly_stride + ((size_t)u.li << LOGN)});
 }
 
-template <int A, int B, bool FWD, typename Fp>
+template <int A, int B, bool FWD, bool BLK, typename Fp>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ntt_waves(B)))) void ntt_rows_kernel(
     NttBatch b, Fp, MixGrid m, const TwPair *__restrict__ tw_rows, const TwPair *__restrict__ tw_all,
     const PrimeConst *__restrict__ pcs) {
@@ -115,33 +99,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ntt_wa
     const MixUnit u = mix_unit<A, B, false, Fp>(m);
     const PrimeConst pc = pcs[u.g];
     const size_t tl = (size_t)u.g << LOGN;
-    ntt_rows_mixed<A, B, FWD>(lds, PlainPro<!FWD>{b.in + (size_t)u.poly * b.in_poly_stride + ((size_t)u.li << LOGN)},
+    ntt_rows_mixed<A, B, FWD>(lds, RowLoad<FWD, BLK>{b.in + (size_t)u.poly * b.in_poly_stride + ((size_t)u.li << LOGN)},
                               tw_rows + tl, tw_all + tl, pc, u.fp, u.tile,
-                              RowStore<FWD>{b.out + (size_t)u.poly * b.out_poly_stride + ((size_t)u.li << LOGN)});
-}
-
-// Prologue of the first pass of NTT(conv): the ModDown conversion of target i
-// of polynomial c from the K P-limbs of ip[c] ([2][nl + K][N]).
-template <int KP, int LOGN>
-__device__ __forceinline__ ModdownPro<KP> moddown_pro(const uint64_t *ip, const PrimeConst *__restrict__ pcs,
-                                                      const PrimeConst &pc, const uint64_t *__restrict__ cross,
-                                                      const uint64_t *__restrict__ negp, uint32_t c, uint32_t i,
-                                                      uint32_t nl, uint32_t L, uint32_t K) {
-    ModdownPro<KP> pro;
-    pro.src = ip + (((size_t)c * (nl + K) + nl) << LOGN);
-    pro.stride = (size_t)1 << LOGN;
-    pro.K = K;
-#pragma unroll
-    for (int a = 0; a < KP; ++a) {
-        pro.half[a] = a < (int)K ? pcs[L + a].q >> 1 : 0;
-        pro.cross[a] = a < (int)K ? cross[(size_t)i * K + a] : 0;
-    }
-    pro.negp = negp[i];
-    pro.q = pc.q;
-    pro.r64 = pc.r64;
-    pro.r64_p = pc.r64_p;
-    pro.one_p = pc.one_p;
-    return pro;
+                              RowStore<FWD, BLK>{b.out + (size_t)u.poly * b.out_poly_stride + ((size_t)u.li << LOGN)});
 }
 
 // Prologue of the first pass of NTT(lift): the lift of polynomial c's last
@@ -179,7 +139,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(KP == 
     const uint32_t c = u.poly, i = u.li;
     const PrimeConst pc = pcs[i];
     const ModdownPro<KP> pro = moddown_pro<KP, LOGN>(ip, pcs, pc, cross, negp, c, i, nl, L, K);
-    ntt_cols_mixed<A, B, true>(lds, conv + (((size_t)c * nl + i) << LOGN), tw_all + ((size_t)i << LOGN), pc, u.fp,
+    ntt_cols_mixed<A, B, true, true>(lds, conv + (((size_t)c * nl + i) << LOGN), tw_all + ((size_t)i << LOGN), pc, u.fp,
                                u.tile, pro);
 }
 
@@ -196,7 +156,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kNttWa
     const uint32_t c = u.poly, i = u.li;
     const PrimeConst pc = pcs[i];
     const LiftPro<KEEP_T> pro = lift_pro<KEEP_T, LOGN>(last, pcs, pc, tab, c, i, nl, L);
-    ntt_cols_mixed<A, B, true>(lds, lift + (((size_t)c * l + i) << LOGN), tw_all + ((size_t)i << LOGN), pc, u.fp,
+    ntt_cols_mixed<A, B, true, true>(lds, lift + (((size_t)c * l + i) << LOGN), tw_all + ((size_t)i << LOGN), pc, u.fp,
                                u.tile, pro);
 }
 
@@ -213,7 +173,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ntt_wa
     const PrimeConst pc = pcs[i];
     const ModdownFoldEpi epi{ip + (((size_t)c * (nl + K) + i) << LOGN), out + (((size_t)c * nl + i) << LOGN),
                              pinv[2 * i], pinv[2 * i + 1], pc.q};
-    ntt_rows_mixed<A, B, true>(lds, RawPro{conv + (((size_t)c * nl + i) << LOGN)}, tw_rows + ((size_t)i << LOGN),
+    ntt_rows_mixed<A, B, true>(lds, BlkRawPro{conv + (((size_t)c * nl + i) << LOGN)}, tw_rows + ((size_t)i << LOGN),
                                tw_all + ((size_t)i << LOGN), pc, u.fp, u.tile, epi);
 }
 
@@ -230,7 +190,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ntt_wa
     const PrimeConst pc = pcs[i];
     const size_t li = (size_t)i << LOGN, poly = (size_t)nl << LOGN;
     const TensorPro pro{a + poly + li, b + poly + li, pc.q, pc.r64, pc.r64_p, pc.one_p};
-    ntt_rows_mixed<A, B, false>(lds, pro, tw_rows + li, tw_all + li, pc, u.fp, u.tile, RawEpi{dc + li});
+    ntt_rows_mixed<A, B, false>(lds, pro, tw_rows + li, tw_all + li, pc, u.fp, u.tile, BlkRawEpi{dc + li});
 }
 
 // First inverse pass of INTT(sigma_g(a1)) with the automorphism as its
@@ -246,7 +206,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ntt_wa
     const PrimeConst pc = pcs[i];
     const size_t li = (size_t)i << LOGN;
     const GatherPro pro{a1 + li, galois, (uint32_t)LOGN};
-    ntt_rows_mixed<A, B, false>(lds, pro, tw_rows + li, tw_all + li, pc, u.fp, u.tile, RawEpi{dc + li});
+    ntt_rows_mixed<A, B, false>(lds, pro, tw_rows + li, tw_all + li, pc, u.fp, u.tile, BlkRawEpi{dc + li});
 }
 
 // Last forward pass of NTT(lift) with the rescale tail: limb (c, i) of lift
@@ -263,11 +223,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ntt_wa
     const PrimeConst pc = pcs[i];
     const uint64_t *t = tab + ((size_t)l * L + i) * 3;
     RescaleTailEpi epi{in + (((size_t)c * nl + i) << LOGN), out + (((size_t)c * l + i) << LOGN), t[0], t[1], pc.q};
-    ntt_rows_mixed<A, B, true>(lds, RawPro{lift + (((size_t)c * l + i) << LOGN)}, tw_rows + ((size_t)i << LOGN),
+    ntt_rows_mixed<A, B, true>(lds, BlkRawPro{lift + (((size_t)c * l + i) << LOGN)}, tw_rows + ((size_t)i << LOGN),
                                tw_all + ((size_t)i << LOGN), pc, u.fp, u.tile, epi);
 }
 
-template <int A, int B, bool FWD, bool COLS, int TILE, int E, typename Fp>
+template <int A, int B, bool FWD, bool COLS, int TILE, int E, bool BLK, typename Fp>
 __global__ __launch_bounds__(TILE / E) void ntt_small_kernel(NttBatch b, Fp fpm, const TwPair *__restrict__ tw_all,
                                                              const PrimeConst *__restrict__ pcs) {
     constexpr int S = COLS ? (1 << A) : (1 << B);
@@ -275,8 +235,8 @@ __global__ __launch_bounds__(TILE / E) void ntt_small_kernel(NttBatch b, Fp fpm,
     const LimbView v = limb_view(b, A + B, blockIdx.y);
     const PrimeConst pc = pcs[v.g];
     const TwPair *tw = tw_all + ((size_t)v.g << (A + B));
-    if constexpr (COLS) ntt_cols_small<A, B, FWD, TILE, E>(lds, v.in, v.out, tw, pc, fpm.has(v.g), xcd_grouped_tile<TILE, A>(blockIdx.x, gridDim.x));
-    else ntt_rows_small<A, B, FWD, TILE, E>(lds, v.in, v.out, tw, pc, fpm.has(v.g), blockIdx.x);
+    if constexpr (COLS) ntt_cols_small<A, B, FWD, TILE, E, BLK>(lds, v.in, v.out, tw, pc, fpm.has(v.g), xcd_grouped_tile<TILE, A>(blockIdx.x, gridDim.x));
+    else ntt_rows_small<A, B, FWD, TILE, E, BLK>(lds, v.in, v.out, tw, pc, fpm.has(v.g), blockIdx.x);
 }
 
 // Default residues per thread of the few-limb passes (4 measured faster than 8:
@@ -296,7 +256,7 @@ __global__ __launch_bounds__(TILE / kSmallE) void ntt_small_cols_moddown_kernel(
     const uint32_t c = blockIdx.y & 1, i = blockIdx.y >> 1;
     const PrimeConst pc = pcs[i];
     const ModdownPro<KP> pro = moddown_pro<KP, LOGN>(ip, pcs, pc, cross, negp, c, i, nl, L, K);
-    ntt_cols_small_pro<A, B, true, TILE, kSmallE>(lds, pro, conv + (((size_t)c * nl + i) << LOGN),
+    ntt_cols_small_pro<A, B, true, TILE, kSmallE, true>(lds, pro, conv + (((size_t)c * nl + i) << LOGN),
                                                   tw_all + ((size_t)i << LOGN), pc, fpm.has(i), xcd_grouped_tile<TILE, A>(blockIdx.x, gridDim.x));
 }
 
@@ -310,7 +270,7 @@ __global__ __launch_bounds__(TILE / kSmallE) void ntt_small_rows_moddown_kernel(
     const PrimeConst pc = pcs[i];
     const ModdownFoldEpi epi{ip + (((size_t)c * (nl + K) + i) << LOGN), out + (((size_t)c * nl + i) << LOGN),
                              pinv[2 * i], pinv[2 * i + 1], pc.q};
-    ntt_rows_small_pe<A, B, true, TILE, kSmallE>(lds, RawPro{conv + (((size_t)c * nl + i) << LOGN)},
+    ntt_rows_small_pe<A, B, true, TILE, kSmallE>(lds, BlkRawPro{conv + (((size_t)c * nl + i) << LOGN)},
                                                  tw_all + ((size_t)i << LOGN), pc, fpm.has(i), blockIdx.x, epi);
 }
 
@@ -324,7 +284,7 @@ __global__ __launch_bounds__(TILE / kSmallE) void ntt_small_cols_lift_kernel(
     const uint32_t c = blockIdx.y & 1, i = blockIdx.y >> 1;
     const PrimeConst pc = pcs[i];
     const LiftPro<KEEP_T> pro = lift_pro<KEEP_T, LOGN>(last, pcs, pc, tab, c, i, nl, L);
-    ntt_cols_small_pro<A, B, true, TILE, kSmallE>(lds, pro, lift + (((size_t)c * l + i) << LOGN),
+    ntt_cols_small_pro<A, B, true, TILE, kSmallE, true>(lds, pro, lift + (((size_t)c * l + i) << LOGN),
                                                   tw_all + ((size_t)i << LOGN), pc, fpm.has(i), xcd_grouped_tile<TILE, A>(blockIdx.x, gridDim.x));
 }
 
@@ -340,7 +300,7 @@ __global__ __launch_bounds__(TILE / kSmallE) void ntt_small_rows_rescale_kernel(
     const uint64_t *t = tab + ((size_t)l * L + i) * 3;
     const RescaleTailEpi epi{in + (((size_t)c * nl + i) << LOGN), out + (((size_t)c * l + i) << LOGN), t[0], t[1],
                              pc.q};
-    ntt_rows_small_pe<A, B, true, TILE, kSmallE>(lds, RawPro{lift + (((size_t)c * l + i) << LOGN)},
+    ntt_rows_small_pe<A, B, true, TILE, kSmallE>(lds, BlkRawPro{lift + (((size_t)c * l + i) << LOGN)},
                                                  tw_all + ((size_t)i << LOGN), pc, fpm.has(i), blockIdx.x, epi);
 }
 
@@ -357,16 +317,16 @@ __global__ __launch_bounds__(TILE / kSmallE) void ntt_small_inv_rows_first_kerne
     const size_t li = (size_t)i << LOGN, poly = (size_t)nl << LOGN;
     if (galois) {
         const GatherPro pro{a + poly + li, galois, (uint32_t)LOGN};
-        ntt_rows_small_pe<A, B, false, TILE, kSmallE>(lds, pro, tw_all + li, pc, fpm.has(i), blockIdx.x, RawEpi{dc + li});
+        ntt_rows_small_pe<A, B, false, TILE, kSmallE>(lds, pro, tw_all + li, pc, fpm.has(i), blockIdx.x, BlkRawEpi{dc + li});
     } else {
         const TensorPro pro{a + poly + li, b + poly + li, pc.q, pc.r64, pc.r64_p, pc.one_p};
-        ntt_rows_small_pe<A, B, false, TILE, kSmallE>(lds, pro, tw_all + li, pc, fpm.has(i), blockIdx.x, RawEpi{dc + li});
+        ntt_rows_small_pe<A, B, false, TILE, kSmallE>(lds, pro, tw_all + li, pc, fpm.has(i), blockIdx.x, BlkRawEpi{dc + li});
     }
 }
 
 
 // Launchers: fpm is the context's FpMask, or NoFp.
-template <int A, int B, int TILE, int E, typename Fp>
+template <int A, int B, int TILE, int E, bool BLK, typename Fp>
 static void launch_two_pass_small(const rf_ctx *c, Fp fpm, const NttBatch &b, bool forward, hipStream_t s,
                                   const PrimeConst *pcs) {
     const uint32_t limbs = b.per_poly * b.n_polys;
@@ -377,22 +337,22 @@ static void launch_two_pass_small(const rf_ctx *c, Fp fpm, const NttBatch &b, bo
     if (forward) {
         {
             ProfScope p("ntt_fwd_cols_small", s);
-            hipLaunchKernelGGL((ntt_small_kernel<A, B, true, true, TILE, E>), grid, block, 0, s, b, fpm, c->d_tw_fwd, pcs);
+            hipLaunchKernelGGL((ntt_small_kernel<A, B, true, true, TILE, E, BLK>), grid, block, 0, s, b, fpm, c->d_tw_fwd, pcs);
         }
         ProfScope p("ntt_fwd_rows_small", s);
-        hipLaunchKernelGGL((ntt_small_kernel<A, B, true, false, TILE, E>), grid, block, 0, s, b2, fpm, c->d_tw_fwd, pcs);
+        hipLaunchKernelGGL((ntt_small_kernel<A, B, true, false, TILE, E, BLK>), grid, block, 0, s, b2, fpm, c->d_tw_fwd, pcs);
     } else {
         {
             ProfScope p("ntt_inv_rows_small", s);
-            hipLaunchKernelGGL((ntt_small_kernel<A, B, false, false, TILE, E>), grid, block, 0, s, b, fpm, c->d_tw_inv,
+            hipLaunchKernelGGL((ntt_small_kernel<A, B, false, false, TILE, E, BLK>), grid, block, 0, s, b, fpm, c->d_tw_inv,
                                pcs);
         }
         ProfScope p("ntt_inv_cols_small", s);
-        hipLaunchKernelGGL((ntt_small_kernel<A, B, false, true, TILE, E>), grid, block, 0, s, b2, fpm, c->d_tw_inv, pcs);
+        hipLaunchKernelGGL((ntt_small_kernel<A, B, false, true, TILE, E, BLK>), grid, block, 0, s, b2, fpm, c->d_tw_inv, pcs);
     }
 }
 
-template <int A, int B, typename Fp>
+template <int A, int B, bool BLK, typename Fp>
 static void launch_mixed(const rf_ctx *c, Fp fpm, const NttBatch &b, const MixGrid &m, bool forward, hipStream_t s,
                          const PrimeConst *pcs) {
     const dim3 block(kThreads), grid = mix_grid(c, m.n_wide, b.per_poly, b.n_polys);
@@ -402,34 +362,34 @@ static void launch_mixed(const rf_ctx *c, Fp fpm, const NttBatch &b, const MixGr
     if (forward) {
         {
             ProfScope p("ntt_fwd_cols", s);
-            hipLaunchKernelGGL((ntt_cols_kernel<A, B, true>), grid, block, 0, s, b, fpm, m, c->d_tw_fwd, pcs);
+            hipLaunchKernelGGL((ntt_cols_kernel<A, B, true, BLK>), grid, block, 0, s, b, fpm, m, c->d_tw_fwd, pcs);
         }
         ProfScope p("ntt_fwd_rows", s);
-        hipLaunchKernelGGL((ntt_rows_kernel<A, B, true>), grid, block, 0, s, b2, fpm, m, c->d_tw_fwd_rows, c->d_tw_fwd, pcs);
+        hipLaunchKernelGGL((ntt_rows_kernel<A, B, true, BLK>), grid, block, 0, s, b2, fpm, m, c->d_tw_fwd_rows, c->d_tw_fwd, pcs);
     } else {
         {
             ProfScope p("ntt_inv_rows", s);
-            hipLaunchKernelGGL((ntt_rows_kernel<A, B, false>), grid, block, 0, s, b, fpm, m, c->d_tw_inv_rows, c->d_tw_inv,
+            hipLaunchKernelGGL((ntt_rows_kernel<A, B, false, BLK>), grid, block, 0, s, b, fpm, m, c->d_tw_inv_rows, c->d_tw_inv,
                                pcs);
         }
         ProfScope p("ntt_inv_cols", s);
-        hipLaunchKernelGGL((ntt_cols_kernel<A, B, false>), grid, block, 0, s, b2, fpm, m, c->d_tw_inv, pcs);
+        hipLaunchKernelGGL((ntt_cols_kernel<A, B, false, BLK>), grid, block, 0, s, b2, fpm, m, c->d_tw_inv, pcs);
     }
 }
 
-template <int A, int B, typename Fp>
-static void launch_two_pass(const rf_ctx *c, Fp fpm, const NttBatch &b, bool forward, hipStream_t s,
+template <int A, int B, bool BLK, typename Fp>
+static void launch_two_pass_blk(const rf_ctx *c, Fp fpm, const NttBatch &b, bool forward, hipStream_t s,
                             const PrimeConst *pcs, const rf_tuning &tn) {
     const uint32_t limbs = b.per_poly * b.n_polys;
     const uint32_t tiles = limbs << (A + B - 12);
     if (tiles < tn.ntt_small_below) {
         const bool big = tn.ntt_small_tile == 2048 || (tn.ntt_small_tile == 0 && tiles * 2 >= tn.ntt_small_below);
         if (tn.ntt_small_radix == 8) {
-            if (big) launch_two_pass_small<A, B, 2048, 8>(c, fpm, b, forward, s, pcs);
-            else launch_two_pass_small<A, B, 1024, 8>(c, fpm, b, forward, s, pcs);
+            if (big) launch_two_pass_small<A, B, 2048, 8, BLK>(c, fpm, b, forward, s, pcs);
+            else launch_two_pass_small<A, B, 1024, 8, BLK>(c, fpm, b, forward, s, pcs);
         } else {
-            if (big) launch_two_pass_small<A, B, 2048, kSmallE>(c, fpm, b, forward, s, pcs);
-            else launch_two_pass_small<A, B, 1024, kSmallE>(c, fpm, b, forward, s, pcs);
+            if (big) launch_two_pass_small<A, B, 2048, kSmallE, BLK>(c, fpm, b, forward, s, pcs);
+            else launch_two_pass_small<A, B, 1024, kSmallE, BLK>(c, fpm, b, forward, s, pcs);
         }
         return;
     }
@@ -442,11 +402,70 @@ static void launch_two_pass(const rf_ctx *c, Fp fpm, const NttBatch &b, bool for
             r.in += (size_t)i * c->n;
             r.out += (size_t)i * c->n;
             r.per_poly = j - i;
-            launch_mixed<A, B>(c, fpm, r, MixGrid{nullptr, wide ? j - i : 0, b.n_polys, b.prime_base + i}, forward, s, pcs);
+            launch_mixed<A, B, BLK>(c, fpm, r, MixGrid{nullptr, wide ? j - i : 0, b.n_polys, b.prime_base + i}, forward, s, pcs);
         }
         return;
     }
-    launch_mixed<A, B>(c, fpm, b, MixGrid{b.order.ent, b.order.n_wide, b.n_polys, 0}, forward, s, pcs);
+    launch_mixed<A, B, BLK>(c, fpm, b, MixGrid{b.order.ent, b.order.n_wide, b.n_polys, 0}, forward, s, pcs);
+}
+
+template <int A, int B, typename Fp>
+static void launch_two_pass(const rf_ctx *c, Fp fpm, const NttBatch &b, bool forward, hipStream_t s,
+                            const PrimeConst *pcs, const rf_tuning &tn) {
+    if (b.blocked) launch_two_pass_blk<A, B, true>(c, fpm, b, forward, s, pcs, tn);
+    else launch_two_pass_blk<A, B, false>(c, fpm, b, forward, s, pcs, tn);
+}
+
+template <int A, int B, bool BLK, typename Fp>
+static void launch_fwd_rows_blk(const rf_ctx *c, Fp fpm, const NttBatch &b, hipStream_t s, const rf_tuning &tn) {
+    const uint32_t limbs = b.per_poly * b.n_polys;
+    const uint32_t tiles = limbs << (A + B - 12);
+    if (tiles < tn.ntt_small_below) {
+        const bool big = tn.ntt_small_tile == 2048 || (tn.ntt_small_tile == 0 && tiles * 2 >= tn.ntt_small_below);
+        ProfScope p("ntt_fwd_rows_small", s);
+#define RF_FR(T, E)                                                                                              \
+    hipLaunchKernelGGL((ntt_small_kernel<A, B, true, false, T, E, BLK>), dim3((1u << (A + B)) / T, limbs), dim3(T / E), 0, \
+                       s, b, fpm, c->d_tw_fwd, c->d_pc)
+        if (tn.ntt_small_radix == 8) {
+            if (big) RF_FR(2048, 8);
+            else RF_FR(1024, 8);
+        } else {
+            if (big) RF_FR(2048, kSmallE);
+            else RF_FR(1024, kSmallE);
+        }
+#undef RF_FR
+        return;
+    }
+    const MixGrid m{b.order.ent, b.order.n_wide, b.n_polys, 0};
+    ProfScope p("ntt_fwd_rows", s);
+    hipLaunchKernelGGL((ntt_rows_kernel<A, B, true, BLK>), mix_grid(c, m.n_wide, b.per_poly, b.n_polys), dim3(kThreads), 0,
+                       s, b, fpm, m, c->d_tw_fwd_rows, c->d_tw_fwd, c->d_pc);
+}
+
+template <int A, int B, typename Fp>
+static void launch_fwd_rows(const rf_ctx *c, Fp fpm, const NttBatch &b, hipStream_t s, const rf_tuning &tn) {
+    if (b.blocked) launch_fwd_rows_blk<A, B, true>(c, fpm, b, s, tn);
+    else launch_fwd_rows_blk<A, B, false>(c, fpm, b, s, tn);
+}
+
+template <typename Fp>
+static int launch_ntt_fwd_rows_t(const rf_ctx *c, Fp fpm, const NttBatch &b, hipStream_t s, const rf_tuning &tn) {
+    if (b.per_poly * b.n_polys > 65535) return fail(RF_EUNSUPPORTED, "too many limbs in one NTT launch");
+    switch (c->log_n) {
+        case 13: launch_fwd_rows<7, 6>(c, fpm, b, s, tn); break;
+        case 14: launch_fwd_rows<7, 7>(c, fpm, b, s, tn); break;
+        case 15: launch_fwd_rows<8, 7>(c, fpm, b, s, tn); break;
+        case 16: launch_fwd_rows<8, 8>(c, fpm, b, s, tn); break;
+        default: return fail(RF_EUNSUPPORTED, "NTT row pass: ring degree");
+    }
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return fail(RF_EHIP, std::string("NTT launch: ") + hipGetErrorString(e));
+    return RF_OK;
+}
+
+int launch_ntt_fwd_rows(const rf_ctx *c, const NttBatch &b, hipStream_t s, const rf_tuning *tn) {
+    const rf_tuning &t = tn ? *tn : kDefaultTuning;
+    return c->fp_mask.any() ? launch_ntt_fwd_rows_t(c, c->fp_mask, b, s, t) : launch_ntt_fwd_rows_t(c, NoFp{}, b, s, t);
 }
 
 // Small-tile size of a fused launch of `limbs` limbs, or 0 for the 4096-residue
@@ -467,13 +486,16 @@ static int launch_ntt_fwd_moddown_t(const rf_ctx *c, Fp fpm, uint64_t *conv, con
     const MixGrid mg = q_mix(c, nl, 2);
     const dim3 g = mix_grid(c, mg.n_wide, nl, 2);
     const int st = small_tile_of(c, 2 * nl, tn);
+    // with narrow primes the conversion and the column pass are convert.hip's
+    if constexpr (!std::is_same_v<Fp, NoFp>)
+        if (const int rc = launch_moddown_cols(c, ip, conv, nl, s)) return rc;
     if (st) {
 #define RF_SMDK(A, B, T, KP)                                                                                     \
     hipLaunchKernelGGL((ntt_small_cols_moddown_kernel<A, B, T, KP>), dim3(c->n / T, 2 * nl), dim3(T / kSmallE), 0, s, \
                        fpm, ip, conv, c->d_tw_fwd, c->d_pc, cross, negp, nl, c->L, c->K)
 #define RF_SMD(A, B, T)                                                                                          \
     {                                                                                                            \
-        {                                                                                                        \
+        if constexpr (std::is_same_v<Fp, NoFp>) {                                                                \
             ProfScope p("ntt_fwd_cols_moddown_small", s);                                                        \
             switch (c->K) {                                                                                      \
                 case 1: RF_SMDK(A, B, T, 1); break;                                                              \
@@ -507,7 +529,7 @@ static int launch_ntt_fwd_moddown_t(const rf_ctx *c, Fp fpm, uint64_t *conv, con
                        0, s, fpm, mg, ip, conv, c->d_tw_fwd, c->d_pc, cross, negp, nl, c->L, c->K)
 #define RF_MD(A, B)                                                                                              \
     {                                                                                                            \
-        {                                                                                                        \
+        if constexpr (std::is_same_v<Fp, NoFp>) {                                                                \
             ProfScope p("ntt_fwd_cols_moddown", s);                                                              \
             switch (c->K) {                                                                                      \
                 case 1: RF_MDK(A, B, 1); break;                                                                  \
@@ -629,7 +651,7 @@ static int launch_intt_first_t(const rf_ctx *c, Fp fpm, const uint64_t *a, const
         }                                                                                                        \
         NttBatch bc{dc, dc, 0, 0, nl, 1, 0, nullptr, {}};                                                        \
         ProfScope p("ntt_inv_cols_small", s);                                                                    \
-        hipLaunchKernelGGL((ntt_small_kernel<A, B, false, true, T, kSmallE>), gs, bs, 0, s, bc, fpm, c->d_tw_inv, \
+        hipLaunchKernelGGL((ntt_small_kernel<A, B, false, true, T, kSmallE, true>), gs, bs, 0, s, bc, fpm, c->d_tw_inv, \
                            pc_modup(c, nl));                                                                     \
     }
 #define RF_SIFT(A, B)                                                                                            \
@@ -661,7 +683,7 @@ static int launch_intt_first_t(const rf_ctx *c, Fp fpm, const uint64_t *a, const
         }                                                                                                        \
         NttBatch bc{dc, dc, 0, 0, nl, 1, 0, nullptr, {}};                                                        \
         ProfScope p("ntt_inv_cols", s);                                                                          \
-        hipLaunchKernelGGL((ntt_cols_kernel<A, B, false>), gr, dim3(kThreads), 0, s, bc, fpm, mg, c->d_tw_inv, pc_modup(c, nl)); \
+        hipLaunchKernelGGL((ntt_cols_kernel<A, B, false, true>), gr, dim3(kThreads), 0, s, bc, fpm, mg, c->d_tw_inv, pc_modup(c, nl)); \
     }
     switch (c->log_n) {
         case 13: RF_IF(7, 6) break;
@@ -717,10 +739,10 @@ static int launch_intt_cols_t(const rf_ctx *c, Fp fpm, uint64_t *data, uint32_t 
     ProfScope p(small ? "ntt_inv_cols_small" : "ntt_inv_cols", s);
 #define RF_IC(A, B)                                                                                              \
     if (small)                                                                                                   \
-        hipLaunchKernelGGL((ntt_small_kernel<A, B, false, true, 1024, kSmallE, Fp>), dim3(c->n / 1024, nl),      \
+        hipLaunchKernelGGL((ntt_small_kernel<A, B, false, true, 1024, kSmallE, false, Fp>), dim3(c->n / 1024, nl),      \
                            dim3(1024 / kSmallE), 0, s, b, fpm, c->d_tw_inv, c->d_pc);                            \
     else                                                                                                         \
-        hipLaunchKernelGGL((ntt_cols_kernel<A, B, false, Fp>), mix_grid(c, mg.n_wide, nl, 1), dim3(kThreads),    \
+        hipLaunchKernelGGL((ntt_cols_kernel<A, B, false, false, Fp>), mix_grid(c, mg.n_wide, nl, 1), dim3(kThreads),    \
                            0, s, b, fpm, mg, c->d_tw_inv, c->d_pc)
     switch (c->log_n) {
         case 13: RF_IC(7, 6); break;

@@ -329,6 +329,45 @@ __device__ __forceinline__ const typename Ar::Tw *twiddles(const TwPair *__restr
     return reinterpret_cast<const typename Ar::Tw *>(tw);
 }
 
+// Blocked layout of a limb between the steps of a key switch or a rescale
+// (workspace only, never an operand): blocks of U_r rows x U_c columns, U_r =
+// 1024 / 2^B, U_c = 1024 / 2^A, a row of blocks after another.  A tile of 1024
+// residues of a row pass is contiguous, as in the natural order, and one of a
+// column pass is whole blocks, 128 bytes or more, where the natural order gives
+// it 32 bytes a row at N = 2^16: the ModUp column pass of 60 limbs there sends
+// the L2s 4.5 million requests against 1.1, at 128 a cycle 16 us of its 28.
+// A pass whose both sides are blocked works in place; natural to blocked does not.
+constexpr int kBlkLog = 10, kBlkTile = 1 << kBlkLog;
+
+template <int A, int B>
+__device__ __forceinline__ size_t blk_index(uint32_t p, uint32_t c) {
+    constexpr int LUR = kBlkLog - B, LUC = kBlkLog - A;
+    return ((size_t)(p >> LUR) << kBlkLog) + ((c >> LUC) << (LUR + LUC)) + ((p & ((1u << LUR) - 1)) << LUC) +
+           (c & ((1u << LUC) - 1));
+}
+
+// Memory index of a residue of a column pass.
+template <int A, int B, bool BLK>
+__device__ __forceinline__ size_t col_index(uint32_t row, uint32_t col) {
+    if constexpr (BLK) return blk_index<A, B>(row, col);
+    else return ((size_t)row << B) + col;
+}
+
+// Row (from the tile's first) and column of the k-th residue in memory of a tile
+// of whole rows (at least 1024 residues), BLK: in the blocked layout.
+template <int A, int B, bool BLK>
+__device__ __forceinline__ void row_elem(int k, int &row, int &col) {
+    if constexpr (BLK) {
+        constexpr int LUR = kBlkLog - B, LUC = kBlkLog - A;
+        const int kk = k & (kBlkTile - 1);
+        row = ((k >> kBlkLog) << LUR) + ((kk >> LUC) & ((1 << LUR) - 1));
+        col = ((kk >> (LUR + LUC)) << LUC) + (kk & ((1 << LUC) - 1));
+    } else {
+        row = k >> B;
+        col = k & ((1 << B) - 1);
+    }
+}
+
 // Inputs and outputs of a pass.  A prologue gives the input residue of limb
 // index idx, pro(idx) for integer arithmetic and pro.fp(idx, f) (a whole number
 // below 2^50 in magnitude) for FP64; an epilogue takes the result, epi(idx, x)
@@ -349,39 +388,67 @@ __device__ __forceinline__ void pass_out(const Epi &epi, size_t idx, typename Ar
 
 // Residues in [0, 4q) (no prologue).
 struct LoadPro {
+    static constexpr bool kBlocked = false;
     const uint64_t *in;
     __device__ __forceinline__ uint64_t operator()(size_t idx) const { return in[idx]; }
     __device__ __forceinline__ double fp(size_t idx, const FpMod &) const { return FpMod::from_u52(in[idx]); }
 };
 
-// What the transform's other pass left (the register form's bits).
-struct RawPro {
+// What the transform's other pass left (the register form's bits); BLK: in the
+// blocked layout (row passes).
+template <bool BLK>
+struct RawInPro {
+    static constexpr bool kBlocked = BLK;
     const uint64_t *in;
     __device__ __forceinline__ uint64_t operator()(size_t idx) const { return in[idx]; }
     __device__ __forceinline__ double fp(size_t idx, const FpMod &) const { return ArFp::raw(in[idx]); }
 };
 
+using RawPro = RawInPro<false>;
+using BlkRawPro = RawInPro<true>;
+
 // Results in [0, q) (the forward transform's last pass).
 struct StoreEpi {
-    static constexpr bool kPrefetch = false;
+    static constexpr bool kPrefetch = false, kBlocked = false;
     uint64_t *out;
     __device__ __forceinline__ void operator()(size_t idx, uint64_t x) const { out[idx] = x; }
     __device__ __forceinline__ void fp(size_t idx, double x, const FpMod &f) const { out[idx] = f.canon(f.red(x)); }
 };
 
-// The register form's bits, for the transform's other pass.
-struct RawEpi {
-    static constexpr bool kPrefetch = false;
+// The register form's bits, for the transform's other pass; BLK: in the blocked
+// layout (row passes).
+template <bool BLK>
+struct RawOutEpi {
+    static constexpr bool kPrefetch = false, kBlocked = BLK;
     uint64_t *out;
     __device__ __forceinline__ void operator()(size_t idx, uint64_t x) const { out[idx] = x; }
     __device__ __forceinline__ void fp(size_t idx, double x, const FpMod &) const { out[idx] = ArFp::bits(x); }
 };
 
+using RawEpi = RawOutEpi<false>;
+using BlkRawEpi = RawOutEpi<true>;
+
 // The prologue of a pass and the epilogue of a row pass that are plain loads and stores.
 template <bool FIRST>
 using PlainPro = std::conditional_t<FIRST, LoadPro, RawPro>;
-template <bool FWD>
-using RowStore = std::conditional_t<FWD, StoreEpi, RawEpi>;
+template <bool FWD, bool BLK>
+using RowLoad = std::conditional_t<FWD, RawInPro<BLK>, LoadPro>;
+template <bool FWD, bool BLK = false>
+using RowStore = std::conditional_t<FWD, StoreEpi, RawOutEpi<BLK>>;
+
+// Tile of a small column pass.  Its U = TILE / 2^A columns are narrower than
+// a 128-byte line (G = 16 / U tiles share each line of a row), and workgroups
+// are dealt to the 8 XCDs in turn, each with its own L2: dispatch order
+// w is mapped so that the G tiles of one line group go to the
+// same XCD one after another (w, w + 8, ...), and the line is read from HBM
+// once instead of G times.  Identity when the grid is not a multiple of 8 G.
+template <int TILE, int A>
+__device__ __forceinline__ int xcd_grouped_tile(int w, int tiles) {
+    constexpr int U = TILE >> A, G = U >= 16 ? 1 : 16 / U;
+    if (G == 1 || tiles % (8 * G) != 0) return w;
+    const int x = w & 7, r = w >> 3;
+    return ((r / G) * 8 + x) * G + r % G;
+}
 
 // Passes of launches with few limbs (the INTT of the special-prime limbs before
 // ModDown, the INTT of the dropped limb before a rescale): a tile of TILE
@@ -392,7 +459,7 @@ using RowStore = std::conditional_t<FWD, StoreEpi, RawEpi>;
 // ranges as the kTile passes (forward columns lazy below 4q, forward rows in
 // [0, q); inverse rows lazy below 2q, inverse columns in [0, q)).  Ends with a
 // barrier.
-template <typename Ar, int A, int B, bool FWD, int TILE, int E, typename Pro>
+template <typename Ar, int A, int B, bool FWD, int TILE, int E, bool BLK = false, typename Pro>
 __device__ __forceinline__ void ntt_cols_small_t(uint64_t *lds, const Pro &pro, uint64_t *out,
                                                  const TwPair *__restrict__ tw_all, const Ar &ar, int tile) {
     using V = typename Ar::V;
@@ -404,7 +471,7 @@ __device__ __forceinline__ void ntt_cols_small_t(uint64_t *lds, const Pro &pro, 
 #pragma unroll
     for (int r = 0; r < E; ++r) {
         const int idx = threadIdx.x + r * NT;
-        vin[r] = pass_in(pro, ((size_t)(idx / U) << B) + col0 + idx % U, ar);
+        vin[r] = pass_in(pro, col_index<A, B, BLK>(idx / U, col0 + idx % U), ar);
     }
     typename Ar::Tw twc[tw_slots(A, E)];
     ntt_rounds<Ar, A, FWD, !FWD, 0, E, kTwPrefetch>(TileLds{lds, LDU, (int)(threadIdx.x % U)}, threadIdx.x / U, 1u, tw, ar, twc);
@@ -419,22 +486,22 @@ __device__ __forceinline__ void ntt_cols_small_t(uint64_t *lds, const Pro &pro, 
     for (int r = 0; r < E; ++r) {
         const int idx = threadIdx.x + r * NT;
         const uint64_t x = lds[(idx / U) * LDU + idx % U];
-        out[((size_t)(idx / U) << B) + col0 + idx % U] = FWD ? x : ar.canon_last(Ar::raw(x));
+        out[col_index<A, B, BLK>(idx / U, col0 + idx % U)] = FWD ? x : ar.canon_last(Ar::raw(x));
     }
     __syncthreads();
 }
 
-template <int A, int B, bool FWD, int TILE, int E, typename Pro>
+template <int A, int B, bool FWD, int TILE, int E, bool BLK = false, typename Pro>
 __device__ __forceinline__ void ntt_cols_small_pro(uint64_t *lds, const Pro &pro, uint64_t *out,
                                                    const TwPair *__restrict__ tw, const PrimeConst &pc, bool fp, int tile) {
-    if (fp) ntt_cols_small_t<ArFp, A, B, FWD, TILE, E>(lds, pro, out, tw, ArFp(pc), tile);
-    else ntt_cols_small_t<ArInt, A, B, FWD, TILE, E>(lds, pro, out, tw, ArInt(pc), tile);
+    if (fp) ntt_cols_small_t<ArFp, A, B, FWD, TILE, E, BLK>(lds, pro, out, tw, ArFp(pc), tile);
+    else ntt_cols_small_t<ArInt, A, B, FWD, TILE, E, BLK>(lds, pro, out, tw, ArInt(pc), tile);
 }
 
-template <int A, int B, bool FWD, int TILE, int E>
+template <int A, int B, bool FWD, int TILE, int E, bool BLK>
 __device__ __forceinline__ void ntt_cols_small(uint64_t *lds, const uint64_t *in, uint64_t *out,
                                                const TwPair *__restrict__ tw, const PrimeConst &pc, bool fp, int tile) {
-    ntt_cols_small_pro<A, B, FWD, TILE, E>(lds, PlainPro<FWD>{in}, out, tw, pc, fp, tile);
+    ntt_cols_small_pro<A, B, FWD, TILE, E, BLK>(lds, PlainPro<FWD>{in}, out, tw, pc, fp, tile);
 }
 
 // The result for limb index idx goes through epi (integer: in [0, q) forward,
@@ -444,7 +511,7 @@ template <typename Ar, int A, int B, bool FWD, int TILE, int E, typename Pro, ty
 __device__ __forceinline__ void ntt_rows_small_t(uint64_t *lds, const Pro &pro, const TwPair *__restrict__ tw_all,
                                                  const Ar &ar, int tile, const Epi &epi) {
     using V = typename Ar::V;
-    constexpr int S = 1 << B, U = TILE >> B, LDU = U + 1, NT = TILE / E;
+    constexpr int U = TILE >> B, LDU = U + 1, NT = TILE / E;
     static_assert(U >= 1 && NT >= 64, "small row tile");
     const int row0 = tile * U;
     const auto *tw = twiddles<Ar>(tw_all);
@@ -452,7 +519,7 @@ __device__ __forceinline__ void ntt_rows_small_t(uint64_t *lds, const Pro &pro, 
 #pragma unroll
     for (int r = 0; r < E; ++r) {
         const int idx = threadIdx.x + r * NT;
-        vin[r] = pass_in(pro, ((size_t)(row0 + (idx >> B)) << B) + (idx & (S - 1)), ar);
+        vin[r] = pass_in(pro, ((size_t)row0 << B) + idx, ar);
     }
     // an epilogue that reads an operand of its own (the ModDown and rescale
     // tails) has it loaded here, with the tile, instead of after the last
@@ -462,7 +529,7 @@ __device__ __forceinline__ void ntt_rows_small_t(uint64_t *lds, const Pro &pro, 
 #pragma unroll
         for (int r = 0; r < E; ++r) {
             const int idx = threadIdx.x + r * NT;
-            opnd[r] = epi.operand(((size_t)(row0 + (idx >> B)) << B) + (idx & (S - 1)));
+            opnd[r] = epi.operand(((size_t)row0 << B) + idx);
         }
     }
     const int u = threadIdx.x % U;
@@ -471,15 +538,19 @@ __device__ __forceinline__ void ntt_rows_small_t(uint64_t *lds, const Pro &pro, 
 #pragma unroll
     for (int r = 0; r < E; ++r) {
         const int idx = threadIdx.x + r * NT;
-        lds[(idx & (S - 1)) * LDU + (idx >> B)] = Ar::bits(vin[r]);
+        int row, col;
+        row_elem<A, B, Pro::kBlocked>(idx, row, col);
+        lds[col * LDU + row] = Ar::bits(vin[r]);
     }
     __syncthreads();
     ntt_rounds<Ar, B, FWD, false, 0, E, kTwCached>(TileLds{lds, LDU, u}, threadIdx.x / U, (1u << A) + row0 + u, tw, ar, twc);
 #pragma unroll
     for (int r = 0; r < E; ++r) {
         const int idx = threadIdx.x + r * NT;
-        V v = Ar::raw(lds[(idx & (S - 1)) * LDU + (idx >> B)]);
-        const size_t gi = ((size_t)(row0 + (idx >> B)) << B) + (idx & (S - 1));
+        int row, col;
+        row_elem<A, B, Epi::kBlocked>(idx, row, col);
+        V v = Ar::raw(lds[col * LDU + row]);
+        const size_t gi = ((size_t)row0 << B) + idx;
         if constexpr (!Ar::kFp && FWD) v = csub(csub(v, ar.q2), ar.q);
         if constexpr (Epi::kPrefetch) {
             if constexpr (Ar::kFp) epi.finish_fp(gi, v, opnd[r], ar.f);
@@ -498,10 +569,10 @@ __device__ __forceinline__ void ntt_rows_small_pe(uint64_t *lds, const Pro &pro,
     else ntt_rows_small_t<ArInt, A, B, FWD, TILE, E>(lds, pro, tw, ArInt(pc), tile, epi);
 }
 
-template <int A, int B, bool FWD, int TILE, int E>
+template <int A, int B, bool FWD, int TILE, int E, bool BLK>
 __device__ __forceinline__ void ntt_rows_small(uint64_t *lds, const uint64_t *in, uint64_t *out,
                                                const TwPair *__restrict__ tw, const PrimeConst &pc, bool fp, int tile) {
-    ntt_rows_small_pe<A, B, FWD, TILE, E>(lds, PlainPro<!FWD>{in}, tw, pc, fp, tile, RowStore<FWD>{out});
+    ntt_rows_small_pe<A, B, FWD, TILE, E>(lds, RowLoad<FWD, BLK>{in}, tw, pc, fp, tile, RowStore<FWD, BLK>{out});
 }
 
 // Column pass: sub-transforms are columns (2^A rows, stride 2^B), tile
@@ -525,7 +596,7 @@ __device__ __forceinline__ constexpr int tile_tw() {
     return Ar::kFp ? kTwCached : kTwLoad;
 }
 
-template <typename Ar, int A, int B, bool FWD, typename Pro>
+template <typename Ar, int A, int B, bool FWD, bool BLK, typename Pro>
 __device__ __forceinline__ void ntt_cols_load(typename Ar::V (&regs)[kElems], int tile, const Pro &pro, const Ar &ar) {
     static_assert(A > kElemsLog && A <= 2 * kElemsLog, "two rounds");
     constexpr int U = kTile >> A;
@@ -536,19 +607,19 @@ __device__ __forceinline__ void ntt_cols_load(typename Ar::V (&regs)[kElems], in
         // The first forward round works on rows t + e 2^(A-4) of column u, the
         // order in which the tile arrives: it starts from registers.
 #pragma unroll
-        for (int e = 0; e < kElems; ++e) regs[e] = pass_in(pro, ((size_t)(t + (e << C2)) << B) + col0 + u, ar);
+        for (int e = 0; e < kElems; ++e) regs[e] = pass_in(pro, col_index<A, B, BLK>(t + (e << C2), col0 + u), ar);
     } else {
 #pragma unroll
         for (int r = 0; r < kTile / kThreads; ++r) {
             const int idx = threadIdx.x + r * kThreads;
-            regs[r] = pass_in(pro, ((size_t)(idx / U) << B) + col0 + idx % U, ar);
+            regs[r] = pass_in(pro, col_index<A, B, BLK>(idx / U, col0 + idx % U), ar);
         }
     }
 }
 
 // Ends with a barrier, so lds may be reused at once.  The forward output is
 // left as Ar's bits (integer: lazy below 4q).
-template <typename Ar, int A, int B, bool FWD>
+template <typename Ar, int A, int B, bool FWD, bool BLK>
 __device__ __forceinline__ void ntt_cols_compute(uint64_t *lds, uint64_t *out, const TwPair *__restrict__ tw_all,
                                                  const Ar &ar, int tile, typename Ar::V (&regs)[kElems],
                                                  typename Ar::Tw *twc) {
@@ -570,7 +641,7 @@ __device__ __forceinline__ void ntt_cols_compute(uint64_t *lds, uint64_t *out, c
         for (int r = 0; r < kTile / kThreads; ++r) {
             const int idx = threadIdx.x + r * kThreads;
             const int row = idx / U, col = idx % U;
-            out[((size_t)row << B) + col0 + col] = lds[row * LDU + col];
+            out[col_index<A, B, BLK>(row, col0 + col)] = lds[row * LDU + col];
         }
     } else {
 #pragma unroll
@@ -592,22 +663,22 @@ __device__ __forceinline__ void ntt_cols_compute(uint64_t *lds, uint64_t *out, c
 #pragma unroll
             for (int e = 0; e < G; ++e) {
                 const int row = t * NG + gi + (e << kElemsLog);
-                out[((size_t)row << B) + col0 + u] = ar.canon_last(regs[gi * G + e]);
+                out[col_index<A, B, BLK>(row, col0 + u)] = ar.canon_last(regs[gi * G + e]);
             }
     }
     __syncthreads();
 }
 
-template <typename Ar, int A, int B, bool FWD, typename Pro>
+template <typename Ar, int A, int B, bool FWD, bool BLK = false, typename Pro>
 __device__ __forceinline__ void ntt_cols_unit_t(uint64_t *lds, uint64_t *out, const TwPair *__restrict__ tw,
                                                 const Ar &ar, int tile, const Pro &pro) {
     typename Ar::V regs[kElems];
     typename Ar::Tw twc[tile_tw<Ar>() == kTwCached ? tw_slots(A, kElems) : 1];
-    ntt_cols_load<Ar, A, B, FWD>(regs, tile, pro, ar);
+    ntt_cols_load<Ar, A, B, FWD, BLK>(regs, tile, pro, ar);
     if constexpr (tile_tw<Ar>() == kTwCached)
         ntt_rounds<Ar, A, FWD, !FWD, 0, kElems, kTwPrefetch>(TileLds{}, threadIdx.x / (kTile >> A), 1u, twiddles<Ar>(tw),
                                                              ar, twc);
-    ntt_cols_compute<Ar, A, B, FWD>(lds, out, tw, ar, tile, regs, twc);
+    ntt_cols_compute<Ar, A, B, FWD, BLK>(lds, out, tw, ar, tile, regs, twc);
 }
 
 // The prime decides the arithmetic (fp: it is below kFpPrimeBound; uniform
@@ -628,11 +699,11 @@ __device__ __forceinline__ void ntt_cols_unit_pro(uint64_t *lds, uint64_t *out, 
 // 2^16 13.4 to 22.0 and now 12.9 to 21.7.
 constexpr int kMixTile = 1024, kMixE = kMixTile / kThreads;
 
-template <int A, int B, bool FWD, typename Pro>
+template <int A, int B, bool FWD, bool BLK, typename Pro>
 __device__ __forceinline__ void ntt_cols_mixed(uint64_t *lds, uint64_t *out, const TwPair *__restrict__ tw,
                                                const PrimeConst &pc, bool fp, int tile, const Pro &pro) {
-    if (fp) ntt_cols_unit_t<ArFp, A, B, FWD>(lds, out, tw, ArFp(pc), tile, pro);
-    else ntt_cols_small_t<ArInt, A, B, FWD, kMixTile, kMixE>(lds, pro, out, tw, ArInt(pc), tile);
+    if (fp) ntt_cols_unit_t<ArFp, A, B, FWD, BLK>(lds, out, tw, ArFp(pc), tile, pro);
+    else ntt_cols_small_t<ArInt, A, B, FWD, kMixTile, kMixE, BLK>(lds, pro, out, tw, ArInt(pc), tile);
 }
 
 template <int A, int B, bool FWD>
@@ -649,6 +720,7 @@ __device__ __forceinline__ void ntt_cols_unit(uint64_t *lds, const uint64_t *in,
 // the centred representative of a q_l below kFpPrimeBound is an input as it is.
 template <bool KEEP_T>
 struct LiftPro {
+    static constexpr bool kBlocked = false;
     const uint64_t *last;
     uint64_t ql, ql_half, tinv, tinv_p;  // dropped prime q_l, t^-1 mod q_l
     double qld;                          // q_l in FP64
@@ -676,6 +748,7 @@ struct LiftPro {
 // KP: the number of special primes K, or 8 for any K <= 8 (runtime K).
 template <int KP>
 struct ModdownPro {
+    static constexpr bool kBlocked = false;
     const uint64_t *src;  // P-limb 0 of the polynomial; limb a at src + a * stride
     size_t stride;
     uint32_t K;
@@ -698,6 +771,30 @@ struct ModdownPro {
     __device__ __forceinline__ double fp(size_t idx, const FpMod &) const { return FpMod::from_u52((*this)(idx)); }
 };
 
+// Prologue of the first pass of NTT(conv): the ModDown conversion of target i
+// of polynomial c from the K P-limbs of ip[c] ([2][nl + K][N]).
+template <int KP, int LOGN>
+__device__ __forceinline__ ModdownPro<KP> moddown_pro(const uint64_t *ip, const PrimeConst *__restrict__ pcs,
+                                                      const PrimeConst &pc, const uint64_t *__restrict__ cross,
+                                                      const uint64_t *__restrict__ negp, uint32_t c, uint32_t i,
+                                                      uint32_t nl, uint32_t L, uint32_t K) {
+    ModdownPro<KP> pro;
+    pro.src = ip + (((size_t)c * (nl + K) + nl) << LOGN);
+    pro.stride = (size_t)1 << LOGN;
+    pro.K = K;
+#pragma unroll
+    for (int a = 0; a < KP; ++a) {
+        pro.half[a] = a < (int)K ? pcs[L + a].q >> 1 : 0;
+        pro.cross[a] = a < (int)K ? cross[(size_t)i * K + a] : 0;
+    }
+    pro.negp = negp[i];
+    pro.q = pc.q;
+    pro.r64 = pc.r64;
+    pro.r64_p = pc.r64_p;
+    pro.one_p = pc.one_p;
+    return pro;
+}
+
 // Row pass: sub-transforms are rows (2^B contiguous residues), tile `tile`
 // covers 4096 / 2^B consecutive rows.  Forward: the last B stages (output in
 // [0, q)); inverse: the first B stages (output lazy in [0, 2q)).  The result
@@ -711,11 +808,12 @@ __device__ __forceinline__ void ntt_rows_load(typename Ar::V (&regs)[kElems], in
 #pragma unroll
     for (int r = 0; r < kTile / kThreads; ++r) {
         const int idx = threadIdx.x + r * kThreads;
-        regs[r] = pass_in(pro, ((size_t)(row0 + (idx >> B)) << B) + (idx & (S - 1)), ar);
+        regs[r] = pass_in(pro, ((size_t)row0 << B) + idx, ar);
     }
 }
 
-template <typename Ar, int A, int B, bool FWD, typename Epi>
+// BLK_IN: the tile came in the blocked layout.
+template <typename Ar, int A, int B, bool FWD, bool BLK_IN, typename Epi>
 __device__ __forceinline__ void ntt_rows_compute(uint64_t *lds, const TwPair *__restrict__ tw_all, const Ar &ar,
                                                  int tile, const Epi &epi, typename Ar::V (&regs)[kElems],
                                                  typename Ar::Tw *twc) {
@@ -727,7 +825,9 @@ __device__ __forceinline__ void ntt_rows_compute(uint64_t *lds, const TwPair *__
 #pragma unroll
     for (int r = 0; r < kTile / kThreads; ++r) {
         const int idx = threadIdx.x + r * kThreads;
-        lds[(idx & (S - 1)) * LDU + (idx >> B)] = Ar::bits(regs[r]);
+        int row, col;
+        row_elem<A, B, BLK_IN>(idx, row, col);
+        lds[col * LDU + row] = Ar::bits(regs[r]);
     }
     __syncthreads();
     const int u = threadIdx.x % U, t = threadIdx.x / U;
@@ -735,12 +835,13 @@ __device__ __forceinline__ void ntt_rows_compute(uint64_t *lds, const TwPair *__
 #pragma unroll
     for (int r = 0; r < kTile / kThreads; ++r) {
         const int idx = threadIdx.x + r * kThreads;
-        const int row = idx >> B, p = idx & (S - 1);
-        typename Ar::V x = Ar::raw(lds[p * LDU + row]);
+        int row, col;
+        row_elem<A, B, Epi::kBlocked>(idx, row, col);
+        typename Ar::V x = Ar::raw(lds[col * LDU + row]);
         if constexpr (!Ar::kFp) {
             if (FWD) x = csub(csub(x, ar.q2), ar.q);
         }
-        pass_out(epi, ((size_t)(row0 + row) << B) + p, x, ar);
+        pass_out(epi, ((size_t)row0 << B) + idx, x, ar);
     }
     __syncthreads();
 }
@@ -757,7 +858,7 @@ __device__ __forceinline__ void ntt_rows_unit_t(uint64_t *lds, const Pro &pro, c
                                                               (1u << A) + tile * U + threadIdx.x % U, twiddles<Ar>(tw),
                                                               ar, twc);
     }
-    ntt_rows_compute<Ar, A, B, FWD>(lds, tw, ar, tile, epi, regs, twc);
+    ntt_rows_compute<Ar, A, B, FWD, Pro::kBlocked>(lds, tw, ar, tile, epi, regs, twc);
 }
 
 template <int A, int B, bool FWD, typename Pro, typename Epi>
@@ -793,6 +894,7 @@ __device__ __forceinline__ void ntt_rows_unit(uint64_t *lds, const uint64_t *in,
 // computes d0, d1 and its own d2 residues from a and b itself), lazy in
 // [0, 2q), the range the inverse butterflies accept.
 struct TensorPro {
+    static constexpr bool kBlocked = false;
     const uint64_t *a1, *b1;  // limb i of a1, b1
     uint64_t q, r64, r64_p, one_p;
     __device__ __forceinline__ uint64_t operator()(size_t idx) const {
@@ -807,6 +909,7 @@ struct TensorPro {
 
 // HRotate: sigma_g(a1) as the prologue of its INTT.
 struct GatherPro {
+    static constexpr bool kBlocked = false;
     const uint64_t *in;  // limb i of a1
     uint32_t galois, log_n;
     __device__ __forceinline__ uint64_t operator()(size_t idx) const {
@@ -819,7 +922,7 @@ struct GatherPro {
 // product having left ip' = ip P^-1 + add: out = ip' - NTT(conv) P^-1 mod q.
 struct ModdownFoldEpi {
     // the small-tile row pass loads ip with its tile (operand), then finish
-    static constexpr bool kPrefetch = true;
+    static constexpr bool kPrefetch = true, kBlocked = false;
     const uint64_t *ip;
     uint64_t *out;
     uint64_t pinv, pinv_p, q;
@@ -837,7 +940,7 @@ struct ModdownFoldEpi {
 // Rescale / modulus-switch tail as the epilogue of the NTT of the lifted limb:
 // out = (in - NTT(lift)) * q_l^-1 mod q.
 struct RescaleTailEpi {
-    static constexpr bool kPrefetch = true;  // as ModdownFoldEpi
+    static constexpr bool kPrefetch = true, kBlocked = false;  // as ModdownFoldEpi
     const uint64_t *in;
     uint64_t *out;
     uint64_t qlinv, qlinv_p, q;

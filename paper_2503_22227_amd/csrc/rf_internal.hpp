@@ -74,6 +74,7 @@ struct NttBatch {
     uint32_t prime_base;
     const uint32_t *pmap;      // device array [per_poly] or nullptr
     LimbOrder order;           // the same limbs in launch order (ent null: made from prime_base)
+    bool blocked = false;      // the coefficient side is in the blocked layout (ntt_dev.hpp)
 };
 
 // Offsets (uint64 entries) of the BEHZ tables of a BFV context (L Q-primes,
@@ -105,6 +106,21 @@ struct ModupLevel {
     uint32_t ext_limbs;   // sum over digits of (nl - alpha_j + k)
     uint32_t pmap_off;    // offset of this level's prime map in Context::d_pmaps
 };
+
+// The targets one workgroup of a fused base conversion takes (convert.hip): one
+// limb of a wide prime, or up to four of narrow ones.
+struct ConvUnit {
+    uint32_t digit, size;  // ModUp: the digit and its number of primes
+    uint32_t count, wide;
+    uint32_t e[4];         // limb | prime << 16, the last one repeated from count on
+};
+
+// Constants of a conversion as the matrix instruction's operand (convert.hip):
+// per block (ModUp: modup_block's order; ModDown: one) and target prime g the
+// bytes [8][kp][8] at (block * primes + g) * conv_bytes(kp), kp = 4 or 8 sources,
+// and off[block * primes + g].
+inline uint32_t conv_kp(uint32_t sources) { return sources <= 4 ? 4 : 8; }
+inline size_t conv_bytes(uint32_t kp) { return 64 * (size_t)kp; }
 
 }  // namespace rf
 
@@ -142,6 +158,14 @@ struct rf_ctx {
     };
     std::vector<OrderRef> q_order, ext_order;  // index nl: q_0..q_{nl-1}; the ModUp extension
     OrderRef p_order, all_order, qb_order;     // the special primes; Q u P; q u B_sk (BFV)
+    struct UnitRef {
+        uint32_t off = 0, n = 0;
+    };
+    std::vector<UnitRef> modup_units, moddown_units;  // index nl: rf::ConvUnit windows of d_units
+    rf::ConvUnit *d_units = nullptr;
+    // narrow targets' conversion constants (null without narrow primes): ModUp, ModDown (BGV: t's)
+    int8_t *d_conv_mu = nullptr, *d_conv_md = nullptr;
+    double *d_conv_mu_off = nullptr, *d_conv_md_off = nullptr;
     rf::LimbOrder order(const OrderRef &r) const { return rf::LimbOrder{d_order + r.off, r.n_wide}; }
     // BFV: auxiliary base B and m_sk follow the special primes in `primes`
     uint32_t nb = 0;
@@ -235,9 +259,19 @@ int launch_ntt(const rf_ctx *c, const NttBatch &b, bool forward, hipStream_t s, 
                const rf_tuning *tn = nullptr);
 // Second pass alone of the INTT of data [nl][N] over q_0.. (two-pass ring degrees, default variants).
 int launch_intt_cols(const rf_ctx *c, uint64_t *data, uint32_t nl, hipStream_t s);
+// Last pass alone of the forward NTT of b's limbs after launch_modup_cols.
+int launch_ntt_fwd_rows(const rf_ctx *c, const NttBatch &b, hipStream_t s, const rf_tuning *tn);
+// ModUp conversion and the first pass of the extension's NTT in one launch
+// (convert.hip): x [nl][N] as launch_modup_bconv's scaled input, ext its output
+// after the column pass, both in the blocked layout or both not.  modup_fused:
+// whether a key switch takes it.
+bool modup_fused(const rf_ctx *c, bool scaled);
+int launch_modup_cols(const rf_ctx *c, const uint64_t *x, uint64_t *ext, uint32_t nl, bool blocked, hipStream_t s);
+// The first pass of NTT(conv) after the ModDown conversion, likewise (contexts with narrow primes).
+int launch_moddown_cols(const rf_ctx *c, const uint64_t *ip, uint64_t *conv, uint32_t nl, hipStream_t s);
 // ModDown after the inner product, two-pass ring degrees only: ip = [2][nl + K][N]
 // whose K P-limbs hold the INTT with d_pc_md (so already scaled by the input
-// factor).  The first forward pass computes the base conversion of each Q
+// factor; blocked layout).  The first forward pass computes the base conversion of each Q
 // target in its prologue (into conv [2][nl][N]), the last applies the tail:
 // out[c][i] = (ip[c][i] - NTT(conv)) P^-1 + add_c.
 // ip's Q-limbs must come from launch_inner_product with fold (P^-1 and the addends
@@ -246,12 +280,12 @@ int launch_ntt_fwd_moddown(const rf_ctx *c, uint64_t *conv, const uint64_t *ip, 
                            hipStream_t s, const rf_tuning *tn = nullptr);
 // INTT of the polynomial to key-switch (two-pass ring degrees only), with the
 // step that produces it as the prologue of its first pass, into dc [nl][N]
-// (coefficient domain, scaled for ModUp by pc_modup(c, nl)):
+// (coefficient domain, blocked layout, scaled for ModUp by pc_modup(c, nl)):
 //   galois == 0 (HMult): d2 = a1 b1 of a, b ([2][nl][N]);
 //   galois != 0 (HRotate): sigma_g of a's polynomial 1.
 int launch_intt_first(const rf_ctx *c, const uint64_t *a, const uint64_t *b, uint64_t *dc, uint32_t galois,
                       uint32_t nl, hipStream_t s, const rf_tuning *tn = nullptr);
-// Rescale / modulus switch after the INTT of the last limb (last = [2][N]),
+// Rescale / modulus switch after the INTT of the last limb (last = [2][N], blocked),
 // two-pass ring degrees only: the first forward pass lifts the last limb into
 // each remaining prime in its prologue (into lift [2][nl-1][N]; KEEP_T for BGV),
 // the last applies the tail out[c][i] = (in[c][i] - NTT(lift)) q_l^-1.

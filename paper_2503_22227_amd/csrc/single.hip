@@ -116,6 +116,7 @@ __global__ __launch_bounds__(kSThreads) void single_first_kernel(SingleArgs a, F
 // ModUp conversion of a digit (source limbs x, s of them) to one target, as the
 // prologue of the target's NTT.  factor non-null: x is unscaled.
 struct ModupPro {
+    static constexpr bool kBlocked = false;
     const uint64_t *x, *factor, *cross;
     const PrimeConst *src;  // the sources' constants
     uint32_t s, narrow;     // narrow: bit i set if source i is below kFpPrimeBound
@@ -179,6 +180,7 @@ __global__ __launch_bounds__(kSThreads) void single_modup_kernel(SingleArgs a, F
 
 // Inner product sum_j ext_j evk_{j,c} on special limb a, as the prologue of its INTT.
 struct IpPro {
+    static constexpr bool kBlocked = false;
     const uint64_t *ext, *key;  // at the limb; digit strides below
     size_t key_stride;
     uint32_t dn, nl, K, alpha;
