@@ -8,6 +8,9 @@
 // ModDown-conversion and tail steps keep their stage numbers with no work
 // units.
 //
+// The ModUp conversion runs in the first pass of its NTT where modup_fused, which
+// leaves its own step to the other items.
+//
 // Launches: each element-wise step (ModUp conversion, inner product) is ONE
 // launch over the work units of every item; each NTT pass is one launch per
 // ring degree present (one transform shape per kernel keeps the unrolled
@@ -16,9 +19,10 @@
 // walking a contiguous range of units (a persistent form the autotuner can
 // pick).
 //
-// Work units: an NTT pass unit is one 4096-residue tile of one limb
-// (N / 4096 tiles per limb); an element-wise unit is 256 coefficients of one
-// limb, digit or polynomial.  The units of a step are numbered item after
+// Work units: an NTT pass unit is one 4096-residue tile of one limb, or 1024
+// residues of a wide limb (kBatchSmallBelow) or of a conversion's targets
+// (ConvUnit); an element-wise unit is 256 coefficients of one limb, digit or
+// polynomial.  The units of a step are numbered item after
 // item (prefix sums in the job tables); a workgroup finds the item of its
 // first unit by binary search and then walks forward, so the per-unit
 // overhead is a compare.  Mixed ring degrees are dispatched per unit to the
@@ -32,8 +36,8 @@
 #include <algorithm>
 #include <vector>
 
+#include "conv_dev.hpp"
 #include "ks_dev.hpp"
-#include "ntt_dev.hpp"
 
 namespace rf {
 
@@ -64,20 +68,27 @@ struct KsJob {
 };
 
 struct NttJob {
-    NttBatch b;
-    const TwPair *tw_all;   // natural table (column passes)
-    const TwPair *tw_rows;  // row-pass layout (row passes)
+    NttBatch b;             // in place but for the first pass of the INTT of d2
+    const TwPair *tw_all;   // natural table (column passes, small tiles)
+    const TwPair *tw_rows;  // row-pass layout (4096-residue row tiles)
     const PrimeConst *pcs;
     uint32_t log_n;
-    uint32_t unit_begin;
+    uint32_t unit_begin[2];  // first and second pass
+    uint32_t small;         // units of the wide limbs, first in b.order, are 1024 residues (limb_units)
     // prologue of the INTT of d2: the item's ciphertexts a, b ([2][nl][N])
     const uint64_t *ct_a, *ct_b;
+    // fused conversion before the first pass of NTT(ext), NTT(conv) (conv_dev.hpp; units null: none)
+    const ConvUnit *units;
+    const int8_t *frag;
+    const double *off;
+    const uint64_t *x, *modup_tab;  // ModUp: d_coeff, table
+    uint64_t modup_stride;
     // ModDown in NTT(conv): conversion from the P-limbs of ip in the first pass,
     // tail out = ip' - NTT(conv) P^-1 in the last
     const uint64_t *ip;
     uint64_t *out;
     const uint64_t *pinv, *md_cross, *md_negp;
-    uint32_t nl, K, L;
+    uint32_t nl, K, L, alpha;
 };
 
 template <typename J>
@@ -87,8 +98,8 @@ __device__ __forceinline__ uint32_t unit_begin_of<KsJob>(const KsJob &j, int sta
     return j.unit_begin[stage];
 }
 template <>
-__device__ __forceinline__ uint32_t unit_begin_of<NttJob>(const NttJob &j, int) {
-    return j.unit_begin;
+__device__ __forceinline__ uint32_t unit_begin_of<NttJob>(const NttJob &j, int pass) {
+    return j.unit_begin[pass];
 }
 
 // The pointers of a job table address device memory, but loaded from the table
@@ -124,7 +135,7 @@ __device__ __forceinline__ NttJob global_job(const NttJob &J) {
     NttJob g = J;
     g.b.in = gptr(J.b.in);
     g.b.out = gptr(J.b.out);
-    g.b.pmap = gptr(J.b.pmap);
+    g.b.order.ent = gptr(J.b.order.ent);
     g.tw_all = gptr(J.tw_all);
     g.tw_rows = gptr(J.tw_rows);
     g.pcs = gptr(J.pcs);
@@ -135,6 +146,11 @@ __device__ __forceinline__ NttJob global_job(const NttJob &J) {
     g.pinv = gptr(J.pinv);
     g.md_cross = gptr(J.md_cross);
     g.md_negp = gptr(J.md_negp);
+    g.units = gptr(J.units);
+    g.frag = gptr(J.frag);
+    g.off = gptr(J.off);
+    g.x = gptr(J.x);
+    g.modup_tab = gptr(J.modup_tab);
     return g;
 }
 
@@ -185,106 +201,187 @@ __global__ __launch_bounds__(kEw) void ks_batched_kernel(const KsJob *__restrict
     }
 }
 
-// First pass of NTT(conv) of target li of polynomial poly with the ModDown
-// conversion from the item's P-limbs as its prologue (KP: see ModdownPro).
-template <int A, int B, int KP>
-__device__ __forceinline__ void moddown_cols_pass(uint64_t *lds, const NttJob &J, uint32_t poly, uint32_t li,
-                                                  uint64_t *out, const TwPair *tw, const PrimeConst &pc, uint32_t tile) {
-    constexpr int LOGN = A + B;
-    ModdownPro<KP> pro;
-    pro.src = J.ip + (((size_t)poly * (J.nl + J.K) + J.nl) << LOGN);
-    pro.stride = (size_t)1 << LOGN;
-    pro.K = J.K;
-#pragma unroll
-    for (int a = 0; a < KP; ++a) {
-        pro.half[a] = a < (int)J.K ? J.pcs[J.L + a].q >> 1 : 0;
-        pro.cross[a] = a < (int)J.K ? J.md_cross[(size_t)li * J.K + a] : 0;
-    }
-    pro.negp = J.md_negp[li];
-    pro.q = pc.q;
-    pro.r64 = pc.r64;
-    pro.r64_p = pc.r64_p;
-    pro.one_p = pc.one_p;
-    ntt_cols_unit_pro<A, B, true>(lds, out, tw, pc, pc.q < kFpPrimeBound, tile, pro);
+// The NTT passes of a batch.  The transforms' coefficient sides and what lies
+// between their passes are in the blocked layout (ntt_dev.hpp).
+enum BatchPass {
+    kPassTensor,    // INTT of d2 = a1 b1: rows
+    kPassInvRows,   // INTT of the P-limbs: rows
+    kPassInvCols,   // either's columns
+    kPassModup,     // NTT of the extension: columns, with the conversion where it is fused
+    kPassFwdRows,   // its rows
+    kPassModdown4,  // NTT of the ModDown conversion: columns and the conversion from 4 special primes
+    kPassModdown8,  // or any number up to 8
+    kPassTail       // its rows, with the tail
+};
+__host__ __device__ constexpr bool pass_cols(BatchPass p) {
+    return p == kPassInvCols || p == kPassModup || p == kPassModdown4 || p == kPassModdown8;
+}
+__host__ __device__ constexpr int pass_second(BatchPass p) {
+    return p == kPassInvCols || p == kPassFwdRows || p == kPassTail;
 }
 
-// One pass of a batched (I)NTT over the items of one ring degree 2^(A+B) (the
-// plan launches each NTT step once per ring degree present: one transform
-// shape per kernel keeps the unrolled rounds free of register spills).
-// FIRST = the pass that reads b.in (forward: columns; inverse: rows); the
-// second pass works in place on b.out.  TAIL (the forward row pass of
-// NTT(conv)) writes the ModDown result instead.  PRO: the first pass computes
-// its input: 1 = d2 from a, b (INTT of d2), 2 / 3 = the ModDown conversion
-// (NTT of conv) from 4 / up to 8 special primes.  Units [unit0, unit0 + total) of the step; jobs = the items of the
-// ring degree, whose unit_begin values are absolute.
-template <int A, int B, bool FWD, bool FIRST, bool TAIL, int PRO>
+// Unit `local` of a job's limbs.
+struct BatchUnit {
+    uint32_t li, poly, g;
+    int tile;
+    int kind;  // 0: a wide limb's 4096 residues, 1: its 1024, 2: a narrow one's 4096
+};
+template <int LOGN>
+__device__ __forceinline__ BatchUnit batch_unit(const NttJob &J, uint32_t local) {
+    constexpr int TW = LOGN - 10, TN = LOGN - 12;
+    BatchUnit u;
+    uint32_t e;
+    const uint32_t wide = J.b.order.n_wide * J.b.n_polys, tw = J.small ? TW : TN;
+    if (local < wide << tw) {
+        u.kind = J.small ? 1 : 0;
+        e = local >> tw;
+        u.tile = local & ((1 << tw) - 1);
+    } else {
+        u.kind = 2;
+        local -= wide << tw;
+        e = wide + (local >> TN);
+        u.tile = local & ((1 << TN) - 1);
+    }
+    const uint32_t k = J.b.n_polys == 1 ? e : e >> 1;
+    u.poly = J.b.n_polys == 1 ? 0 : e & 1;
+    const uint32_t x = J.b.order.ent[k];
+    u.li = x & 0xffffu;
+    u.g = x >> 16;
+    return u;
+}
+
+template <int A, int B, bool FWD, typename Pro, typename Epi>
+__device__ __forceinline__ void batch_rows(uint64_t *lds, const NttJob &J, const BatchUnit &u, const PrimeConst &pc,
+                                           const Pro &pro, const Epi &epi) {
+    const size_t t = (size_t)u.g << (A + B);
+    if (u.kind == 2) ntt_rows_unit_t<ArFp, A, B, FWD>(lds, pro, J.tw_rows + t, ArFp(pc), u.tile, epi);
+    else if (u.kind == 1) ntt_rows_small_t<ArInt, A, B, FWD, kMixTile, kMixE>(lds, pro, J.tw_all + t, ArInt(pc), u.tile, epi);
+    else ntt_rows_unit_t<ArInt, A, B, FWD>(lds, pro, J.tw_rows + t, ArInt(pc), u.tile, epi);
+}
+
+// Column pass with a ModUp conversion: unit `local` of the extension's units.
+template <int A, int B, int KP>
+__device__ __forceinline__ void batch_modup(uint64_t *lds, const NttJob &J, uint32_t local) {
+    constexpr int LOGN = A + B, TL = LOGN - 10;
+    const int tile = xcd_grouped_tile<kMixTile, A>(local & ((1 << TL) - 1), 1 << TL);
+    const ConvUnit *un = J.units + (local >> TL);
+    const uint32_t j = un->digit, s = un->size, blk = j * J.alpha + s - 1;
+    const uint64_t *src = J.x + ((size_t)j * J.alpha << LOGN);
+    uint64_t *dst = J.b.out + ((size_t)j * (J.nl + J.K - J.alpha) << LOGN);
+    if (un->wide) {
+        const uint32_t li = un->e[0] & 0xffffu, g = un->e[0] >> 16;
+        const PrimeConst pc = J.pcs[g];
+        const ModupColsPro<KP> pro = modup_cols_pro<KP, LOGN>(
+            src, s, J.modup_tab + blk * J.modup_stride + 2 * J.alpha + (size_t)g * J.alpha, pc);
+        ntt_cols_small_t<ArInt, A, B, true, kMixTile, kMixE, true>(lds, pro, dst + ((size_t)li << LOGN),
+                                                                   J.tw_all + ((size_t)g << LOGN), ArInt(pc), tile);
+    } else {
+        const size_t b = (size_t)blk * (J.L + J.K);
+        conv_cols_narrow<A, B, KP, false, true>(lds, src, s, nullptr, J.frag + b * (64 * KP), J.off + b, J.tw_all, J.pcs,
+                                                un, dst, tile);
+    }
+}
+
+// One pass over unit u of a job.
+template <int A, int B, BatchPass PASS>
 __device__ __forceinline__ void ntt_batched_unit(uint64_t *lds, const NttJob &J, uint32_t u) {
     constexpr int LOGN = A + B;
-    constexpr bool COLS = FWD == FIRST;
-    const uint32_t local = u - J.unit_begin;
-    constexpr uint32_t tshift = LOGN - 12;  // N / 4096 tiles per limb
-    const uint32_t limb = local >> tshift, tile = local & ((1u << tshift) - 1);
-    const uint32_t poly = limb / J.b.per_poly, li = limb - poly * J.b.per_poly;
-    const uint32_t g = J.b.pmap ? (uint32_t)J.b.pmap[li] : J.b.prime_base + li;
-    const uint64_t *base_in = FIRST ? J.b.in : J.b.out;
-    const uint64_t in_stride = FIRST ? J.b.in_poly_stride : J.b.out_poly_stride;
-    const uint64_t *in = base_in + (size_t)poly * in_stride + ((size_t)li << LOGN);
-    uint64_t *out = J.b.out + (size_t)poly * J.b.out_poly_stride + ((size_t)li << LOGN);
-    const PrimeConst pc = J.pcs[g];
-    const bool fp = pc.q < kFpPrimeBound;
-    const TwPair *tw = (COLS ? J.tw_all : J.tw_rows) + ((size_t)g << LOGN);
-    if constexpr (PRO == 1) {
-        // first pass of INTT(d2): d2 = a1 b1 of limb li
-        const size_t poly1 = ((size_t)J.nl + li) << LOGN;
+    const uint32_t local = u - J.unit_begin[pass_second(PASS)];
+    if constexpr (PASS == kPassModup) {
+        if (J.units) {
+            if (J.alpha <= 4) batch_modup<A, B, 4>(lds, J, local);
+            else batch_modup<A, B, 8>(lds, J, local);
+            return;
+        }
+    }
+    if constexpr (PASS == kPassModdown4 || PASS == kPassModdown8) {
+        constexpr int KP = PASS == kPassModdown4 ? 4 : 8;
+        if (J.units) {
+            constexpr int TL = LOGN - 10;
+            const int tile = xcd_grouped_tile<kMixTile, A>(local & ((1 << TL) - 1), 1 << TL);
+            const uint32_t w = local >> TL, poly = w & 1;
+            const ConvUnit *un = J.units + (w >> 1);
+            uint64_t *dst = J.b.out + ((size_t)poly * J.nl << LOGN);
+            if (un->wide) {
+                const uint32_t i = un->e[0] & 0xffffu;
+                const PrimeConst pc = J.pcs[i];
+                ntt_cols_small_t<ArInt, A, B, true, kMixTile, kMixE, true>(
+                    lds, moddown_pro<KP, LOGN>(J.ip, J.pcs, pc, J.md_cross, J.md_negp, poly, i, J.nl, J.L, J.K),
+                    dst + ((size_t)i << LOGN), J.tw_all + ((size_t)i << LOGN), ArInt(pc), tile);
+            } else {
+                const uint64_t *src = J.ip + (((size_t)poly * (J.nl + J.K) + J.nl) << LOGN);
+                if (KP == 4 || J.K <= 4)
+                    conv_cols_narrow<A, B, 4, true, true>(lds, src, J.K, J.pcs + J.L, J.frag, J.off, J.tw_all, J.pcs, un,
+                                                          dst, tile);
+                else
+                    conv_cols_narrow<A, B, 8, true, true>(lds, src, J.K, J.pcs + J.L, J.frag, J.off, J.tw_all, J.pcs, un,
+                                                          dst, tile);
+            }
+            return;
+        }
+    }
+    const BatchUnit w = batch_unit<LOGN>(J, local);
+    const PrimeConst pc = J.pcs[w.g];
+    const size_t t = (size_t)w.g << LOGN;
+    uint64_t *out = J.b.out + (size_t)w.poly * J.b.out_poly_stride + ((size_t)w.li << LOGN);
+    if constexpr (PASS == kPassTensor) {
+        // d2 = a1 b1 of limb li
+        const size_t poly1 = ((size_t)J.nl + w.li) << LOGN;
         const TensorPro pro{J.ct_a + poly1, J.ct_b + poly1, pc.q, pc.r64, pc.r64_p, pc.one_p};
-        ntt_rows_unit_pe<A, B, false>(lds, pro, tw, pc, fp, tile, RawEpi{out});
-    } else if constexpr (PRO == 2 || PRO == 3) {
-        // first pass of NTT(conv): ModDown conversion of target li of polynomial
-        // poly (2: 4 special primes; 3: any K <= 8).  One variant per kernel: both
-        // behind a runtime switch cost the register allocation of the larger.
-        moddown_cols_pass<A, B, PRO == 2 ? 4 : 8>(lds, J, poly, li, out, tw, pc, tile);
-    } else if constexpr (TAIL) {
+        batch_rows<A, B, false>(lds, J, w, pc, pro, BlkRawEpi{out});
+    } else if constexpr (PASS == kPassInvRows) {
+        batch_rows<A, B, false>(lds, J, w, pc, LoadPro{out}, BlkRawEpi{out});
+    } else if constexpr (PASS == kPassFwdRows) {
+        batch_rows<A, B, true>(lds, J, w, pc, BlkRawPro{out}, StoreEpi{out});
+    } else if constexpr (PASS == kPassTail) {
         // limb li of polynomial poly of conv [2][nl][N]: ModDown tail into out
-        const size_t lo = ((size_t)poly * (J.nl + J.K) + li) << LOGN;
-        const size_t oo = ((size_t)poly * J.nl + li) << LOGN;
-        const ModdownFoldEpi epi{J.ip + lo, J.out + oo, J.pinv[2 * li], J.pinv[2 * li + 1], pc.q};
-        ntt_rows_unit_epi<A, B>(lds, in, tw, pc, fp, tile, epi);
-    } else if constexpr (COLS) {
-        ntt_cols_unit<A, B, FWD>(lds, in, out, tw, pc, fp, tile);
+        const size_t lo = ((size_t)w.poly * (J.nl + J.K) + w.li) << LOGN;
+        const size_t oo = ((size_t)w.poly * J.nl + w.li) << LOGN;
+        batch_rows<A, B, true>(lds, J, w, pc, BlkRawPro{out},
+                               ModdownFoldEpi{J.ip + lo, J.out + oo, J.pinv[2 * w.li], J.pinv[2 * w.li + 1], pc.q});
+    } else if constexpr (PASS == kPassInvCols) {
+        if (w.kind == 2) ntt_cols_unit_t<ArFp, A, B, false, true>(lds, out, J.tw_all + t, ArFp(pc), w.tile, RawPro{out});
+        else if (w.kind == 1)
+            ntt_cols_small_t<ArInt, A, B, false, kMixTile, kMixE, true>(lds, RawPro{out}, out, J.tw_all + t, ArInt(pc),
+                                                                        xcd_grouped_tile<kMixTile, A>(w.tile, 1 << (LOGN - 10)));
+        else ntt_cols_unit_t<ArInt, A, B, false, true>(lds, out, J.tw_all + t, ArInt(pc), w.tile, RawPro{out});
+    } else if constexpr (PASS == kPassModup) {
+        // wide primes alone, several a digit: converted by a launch of their own
+        ntt_cols_unit_t<ArInt, A, B, true, true>(lds, out, J.tw_all + t, ArInt(pc), w.tile, LoadPro{out});
     } else {
-        ntt_rows_unit<A, B, FWD>(lds, in, out, tw, pc, fp, tile);
+        constexpr int KP = PASS == kPassModdown4 ? 4 : 8;
+        ntt_cols_unit_t<ArInt, A, B, true, true>(
+            lds, out, J.tw_all + t, ArInt(pc), w.tile,
+            moddown_pro<KP, LOGN>(J.ip, J.pcs, pc, J.md_cross, J.md_negp, w.poly, w.li, J.nl, J.L, J.K));
     }
 }
 
 // One pass of a batched (I)NTT over the items of one ring degree 2^(A+B) (the
 // plan launches each NTT step once per ring degree present: one transform
-// shape per kernel keeps the unrolled rounds free of register spills).
-// FIRST = the pass that reads b.in (forward: columns; inverse: rows); the
-// second pass works in place on b.out.  TAIL (the forward row pass of
-// NTT(conv)) writes the ModDown result instead.  PRO: the first pass computes
-// its input: 1 = d2 from a, b (INTT of d2), 2 / 3 = the ModDown conversion
-// (NTT of conv) from 4 / up to 8 special primes.  Units [unit0, unit0 + total) of the step; jobs = the items of the
-// ring degree, whose unit_begin values are absolute.  LOOP: workgroups walk
-// per_wg consecutive units; otherwise each takes one unit (per_wg == 1).
-template <int A, int B, bool FWD, bool FIRST, bool TAIL, int PRO, bool LOOP>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(PRO == 3 ? 3 : ntt_waves(FWD == FIRST ? A : B)))) void ntt_batched_kernel(
+// shape per kernel keeps the unrolled rounds free of register spills).  Units
+// [unit0, unit0 + total) of the step; jobs = the items of the ring degree, whose
+// unit_begin values are absolute.  LOOP: workgroups walk per_wg consecutive
+// units; otherwise each takes one unit (per_wg == 1).
+template <int A, int B, BatchPass PASS, bool LOOP>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(PASS == kPassModdown8 ? 3 : ntt_waves(pass_cols(PASS) ? A : B)))) void ntt_batched_kernel(
     const NttJob *__restrict__ jobs, uint32_t njobs, uint32_t unit0, uint32_t total, uint32_t per_wg) {
-    constexpr bool COLS = FWD == FIRST;
-    __shared__ uint64_t lds[COLS ? (1 << A) * (kTile / (1 << A) + 1) : (1 << B) * (kTile / (1 << B) + 1)];
-    static_assert(!TAIL || (FWD && !FIRST), "the tail follows the forward row pass");
-    static_assert(PRO == 0 || FIRST, "prologues belong to the first pass");
+    constexpr bool COLS = pass_cols(PASS);
+    constexpr int kTileWords = COLS ? (1 << A) * (kTile / (1 << A) + 1) : (1 << B) * (kTile / (1 << B) + 1);
+    constexpr int kConvWords = COLS ? conv_lds<A, FpMask>() : 0;
+    __shared__ uint64_t lds[kTileWords > kConvWords ? kTileWords : kConvWords];
+    constexpr int pass = pass_second(PASS);
     if constexpr (!LOOP) {
         if (blockIdx.x >= total) return;
         const uint32_t u = unit0 + blockIdx.x;
-        ntt_batched_unit<A, B, FWD, FIRST, TAIL, PRO>(lds, global_job(jobs[find_job(jobs, njobs, u, 0)]), u);
+        ntt_batched_unit<A, B, PASS>(lds, global_job(jobs[find_job(jobs, njobs, u, pass)]), u);
     } else {
         const uint32_t u0 = unit0 + blockIdx.x * per_wg;
         const uint32_t u1 = unit0 + min(total, (blockIdx.x + 1) * per_wg);
         if (u0 >= u1) return;
-        uint32_t j = find_job(jobs, njobs, u0, 0);
+        uint32_t j = find_job(jobs, njobs, u0, pass);
         for (uint32_t u = u0; u < u1; ++u) {
-            while (j + 1 < njobs && jobs[j + 1].unit_begin <= u) ++j;
-            ntt_batched_unit<A, B, FWD, FIRST, TAIL, PRO>(lds, global_job(jobs[j]), u);
+            while (j + 1 < njobs && jobs[j + 1].unit_begin[pass] <= u) ++j;
+            ntt_batched_unit<A, B, PASS>(lds, global_job(jobs[j]), u);
         }
     }
 }
@@ -339,18 +436,39 @@ int validate(const rf_batch_item *items, uint32_t n) {
     return RF_OK;
 }
 
-uint32_t stage_units(const rf_ctx *c, uint32_t nl, int stage, uint32_t chunk) {
-    const uint32_t chunks = c->n / kEw, tiles = c->n / kTile;
+// A step's wide limbs go in 1024-residue tiles, launched before the narrow ones',
+// where the step is short, up to four rounds of the chip (4 workgroups on each
+// of 256 CUs), or they are less than an eighth of it: a 4096-residue workgroup
+// of a wide limb runs three times a narrow one's time and would end last.  In
+// longer steps with more of them the larger tile is the cheaper one (the P-limbs
+// of 64 items: 117 us against 151; their extension's rows 332 against 383).
+// Whole batches by this rule, all in 4096 and all in 1024: 4 items of N <= 2^15
+// 139, 179, 140 us; 8 of N <= 2^16 413, 509, 414; 16 748, 779, 757; 64 2607, 2633, 2697.
+constexpr uint64_t kBatchSmallBelow = 4096;
+
+// Units of a pass over np polynomials of `limbs` limbs, n_wide of them wide, those
+// in tiles of 1024 residues if small (batch_unit), else all in 4096.
+uint32_t limb_units(const rf_ctx *c, uint32_t limbs, uint32_t n_wide, uint32_t np, bool small) {
+    return np * (n_wide * (c->n / (small ? kMixTile : kTile)) + (limbs - n_wide) * (c->n / kTile));
+}
+
+uint32_t stage_units(const rf_ctx *c, uint32_t nl, int stage, uint32_t chunk, bool small) {
+    const uint32_t chunks = c->n / kEw;
     const uint32_t dn = (nl + c->alpha - 1) / c->alpha;
+    const bool fused = modup_fused(c, true);
+    const uint32_t ext = c->modup_levels[nl].ext_limbs;
     switch (stage) {
         case kTensor: return 0;  // formed by the INTT of d2 and the inner product
-        case kInttD0: case kInttD1: return nl * tiles;
-        case kModupConv: return dn * modup_chunks(nl, c->K, chunk) * chunks;
-        case kNttExt0: case kNttExt1: return c->modup_levels[nl].ext_limbs * tiles;
+        case kInttD0: case kInttD1: return limb_units(c, nl, c->q_order[nl].n_wide, 1, small);
+        case kModupConv: return fused ? 0 : dn * modup_chunks(nl, c->K, chunk) * chunks;
+        case kNttExt0: return fused ? c->modup_units[nl].n * (c->n / kMixTile) : ext * (c->n / kTile);
+        case kNttExt1: return limb_units(c, ext, c->ext_order[nl].n_wide, 1, small);
         case kInnerProduct: return (nl + c->K) * chunks;
-        case kInttP0: case kInttP1: return 2 * c->K * tiles;
+        case kInttP0: case kInttP1: return limb_units(c, c->K, c->p_order.n_wide, 2, small);
         case kModdownConv: return 0;  // computed in the first pass of NTT(conv)
-        case kNttConv0: case kNttConv1: return 2 * nl * tiles;
+        case kNttConv0:
+            return c->fp_mask.any() ? 2 * c->moddown_units[nl].n * (c->n / kMixTile) : 2 * nl * (c->n / kTile);
+        case kNttConv1: return limb_units(c, nl, c->q_order[nl].n_wide, 2, small);
         case kTail: return 0;  // applied by the last pass of NTT(conv)
     }
     return 0;
@@ -402,29 +520,26 @@ int enqueue(rf_batch *p, hipStream_t s, bool profile) {
                             : st == kInttP0 || st == kInttP1 ? 2 : 3;
                 const NttJob *jobs = p->d_ntt[k] + G.job0;
                 const uint32_t nj = G.job1 - G.job0, u0 = G.unit0[st];
-#define RF_BLK(A, B, FWD, FIRST, TAIL, PRO)                                                                      \
+#define RF_BLK(A, B, PASS)                                                                                       \
     if (per == 1)                                                                                                \
-        hipLaunchKernelGGL((ntt_batched_kernel<A, B, FWD, FIRST, TAIL, PRO, false>), blocks, kThreads, 0, s, jobs, \
-                           nj, u0, units, per);                                                                  \
+        hipLaunchKernelGGL((ntt_batched_kernel<A, B, PASS, false>), blocks, kThreads, 0, s, jobs, nj, u0, units, per); \
     else                                                                                                         \
-        hipLaunchKernelGGL((ntt_batched_kernel<A, B, FWD, FIRST, TAIL, PRO, true>), blocks, kThreads, 0, s, jobs, \
-                           nj, u0, units, per)
+        hipLaunchKernelGGL((ntt_batched_kernel<A, B, PASS, true>), blocks, kThreads, 0, s, jobs, nj, u0, units, per)
 #define RF_BL(A, B)                                                                                              \
     switch (st) {                                                                                                \
-        case kInttD0: RF_BLK(A, B, false, true, false, 1); break;                                                \
-        case kInttD1: RF_BLK(A, B, false, false, false, 0); break;                                               \
-        case kNttExt0: RF_BLK(A, B, true, true, false, 0); break;                                                \
-        case kNttExt1: RF_BLK(A, B, true, false, false, 0); break;                                               \
-        case kInttP0: RF_BLK(A, B, false, true, false, 0); break;                                                \
-        case kInttP1: RF_BLK(A, B, false, false, false, 0); break;                                               \
+        case kInttD0: RF_BLK(A, B, kPassTensor); break;                                                          \
+        case kInttP0: RF_BLK(A, B, kPassInvRows); break;                                                         \
+        case kInttD1: case kInttP1: RF_BLK(A, B, kPassInvCols); break;                                           \
+        case kNttExt0: RF_BLK(A, B, kPassModup); break;                                                          \
+        case kNttExt1: RF_BLK(A, B, kPassFwdRows); break;                                                        \
         case kNttConv0:                                                                                          \
             if (G.k4) {                                                                                          \
-                RF_BLK(A, B, true, true, false, 2);                                                              \
+                RF_BLK(A, B, kPassModdown4);                                                                     \
             } else {                                                                                             \
-                RF_BLK(A, B, true, true, false, 3);                                                              \
+                RF_BLK(A, B, kPassModdown8);                                                                     \
             }                                                                                                    \
             break;                                                                                               \
-        case kNttConv1: RF_BLK(A, B, true, false, true, 0); break;                                               \
+        case kNttConv1: RF_BLK(A, B, kPassTail); break;                                                          \
     }
                 switch (G.log_n) {
                     case 16: RF_BL(8, 8) break;
@@ -463,6 +578,17 @@ void build_tables(rf_batch *p, std::vector<KsJob> &jobs, std::vector<NttJob> (&n
     for (uint32_t i = 0; i < n; ++i) order[i] = i;
     std::stable_sort(order.begin(), order.end(),
                      [&](uint32_t x, uint32_t y) { return items[x].ctx->log_n < items[y].ctx->log_n; });
+    bool small[kStages];
+    for (int st = 0; st < kStages; ++st) {
+        uint64_t tiles = 0, more = 0;  // in 4096-residue tiles; what small ones would add, 3 for each wide tile
+        for (uint32_t i = 0; i < n; ++i) {
+            const rf_ctx *c = items[i].ctx;
+            const uint32_t t = stage_units(c, items[i].n_limbs, st, p->modup_chunk, false);
+            tiles += t;
+            more += stage_units(c, items[i].n_limbs, st, p->modup_chunk, true) - t;
+        }
+        small[st] = tiles < kBatchSmallBelow || more * 8 < tiles * 3;
+    }
     std::vector<rf_batch::Group> groups;
     for (uint32_t i = 0; i < n; ++i) {
         const rf_batch_item &it = items[order[i]];
@@ -506,13 +632,14 @@ void build_tables(rf_batch *p, std::vector<KsJob> &jobs, std::vector<NttJob> (&n
         J.alpha = c->alpha;
         for (int st = 0; st < kStages; ++st) {
             J.unit_begin[st] = acc[st];
-            acc[st] += stage_units(c, nl, st, p->modup_chunk);
+            acc[st] += stage_units(c, nl, st, p->modup_chunk, small[st] && c->fp_mask.any());
         }
         const uint64_t ipstride = (uint64_t)(nl + c->K) * N;
-        NttBatch bd{J.d2, J.d_coeff, 0, 0, nl, 1, 0, nullptr, {}};
-        NttBatch be{J.ext, J.ext, 0, 0, lv.ext_limbs, 1, 0, c->d_pmaps + lv.pmap_off, {}};
-        NttBatch bp{J.ip + (size_t)nl * N, J.ip + (size_t)nl * N, ipstride, ipstride, c->K, 2, c->L, nullptr, {}};
-        NttBatch bc{J.conv, J.conv, (uint64_t)nl * N, (uint64_t)nl * N, nl, 2, 0, nullptr, {}};
+        NttBatch bd{J.d_coeff, J.d_coeff, 0, 0, nl, 1, 0, nullptr, c->order(c->q_order[nl])};
+        NttBatch be{J.ext, J.ext, 0, 0, lv.ext_limbs, 1, 0, nullptr, c->order(c->ext_order[nl])};
+        NttBatch bp{J.ip + (size_t)nl * N, J.ip + (size_t)nl * N, ipstride, ipstride, c->K, 2, c->L, nullptr,
+                    c->order(c->p_order)};
+        NttBatch bc{J.conv, J.conv, (uint64_t)nl * N, (uint64_t)nl * N, nl, 2, 0, nullptr, c->order(c->q_order[nl])};
         const NttBatch bs[4] = {bd, be, bp, bc};
         const int first_stage[4] = {kInttD0, kNttExt0, kInttP0, kNttConv0};
         for (int k = 0; k < 4; ++k) {
@@ -523,7 +650,21 @@ void build_tables(rf_batch *p, std::vector<KsJob> &jobs, std::vector<NttJob> (&n
             // ModDown input factor into its last stage
             ntt[k][i].pcs = k == 0 ? pc_modup(c, nl) : k == 2 ? c->d_pc_md : c->d_pc;
             ntt[k][i].log_n = c->log_n;
-            ntt[k][i].unit_begin = J.unit_begin[first_stage[k]];
+            for (int pass = 0; pass < 2; ++pass) ntt[k][i].unit_begin[pass] = J.unit_begin[first_stage[k] + pass];
+            ntt[k][i].small = small[first_stage[k] + 1] && c->fp_mask.any();
+            if (k == 1 && modup_fused(c, true)) {
+                ntt[k][i].units = c->d_units + c->modup_units[nl].off;
+                ntt[k][i].frag = c->d_conv_mu;
+                ntt[k][i].off = c->d_conv_mu_off;
+            } else if (k == 3 && c->fp_mask.any()) {
+                ntt[k][i].units = c->d_units + c->moddown_units[nl].off;
+                ntt[k][i].frag = c->d_conv_md;
+                ntt[k][i].off = c->d_conv_md_off;
+            }
+            ntt[k][i].x = J.d_coeff;
+            ntt[k][i].modup_tab = J.modup_tab;
+            ntt[k][i].modup_stride = J.modup_stride;
+            ntt[k][i].alpha = c->alpha;
             ntt[k][i].ct_a = it.a;
             ntt[k][i].ct_b = it.b;
             ntt[k][i].ip = J.ip;

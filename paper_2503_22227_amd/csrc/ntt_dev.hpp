@@ -706,12 +706,6 @@ __device__ __forceinline__ void ntt_cols_mixed(uint64_t *lds, uint64_t *out, con
     else ntt_cols_small_t<ArInt, A, B, FWD, kMixTile, kMixE, BLK>(lds, pro, out, tw, ArInt(pc), tile);
 }
 
-template <int A, int B, bool FWD>
-__device__ __forceinline__ void ntt_cols_unit(uint64_t *lds, const uint64_t *in, uint64_t *out,
-                                              const TwPair *__restrict__ tw, const PrimeConst &pc, bool fp, int tile) {
-    ntt_cols_unit_pro<A, B, FWD>(lds, out, tw, pc, fp, tile, PlainPro<FWD>{in});
-}
-
 // Rescale / modulus-switch lift as the prologue of the NTT of the lifted limb:
 // the last limb x (coefficient domain, in [0, q_l)) taken from its centred
 // representative into prime q: [x]_q, + (q - [q_l]_q) when x > q_l / 2, lazy in
@@ -882,12 +876,6 @@ template <int A, int B, typename Epi>
 __device__ __forceinline__ void ntt_rows_unit_epi(uint64_t *lds, const uint64_t *in, const TwPair *__restrict__ tw,
                                                   const PrimeConst &pc, bool fp, int tile, const Epi &epi) {
     ntt_rows_unit_pe<A, B, true>(lds, RawPro{in}, tw, pc, fp, tile, epi);
-}
-
-template <int A, int B, bool FWD>
-__device__ __forceinline__ void ntt_rows_unit(uint64_t *lds, const uint64_t *in, uint64_t *out,
-                                              const TwPair *__restrict__ tw, const PrimeConst &pc, bool fp, int tile) {
-    ntt_rows_unit_pe<A, B, FWD>(lds, PlainPro<!FWD>{in}, tw, pc, fp, tile, RowStore<FWD>{out});
 }
 
 // HMult: d2 = a1 b1 mod q as the prologue of the INTT of d2 (the inner product

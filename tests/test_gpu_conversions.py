@@ -108,3 +108,42 @@ def test_bfv(bits, k, alpha):
     assert np.array_equal(host(ctx.hmult_relin(dev(a), dev(b), dev(key))), F.hmult_relin(a, b, key, p))
     g = C.galois_element(3, p.n)
     assert np.array_equal(host(ctx.rotate(dev(a), g, dev(key))), F.rotate(a, g, key, p))
+
+
+# bases of every kind in one plan: fused from up to 4 and 8 sources, converted by
+# its own launch (wide primes, two a digit), 2 to 5 special primes
+def test_batch_of_every_kind():
+    from paper_2503_22227_amd import BatchPlan
+    items = []
+    for i, (log_n, q_bits, p_bits, alpha, nl) in enumerate([
+            (13, [W] + [M] * 4, [W] * 4, 4, 5), (13, [W] * 6, [W] * 2, 2, 5), (13, [W] + [M] * 9, [W] * 5, 5, 8),
+            (14, [M] * 12, [M] * 8, 8, 12), (13, [W] * 5, [W], 1, 4)]):
+        p = params(q_bits, p_bits, alpha, log_n)
+        a, b, key = draws(p, 40 + i)
+        items.append((context(p), dev(a[:, :nl]), dev(b[:, :nl]), dev(key)))
+    outs = [torch.empty_like(a) for _, a, _, _ in items]
+    plan = BatchPlan([(c, a, b, k, o) for (c, a, b, k), o in zip(items, outs)])
+    want = [host(c.hmult_relin(a, b, k)) for c, a, b, k in items]
+    for grid in (0, 7):
+        for stage in range(13):
+            plan.set_grid(stage, grid)
+        for o in outs:
+            o.zero_()
+        print("batch of every kind, grid %d" % grid, flush=True)
+        plan.run(graph=False)
+        assert all(np.array_equal(host(o), w) for o, w in zip(outs, want))
+
+
+# steps above and below the size from which wide limbs keep the large tile
+@pytest.mark.parametrize("count", [1, 40])
+def test_batch_tiles(count):
+    from paper_2503_22227_amd import BatchPlan
+    p = params([W] + [M] * 2, [W] * 4, 2, 16)
+    ctx = context(p)
+    a, b, key = (dev(x) for x in draws(p, 9))
+    outs = [torch.zeros_like(a) for _ in range(count)]
+    plan = BatchPlan([(ctx, a, b, key, o) if i % 2 else (ctx, a, a, key, o) for i, o in enumerate(outs)])
+    print("batch of %d items" % count, flush=True)
+    plan.run(graph=False)
+    want = [host(ctx.hmult_relin(a, a, key)), host(ctx.hmult_relin(a, b, key))]
+    assert all(np.array_equal(host(o), want[i % 2]) for i, o in enumerate(outs))
