@@ -120,14 +120,14 @@ int keyswitch_core(const rf_ctx *c, const uint64_t *d, const uint64_t *evk, uint
         if ((rc = launch_modup_bconv(c, x, ext, nl, s, !d_coeff_in, tn.modup_chunk))) return rc;
         if ((rc = launch_ntt(c, eb, true, s, nullptr, &tn))) return rc;
     }
-    // ModDown: the inner product applies P^-1 and the addends to its Q-limbs; the
-    // INTT of the P-limbs folds in the conversion's input factor; the conversion
-    // runs in the first pass of the NTT and the tail in its last pass
+    // ModDown: the inner product applies P^-1 and the addends to its Q-limbs and
+    // starts the INTT of the P-limbs, which folds in the conversion's input factor;
+    // the conversion runs in the first pass of the NTT and the tail in its last pass
     const uint64_t ip_stride = (uint64_t)(nl + c->K) * N;
     const NttBatch pl = batch(ip + (size_t)nl * N, ip + (size_t)nl * N, ip_stride, ip_stride, c->K, 2, c->L, nullptr,
                               c->order(c->p_order), true);
-    if ((rc = launch_inner_product(c, d, ext, evk, ip, nl, s, &f))) return rc;
-    if ((rc = launch_ntt(c, pl, false, s, c->d_pc_md, &tn))) return rc;
+    if ((rc = launch_inner_product(c, d, ext, evk, ip, nl, s, f))) return rc;
+    if ((rc = launch_intt_cols(c, pl, s, c->d_pc_md, &tn))) return rc;
     return launch_ntt_fwd_moddown(c, conv, ip, out, nl, s, &tn);
 }
 

@@ -631,7 +631,7 @@ extern "C" int rf_decrypt(const rf_ctx *c, const uint64_t *ct, const uint64_t *s
         // c0 + c1 s in the first pass of its INTT
         ClientArgs ca{nullptr, nullptr, ct, s_ntt, out, nullptr, nullptr, nl, false};
         if ((rc = client_pass<2>(c, ca, s, "client_decrypt_rows"))) return rc;
-        return launch_intt_cols(c, out, nl, s);
+        return launch_intt_cols(c, plain_batch(c, out, 0, nl, 1), s);
     }
     {
         ProfScope prof("client_decrypt", s);

@@ -17,6 +17,7 @@
 #include <hip/hip_runtime.h>
 
 #include "ks_dev.hpp"
+#include "ntt_dev.hpp"
 
 namespace rf {
 
@@ -57,15 +58,77 @@ __global__ __launch_bounds__(kEw) void modup_bconv_kernel(const uint64_t *__rest
     modup_bconv_unit<SCALED, CH>(x, ext, pcs, tab, tab_stride, log_n, nl, L, K, alpha, blockIdx.x, blockIdx.y);
 }
 
-template <int V>
-__global__ __launch_bounds__(kEw) void inner_product_kernel(const uint64_t *__restrict__ d,
-                                                            const uint64_t *__restrict__ ext,
-                                                            const uint64_t *__restrict__ evk,
-                                                            uint64_t *__restrict__ ip,
-                                                            const PrimeConst *__restrict__ pcs, uint32_t log_n,
-                                                            uint32_t nl, uint32_t L, uint32_t K, uint32_t alpha,
-                                                            IpFold fold) {
-    inner_product_unit<V>(d, ext, evk, ip, pcs, log_n, nl, L, K, alpha, blockIdx.x, blockIdx.y, fold);
+// Inner product of a P-limb as the prologue of its INTT: E residues a thread,
+// digit by digit.  The P-limbs lie in no digit, so every source is the extension's.
+template <int E>
+struct IpRowsPro {
+    static constexpr bool kBlocked = false;
+    const uint64_t *ext, *key;  // the limb in digit 0's extension and key
+    size_t ext_step, key_step;  // from a digit to the next
+    size_t short_step;          // what the last digit's limb lies further on (fewer of its own primes)
+    uint32_t dn;
+    uint64_t q, r64, r64_p, one_p;
+    template <typename Ar>
+    __device__ __forceinline__ void tile(typename Ar::V (&v)[E], size_t first, int step, const Ar &) const {
+        u128 acc[E];
+#pragma unroll
+        for (int r = 0; r < E; ++r) acc[r] = u128{0, 0};
+#pragma unroll 1
+        for (uint32_t j = 0; j < dn; ++j) {
+            const uint64_t *e = ext + j * ext_step + (j + 1 == dn ? short_step : 0) + first;
+            const uint64_t *k = key + j * key_step + first;
+#pragma unroll
+            for (int r = 0; r < E; ++r) mac(acc[r], e[r * step], k[r * step]);
+        }
+#pragma unroll
+        for (int r = 0; r < E; ++r) {
+            const uint64_t x = csub(reduce128_lazy(acc[r], q, r64, r64_p, one_p), 2 * q);
+            if constexpr (Ar::kFp) v[r] = FpMod::from_u52(x);
+            else v[r] = x;
+        }
+    }
+};
+template <int E>
+constexpr bool kTilePro<IpRowsPro<E>> = true;
+
+// The inner product on Q_l u P with the first pass of the INTT of its P-limbs,
+// which come first: (limb, polynomial, tile of 1024 residues) a workgroup; then
+// 256 coefficients of a Q-limb each.  Bound by the keys' and the extension's bytes.
+// At 64 registers the streaming part keeps its 8 waves on a SIMD (the P-limbs' part
+// spills 11), and that pass costs no launch of its own: with it, N = 2^16, 24 + 4
+// limbs, alpha = 8: 40.0 us against 35.2 + 6.4; 9 + 4 limbs, alpha = 4: 19.0 against
+// 15.9 + 6.2; N = 2^13, 5 + 4 limbs 5.3 against 3.9 + 4.2.
+template <int A, int B, typename Fp>
+__global__ __launch_bounds__(kEw) __attribute__((amdgpu_waves_per_eu(8))) void inner_product_kernel(
+    const uint64_t *__restrict__ d, const uint64_t *__restrict__ ext, const uint64_t *__restrict__ evk,
+    uint64_t *__restrict__ ip, const PrimeConst *__restrict__ pcs, const TwPair *__restrict__ tw_inv, Fp fpm, uint32_t nl,
+    uint32_t L, uint32_t K, uint32_t alpha, IpFold fold) {
+    __shared__ uint64_t lds[(1 << B) * ((kMixTile >> B) + 1)];
+    constexpr int LOGN = A + B, TL = LOGN - 10;
+    const uint32_t np = 2 * K << TL;
+    if (blockIdx.x >= np) {
+        const uint32_t w = blockIdx.x - np;
+        inner_product_unit<1>(d, ext, evk, ip, pcs, LOGN, nl, L, K, alpha, w & ((1u << (LOGN - 8)) - 1), w >> (LOGN - 8),
+                              fold);
+        return;
+    }
+    const uint32_t u = blockIdx.x >> TL, poly = u & 1, m = nl + (u >> 1), g = L + (u >> 1);
+    const PrimeConst pc = pcs[g];
+    const uint32_t dn = (nl + alpha - 1) / alpha, full = min(alpha, nl);
+    IpRowsPro<kMixE> pro;
+    pro.ext = ext + ((size_t)(m - full) << LOGN);
+    pro.key = evk + (((size_t)poly * (L + K) + g) << LOGN);
+    pro.ext_step = (size_t)(nl + K - alpha) << LOGN;
+    pro.key_step = (size_t)2 * (L + K) << LOGN;
+    pro.short_step = (size_t)(full - (nl - (dn - 1) * alpha)) << LOGN;
+    pro.dn = dn;
+    pro.q = pc.q;
+    pro.r64 = pc.r64;
+    pro.r64_p = pc.r64_p;
+    pro.one_p = pc.one_p;
+    ntt_rows_small_pe<A, B, false, kMixTile, kMixE>(lds, pro, tw_inv + ((size_t)g << LOGN), pc, fpm.has(g),
+                                                    blockIdx.x & ((1u << TL) - 1),
+                                                    BlkRawEpi{ip + (((size_t)poly * (nl + K) + m) << LOGN)});
 }
 
 __global__ __launch_bounds__(kEw) void automorphism_kernel(const uint64_t *__restrict__ in, uint64_t *__restrict__ out,
@@ -146,16 +209,30 @@ int launch_modup_bconv(const rf_ctx *c, const uint64_t *x, uint64_t *ext, uint32
     return check_launch("modup_bconv");
 }
 
+template <int A, int B>
+static void launch_ip(const rf_ctx *c, const uint64_t *d, const uint64_t *ext, const uint64_t *evk, uint64_t *ip,
+                      uint32_t nl, hipStream_t s, const IpFold &f) {
+    const dim3 grid(2 * c->K * (c->n / kMixTile) + nl * (c->n / kEw));
+    if (c->fp_mask.any())
+        hipLaunchKernelGGL((inner_product_kernel<A, B, FpMask>), grid, dim3(kEw), 0, s, d, ext, evk, ip, c->d_pc,
+                           c->d_tw_inv, c->fp_mask, nl, c->L, c->K, c->alpha, f);
+    else
+        hipLaunchKernelGGL((inner_product_kernel<A, B, NoFp>), grid, dim3(kEw), 0, s, d, ext, evk, ip, c->d_pc,
+                           c->d_tw_inv, NoFp{}, nl, c->L, c->K, c->alpha, f);
+}
+
 int launch_inner_product(const rf_ctx *c, const uint64_t *d, const uint64_t *ext, const uint64_t *evk, uint64_t *ip,
-                         uint32_t nl, hipStream_t s, const IpFold *fold) {
+                         uint32_t nl, hipStream_t s, const IpFold &fold) {
     ProfScope prof("inner_product", s);
-    IpFold f;
-    if (fold) {
-        f = *fold;
-        f.pinv = c->d_moddown + moddown_pinv_off(c);
+    IpFold f = fold;
+    f.pinv = c->d_moddown + moddown_pinv_off(c);
+    switch (c->log_n) {
+        case 13: launch_ip<7, 6>(c, d, ext, evk, ip, nl, s, f); break;
+        case 14: launch_ip<7, 7>(c, d, ext, evk, ip, nl, s, f); break;
+        case 15: launch_ip<8, 7>(c, d, ext, evk, ip, nl, s, f); break;
+        case 16: launch_ip<8, 8>(c, d, ext, evk, ip, nl, s, f); break;
+        default: return fail(RF_EUNSUPPORTED, "inner product: ring degree");
     }
-    hipLaunchKernelGGL(inner_product_kernel<kIpVec>, dim3(c->n / (kEw * kIpVec), nl + c->K), dim3(kEw), 0, s, d, ext,
-                       evk, ip, c->d_pc, c->log_n, nl, c->L, c->K, c->alpha, f);
     return check_launch("inner_product");
 }
 

@@ -731,19 +731,40 @@ int launch_ntt(const rf_ctx *c, const NttBatch &b, bool forward, hipStream_t s, 
                             : launch_ntt_t(c, NoFp{}, b, forward, s, pcs, tn);
 }
 
+template <int A, int B, bool BLK, typename Fp>
+static void launch_inv_cols(const rf_ctx *c, Fp fpm, const NttBatch &b, hipStream_t s, const PrimeConst *pcs,
+                            const rf_tuning &tn) {
+    const uint32_t limbs = b.per_poly * b.n_polys;
+    const uint32_t tiles = limbs << (A + B - 12);
+    if (tiles < tn.ntt_small_below) {
+        const bool big = tn.ntt_small_tile == 2048 || (tn.ntt_small_tile == 0 && tiles * 2 >= tn.ntt_small_below);
+        ProfScope p("ntt_inv_cols_small", s);
+#define RF_IC(T, E)                                                                                              \
+    hipLaunchKernelGGL((ntt_small_kernel<A, B, false, true, T, E, BLK>), dim3((1u << (A + B)) / T, limbs), dim3(T / E), \
+                       0, s, b, fpm, c->d_tw_inv, pcs)
+        if (tn.ntt_small_radix == 8) {
+            if (big) RF_IC(2048, 8);
+            else RF_IC(1024, 8);
+        } else {
+            if (big) RF_IC(2048, kSmallE);
+            else RF_IC(1024, kSmallE);
+        }
+#undef RF_IC
+        return;
+    }
+    const MixGrid m{b.order.ent, b.order.n_wide, b.n_polys, 0};
+    ProfScope p("ntt_inv_cols", s);
+    hipLaunchKernelGGL((ntt_cols_kernel<A, B, false, BLK>), mix_grid(c, m.n_wide, b.per_poly, b.n_polys),
+                       dim3(kThreads), 0, s, b, fpm, m, c->d_tw_inv, pcs);
+}
+
 template <typename Fp>
-static int launch_intt_cols_t(const rf_ctx *c, Fp fpm, uint64_t *data, uint32_t nl, hipStream_t s) {
-    const NttBatch b{data, data, 0, 0, nl, 1, 0, nullptr, {}};
-    const MixGrid mg = q_mix(c, nl, 1);
-    const bool small = nl * (c->n / kTile) < kDefaultTuning.ntt_small_below;
-    ProfScope p(small ? "ntt_inv_cols_small" : "ntt_inv_cols", s);
+static int launch_intt_cols_t(const rf_ctx *c, Fp fpm, const NttBatch &b, hipStream_t s, const PrimeConst *pcs,
+                              const rf_tuning &tn) {
+    if (b.per_poly * b.n_polys > 65535) return fail(RF_EUNSUPPORTED, "too many limbs in one NTT launch");
 #define RF_IC(A, B)                                                                                              \
-    if (small)                                                                                                   \
-        hipLaunchKernelGGL((ntt_small_kernel<A, B, false, true, 1024, kSmallE, false, Fp>), dim3(c->n / 1024, nl),      \
-                           dim3(1024 / kSmallE), 0, s, b, fpm, c->d_tw_inv, c->d_pc);                            \
-    else                                                                                                         \
-        hipLaunchKernelGGL((ntt_cols_kernel<A, B, false, false, Fp>), mix_grid(c, mg.n_wide, nl, 1), dim3(kThreads),    \
-                           0, s, b, fpm, mg, c->d_tw_inv, c->d_pc)
+    if (b.blocked) launch_inv_cols<A, B, true>(c, fpm, b, s, pcs, tn);                                           \
+    else launch_inv_cols<A, B, false>(c, fpm, b, s, pcs, tn)
     switch (c->log_n) {
         case 13: RF_IC(7, 6); break;
         case 14: RF_IC(7, 7); break;
@@ -757,8 +778,11 @@ static int launch_intt_cols_t(const rf_ctx *c, Fp fpm, uint64_t *data, uint32_t 
     return RF_OK;
 }
 
-int launch_intt_cols(const rf_ctx *c, uint64_t *data, uint32_t nl, hipStream_t s) {
-    return c->fp_mask.any() ? launch_intt_cols_t(c, c->fp_mask, data, nl, s) : launch_intt_cols_t(c, NoFp{}, data, nl, s);
+int launch_intt_cols(const rf_ctx *c, const NttBatch &b, hipStream_t s, const PrimeConst *pcs, const rf_tuning *tn) {
+    const rf_tuning &t = tn ? *tn : kDefaultTuning;
+    if (!pcs) pcs = c->d_pc;
+    return c->fp_mask.any() ? launch_intt_cols_t(c, c->fp_mask, b, s, pcs, t)
+                            : launch_intt_cols_t(c, NoFp{}, b, s, pcs, t);
 }
 
 }  // namespace rf

@@ -504,6 +504,11 @@ __device__ __forceinline__ void ntt_cols_small(uint64_t *lds, const uint64_t *in
     ntt_cols_small_pro<A, B, FWD, TILE, E, BLK>(lds, PlainPro<FWD>{in}, out, tw, pc, fp, tile);
 }
 
+// A prologue that computes a thread's residues together (a loop over something
+// else outside) takes them all: pro.tile(v, first index, step, ar).
+template <typename Pro>
+constexpr bool kTilePro = false;
+
 // The result for limb index idx goes through epi (integer: in [0, q) forward,
 // lazy in [0, 2q) inverse), or, when Epi::kPrefetch, through
 // epi.finish(idx, value, epi.operand(idx)) with the operand loaded at the start.
@@ -516,10 +521,14 @@ __device__ __forceinline__ void ntt_rows_small_t(uint64_t *lds, const Pro &pro, 
     const int row0 = tile * U;
     const auto *tw = twiddles<Ar>(tw_all);
     V vin[E];
+    if constexpr (kTilePro<Pro>) {
+        pro.tile(vin, ((size_t)row0 << B) + threadIdx.x, NT, ar);
+    } else {
 #pragma unroll
-    for (int r = 0; r < E; ++r) {
-        const int idx = threadIdx.x + r * NT;
-        vin[r] = pass_in(pro, ((size_t)row0 << B) + idx, ar);
+        for (int r = 0; r < E; ++r) {
+            const int idx = threadIdx.x + r * NT;
+            vin[r] = pass_in(pro, ((size_t)row0 << B) + idx, ar);
+        }
     }
     // an epilogue that reads an operand of its own (the ModDown and rescale
     // tails) has it loaded here, with the tile, instead of after the last

@@ -257,8 +257,9 @@ int fail(int code, const std::string &msg);
 // tn: the level's kernel variants (null: the defaults).
 int launch_ntt(const rf_ctx *c, const NttBatch &b, bool forward, hipStream_t s, const PrimeConst *pcs = nullptr,
                const rf_tuning *tn = nullptr);
-// Second pass alone of the INTT of data [nl][N] over q_0.. (two-pass ring degrees, default variants).
-int launch_intt_cols(const rf_ctx *c, uint64_t *data, uint32_t nl, hipStream_t s);
+// Second pass alone of the INTT of b's limbs, in place (two-pass ring degrees).
+int launch_intt_cols(const rf_ctx *c, const NttBatch &b, hipStream_t s, const PrimeConst *pcs = nullptr,
+                     const rf_tuning *tn = nullptr);
 // Last pass alone of the forward NTT of b's limbs after launch_modup_cols.
 int launch_ntt_fwd_rows(const rf_ctx *c, const NttBatch &b, hipStream_t s, const rf_tuning *tn);
 // ModUp conversion and the first pass of the extension's NTT in one launch
@@ -298,11 +299,11 @@ int launch_tensor(const rf_ctx *c, const uint64_t *a, const uint64_t *b, uint64_
 // chunk: output limbs per thread (4, 8 or 16).
 int launch_modup_bconv(const rf_ctx *c, const uint64_t *x, uint64_t *ext, uint32_t nl, hipStream_t s,
                        bool scaled = false, uint32_t chunk = 8);
-// fold (non-null): the Q-limbs leave as ip P^-1 + add_c with the sources fold
-// names (its pinv is filled in here), for launch_ntt_fwd_moddown.
-int launch_inner_product(const rf_ctx *c, const uint64_t *d_ntt, const uint64_t *ext,
-                         const uint64_t *evk, uint64_t *ip, uint32_t nl, hipStream_t s,
-                         const IpFold *fold = nullptr);
+// The Q-limbs leave as ip P^-1 + add_c with the sources fold names (its pinv is
+// filled in here), for launch_ntt_fwd_moddown; the P-limbs after the first pass
+// of their INTT (launch_intt_cols follows; two-pass ring degrees only).
+int launch_inner_product(const rf_ctx *c, const uint64_t *d_ntt, const uint64_t *ext, const uint64_t *evk, uint64_t *ip,
+                         uint32_t nl, hipStream_t s, const IpFold &fold);
 
 // N = 2^12: a workgroup holds a whole limb, so a step that precedes or follows
 // a transform needs no launch of its own (single.hip).
