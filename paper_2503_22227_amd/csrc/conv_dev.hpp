@@ -169,6 +169,104 @@ __device__ __forceinline__ ModupColsPro<KP> modup_cols_pro(const uint64_t *src, 
     return pro;
 }
 
+// Last pass of a limb's INTT on tile `tile` (1024 residues, blocked layout) by the
+// workgroup, its results in [0, q) left in lds at row (U + 1) + column.  Ends with a barrier.
+template <typename Ar, int A, int B>
+__device__ __forceinline__ void inv_cols_lds(uint64_t *lds, const uint64_t *in, const TwPair *__restrict__ tw_all,
+                                             const Ar &ar, int tile) {
+    constexpr int U = kMixTile >> A, LDU = U + 1, E = kMixE;
+    const auto *tw = twiddles<Ar>(tw_all);
+    const TileLds l{lds, LDU, (int)(threadIdx.x % U)};
+    uint64_t vin[E];
+#pragma unroll
+    for (int r = 0; r < E; ++r) {
+        const int idx = threadIdx.x + r * kThreads;
+        vin[r] = in[blk_index<A, B>(idx / U, tile * U + idx % U)];
+    }
+    typename Ar::Tw twc[tw_slots(A, E)];
+    ntt_rounds<Ar, A, false, true, 0, E, kTwPrefetch>(l, threadIdx.x / U, 1u, tw, ar, twc);
+#pragma unroll
+    for (int r = 0; r < E; ++r) {
+        const int idx = threadIdx.x + r * kThreads;
+        lds[(idx / U) * LDU + idx % U] = vin[r];
+    }
+    __syncthreads();
+    ntt_rounds<Ar, A, false, true, 0, E, kTwCached>(l, threadIdx.x / U, 1u, tw, ar, twc);
+#pragma unroll
+    for (int r = 0; r < E; ++r) {
+        const int idx = threadIdx.x + r * kThreads;
+        uint64_t &x = lds[(idx / U) * LDU + idx % U];
+        x = ar.canon_last(Ar::raw(x));
+    }
+    __syncthreads();
+}
+
+// Column passes of up to four narrow targets of a lift, from inv_cols_lds's tile: a
+// wave each, the first round from registers.
+template <int A, int B, bool KEEP_T>
+__device__ __forceinline__ void lift_cols_narrow(uint64_t *lds, const PrimeConst *__restrict__ pcs,
+                                                 const uint64_t *__restrict__ tab, const TwPair *__restrict__ tw_all,
+                                                 const ConvUnit *__restrict__ un, uint64_t *dst, uint32_t nl, uint32_t L,
+                                                 int tile) {
+    using Tile = WaveTile<A>;
+    constexpr int LOGN = A + B, U = Tile::U, LDU = U + 1, C2 = A - kElemsLog;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int t = lane / U, u = lane % U;
+    const uint32_t i = un->e[w] & 0xffffu;
+    const PrimeConst pc = pcs[i];
+    const ArFp ar(pc);
+    const auto *tw = twiddles<ArFp>(tw_all + ((size_t)i << LOGN));
+    const LiftPro<KEEP_T> pro = lift_pro<KEEP_T, LOGN>(nullptr, pcs, pc, tab, 0, i, nl, L);
+    ArFp::Tw twc[tw_slots(A, kElems)];
+    const Tile mine{lds + w * Tile::kWords, u};
+    ntt_rounds<ArFp, A, true, false, 0, kElems, kTwPrefetch>(mine, t, 1u, tw, ar, twc);
+    double regs[kElems];
+#pragma unroll
+    for (int e = 0; e < kElems; ++e) regs[e] = pro.lift_fp(lds[(t + (e << C2)) * LDU + u]);
+    __syncthreads();  // the waves' tiles lie over what they have read
+    ntt_round<ArFp, A, 0, kElemsLog, true, false, 0, true, false, kElems, kTwCached>(mine, t, 1u, tw, ar, regs, twc);
+    __syncthreads();
+    ntt_round<ArFp, A, kElemsLog, C2, true, false, 0, false, false, kElems, kTwCached, kElems * kElemsLog>(
+        mine, t, 1u, tw, ar, nullptr, twc);
+    __syncthreads();
+    if (w < (int)un->count) {
+        uint64_t *out = dst + ((size_t)i << LOGN);
+#pragma unroll
+        for (int r = 0; r < kElems; ++r) {
+            const int idx = lane + r * 64;
+            out[blk_index<A, B>(idx / U, tile * U + idx % U)] = mine.p[Tile::at(idx / U, idx % U)];
+        }
+    }
+}
+
+// The same of one wide target, by the workgroup.
+template <int A, int B, bool KEEP_T>
+__device__ __forceinline__ void lift_cols_wide(uint64_t *lds, const PrimeConst *__restrict__ pcs,
+                                               const uint64_t *__restrict__ tab, const TwPair *__restrict__ tw_all,
+                                               uint32_t i, uint64_t *dst, uint32_t nl, uint32_t L, int tile) {
+    constexpr int LOGN = A + B, U = kMixTile >> A, LDU = U + 1, E = kMixE;
+    const PrimeConst pc = pcs[i];
+    const ArInt ar(pc);
+    const TwPair *tw = tw_all + ((size_t)i << LOGN);
+    const LiftPro<KEEP_T> pro = lift_pro<KEEP_T, LOGN>(nullptr, pcs, pc, tab, 0, i, nl, L);
+    const TileLds l{lds, LDU, (int)(threadIdx.x % U)};
+    TwPair twc[tw_slots(A, E)];
+    ntt_rounds<ArInt, A, true, false, 0, E, kTwPrefetch>(l, threadIdx.x / U, 1u, tw, ar, twc);
+#pragma unroll
+    for (int r = 0; r < E; ++r) {
+        const int idx = threadIdx.x + r * kThreads;
+        uint64_t &x = lds[(idx / U) * LDU + idx % U];
+        x = pro.lift(x);
+    }
+    __syncthreads();
+    ntt_rounds<ArInt, A, true, false, 0, E, kTwCached>(l, threadIdx.x / U, 1u, tw, ar, twc);
+#pragma unroll
+    for (int r = 0; r < E; ++r) {
+        const int idx = threadIdx.x + r * kThreads;
+        dst[((size_t)i << LOGN) + blk_index<A, B>(idx / U, tile * U + idx % U)] = lds[(idx / U) * LDU + idx % U];
+    }
+}
+
 // LDS of a workgroup: four waves' tiles, or the one tile of a wide target.
 template <int A, typename Fp>
 constexpr int conv_lds() {

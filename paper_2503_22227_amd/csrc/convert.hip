@@ -66,6 +66,31 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
     }
 }
 
+// Last pass of the INTT of the dropped limb (last [2][N] after its row pass), the
+// lift and the column pass of its targets, units as moddown's: every workgroup
+// transforms the tile of the dropped limb for itself, for up to four targets.  The
+// INTT's pass had a launch of 128 workgroups: with it N = 2^16, 46 targets 17.5 us
+// against 7.0 + 14.2, N = 2^14, 20 targets 9.4 against 4.5 + 5.0 and a launch less
+// for the host.  Bound by latency; the targets' twiddles fetched before the
+// dropped limb's pass spill (19.1).
+template <int A, int B, bool KEEP_T>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void lift_cols_kernel(
+    ConvArgs c, FpMask fpm, const uint64_t *last, uint64_t *lift, const TwPair *__restrict__ tw_inv,
+    const uint64_t *__restrict__ tab) {
+    __shared__ uint64_t lds[conv_lds<A, FpMask>()];
+    constexpr int LOGN = A + B, TL = LOGN - 10;
+    const int tile = xcd_grouped_tile<kMixTile, A>(blockIdx.x & ((1 << TL) - 1), 1 << TL);
+    const uint32_t u = blockIdx.x >> TL, poly = u & 1, l = c.nl - 1;
+    const ConvUnit *un = c.units + (u >> 1);
+    const PrimeConst pl = c.pcs[l];
+    const TwPair *tw = tw_inv + ((size_t)l << LOGN);
+    if (fpm.has(l)) inv_cols_lds<ArFp, A, B>(lds, last + ((size_t)poly << LOGN), tw, ArFp(pl), tile);
+    else inv_cols_lds<ArInt, A, B>(lds, last + ((size_t)poly << LOGN), tw, ArInt(pl), tile);
+    uint64_t *dst = lift + ((size_t)poly * l << LOGN);
+    if (un->wide) lift_cols_wide<A, B, KEEP_T>(lds, c.pcs, tab, c.tw, un->e[0] & 0xffffu, dst, c.nl, c.L, tile);
+    else lift_cols_narrow<A, B, KEEP_T>(lds, c.pcs, tab, c.tw, un, dst, c.nl, c.L, tile);
+}
+
 static int check_conv() {
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? RF_OK : fail(RF_EHIP, std::string("conversion launch: ") + hipGetErrorString(e));
@@ -145,6 +170,32 @@ int launch_moddown_cols(const rf_ctx *c, const uint64_t *ip, uint64_t *conv, uin
         case 15: moddown_cols<8, 7>(c, a, grid, ip, conv, cross, negp, s); break;
         case 16: moddown_cols<8, 8>(c, a, grid, ip, conv, cross, negp, s); break;
         default: return fail(RF_EUNSUPPORTED, "ModDown column pass: ring degree");
+    }
+    return check_conv();
+}
+
+template <int A, int B>
+static void lift_cols(const rf_ctx *c, const ConvArgs &a, dim3 grid, const uint64_t *last, uint64_t *lift, bool keep_t,
+                      hipStream_t s) {
+    if (keep_t)
+        hipLaunchKernelGGL((lift_cols_kernel<A, B, true>), grid, dim3(kThreads), 0, s, a, c->fp_mask, last, lift,
+                           c->d_tw_inv, c->d_rescale);
+    else
+        hipLaunchKernelGGL((lift_cols_kernel<A, B, false>), grid, dim3(kThreads), 0, s, a, c->fp_mask, last, lift,
+                           c->d_tw_inv, c->d_rescale);
+}
+
+int launch_lift_cols(const rf_ctx *c, const uint64_t *last, uint64_t *lift, uint32_t nl, bool keep_t, hipStream_t s) {
+    const rf_ctx::UnitRef u = c->moddown_units[nl - 1];
+    const ConvArgs a{c->d_units + u.off, c->d_tw_fwd, c->d_pc, nullptr, nullptr, nl, c->L, c->K, c->alpha};
+    const dim3 grid(2 * u.n * (c->n / kMixTile));
+    ProfScope p("lift_cols", s);
+    switch (c->log_n) {
+        case 13: lift_cols<7, 6>(c, a, grid, last, lift, keep_t, s); break;
+        case 14: lift_cols<7, 7>(c, a, grid, last, lift, keep_t, s); break;
+        case 15: lift_cols<8, 7>(c, a, grid, last, lift, keep_t, s); break;
+        case 16: lift_cols<8, 8>(c, a, grid, last, lift, keep_t, s); break;
+        default: return fail(RF_EUNSUPPORTED, "lift column pass: ring degree");
     }
     return check_conv();
 }

@@ -104,29 +104,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ntt_wa
                               RowStore<FWD, BLK>{b.out + (size_t)u.poly * b.out_poly_stride + ((size_t)u.li << LOGN)});
 }
 
-// Prologue of the first pass of NTT(lift): the lift of polynomial c's last
-// limb (last [2][N], dropped prime l = nl - 1) into prime i.
-template <bool KEEP_T, int LOGN>
-__device__ __forceinline__ LiftPro<KEEP_T> lift_pro(const uint64_t *last, const PrimeConst *__restrict__ pcs,
-                                                    const PrimeConst &pc, const uint64_t *__restrict__ tab,
-                                                    uint32_t c, uint32_t i, uint32_t nl, uint32_t L) {
-    const uint32_t l = nl - 1;
-    const PrimeConst pl = pcs[l];
-    LiftPro<KEEP_T> pro;
-    pro.last = last + ((size_t)c << LOGN);
-    pro.ql = pl.q;
-    pro.ql_half = pl.q >> 1;
-    pro.tinv = pl.tinv;
-    pro.tinv_p = pl.tinv_p;
-    pro.qld = pl.qd;
-    pro.q = pc.q;
-    pro.one_p = pc.one_p;
-    pro.corr = tab[((size_t)l * L + i) * 3 + 2];
-    pro.tmod = pc.tmod;
-    pro.tmod_p = pc.tmod_p;
-    return pro;
-}
-
 // First forward pass of NTT(conv) with the ModDown base conversion as its
 // prologue: limb (c, i) of conv [2][nl][N] from the K P-limbs of ip[c].
 template <int A, int B, int KP, typename Fp>
@@ -570,11 +547,14 @@ static int launch_ntt_fwd_rescale_t(const rf_ctx *c, Fp fpm, const uint64_t *las
     const MixGrid mg = q_mix(c, l, 2);
     const dim3 g = mix_grid(c, mg.n_wide, l, 2);
     const int st = small_tile_of(c, 2 * l, tn);
+    // with narrow primes the INTT's last pass, the lift and the column pass are convert.hip's
+    if constexpr (!std::is_same_v<Fp, NoFp>)
+        if (const int rc = launch_lift_cols(c, last, lift, nl, keep_t, s)) return rc;
     if (st) {
 #define RF_SRS(A, B, T)                                                                                          \
     {                                                                                                            \
         const dim3 gs(c->n / T, 2 * l), bs(T / kSmallE);                                                         \
-        {                                                                                                        \
+        if constexpr (std::is_same_v<Fp, NoFp>) {                                                                \
             ProfScope p("ntt_fwd_cols_lift_small", s);                                                           \
             if (keep_t)                                                                                          \
                 hipLaunchKernelGGL((ntt_small_cols_lift_kernel<A, B, T, true>), gs, bs, 0, s, fpm, last, lift,   \
@@ -603,7 +583,7 @@ static int launch_ntt_fwd_rescale_t(const rf_ctx *c, Fp fpm, const uint64_t *las
     }
 #define RF_RS(A, B)                                                                                              \
     {                                                                                                            \
-        {                                                                                                        \
+        if constexpr (std::is_same_v<Fp, NoFp>) {                                                                \
             ProfScope p("ntt_fwd_cols_lift", s);                                                                 \
             if (keep_t)                                                                                          \
                 hipLaunchKernelGGL((ntt_cols_lift_kernel<A, B, true>), g, dim3(kThreads), 0, s, fpm, mg, last, lift, \
@@ -729,6 +709,27 @@ int launch_ntt(const rf_ctx *c, const NttBatch &b, bool forward, hipStream_t s, 
                const rf_tuning *tn) {
     return c->fp_mask.any() ? launch_ntt_t(c, c->fp_mask, b, forward, s, pcs, tn)
                             : launch_ntt_t(c, NoFp{}, b, forward, s, pcs, tn);
+}
+
+template <int A, int B, typename Fp>
+static void launch_inv_rows(const rf_ctx *c, Fp fpm, const NttBatch &b, hipStream_t s) {
+    const uint32_t limbs = b.per_poly * b.n_polys;
+    ProfScope p("ntt_inv_rows_small", s);
+    hipLaunchKernelGGL((ntt_small_kernel<A, B, false, false, 1024, kSmallE, true>), dim3((1u << (A + B)) / 1024, limbs),
+                       dim3(1024 / kSmallE), 0, s, b, fpm, c->d_tw_inv, c->d_pc);
+}
+
+int launch_intt_rows(const rf_ctx *c, const NttBatch &b, hipStream_t s) {
+    switch (c->log_n) {
+        case 13: launch_inv_rows<7, 6>(c, c->fp_mask, b, s); break;
+        case 14: launch_inv_rows<7, 7>(c, c->fp_mask, b, s); break;
+        case 15: launch_inv_rows<8, 7>(c, c->fp_mask, b, s); break;
+        case 16: launch_inv_rows<8, 8>(c, c->fp_mask, b, s); break;
+        default: return fail(RF_EUNSUPPORTED, "INTT row pass: ring degree");
+    }
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return fail(RF_EHIP, std::string("NTT launch: ") + hipGetErrorString(e));
+    return RF_OK;
 }
 
 template <int A, int B, bool BLK, typename Fp>

@@ -728,20 +728,20 @@ struct LiftPro {
     uint64_t ql, ql_half, tinv, tinv_p;  // dropped prime q_l, t^-1 mod q_l
     double qld;                          // q_l in FP64
     uint64_t q, one_p, corr, tmod, tmod_p;
-    __device__ __forceinline__ uint64_t operator()(size_t idx) const {
-        uint64_t x = last[idx];
+    __device__ __forceinline__ uint64_t lift(uint64_t x) const {
         if (KEEP_T) x = shoup(x, tinv, tinv_p, ql);
         uint64_t r = x - mulhi64(x, one_p) * q;
         if (x > ql_half) r += corr;
         if (KEEP_T) r = shoup_lazy(r, tmod, tmod_p, q);
         return r;
     }
-    __device__ __forceinline__ double fp(size_t idx, const FpMod &) const {
-        if (KEEP_T || ql >= kFpPrimeBound) return FpMod::from_u52((*this)(idx));
-        const uint64_t x = last[idx];
+    __device__ __forceinline__ double lift_fp(uint64_t x) const {
+        if (KEEP_T || ql >= kFpPrimeBound) return FpMod::from_u52(lift(x));
         const double d = FpMod::from_u52(x);
         return x > ql_half ? d - qld : d;
     }
+    __device__ __forceinline__ uint64_t operator()(size_t idx) const { return lift(last[idx]); }
+    __device__ __forceinline__ double fp(size_t idx, const FpMod &) const { return lift_fp(last[idx]); }
 };
 
 // ModDown base conversion P -> q_i as the prologue of the NTT of target i:
@@ -795,6 +795,29 @@ __device__ __forceinline__ ModdownPro<KP> moddown_pro(const uint64_t *ip, const 
     pro.r64 = pc.r64;
     pro.r64_p = pc.r64_p;
     pro.one_p = pc.one_p;
+    return pro;
+}
+
+// Prologue of the first pass of NTT(lift): the lift of polynomial c's last
+// limb (last [2][N], dropped prime l = nl - 1) into prime i.
+template <bool KEEP_T, int LOGN>
+__device__ __forceinline__ LiftPro<KEEP_T> lift_pro(const uint64_t *last, const PrimeConst *__restrict__ pcs,
+                                                    const PrimeConst &pc, const uint64_t *__restrict__ tab,
+                                                    uint32_t c, uint32_t i, uint32_t nl, uint32_t L) {
+    const uint32_t l = nl - 1;
+    const PrimeConst pl = pcs[l];
+    LiftPro<KEEP_T> pro;
+    pro.last = last + ((size_t)c << LOGN);
+    pro.ql = pl.q;
+    pro.ql_half = pl.q >> 1;
+    pro.tinv = pl.tinv;
+    pro.tinv_p = pl.tinv_p;
+    pro.qld = pl.qd;
+    pro.q = pc.q;
+    pro.one_p = pc.one_p;
+    pro.corr = tab[((size_t)l * L + i) * 3 + 2];
+    pro.tmod = pc.tmod;
+    pro.tmod_p = pc.tmod_p;
     return pro;
 }
 

@@ -257,6 +257,8 @@ int fail(int code, const std::string &msg);
 // tn: the level's kernel variants (null: the defaults).
 int launch_ntt(const rf_ctx *c, const NttBatch &b, bool forward, hipStream_t s, const PrimeConst *pcs = nullptr,
                const rf_tuning *tn = nullptr);
+// First pass alone of the INTT of b's few limbs, into the blocked layout (contexts with narrow primes).
+int launch_intt_rows(const rf_ctx *c, const NttBatch &b, hipStream_t s);
 // Second pass alone of the INTT of b's limbs, in place (two-pass ring degrees).
 int launch_intt_cols(const rf_ctx *c, const NttBatch &b, hipStream_t s, const PrimeConst *pcs = nullptr,
                      const rf_tuning *tn = nullptr);
@@ -286,7 +288,10 @@ int launch_ntt_fwd_moddown(const rf_ctx *c, uint64_t *conv, const uint64_t *ip, 
 //   galois != 0 (HRotate): sigma_g of a's polynomial 1.
 int launch_intt_first(const rf_ctx *c, const uint64_t *a, const uint64_t *b, uint64_t *dc, uint32_t galois,
                       uint32_t nl, hipStream_t s, const rf_tuning *tn = nullptr);
-// Rescale / modulus switch after the INTT of the last limb (last = [2][N], blocked),
+// The last pass of the INTT of last, the lift and the first pass of NTT(lift) (contexts with narrow primes).
+int launch_lift_cols(const rf_ctx *c, const uint64_t *last, uint64_t *lift, uint32_t nl, bool keep_t, hipStream_t s);
+// Rescale / modulus switch after the INTT of the last limb (last = [2][N],
+// blocked; with narrow primes in the context after its row pass only),
 // two-pass ring degrees only: the first forward pass lifts the last limb into
 // each remaining prime in its prologue (into lift [2][nl-1][N]; KEEP_T for BGV),
 // the last applies the tail out[c][i] = (in[c][i] - NTT(lift)) q_l^-1.
