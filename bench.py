@@ -513,15 +513,14 @@ def _counter_traffic(kernel: str):
 
 def _kernel_symbol(name: str) -> str:
     """Profiler name of a kernel as it appears in rocprofv3 tables."""
-    table = {"ntt_fwd_cols": "ntt_cols_kernel<8, 8, true>", "ntt_fwd_rows": "ntt_rows_kernel<8, 8, true>",
-             "ntt_inv_cols": "ntt_cols_kernel<8, 8, false>", "ntt_inv_rows": "ntt_rows_kernel<8, 8, false>",
-             "ntt_fwd_rows_moddown": "ntt_rows_moddown_kernel<8, 8>",
-             "ntt_fwd_rows_rescale": "ntt_rows_rescale_kernel<8, 8>",
-             "ntt_fwd_cols_moddown": "ntt_cols_moddown_kernel<8, 8, 4>",
-             "ntt_fwd_cols_lift": "ntt_cols_lift_kernel<8, 8, false>",
-             "ntt_inv_rows_tensor": "ntt_inv_rows_tensor_kernel<8, 8>",
-             "ntt_inv_rows_gather": "ntt_inv_rows_gather_kernel<8, 8>",
-             "modup_bconv": "modup_bconv_kernel<true, 8>", "inner_product": "inner_product_kernel<1>"}
+    table = {"ntt_fwd_cols": "ntt_cols_kernel<8, 8, true", "ntt_fwd_rows": "ntt_rows_kernel<8, 8, true",
+             "ntt_inv_cols": "ntt_cols_kernel<8, 8, false", "ntt_inv_rows": "ntt_rows_kernel<8, 8, false",
+             "ntt_fwd_rows_moddown": "ntt_rows_moddown_kernel<8, 8",
+             "ntt_fwd_rows_rescale": "ntt_rows_rescale_kernel<8, 8",
+             "ntt_inv_rows_tensor": "ntt_inv_rows_tensor_kernel<8, 8",
+             "ntt_inv_rows_gather": "ntt_inv_rows_gather_kernel<8, 8",
+             "modup_cols": "modup_cols_kernel<8, 8", "moddown_cols": "moddown_cols_kernel<8, 8",
+             "lift_cols": "lift_cols_kernel<8, 8", "inner_product": "inner_product_kernel<8, 8"}
     return table.get(name, name + "_kernel")
 
 
@@ -530,7 +529,8 @@ def _ntt_launch_model(name: str, L: int, K: int, alpha: int, n: int):
     one step (HMult+Relin, rescale of its result, HRotate, at L limbs).  Bytes: every
     residue the pass and its fused prologue / epilogue must read or write once
     (8 B), plus, for row passes, each distinct prime's twiddle table once
-    (N pairs of 16 B; column passes use 2^A - 1 pairs per prime, negligible)."""
+    (N pairs of 16 B; narrow primes' tables are half of that, so a row pass's fraction
+    is an upper bound; column passes use 2^A - 1 entries per prime, negligible)."""
     dn = (L + alpha - 1) // alpha
     ext = sum(L - min(alpha, L - j * alpha) + K for j in range(dn))
     limb, tw = 8.0 * n, 16.0 * n
@@ -538,16 +538,17 @@ def _ntt_launch_model(name: str, L: int, K: int, alpha: int, n: int):
     launches = {
         "ntt_inv_rows_tensor": [(L, 2 * L + L, L)],                   # a1, b1 in; row pass of d2 = a1 b1 out
         "ntt_inv_rows_gather": [(L, L + L, L)],                       # c1 gathered in; row pass out
-        # few-limb launches (fewer tiles than CUs) run the small-tile passes:
-        # the P-limbs of both key switches and rescale's last limb
-        "ntt_inv_rows_small": [(2 * K, 4 * K, K)] * 2 + [(2, 4, 1)],
-        "ntt_inv_cols_small": [(2 * K, 4 * K, 0)] * 2 + [(2, 4, 0)],
+        # few-limb launches (fewer tiles than CUs) run the small-tile passes: the row
+        # pass of rescale's last limb, the column pass of the P-limbs of both key switches
+        "ntt_inv_rows_small": [(2, 4, 1)],
+        "ntt_inv_cols_small": [(2 * K, 4 * K, 0)] * 2,
         "ntt_inv_cols": [(L, 2 * L, 0)] * 2,                          # d2 / sigma(c1)
         "ntt_fwd_cols": [(ext, 2 * ext, 0)] * 2,                      # ModUp NTT
         "ntt_fwd_rows": [(ext, 2 * ext, L + K)] * 2,
-        "ntt_fwd_cols_moddown": [(2 * L, 2 * K + 2 * L, 0)] * 2,      # P-limbs in, conv out
+        "modup_cols": [(ext, L + ext, 0)] * 2,                        # digits in, extension out
+        "moddown_cols": [(2 * L, 2 * K + 2 * L, 0)] * 2,              # P-limbs in, conv out
         "ntt_fwd_rows_moddown": [(2 * L, 6 * L, L)] * 2,              # conv, folded ip in; out
-        "ntt_fwd_cols_lift": [(2 * (L - 1), 2 + 2 * (L - 1), 0)],     # last limb in, lift out
+        "lift_cols": [(2 * (L - 1), 2 + 2 * (L - 1), 0)],             # last limb in, lift out
         "ntt_fwd_rows_rescale": [(2 * (L - 1), 2 * (L - 1) * 3, L - 1)],
     }.get(name)
     if launches is None:
@@ -782,6 +783,8 @@ def batch_section(reps: int, tune: bool = True):
     prof = _lib.profile_read()
     _lib.profile_enable(False)
     sbytes = batch_stage_bytes(shapes, len(ch["q"]), len(ch["p"]), w["alpha"])
+    if "batch_modup_bconv" not in prof:  # converted inside the column pass: digits in, extension out
+        sbytes["batch_ntt_fwd_cols"] = sbytes["batch_modup_bconv"]
     stages = {}
     for name, (cnt, ms) in sorted(prof.items()):
         if name in sbytes and cnt:
