@@ -116,7 +116,9 @@ void rf_ctx_destroy(rf_ctx *ctx);
  *                    stages per LDS round: 4 (radix-4, default) or 8 (radix-8).
  *                    The 4096-residue tiles always hold 16 (radix-16 rounds).
  *   modup_chunk      ModUp base-conversion output limbs per thread (the limb
- *                    grouping of the conversion): 4, 8 (default) or 16.
+ *                    grouping of the conversion): 4, 8 (default) or 16;
+ *                    bases whose conversion runs inside the NTT's first pass
+ *                    (a prime below 2^46, or digits of one limb) do not use it.
  *   ntt_fused_small_below  the same threshold for the (I)NTT launches that carry a
  *                    fused step (the tensor or automorphism before the first INTT
  *                    pass, the ModDown conversion and tail, the rescale lift and
