@@ -213,10 +213,10 @@ enum BatchPass {
     kPassModdown8,  // or any number up to 8
     kPassTail       // its rows, with the tail
 };
-__host__ __device__ constexpr bool pass_cols(BatchPass p) {
+__host__ __device__ constexpr bool pass_cols(int p) {
     return p == kPassInvCols || p == kPassModup || p == kPassModdown4 || p == kPassModdown8;
 }
-__host__ __device__ constexpr int pass_second(BatchPass p) {
+__host__ __device__ constexpr int pass_second(int p) {
     return p == kPassInvCols || p == kPassFwdRows || p == kPassTail;
 }
 
@@ -283,7 +283,7 @@ __device__ __forceinline__ void batch_modup(uint64_t *lds, const NttJob &J, uint
 }
 
 // One pass over unit u of a job.
-template <int A, int B, BatchPass PASS>
+template <int A, int B, int PASS>
 __device__ __forceinline__ void ntt_batched_unit(uint64_t *lds, const NttJob &J, uint32_t u) {
     constexpr int LOGN = A + B;
     const uint32_t local = u - J.unit_begin[pass_second(PASS)];
@@ -362,7 +362,7 @@ __device__ __forceinline__ void ntt_batched_unit(uint64_t *lds, const NttJob &J,
 // [unit0, unit0 + total) of the step; jobs = the items of the ring degree, whose
 // unit_begin values are absolute.  LOOP: workgroups walk per_wg consecutive
 // units; otherwise each takes one unit (per_wg == 1).
-template <int A, int B, BatchPass PASS, bool LOOP>
+template <int A, int B, int PASS, bool LOOP>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(PASS == kPassModdown8 ? 3 : ntt_waves(pass_cols(PASS) ? A : B)))) void ntt_batched_kernel(
     const NttJob *__restrict__ jobs, uint32_t njobs, uint32_t unit0, uint32_t total, uint32_t per_wg) {
     constexpr bool COLS = pass_cols(PASS);
