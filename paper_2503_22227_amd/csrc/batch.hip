@@ -361,9 +361,11 @@ __device__ __forceinline__ void ntt_batched_unit(uint64_t *lds, const NttJob &J,
 // shape per kernel keeps the unrolled rounds free of register spills).  Units
 // [unit0, unit0 + total) of the step; jobs = the items of the ring degree, whose
 // unit_begin values are absolute.  LOOP: workgroups walk per_wg consecutive
-// units; otherwise each takes one unit (per_wg == 1).
+// units; otherwise each takes one unit (per_wg == 1).  The loop keeps every
+// path's addresses in registers: at 2 waves per SIMD it hardly spills (at 4, 52 to 143
+// registers: 64 items of N = 2^14..2^16 with 2048 workgroups a launch 5085 us, and 3858).
 template <int A, int B, int PASS, bool LOOP>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(PASS == kPassModdown8 ? 3 : ntt_waves(pass_cols(PASS) ? A : B)))) void ntt_batched_kernel(
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(LOOP ? 2 : PASS == kPassModdown8 ? 3 : ntt_waves(pass_cols(PASS) ? A : B)))) void ntt_batched_kernel(
     const NttJob *__restrict__ jobs, uint32_t njobs, uint32_t unit0, uint32_t total, uint32_t per_wg) {
     constexpr bool COLS = pass_cols(PASS);
     constexpr int kTileWords = COLS ? (1 << A) * (kTile / (1 << A) + 1) : (1 << B) * (kTile / (1 << B) + 1);
