@@ -338,7 +338,7 @@ static int divide_last(const rf_ctx *c, const uint64_t *in, uint64_t *out, uint3
     } else {
         const rf_tuning &tn = level_tuning(c, nl);
         const NttBatch b = batch(in + (size_t)(nl - 1) * N, last, in_stride, N, 1, 2, nl - 1, nullptr, LimbOrder(), true);
-        rc = c->fp_mask.any() ? launch_intt_rows(c, b, s) : launch_ntt(c, b, false, s, nullptr, &tn);
+        rc = lift_fused(c, nl) ? launch_intt_rows(c, b, s) : launch_ntt(c, b, false, s, nullptr, &tn);
         if (rc) return rc;
         // the lift runs in the first pass of the NTT and the tail in its last pass
         rc = launch_ntt_fwd_rescale(c, last, lift, in, to, nl, keep_t, s, &tn);

@@ -185,6 +185,13 @@ static void lift_cols(const rf_ctx *c, const ConvArgs &a, dim3 grid, const uint6
                            c->d_tw_inv, c->d_rescale);
 }
 
+// A wide target's workgroup transforms the dropped limb's tile for itself alone: with
+// 10 wide targets of 19 a rescale at N = 2^16 takes 41.6 us against 43.2, with 16 of
+// 19 44.5 against 42.5.
+bool lift_fused(const rf_ctx *c, uint32_t nl) {
+    return c->fp_mask.any() && 4 * c->q_order[nl - 1].n_wide <= 3 * (nl - 1);
+}
+
 int launch_lift_cols(const rf_ctx *c, const uint64_t *last, uint64_t *lift, uint32_t nl, bool keep_t, hipStream_t s) {
     const rf_ctx::UnitRef u = c->moddown_units[nl - 1];
     const ConvArgs a{c->d_units + u.off, c->d_tw_fwd, c->d_pc, nullptr, nullptr, nl, c->L, c->K, c->alpha};

@@ -547,14 +547,14 @@ static int launch_ntt_fwd_rescale_t(const rf_ctx *c, Fp fpm, const uint64_t *las
     const MixGrid mg = q_mix(c, l, 2);
     const dim3 g = mix_grid(c, mg.n_wide, l, 2);
     const int st = small_tile_of(c, 2 * l, tn);
-    // with narrow primes the INTT's last pass, the lift and the column pass are convert.hip's
-    if constexpr (!std::is_same_v<Fp, NoFp>)
+    const bool fused = lift_fused(c, nl);  // convert.hip has the INTT's last pass, the lift and the column pass
+    if (fused)
         if (const int rc = launch_lift_cols(c, last, lift, nl, keep_t, s)) return rc;
     if (st) {
 #define RF_SRS(A, B, T)                                                                                          \
     {                                                                                                            \
         const dim3 gs(c->n / T, 2 * l), bs(T / kSmallE);                                                         \
-        if constexpr (std::is_same_v<Fp, NoFp>) {                                                                \
+        if (!fused) {                                                                                            \
             ProfScope p("ntt_fwd_cols_lift_small", s);                                                           \
             if (keep_t)                                                                                          \
                 hipLaunchKernelGGL((ntt_small_cols_lift_kernel<A, B, T, true>), gs, bs, 0, s, fpm, last, lift,   \
@@ -583,7 +583,7 @@ static int launch_ntt_fwd_rescale_t(const rf_ctx *c, Fp fpm, const uint64_t *las
     }
 #define RF_RS(A, B)                                                                                              \
     {                                                                                                            \
-        if constexpr (std::is_same_v<Fp, NoFp>) {                                                                \
+        if (!fused) {                                                                                            \
             ProfScope p("ntt_fwd_cols_lift", s);                                                                 \
             if (keep_t)                                                                                          \
                 hipLaunchKernelGGL((ntt_cols_lift_kernel<A, B, true>), g, dim3(kThreads), 0, s, fpm, mg, last, lift, \

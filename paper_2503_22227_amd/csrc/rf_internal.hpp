@@ -288,10 +288,12 @@ int launch_ntt_fwd_moddown(const rf_ctx *c, uint64_t *conv, const uint64_t *ip, 
 //   galois != 0 (HRotate): sigma_g of a's polynomial 1.
 int launch_intt_first(const rf_ctx *c, const uint64_t *a, const uint64_t *b, uint64_t *dc, uint32_t galois,
                       uint32_t nl, hipStream_t s, const rf_tuning *tn = nullptr);
-// The last pass of the INTT of last, the lift and the first pass of NTT(lift) (contexts with narrow primes).
+// The last pass of the INTT of last, the lift and the first pass of NTT(lift).
+// lift_fused: whether a division by the last of nl primes takes it.
+bool lift_fused(const rf_ctx *c, uint32_t nl);
 int launch_lift_cols(const rf_ctx *c, const uint64_t *last, uint64_t *lift, uint32_t nl, bool keep_t, hipStream_t s);
 // Rescale / modulus switch after the INTT of the last limb (last = [2][N],
-// blocked; with narrow primes in the context after its row pass only),
+// blocked; where lift_fused after its row pass only),
 // two-pass ring degrees only: the first forward pass lifts the last limb into
 // each remaining prime in its prologue (into lift [2][nl-1][N]; KEEP_T for BGV),
 // the last applies the tail out[c][i] = (in[c][i] - NTT(lift)) q_l^-1.

@@ -60,6 +60,7 @@ W, M, S = 60, 45, 30  # a wide prime, a narrow one, a small narrow one
     (13, [S] * 6 + [W] * 3, [M, W], 3, 9),    # small primes, wide ones last
     (15, [W] + [M] * 12, [W] * 4, 8, 13),
     (16, [W] + [M] * 8, [W] * 4, 4, 9),
+    (13, [W] * 6 + [M] * 2, [W] * 2, 4, 8),   # too many wide targets for the fused lift
     (13, [W] * 6, [W] * 2, 2, 5),             # wide primes alone, more than one a digit
     (13, [W] * 5, [W], 1, 5),
 ])
