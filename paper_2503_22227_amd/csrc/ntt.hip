@@ -34,8 +34,8 @@ __device__ __forceinline__ LimbView limb_view(const NttBatch &b, int log_n, uint
 // since their workgroups take longest, N / 1024 workgroups each, then the narrow
 // ones, N / 4096 each; polynomials interleaved.
 struct MixGrid {
-    const uint32_t *ent;
-    uint32_t n_wide, np, base;
+    LimbOrder o;
+    uint32_t np;
 };
 struct MixUnit {
     uint32_t li, poly, g;
@@ -47,7 +47,7 @@ template <int A, int B, bool COLS, typename Fp>
 __device__ __forceinline__ MixUnit mix_unit(const MixGrid &m) {
     constexpr int LOGN = A + B, TW = LOGN - 10, TN = LOGN - 12;
     MixUnit u;
-    const uint32_t wide = m.n_wide * m.np;
+    const uint32_t wide = m.o.n_wide * m.np;
     uint32_t w = blockIdx.x, e;
     u.fp = !std::is_same_v<Fp, NoFp> && w >= wide << TW;
     if (u.fp) {
@@ -61,16 +61,15 @@ __device__ __forceinline__ MixUnit mix_unit(const MixGrid &m) {
     }
     const uint32_t k = __builtin_amdgcn_readfirstlane(m.np == 1 ? e : m.np == 2 ? e >> 1 : e / m.np);
     u.poly = e - k * m.np;
-    const uint32_t x = m.ent ? m.ent[k] : k | (m.base + k) << 16;
-    u.li = x & 0xffffu;
+    const uint32_t x = m.o.ent[u.fp ? k + m.o.gap : k];
+    u.li = (x & 0xffffu) - m.o.base;
     u.g = x >> 16;
     return u;
 }
 
 // The first `limbs` Q-limbs of np polynomials.
 static MixGrid q_mix(const rf_ctx *c, uint32_t limbs, uint32_t np) {
-    const LimbOrder o = c->order(c->q_order[limbs]);
-    return MixGrid{o.ent, o.n_wide, np, 0};
+    return MixGrid{c->order(c->q_order[limbs]), np};
 }
 
 // Grid of a launch of `limbs` limbs of each of np polynomials.
@@ -332,7 +331,7 @@ static void launch_two_pass_small(const rf_ctx *c, Fp fpm, const NttBatch &b, bo
 template <int A, int B, bool BLK, typename Fp>
 static void launch_mixed(const rf_ctx *c, Fp fpm, const NttBatch &b, const MixGrid &m, bool forward, hipStream_t s,
                          const PrimeConst *pcs) {
-    const dim3 block(kThreads), grid = mix_grid(c, m.n_wide, b.per_poly, b.n_polys);
+    const dim3 block(kThreads), grid = mix_grid(c, m.o.n_wide, b.per_poly, b.n_polys);
     NttBatch b2 = b;
     b2.in = b.out;
     b2.in_poly_stride = b.out_poly_stride;
@@ -370,20 +369,7 @@ static void launch_two_pass_blk(const rf_ctx *c, Fp fpm, const NttBatch &b, bool
         }
         return;
     }
-    // limbs without an order of their own: a launch per run of one class
-    if (!b.order.ent && !b.pmap) {
-        for (uint32_t i = 0, j; i < b.per_poly; i = j) {
-            const bool wide = !fpm.has(b.prime_base + i);
-            for (j = i + 1; j < b.per_poly && wide == !fpm.has(b.prime_base + j);) ++j;
-            NttBatch r = b;
-            r.in += (size_t)i * c->n;
-            r.out += (size_t)i * c->n;
-            r.per_poly = j - i;
-            launch_mixed<A, B, BLK>(c, fpm, r, MixGrid{nullptr, wide ? j - i : 0, b.n_polys, b.prime_base + i}, forward, s, pcs);
-        }
-        return;
-    }
-    launch_mixed<A, B, BLK>(c, fpm, b, MixGrid{b.order.ent, b.order.n_wide, b.n_polys, 0}, forward, s, pcs);
+    launch_mixed<A, B, BLK>(c, fpm, b, MixGrid{b.order, b.n_polys}, forward, s, pcs);
 }
 
 template <int A, int B, typename Fp>
@@ -413,9 +399,9 @@ static void launch_fwd_rows_blk(const rf_ctx *c, Fp fpm, const NttBatch &b, hipS
 #undef RF_FR
         return;
     }
-    const MixGrid m{b.order.ent, b.order.n_wide, b.n_polys, 0};
+    const MixGrid m{b.order, b.n_polys};
     ProfScope p("ntt_fwd_rows", s);
-    hipLaunchKernelGGL((ntt_rows_kernel<A, B, true, BLK>), mix_grid(c, m.n_wide, b.per_poly, b.n_polys), dim3(kThreads), 0,
+    hipLaunchKernelGGL((ntt_rows_kernel<A, B, true, BLK>), mix_grid(c, m.o.n_wide, b.per_poly, b.n_polys), dim3(kThreads), 0,
                        s, b, fpm, m, c->d_tw_fwd_rows, c->d_tw_fwd, c->d_pc);
 }
 
@@ -461,7 +447,7 @@ static int launch_ntt_fwd_moddown_t(const rf_ctx *c, Fp fpm, uint64_t *conv, con
     const uint64_t *cross = tab + moddown_cross_off(c), *negp = tab + moddown_negp_off(c);
     const uint64_t *pinv = c->d_moddown + moddown_pinv_off(c);
     const MixGrid mg = q_mix(c, nl, 2);
-    const dim3 g = mix_grid(c, mg.n_wide, nl, 2);
+    const dim3 g = mix_grid(c, mg.o.n_wide, nl, 2);
     const int st = small_tile_of(c, 2 * nl, tn);
     // with narrow primes the conversion and the column pass are convert.hip's
     if constexpr (!std::is_same_v<Fp, NoFp>)
@@ -545,7 +531,7 @@ static int launch_ntt_fwd_rescale_t(const rf_ctx *c, Fp fpm, const uint64_t *las
                            uint64_t *out, uint32_t nl, bool keep_t, hipStream_t s, const rf_tuning *tn) {
     const uint32_t l = nl - 1;
     const MixGrid mg = q_mix(c, l, 2);
-    const dim3 g = mix_grid(c, mg.n_wide, l, 2);
+    const dim3 g = mix_grid(c, mg.o.n_wide, l, 2);
     const int st = small_tile_of(c, 2 * l, tn);
     const bool fused = lift_fused(c, nl);  // convert.hip has the INTT's last pass, the lift and the column pass
     if (fused)
@@ -651,7 +637,7 @@ static int launch_intt_first_t(const rf_ctx *c, Fp fpm, const uint64_t *a, const
 #define RF_IF(A, B)                                                                                              \
     {                                                                                                            \
         const MixGrid mg = q_mix(c, nl, 1);                                                                      \
-        const dim3 gr = mix_grid(c, mg.n_wide, nl, 1);                                                           \
+        const dim3 gr = mix_grid(c, mg.o.n_wide, nl, 1);                                                           \
         if (galois) {                                                                                            \
             ProfScope p("ntt_inv_rows_gather", s);                                                               \
             hipLaunchKernelGGL((ntt_inv_rows_gather_kernel<A, B>), gr, dim3(kThreads), 0, s, fpm, mg, a + (size_t)nl * N, dc, \
@@ -753,9 +739,9 @@ static void launch_inv_cols(const rf_ctx *c, Fp fpm, const NttBatch &b, hipStrea
 #undef RF_IC
         return;
     }
-    const MixGrid m{b.order.ent, b.order.n_wide, b.n_polys, 0};
+    const MixGrid m{b.order, b.n_polys};
     ProfScope p("ntt_inv_cols", s);
-    hipLaunchKernelGGL((ntt_cols_kernel<A, B, false, BLK>), mix_grid(c, m.n_wide, b.per_poly, b.n_polys),
+    hipLaunchKernelGGL((ntt_cols_kernel<A, B, false, BLK>), mix_grid(c, m.o.n_wide, b.per_poly, b.n_polys),
                        dim3(kThreads), 0, s, b, fpm, m, c->d_tw_inv, pcs);
 }
 

@@ -55,11 +55,12 @@ struct NoFp {
 };
 
 // The limbs of a launch with those of wide primes first: device entries limb |
-// prime << 16, n_wide of them wide.  ent null: the limbs in order, all of one
-// class (n_wide = 0 or their number).
+// prime << 16, n_wide of them wide.  A window of the chain is two runs of the
+// whole chain's order, its wide primes and, gap entries further on, its narrow
+// ones; base is its first limb (all 0 for an order of its own).
 struct LimbOrder {
     const uint32_t *ent = nullptr;
-    uint32_t n_wide = 0;
+    uint32_t n_wide = 0, gap = 0, base = 0;
 };
 
 // Launch description of a batched (I)NTT over limbs laid out as
@@ -73,7 +74,7 @@ struct NttBatch {
     uint32_t n_polys;
     uint32_t prime_base;
     const uint32_t *pmap;      // device array [per_poly] or nullptr
-    LimbOrder order;           // the same limbs in launch order (ent null: made from prime_base)
+    LimbOrder order;           // the same limbs in launch order
     bool blocked = false;      // the coefficient side is in the blocked layout (ntt_dev.hpp)
 };
 
