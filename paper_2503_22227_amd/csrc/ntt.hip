@@ -45,11 +45,12 @@ struct MixUnit {
 
 template <int A, int B, bool COLS, typename Fp>
 __device__ __forceinline__ MixUnit mix_unit(const MixGrid &m) {
-    constexpr int LOGN = A + B, TW = LOGN - 10, TN = LOGN - 12;
+    constexpr bool BIG = std::is_same_v<Fp, WideTiles>;
+    constexpr int LOGN = A + B, TW = BIG ? LOGN - 12 : LOGN - 10, TN = LOGN - 12;
     MixUnit u;
     const uint32_t wide = m.o.n_wide * m.np;
     uint32_t w = blockIdx.x, e;
-    u.fp = !std::is_same_v<Fp, NoFp> && w >= wide << TW;
+    u.fp = std::is_same_v<Fp, FpMask> && w >= wide << TW;
     if (u.fp) {
         w -= wide << TW;
         e = wide + (w >> TN);
@@ -57,13 +58,18 @@ __device__ __forceinline__ MixUnit mix_unit(const MixGrid &m) {
     } else {
         e = w >> TW;
         u.tile = w & ((1 << TW) - 1);
-        if (COLS) u.tile = xcd_grouped_tile<kMixTile, A>(u.tile, 1 << TW);
+        if (COLS && !BIG) u.tile = xcd_grouped_tile<kMixTile, A>(u.tile, 1 << TW);
     }
     const uint32_t k = __builtin_amdgcn_readfirstlane(m.np == 1 ? e : m.np == 2 ? e >> 1 : e / m.np);
     u.poly = e - k * m.np;
-    const uint32_t x = m.o.ent[u.fp ? k + m.o.gap : k];
-    u.li = (x & 0xffffu) - m.o.base;
-    u.g = x >> 16;
+    if (BIG && !m.o.ent) {
+        u.li = k;
+        u.g = m.o.base + k;
+    } else {
+        const uint32_t x = m.o.ent[u.fp ? k + m.o.gap : k];
+        u.li = (x & 0xffffu) - m.o.base;
+        u.g = x >> 16;
+    }
     return u;
 }
 
@@ -77,6 +83,18 @@ static dim3 mix_grid(const rf_ctx *c, uint32_t n_wide, uint32_t limbs, uint32_t 
     return dim3(np * (n_wide * (c->n / kMixTile) + (limbs - n_wide) * (c->n / kTile)));
 }
 
+// Transforms of wide limbs alone in the natural layout take 4096-residue tiles from
+// two workgroups of them a CU on (half that at N = 2^13, where a 1024-residue tile
+// of columns is half a line and no two of a line meet on an XCD).  Below, smaller
+// tiles spread a launch over more CUs; from there on they only add twiddle loads
+// and part lines.  Forward and inverse in tiles of 1024 against 4096: N = 2^16, 384
+// tiles 48.3 and 54.8 us, 512 56.6 and 57.2, 768 74.1 and 70.2, 1536 127 and 118,
+// 4096 313 and 266; N = 2^15, 512 57.6 and 58.2, 1024 88.8 and 83.8; N = 2^13, 192
+// 32.4 and 32.8, 256 39.1 and 34.5.  The blocked passes, with a step of their own or
+// whole lines in either tile, keep the small ones (768 tiles of a ModDown's rows 22.9
+// and 25.8).
+static uint32_t wide_tiles_from(const rf_ctx *c) { return c->log_n == 13 ? 256 : 512; }
+
 template <int A, int B, bool FWD, bool BLK, typename Fp>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ntt_waves(A)))) void ntt_cols_kernel(
     NttBatch b, Fp, MixGrid m, const TwPair *__restrict__ tw_all, const PrimeConst *__restrict__ pcs) {
@@ -84,7 +102,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ntt_wa
     constexpr int LOGN = A + B;
     const MixUnit u = mix_unit<A, B, true, Fp>(m);
     const PrimeConst pc = pcs[u.g];
-    ntt_cols_mixed<A, B, FWD, BLK>(lds, b.out + (size_t)u.poly * b.out_poly_stride + ((size_t)u.li << LOGN),
+    ntt_cols_mixed<A, B, FWD, BLK, Fp>(lds, b.out + (size_t)u.poly * b.out_poly_stride + ((size_t)u.li << LOGN),
                               tw_all + ((size_t)u.g << LOGN), pc, u.fp, u.tile,
                               PlainPro<FWD>{b.in + (size_t)u.poly * b.in_poly_stride + ((size_t)u.li << LOGN)});
 }
@@ -98,7 +116,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ntt_wa
     const MixUnit u = mix_unit<A, B, false, Fp>(m);
     const PrimeConst pc = pcs[u.g];
     const size_t tl = (size_t)u.g << LOGN;
-    ntt_rows_mixed<A, B, FWD>(lds, RowLoad<FWD, BLK>{b.in + (size_t)u.poly * b.in_poly_stride + ((size_t)u.li << LOGN)},
+    ntt_rows_mixed<A, B, FWD, Fp>(lds, RowLoad<FWD, BLK>{b.in + (size_t)u.poly * b.in_poly_stride + ((size_t)u.li << LOGN)},
                               tw_rows + tl, tw_all + tl, pc, u.fp, u.tile,
                               RowStore<FWD, BLK>{b.out + (size_t)u.poly * b.out_poly_stride + ((size_t)u.li << LOGN)});
 }
@@ -115,7 +133,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(KP == 
     const uint32_t c = u.poly, i = u.li;
     const PrimeConst pc = pcs[i];
     const ModdownPro<KP> pro = moddown_pro<KP, LOGN>(ip, pcs, pc, cross, negp, c, i, nl, L, K);
-    ntt_cols_mixed<A, B, true, true>(lds, conv + (((size_t)c * nl + i) << LOGN), tw_all + ((size_t)i << LOGN), pc, u.fp,
+    ntt_cols_mixed<A, B, true, true, Fp>(lds, conv + (((size_t)c * nl + i) << LOGN), tw_all + ((size_t)i << LOGN), pc, u.fp,
                                u.tile, pro);
 }
 
@@ -132,7 +150,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kNttWa
     const uint32_t c = u.poly, i = u.li;
     const PrimeConst pc = pcs[i];
     const LiftPro<KEEP_T> pro = lift_pro<KEEP_T, LOGN>(last, pcs, pc, tab, c, i, nl, L);
-    ntt_cols_mixed<A, B, true, true>(lds, lift + (((size_t)c * l + i) << LOGN), tw_all + ((size_t)i << LOGN), pc, u.fp,
+    ntt_cols_mixed<A, B, true, true, Fp>(lds, lift + (((size_t)c * l + i) << LOGN), tw_all + ((size_t)i << LOGN), pc, u.fp,
                                u.tile, pro);
 }
 
@@ -149,7 +167,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ntt_wa
     const PrimeConst pc = pcs[i];
     const ModdownFoldEpi epi{ip + (((size_t)c * (nl + K) + i) << LOGN), out + (((size_t)c * nl + i) << LOGN),
                              pinv[2 * i], pinv[2 * i + 1], pc.q};
-    ntt_rows_mixed<A, B, true>(lds, BlkRawPro{conv + (((size_t)c * nl + i) << LOGN)}, tw_rows + ((size_t)i << LOGN),
+    ntt_rows_mixed<A, B, true, Fp>(lds, BlkRawPro{conv + (((size_t)c * nl + i) << LOGN)}, tw_rows + ((size_t)i << LOGN),
                                tw_all + ((size_t)i << LOGN), pc, u.fp, u.tile, epi);
 }
 
@@ -166,7 +184,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ntt_wa
     const PrimeConst pc = pcs[i];
     const size_t li = (size_t)i << LOGN, poly = (size_t)nl << LOGN;
     const TensorPro pro{a + poly + li, b + poly + li, pc.q, pc.r64, pc.r64_p, pc.one_p};
-    ntt_rows_mixed<A, B, false>(lds, pro, tw_rows + li, tw_all + li, pc, u.fp, u.tile, BlkRawEpi{dc + li});
+    ntt_rows_mixed<A, B, false, Fp>(lds, pro, tw_rows + li, tw_all + li, pc, u.fp, u.tile, BlkRawEpi{dc + li});
 }
 
 // First inverse pass of INTT(sigma_g(a1)) with the automorphism as its
@@ -182,7 +200,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ntt_wa
     const PrimeConst pc = pcs[i];
     const size_t li = (size_t)i << LOGN;
     const GatherPro pro{a1 + li, galois, (uint32_t)LOGN};
-    ntt_rows_mixed<A, B, false>(lds, pro, tw_rows + li, tw_all + li, pc, u.fp, u.tile, BlkRawEpi{dc + li});
+    ntt_rows_mixed<A, B, false, Fp>(lds, pro, tw_rows + li, tw_all + li, pc, u.fp, u.tile, BlkRawEpi{dc + li});
 }
 
 // Last forward pass of NTT(lift) with the rescale tail: limb (c, i) of lift
@@ -199,7 +217,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ntt_wa
     const PrimeConst pc = pcs[i];
     const uint64_t *t = tab + ((size_t)l * L + i) * 3;
     RescaleTailEpi epi{in + (((size_t)c * nl + i) << LOGN), out + (((size_t)c * l + i) << LOGN), t[0], t[1], pc.q};
-    ntt_rows_mixed<A, B, true>(lds, BlkRawPro{lift + (((size_t)c * l + i) << LOGN)}, tw_rows + ((size_t)i << LOGN),
+    ntt_rows_mixed<A, B, true, Fp>(lds, BlkRawPro{lift + (((size_t)c * l + i) << LOGN)}, tw_rows + ((size_t)i << LOGN),
                                tw_all + ((size_t)i << LOGN), pc, u.fp, u.tile, epi);
 }
 
@@ -329,9 +347,9 @@ static void launch_two_pass_small(const rf_ctx *c, Fp fpm, const NttBatch &b, bo
 }
 
 template <int A, int B, bool BLK, typename Fp>
-static void launch_mixed(const rf_ctx *c, Fp fpm, const NttBatch &b, const MixGrid &m, bool forward, hipStream_t s,
-                         const PrimeConst *pcs) {
-    const dim3 block(kThreads), grid = mix_grid(c, m.o.n_wide, b.per_poly, b.n_polys);
+static void launch_mixed(const rf_ctx *c, Fp fpm, const NttBatch &b, const MixGrid &m, dim3 grid, bool forward,
+                         hipStream_t s, const PrimeConst *pcs) {
+    const dim3 block(kThreads);
     NttBatch b2 = b;
     b2.in = b.out;
     b2.in_poly_stride = b.out_poly_stride;
@@ -369,7 +387,17 @@ static void launch_two_pass_blk(const rf_ctx *c, Fp fpm, const NttBatch &b, bool
         }
         return;
     }
-    launch_mixed<A, B, BLK>(c, fpm, b, MixGrid{b.order, b.n_polys}, forward, s, pcs);
+    MixGrid m{b.order, b.n_polys};
+    if constexpr (!BLK) {
+        if (m.o.n_wide == b.per_poly && tiles >= wide_tiles_from(c)) {
+            // primes that follow each other need no look at the order, a load ahead of
+            // all others (0.4 us of the passes at N = 2^13)
+            if (!b.pmap) m.o = LimbOrder{nullptr, b.per_poly, 0, b.prime_base};
+            launch_mixed<A, B, false>(c, WideTiles{}, b, m, dim3(tiles), forward, s, pcs);
+            return;
+        }
+    }
+    launch_mixed<A, B, BLK>(c, fpm, b, m, mix_grid(c, m.o.n_wide, b.per_poly, b.n_polys), forward, s, pcs);
 }
 
 template <int A, int B, typename Fp>

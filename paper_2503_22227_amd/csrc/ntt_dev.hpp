@@ -708,10 +708,11 @@ __device__ __forceinline__ void ntt_cols_unit_pro(uint64_t *lds, uint64_t *out, 
 // 2^16 13.4 to 22.0 and now 12.9 to 21.7.
 constexpr int kMixTile = 1024, kMixE = kMixTile / kThreads;
 
-template <int A, int B, bool FWD, bool BLK, typename Pro>
+template <int A, int B, bool FWD, bool BLK, typename Fp, typename Pro>
 __device__ __forceinline__ void ntt_cols_mixed(uint64_t *lds, uint64_t *out, const TwPair *__restrict__ tw,
                                                const PrimeConst &pc, bool fp, int tile, const Pro &pro) {
-    if (fp) ntt_cols_unit_t<ArFp, A, B, FWD, BLK>(lds, out, tw, ArFp(pc), tile, pro);
+    if constexpr (std::is_same_v<Fp, WideTiles>) ntt_cols_unit_t<ArInt, A, B, FWD, BLK>(lds, out, tw, ArInt(pc), tile, pro);
+    else if (fp) ntt_cols_unit_t<ArFp, A, B, FWD, BLK>(lds, out, tw, ArFp(pc), tile, pro);
     else ntt_cols_small_t<ArInt, A, B, FWD, kMixTile, kMixE, BLK>(lds, pro, out, tw, ArInt(pc), tile);
 }
 
@@ -894,12 +895,13 @@ __device__ __forceinline__ void ntt_rows_unit_pe(uint64_t *lds, const Pro &pro, 
     else ntt_rows_unit_t<ArInt, A, B, FWD>(lds, pro, tw, ArInt(pc), tile, epi);
 }
 
-// As ntt_cols_mixed; tw_rows: the row-pass layout (narrow primes), tw: the natural one.
-template <int A, int B, bool FWD, typename Pro, typename Epi>
+// As ntt_cols_mixed; tw_rows: the row-pass layout (4096-residue tiles), tw: the natural one.
+template <int A, int B, bool FWD, typename Fp, typename Pro, typename Epi>
 __device__ __forceinline__ void ntt_rows_mixed(uint64_t *lds, const Pro &pro, const TwPair *__restrict__ tw_rows,
                                                const TwPair *__restrict__ tw, const PrimeConst &pc, bool fp, int tile,
                                                const Epi &epi) {
-    if (fp) ntt_rows_unit_t<ArFp, A, B, FWD>(lds, pro, tw_rows, ArFp(pc), tile, epi);
+    if constexpr (std::is_same_v<Fp, WideTiles>) ntt_rows_unit_t<ArInt, A, B, FWD>(lds, pro, tw_rows, ArInt(pc), tile, epi);
+    else if (fp) ntt_rows_unit_t<ArFp, A, B, FWD>(lds, pro, tw_rows, ArFp(pc), tile, epi);
     else ntt_rows_small_t<ArInt, A, B, FWD, kMixTile, kMixE>(lds, pro, tw, ArInt(pc), tile, epi);
 }
 

@@ -53,6 +53,8 @@ struct FpMask {
 struct NoFp {
     __host__ __device__ __forceinline__ static constexpr bool has(uint32_t) { return false; }
 };
+// A transform of wide primes alone, many limbs: 4096-residue tiles (ntt.hip).
+struct WideTiles {};
 
 // The limbs of a launch with those of wide primes first: device entries limb |
 // prime << 16, n_wide of them wide.  A window of the chain is two runs of the
