@@ -319,7 +319,13 @@ __global__ __launch_bounds__(TILE / kSmallE) void ntt_small_inv_rows_first_kerne
 }
 
 
-// Launchers: fpm is the context's FpMask, or NoFp.
+// Launchers: fpm is the context's FpMask, or NoFp where every limb of the launch is
+// of a wide prime: a kernel that holds both forms is 0.3 to 0.5 us slower on those
+// (N = 2^16, 8 limbs of 60 bits in a chain that ends in 45-bit ones: rescale 27.9
+// against 27.2 us).
+static bool narrow_in(const NttBatch &b) { return b.order.n_wide < b.per_poly; }
+static bool narrow_in(const rf_ctx *c, uint32_t nl) { return c->q_order[nl].n_wide < nl; }
+
 template <int A, int B, int TILE, int E, bool BLK, typename Fp>
 static void launch_two_pass_small(const rf_ctx *c, Fp fpm, const NttBatch &b, bool forward, hipStream_t s,
                                   const PrimeConst *pcs) {
@@ -456,7 +462,7 @@ static int launch_ntt_fwd_rows_t(const rf_ctx *c, Fp fpm, const NttBatch &b, hip
 
 int launch_ntt_fwd_rows(const rf_ctx *c, const NttBatch &b, hipStream_t s, const rf_tuning *tn) {
     const rf_tuning &t = tn ? *tn : kDefaultTuning;
-    return c->fp_mask.any() ? launch_ntt_fwd_rows_t(c, c->fp_mask, b, s, t) : launch_ntt_fwd_rows_t(c, NoFp{}, b, s, t);
+    return narrow_in(b) ? launch_ntt_fwd_rows_t(c, c->fp_mask, b, s, t) : launch_ntt_fwd_rows_t(c, NoFp{}, b, s, t);
 }
 
 // Small-tile size of a fused launch of `limbs` limbs, or 0 for the 4096-residue
@@ -550,7 +556,7 @@ static int launch_ntt_fwd_moddown_t(const rf_ctx *c, Fp fpm, uint64_t *conv, con
 
 int launch_ntt_fwd_moddown(const rf_ctx *c, uint64_t *conv, const uint64_t *ip, uint64_t *out, uint32_t nl,
                            hipStream_t s, const rf_tuning *tn) {
-    return c->fp_mask.any() ? launch_ntt_fwd_moddown_t(c, c->fp_mask, conv, ip, out, nl, s, tn)
+    return narrow_in(c, nl) ? launch_ntt_fwd_moddown_t(c, c->fp_mask, conv, ip, out, nl, s, tn)
                             : launch_ntt_fwd_moddown_t(c, NoFp{}, conv, ip, out, nl, s, tn);
 }
 
@@ -625,8 +631,8 @@ static int launch_ntt_fwd_rescale_t(const rf_ctx *c, Fp fpm, const uint64_t *las
 
 int launch_ntt_fwd_rescale(const rf_ctx *c, const uint64_t *last, uint64_t *lift, const uint64_t *in,
                            uint64_t *out, uint32_t nl, bool keep_t, hipStream_t s, const rf_tuning *tn) {
-    return c->fp_mask.any() ? launch_ntt_fwd_rescale_t(c, c->fp_mask, last, lift, in, out, nl, keep_t, s, tn)
-                            : launch_ntt_fwd_rescale_t(c, NoFp{}, last, lift, in, out, nl, keep_t, s, tn);
+    return narrow_in(c, nl - 1) ? launch_ntt_fwd_rescale_t(c, c->fp_mask, last, lift, in, out, nl, keep_t, s, tn)
+                                : launch_ntt_fwd_rescale_t(c, NoFp{}, last, lift, in, out, nl, keep_t, s, tn);
 }
 
 template <typename Fp>
@@ -694,7 +700,7 @@ static int launch_intt_first_t(const rf_ctx *c, Fp fpm, const uint64_t *a, const
 
 int launch_intt_first(const rf_ctx *c, const uint64_t *a, const uint64_t *b, uint64_t *dc, uint32_t galois,
                       uint32_t nl, hipStream_t s, const rf_tuning *tn) {
-    return c->fp_mask.any() ? launch_intt_first_t(c, c->fp_mask, a, b, dc, galois, nl, s, tn)
+    return narrow_in(c, nl) ? launch_intt_first_t(c, c->fp_mask, a, b, dc, galois, nl, s, tn)
                             : launch_intt_first_t(c, NoFp{}, a, b, dc, galois, nl, s, tn);
 }
 
@@ -721,8 +727,8 @@ static int launch_ntt_t(const rf_ctx *c, Fp fpm, const NttBatch &b, bool forward
 
 int launch_ntt(const rf_ctx *c, const NttBatch &b, bool forward, hipStream_t s, const PrimeConst *pcs,
                const rf_tuning *tn) {
-    return c->fp_mask.any() ? launch_ntt_t(c, c->fp_mask, b, forward, s, pcs, tn)
-                            : launch_ntt_t(c, NoFp{}, b, forward, s, pcs, tn);
+    return narrow_in(b) ? launch_ntt_t(c, c->fp_mask, b, forward, s, pcs, tn)
+                        : launch_ntt_t(c, NoFp{}, b, forward, s, pcs, tn);
 }
 
 template <int A, int B, typename Fp>
@@ -733,17 +739,22 @@ static void launch_inv_rows(const rf_ctx *c, Fp fpm, const NttBatch &b, hipStrea
                        dim3(1024 / kSmallE), 0, s, b, fpm, c->d_tw_inv, c->d_pc);
 }
 
-int launch_intt_rows(const rf_ctx *c, const NttBatch &b, hipStream_t s) {
+template <typename Fp>
+static int launch_intt_rows_t(const rf_ctx *c, Fp fpm, const NttBatch &b, hipStream_t s) {
     switch (c->log_n) {
-        case 13: launch_inv_rows<7, 6>(c, c->fp_mask, b, s); break;
-        case 14: launch_inv_rows<7, 7>(c, c->fp_mask, b, s); break;
-        case 15: launch_inv_rows<8, 7>(c, c->fp_mask, b, s); break;
-        case 16: launch_inv_rows<8, 8>(c, c->fp_mask, b, s); break;
+        case 13: launch_inv_rows<7, 6>(c, fpm, b, s); break;
+        case 14: launch_inv_rows<7, 7>(c, fpm, b, s); break;
+        case 15: launch_inv_rows<8, 7>(c, fpm, b, s); break;
+        case 16: launch_inv_rows<8, 8>(c, fpm, b, s); break;
         default: return fail(RF_EUNSUPPORTED, "INTT row pass: ring degree");
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(RF_EHIP, std::string("NTT launch: ") + hipGetErrorString(e));
     return RF_OK;
+}
+
+int launch_intt_rows(const rf_ctx *c, const NttBatch &b, hipStream_t s) {
+    return narrow_in(b) ? launch_intt_rows_t(c, c->fp_mask, b, s) : launch_intt_rows_t(c, NoFp{}, b, s);
 }
 
 template <int A, int B, bool BLK, typename Fp>
@@ -796,8 +807,8 @@ static int launch_intt_cols_t(const rf_ctx *c, Fp fpm, const NttBatch &b, hipStr
 int launch_intt_cols(const rf_ctx *c, const NttBatch &b, hipStream_t s, const PrimeConst *pcs, const rf_tuning *tn) {
     const rf_tuning &t = tn ? *tn : kDefaultTuning;
     if (!pcs) pcs = c->d_pc;
-    return c->fp_mask.any() ? launch_intt_cols_t(c, c->fp_mask, b, s, pcs, t)
-                            : launch_intt_cols_t(c, NoFp{}, b, s, pcs, t);
+    return narrow_in(b) ? launch_intt_cols_t(c, c->fp_mask, b, s, pcs, t)
+                        : launch_intt_cols_t(c, NoFp{}, b, s, pcs, t);
 }
 
 }  // namespace rf
