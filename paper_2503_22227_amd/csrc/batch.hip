@@ -347,7 +347,10 @@ __device__ __forceinline__ void ntt_batched_unit(uint64_t *lds, const NttJob &J,
         else ntt_cols_unit_t<ArInt, A, B, false, true>(lds, out, J.tw_all + t, ArInt(pc), w.tile, RawPro{out});
     } else if constexpr (PASS == kPassModup) {
         // wide primes alone, several a digit: converted by a launch of their own
-        ntt_cols_unit_t<ArInt, A, B, true, true>(lds, out, J.tw_all + t, ArInt(pc), w.tile, LoadPro{out});
+        if (w.kind == 1)
+            ntt_cols_small_t<ArInt, A, B, true, kMixTile, kMixE, true>(lds, LoadPro{out}, out, J.tw_all + t, ArInt(pc),
+                                                                       xcd_grouped_tile<kMixTile, A>(w.tile, 1 << (LOGN - 10)));
+        else ntt_cols_unit_t<ArInt, A, B, true, true>(lds, out, J.tw_all + t, ArInt(pc), w.tile, LoadPro{out});
     } else {
         constexpr int KP = PASS == kPassModdown4 ? 4 : 8;
         ntt_cols_unit_t<ArInt, A, B, true, true>(
@@ -438,15 +441,25 @@ int validate(const rf_batch_item *items, uint32_t n) {
     return RF_OK;
 }
 
-// A step's wide limbs go in 1024-residue tiles, launched before the narrow ones',
-// where the step is short, up to four rounds of the chip (4 workgroups on each
-// of 256 CUs), or they are less than an eighth of it: a 4096-residue workgroup
-// of a wide limb runs three times a narrow one's time and would end last.  In
-// longer steps with more of them the larger tile is the cheaper one (the P-limbs
-// of 64 items: 117 us against 151; their extension's rows 332 against 383).
-// Whole batches by this rule, all in 4096 and all in 1024: 4 items of N <= 2^15
-// 139, 179, 140 us; 8 of N <= 2^16 413, 509, 414; 16 748, 779, 757; 64 2607, 2633, 2697.
-constexpr uint64_t kBatchSmallBelow = 4096;
+// Job list of an NTT step: INTT of d2, NTT of ext, INTT of the P-limbs, NTT of conv.
+int list_of(int st) {
+    return st == kInttD0 || st == kInttD1 ? 0 : st == kNttExt0 || st == kNttExt1 ? 1 : st == kInttP0 || st == kInttP1 ? 2 : 3;
+}
+
+// The wide limbs of a launch (one job list, one ring degree) go in 1024-residue
+// tiles, ahead of the narrow ones', where it holds fewer 4096-residue tiles than two
+// a CU: a 4096-residue workgroup of a wide limb runs three times a narrow one's time
+// and would end last.  Fuller launches are bound by what all of them issue, of
+// which the larger tile takes less.  Row passes in 4096 and in 1024, tiles (wide ones
+// among them): P-limbs 64 11.1 and 7.5 us, 256 13.0 and 12.6, 512 18.2 and 20.5, 1024
+// 28.6 and 34.1; extension 144 (72) 11.4 and 9.4, 576 (288) 16.9 and 17.8, 1152 (960)
+// 27.3 and 32.1, 4608 (3840) 73 and 104; ModDown's 192 (48) 15.5 and 14.2, 768 (192)
+// 21.8 and 24.5.  The pass that forms d2 = a1 b1 gains from the smaller ones while they
+// are few: 768 (64) 23.6 and 18.7, 1536 (384) 37.5 and 33.5, 1536 (1152) 41.2 and 44.2.
+constexpr uint64_t kBatchSmallBelow = 512;
+bool batch_small(int list, uint64_t wide, uint64_t tiles) {
+    return tiles < kBatchSmallBelow || (list == 0 && wide * 3 <= tiles);
+}
 
 // Units of a pass over np polynomials of `limbs` limbs, n_wide of them wide, those
 // in tiles of 1024 residues if small (batch_unit), else all in 4096.
@@ -463,13 +476,14 @@ uint32_t stage_units(const rf_ctx *c, uint32_t nl, int stage, uint32_t chunk, bo
         case kTensor: return 0;  // formed by the INTT of d2 and the inner product
         case kInttD0: case kInttD1: return limb_units(c, nl, c->q_order[nl].n_wide, 1, small);
         case kModupConv: return fused ? 0 : dn * modup_chunks(nl, c->K, chunk) * chunks;
-        case kNttExt0: return fused ? c->modup_units[nl].n * (c->n / kMixTile) : ext * (c->n / kTile);
+        case kNttExt0:
+            return fused ? c->modup_units[nl].n * (c->n / kMixTile) : limb_units(c, ext, ext, 1, small);
         case kNttExt1: return limb_units(c, ext, c->ext_order[nl].n_wide, 1, small);
         case kInnerProduct: return (nl + c->K) * chunks;
         case kInttP0: case kInttP1: return limb_units(c, c->K, c->p_order.n_wide, 2, small);
         case kModdownConv: return 0;  // computed in the first pass of NTT(conv)
         case kNttConv0:
-            return c->fp_mask.any() ? 2 * c->moddown_units[nl].n * (c->n / kMixTile) : 2 * nl * (c->n / kTile);
+            return c->fp_mask.any() || small ? 2 * c->moddown_units[nl].n * (c->n / kMixTile) : 2 * nl * (c->n / kTile);
         case kNttConv1: return limb_units(c, nl, c->q_order[nl].n_wide, 2, small);
         case kTail: return 0;  // applied by the last pass of NTT(conv)
     }
@@ -518,9 +532,7 @@ int enqueue(rf_batch *p, hipStream_t s, bool profile) {
                     g = std::max(1u, std::min(units, (uint32_t)(((uint64_t)p->grid[st] * units + total - 1) / total)));
                 const uint32_t per = (units + g - 1) / g;
                 const uint32_t blocks = (units + per - 1) / per;
-                const int k = st == kInttD0 || st == kInttD1 ? 0 : st == kNttExt0 || st == kNttExt1 ? 1
-                            : st == kInttP0 || st == kInttP1 ? 2 : 3;
-                const NttJob *jobs = p->d_ntt[k] + G.job0;
+                const NttJob *jobs = p->d_ntt[list_of(st)] + G.job0;
                 const uint32_t nj = G.job1 - G.job0, u0 = G.unit0[st];
 #define RF_BLK(A, B, PASS)                                                                                       \
     if (per == 1)                                                                                                \
@@ -580,17 +592,23 @@ void build_tables(rf_batch *p, std::vector<KsJob> &jobs, std::vector<NttJob> (&n
     for (uint32_t i = 0; i < n; ++i) order[i] = i;
     std::stable_sort(order.begin(), order.end(),
                      [&](uint32_t x, uint32_t y) { return items[x].ctx->log_n < items[y].ctx->log_n; });
-    bool small[kStages];
-    for (int st = 0; st < kStages; ++st) {
-        uint64_t tiles = 0, more = 0;  // in 4096-residue tiles; what small ones would add, 3 for each wide tile
-        for (uint32_t i = 0; i < n; ++i) {
-            const rf_ctx *c = items[i].ctx;
-            const uint32_t t = stage_units(c, items[i].n_limbs, st, p->modup_chunk, false);
-            tiles += t;
-            more += stage_units(c, items[i].n_limbs, st, p->modup_chunk, true) - t;
+    // the tiles of the wide limbs of each launch
+    bool small[17][4] = {};
+    for (uint32_t ln = 13; ln <= 16; ++ln)
+        for (int k = 0; k < 4; ++k) {
+            uint64_t wide = 0, all = 0;  // 4096-residue tiles
+            for (uint32_t i = 0; i < n; ++i) {
+                const rf_ctx *c = items[i].ctx;
+                if (c->log_n != ln) continue;
+                const uint32_t nl = items[i].n_limbs, tiles = c->n / kTile;
+                const uint32_t limbs[4] = {nl, c->modup_levels[nl].ext_limbs, 2 * c->K, 2 * nl};
+                const uint32_t nw[4] = {c->q_order[nl].n_wide, c->ext_order[nl].n_wide, 2 * c->p_order.n_wide,
+                                        2 * c->q_order[nl].n_wide};
+                wide += (uint64_t)nw[k] * tiles;
+                all += (uint64_t)limbs[k] * tiles;
+            }
+            small[ln][k] = batch_small(k, wide, all);
         }
-        small[st] = tiles < kBatchSmallBelow || more * 8 < tiles * 3;
-    }
     std::vector<rf_batch::Group> groups;
     for (uint32_t i = 0; i < n; ++i) {
         const rf_batch_item &it = items[order[i]];
@@ -634,7 +652,7 @@ void build_tables(rf_batch *p, std::vector<KsJob> &jobs, std::vector<NttJob> (&n
         J.alpha = c->alpha;
         for (int st = 0; st < kStages; ++st) {
             J.unit_begin[st] = acc[st];
-            acc[st] += stage_units(c, nl, st, p->modup_chunk, small[st] && c->fp_mask.any());
+            acc[st] += stage_units(c, nl, st, p->modup_chunk, small[c->log_n][list_of(st)]);
         }
         const uint64_t ipstride = (uint64_t)(nl + c->K) * N;
         NttBatch bd{J.d_coeff, J.d_coeff, 0, 0, nl, 1, 0, nullptr, c->order(c->q_order[nl])};
@@ -653,12 +671,12 @@ void build_tables(rf_batch *p, std::vector<KsJob> &jobs, std::vector<NttJob> (&n
             ntt[k][i].pcs = k == 0 ? pc_modup(c, nl) : k == 2 ? c->d_pc_md : c->d_pc;
             ntt[k][i].log_n = c->log_n;
             for (int pass = 0; pass < 2; ++pass) ntt[k][i].unit_begin[pass] = J.unit_begin[first_stage[k] + pass];
-            ntt[k][i].small = small[first_stage[k] + 1] && c->fp_mask.any();
+            ntt[k][i].small = small[c->log_n][k];
             if (k == 1 && modup_fused(c, true)) {
                 ntt[k][i].units = c->d_units + c->modup_units[nl].off;
                 ntt[k][i].frag = c->d_conv_mu;
                 ntt[k][i].off = c->d_conv_mu_off;
-            } else if (k == 3 && c->fp_mask.any()) {
+            } else if (k == 3 && (c->fp_mask.any() || small[c->log_n][k])) {
                 ntt[k][i].units = c->d_units + c->moddown_units[nl].off;
                 ntt[k][i].frag = c->d_conv_md;
                 ntt[k][i].off = c->d_conv_md_off;
