@@ -250,17 +250,17 @@ __device__ __forceinline__ BatchUnit batch_unit(const NttJob &J, uint32_t local)
     return u;
 }
 
-template <int A, int B, bool FWD, typename Pro, typename Epi>
+template <int A, int B, bool FWD, typename Fp, typename Pro, typename Epi>
 __device__ __forceinline__ void batch_rows(uint64_t *lds, const NttJob &J, const BatchUnit &u, const PrimeConst &pc,
                                            const Pro &pro, const Epi &epi) {
     const size_t t = (size_t)u.g << (A + B);
-    if (u.kind == 2) ntt_rows_unit_t<ArFp, A, B, FWD>(lds, pro, J.tw_rows + t, ArFp(pc), u.tile, epi);
+    if (!std::is_same_v<Fp, NoFp> && u.kind == 2) ntt_rows_unit_t<ArFp, A, B, FWD>(lds, pro, J.tw_rows + t, ArFp(pc), u.tile, epi);
     else if (u.kind == 1) ntt_rows_small_t<ArInt, A, B, FWD, kMixTile, kMixE>(lds, pro, J.tw_all + t, ArInt(pc), u.tile, epi);
     else ntt_rows_unit_t<ArInt, A, B, FWD>(lds, pro, J.tw_rows + t, ArInt(pc), u.tile, epi);
 }
 
 // Column pass with a ModUp conversion: unit `local` of the extension's units.
-template <int A, int B, int KP>
+template <int A, int B, int KP, typename Fp>
 __device__ __forceinline__ void batch_modup(uint64_t *lds, const NttJob &J, uint32_t local) {
     constexpr int LOGN = A + B, TL = LOGN - 10;
     const int tile = xcd_grouped_tile<kMixTile, A>(local & ((1 << TL) - 1), 1 << TL);
@@ -268,14 +268,14 @@ __device__ __forceinline__ void batch_modup(uint64_t *lds, const NttJob &J, uint
     const uint32_t j = un->digit, s = un->size, blk = j * J.alpha + s - 1;
     const uint64_t *src = J.x + ((size_t)j * J.alpha << LOGN);
     uint64_t *dst = J.b.out + ((size_t)j * (J.nl + J.K - J.alpha) << LOGN);
-    if (un->wide) {
+    if (std::is_same_v<Fp, NoFp> || un->wide) {
         const uint32_t li = un->e[0] & 0xffffu, g = un->e[0] >> 16;
         const PrimeConst pc = J.pcs[g];
         const ModupColsPro<KP> pro = modup_cols_pro<KP, LOGN>(
             src, s, J.modup_tab + blk * J.modup_stride + 2 * J.alpha + (size_t)g * J.alpha, pc);
         ntt_cols_small_t<ArInt, A, B, true, kMixTile, kMixE, true>(lds, pro, dst + ((size_t)li << LOGN),
                                                                    J.tw_all + ((size_t)g << LOGN), ArInt(pc), tile);
-    } else {
+    } else if constexpr (!std::is_same_v<Fp, NoFp>) {
         const size_t b = (size_t)blk * (J.L + J.K);
         conv_cols_narrow<A, B, KP, false, true>(lds, src, s, nullptr, J.frag + b * (64 * KP), J.off + b, J.tw_all, J.pcs,
                                                 un, dst, tile);
@@ -283,14 +283,14 @@ __device__ __forceinline__ void batch_modup(uint64_t *lds, const NttJob &J, uint
 }
 
 // One pass over unit u of a job.
-template <int A, int B, int PASS>
+template <int A, int B, int PASS, typename Fp>
 __device__ __forceinline__ void ntt_batched_unit(uint64_t *lds, const NttJob &J, uint32_t u) {
     constexpr int LOGN = A + B;
     const uint32_t local = u - J.unit_begin[pass_second(PASS)];
     if constexpr (PASS == kPassModup) {
         if (J.units) {
-            if (J.alpha <= 4) batch_modup<A, B, 4>(lds, J, local);
-            else batch_modup<A, B, 8>(lds, J, local);
+            if (J.alpha <= 4) batch_modup<A, B, 4, Fp>(lds, J, local);
+            else batch_modup<A, B, 8, Fp>(lds, J, local);
             return;
         }
     }
@@ -302,13 +302,13 @@ __device__ __forceinline__ void ntt_batched_unit(uint64_t *lds, const NttJob &J,
             const uint32_t w = local >> TL, poly = w & 1;
             const ConvUnit *un = J.units + (w >> 1);
             uint64_t *dst = J.b.out + ((size_t)poly * J.nl << LOGN);
-            if (un->wide) {
+            if (std::is_same_v<Fp, NoFp> || un->wide) {
                 const uint32_t i = un->e[0] & 0xffffu;
                 const PrimeConst pc = J.pcs[i];
                 ntt_cols_small_t<ArInt, A, B, true, kMixTile, kMixE, true>(
                     lds, moddown_pro<KP, LOGN>(J.ip, J.pcs, pc, J.md_cross, J.md_negp, poly, i, J.nl, J.L, J.K),
                     dst + ((size_t)i << LOGN), J.tw_all + ((size_t)i << LOGN), ArInt(pc), tile);
-            } else {
+            } else if constexpr (!std::is_same_v<Fp, NoFp>) {
                 const uint64_t *src = J.ip + (((size_t)poly * (J.nl + J.K) + J.nl) << LOGN);
                 if (KP == 4 || J.K <= 4)
                     conv_cols_narrow<A, B, 4, true, true>(lds, src, J.K, J.pcs + J.L, J.frag, J.off, J.tw_all, J.pcs, un,
@@ -328,19 +328,19 @@ __device__ __forceinline__ void ntt_batched_unit(uint64_t *lds, const NttJob &J,
         // d2 = a1 b1 of limb li
         const size_t poly1 = ((size_t)J.nl + w.li) << LOGN;
         const TensorPro pro{J.ct_a + poly1, J.ct_b + poly1, pc.q, pc.r64, pc.r64_p, pc.one_p};
-        batch_rows<A, B, false>(lds, J, w, pc, pro, BlkRawEpi{out});
+        batch_rows<A, B, false, Fp>(lds, J, w, pc, pro, BlkRawEpi{out});
     } else if constexpr (PASS == kPassInvRows) {
-        batch_rows<A, B, false>(lds, J, w, pc, LoadPro{out}, BlkRawEpi{out});
+        batch_rows<A, B, false, Fp>(lds, J, w, pc, LoadPro{out}, BlkRawEpi{out});
     } else if constexpr (PASS == kPassFwdRows) {
-        batch_rows<A, B, true>(lds, J, w, pc, BlkRawPro{out}, StoreEpi{out});
+        batch_rows<A, B, true, Fp>(lds, J, w, pc, BlkRawPro{out}, StoreEpi{out});
     } else if constexpr (PASS == kPassTail) {
         // limb li of polynomial poly of conv [2][nl][N]: ModDown tail into out
         const size_t lo = ((size_t)w.poly * (J.nl + J.K) + w.li) << LOGN;
         const size_t oo = ((size_t)w.poly * J.nl + w.li) << LOGN;
-        batch_rows<A, B, true>(lds, J, w, pc, BlkRawPro{out},
+        batch_rows<A, B, true, Fp>(lds, J, w, pc, BlkRawPro{out},
                                ModdownFoldEpi{J.ip + lo, J.out + oo, J.pinv[2 * w.li], J.pinv[2 * w.li + 1], pc.q});
     } else if constexpr (PASS == kPassInvCols) {
-        if (w.kind == 2) ntt_cols_unit_t<ArFp, A, B, false, true>(lds, out, J.tw_all + t, ArFp(pc), w.tile, RawPro{out});
+        if (!std::is_same_v<Fp, NoFp> && w.kind == 2) ntt_cols_unit_t<ArFp, A, B, false, true>(lds, out, J.tw_all + t, ArFp(pc), w.tile, RawPro{out});
         else if (w.kind == 1)
             ntt_cols_small_t<ArInt, A, B, false, kMixTile, kMixE, true>(lds, RawPro{out}, out, J.tw_all + t, ArInt(pc),
                                                                         xcd_grouped_tile<kMixTile, A>(w.tile, 1 << (LOGN - 10)));
@@ -367,18 +367,18 @@ __device__ __forceinline__ void ntt_batched_unit(uint64_t *lds, const NttJob &J,
 // units; otherwise each takes one unit (per_wg == 1).  The loop keeps every
 // path's addresses in registers: at 2 waves per SIMD it hardly spills (at 4, 52 to 143
 // registers: 64 items of N = 2^14..2^16 with 2048 workgroups a launch 5085 us, and 3858).
-template <int A, int B, int PASS, bool LOOP>
+template <int A, int B, int PASS, bool LOOP, typename Fp>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(LOOP ? 2 : PASS == kPassModdown8 ? 3 : ntt_waves(pass_cols(PASS) ? A : B)))) void ntt_batched_kernel(
     const NttJob *__restrict__ jobs, uint32_t njobs, uint32_t unit0, uint32_t total, uint32_t per_wg) {
     constexpr bool COLS = pass_cols(PASS);
     constexpr int kTileWords = COLS ? (1 << A) * (kTile / (1 << A) + 1) : (1 << B) * (kTile / (1 << B) + 1);
-    constexpr int kConvWords = COLS ? conv_lds<A, FpMask>() : 0;
+    constexpr int kConvWords = COLS ? conv_lds<A, Fp>() : 0;
     __shared__ uint64_t lds[kTileWords > kConvWords ? kTileWords : kConvWords];
     constexpr int pass = pass_second(PASS);
     if constexpr (!LOOP) {
         if (blockIdx.x >= total) return;
         const uint32_t u = unit0 + blockIdx.x;
-        ntt_batched_unit<A, B, PASS>(lds, global_job(jobs[find_job(jobs, njobs, u, pass)]), u);
+        ntt_batched_unit<A, B, PASS, Fp>(lds, global_job(jobs[find_job(jobs, njobs, u, pass)]), u);
     } else {
         const uint32_t u0 = unit0 + blockIdx.x * per_wg;
         const uint32_t u1 = unit0 + min(total, (blockIdx.x + 1) * per_wg);
@@ -386,7 +386,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(LOOP ?
         uint32_t j = find_job(jobs, njobs, u0, pass);
         for (uint32_t u = u0; u < u1; ++u) {
             while (j + 1 < njobs && jobs[j + 1].unit_begin[pass] <= u) ++j;
-            ntt_batched_unit<A, B, PASS>(lds, global_job(jobs[j]), u);
+            ntt_batched_unit<A, B, PASS, Fp>(lds, global_job(jobs[j]), u);
         }
     }
 }
@@ -403,6 +403,10 @@ struct rf_batch {
     struct Group {
         uint32_t log_n, job0, job1;
         bool k4;  // every item has 4 special primes (the specialised ModDown prologue)
+        // no item has a narrow prime: kernels of the integer code alone (a workgroup a
+        // unit), 14 limbs of 55 bits at N = 2^15, 8 items 884 and 873 us, 12 of 60 bits at
+        // N = 2^16, 8 items 624 and 616
+        bool wide;
         uint32_t unit0[kStages], units[kStages];
     };
     std::vector<Group> groups;
@@ -535,10 +539,12 @@ int enqueue(rf_batch *p, hipStream_t s, bool profile) {
                 const NttJob *jobs = p->d_ntt[list_of(st)] + G.job0;
                 const uint32_t nj = G.job1 - G.job0, u0 = G.unit0[st];
 #define RF_BLK(A, B, PASS)                                                                                       \
-    if (per == 1)                                                                                                \
-        hipLaunchKernelGGL((ntt_batched_kernel<A, B, PASS, false>), blocks, kThreads, 0, s, jobs, nj, u0, units, per); \
+    if (per == 1 && G.wide)                                                                                      \
+        hipLaunchKernelGGL((ntt_batched_kernel<A, B, PASS, false, NoFp>), blocks, kThreads, 0, s, jobs, nj, u0, units, per); \
+    else if (per == 1)                                                                                           \
+        hipLaunchKernelGGL((ntt_batched_kernel<A, B, PASS, false, FpMask>), blocks, kThreads, 0, s, jobs, nj, u0, units, per); \
     else                                                                                                         \
-        hipLaunchKernelGGL((ntt_batched_kernel<A, B, PASS, true>), blocks, kThreads, 0, s, jobs, nj, u0, units, per)
+        hipLaunchKernelGGL((ntt_batched_kernel<A, B, PASS, true, FpMask>), blocks, kThreads, 0, s, jobs, nj, u0, units, per)
 #define RF_BL(A, B)                                                                                              \
     switch (st) {                                                                                                \
         case kInttD0: RF_BLK(A, B, kPassTensor); break;                                                          \
@@ -621,11 +627,12 @@ void build_tables(rf_batch *p, std::vector<KsJob> &jobs, std::vector<NttJob> (&n
             rf_batch::Group G{};
             G.log_n = c->log_n;
             G.job0 = i;
-            G.k4 = true;
+            G.k4 = G.wide = true;
             for (int st = 0; st < kStages; ++st) G.unit0[st] = acc[st];
             groups.push_back(G);
         }
         if (c->K != 4) groups.back().k4 = false;
+        if (c->fp_mask.any()) groups.back().wide = false;
         const uint32_t nl = it.n_limbs;
         const size_t N = c->n;
         const ModupLevel &lv = c->modup_levels[nl];
