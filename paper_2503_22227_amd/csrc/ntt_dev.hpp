@@ -111,8 +111,11 @@ struct ArInt {
 
 // ArFp (primes below kFpPrimeBound): whole numbers in doubles (FpMod), 8 FP64
 // operations per butterfly against about 30 integer ones.  Forward, x grows by
-// at most 0.75q per stage, so from inputs below 4q every value of both passes
-// stays below 16q < 2^50.  Inverse, the sums double per stage; a round of C
+// at most 0.75q per stage, 12q over both passes of N = 2^16 and 9q at N = 2^12: from
+// inputs below 4q (12q at N = 2^12, where a digit's conversion is a sum of products)
+// every value stays below 21q < 2^51, the range mul and red take.  An input may
+// also be a whole number of any prime's size (a lift, below 2^46): + 12q is below
+// 2^51 as well.  Inverse, the sums double per stage; a round of C
 // stages ends by reducing the values that were sums in its last two stages (a
 // quarter of them, red()), so that every round starts below 1.5q and its
 // sums stay below 24q < 2^51.
@@ -602,8 +605,8 @@ __device__ __forceinline__ void ntt_rows_small(uint64_t *lds, const uint64_t *in
 // starts, which keeps the multi-pass batched kernels within their register
 // budget.
 // A thread of a 4096-residue tile fetches all its twiddles with its residues
-// where they fit the registers: 30 doubles in FP64 (60 pairs of integers do
-// not).  Fetched stage by stage, each stage waits for the table: the passes of 24
+// where they fit the registers: 30 doubles in FP64 (30 pairs of integers, twice
+// that, do not).  Fetched stage by stage, each stage waits for the table: the passes of 24
 // to 60 limbs at N = 2^16 take 2 to 9 % longer.
 template <typename Ar>
 __device__ __forceinline__ constexpr int tile_tw() {

@@ -198,10 +198,15 @@ struct IpPro {
     }
     __device__ __forceinline__ double fp(size_t idx, const FpMod &f) const {
         double acc = 0.0;
+        // 32 digits at a time: below 33 * 0.75 q < 2^51, red's range
+        for (uint32_t j0 = 0; j0 < dn; j0 += 32) {
+            const uint32_t j1 = min(dn, j0 + 32);
 #pragma unroll 2
-        for (uint32_t j = 0; j < dn; ++j)
-            acc += f.mul(FpMod::from_u52(src(j, idx)), FpMod::from_u52(key[j * key_stride + idx]));
-        return f.red(acc);
+            for (uint32_t j = j0; j < j1; ++j)
+                acc += f.mul(FpMod::from_u52(src(j, idx)), FpMod::from_u52(key[j * key_stride + idx]));
+            acc = f.red(acc);
+        }
+        return acc;
     }
 };
 
