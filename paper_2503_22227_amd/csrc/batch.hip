@@ -41,6 +41,8 @@
 
 namespace rf {
 
+// The numbers are rf_batch_set_grid's.  kTensor, kModdownConv and kTail have no
+// work units: their work runs inside the passes next to them.
 enum BatchStage {
     kTensor = 0,
     kInttD0, kInttD1,       // INTT of d2: row pass, column pass
@@ -57,11 +59,10 @@ enum BatchStage {
 struct KsJob {
     const uint64_t *a, *b, *evk;
     uint64_t *out;
-    uint64_t *d2, *d_coeff, *ext, *ip, *conv;
+    uint64_t *d_coeff, *ext, *ip, *conv;
     const PrimeConst *pcs;
     const uint64_t *modup_tab;
     uint64_t modup_stride;
-    const uint64_t *moddown_tab;
     const uint64_t *pinv;
     uint32_t log_n, nl, L, K, alpha;
     uint32_t unit_begin[kStages];
@@ -119,14 +120,12 @@ __device__ __forceinline__ KsJob global_job(const KsJob &J) {
     g.b = gptr(J.b);
     g.evk = gptr(J.evk);
     g.out = gptr(J.out);
-    g.d2 = gptr(J.d2);
     g.d_coeff = gptr(J.d_coeff);
     g.ext = gptr(J.ext);
     g.ip = gptr(J.ip);
     g.conv = gptr(J.conv);
     g.pcs = gptr(J.pcs);
     g.modup_tab = gptr(J.modup_tab);
-    g.moddown_tab = gptr(J.moddown_tab);
     g.pinv = gptr(J.pinv);
     return g;
 }
@@ -180,23 +179,16 @@ __global__ __launch_bounds__(kEw) void ks_batched_kernel(const KsJob *__restrict
         const uint32_t local = u - J.unit_begin[STAGE];
         const uint32_t cshift = J.log_n - 8;  // N / 256 blocks per row
         const uint32_t gy = local >> cshift, gx = local & ((1u << cshift) - 1);
-        if constexpr (STAGE == kTensor) {
-            tensor_unit(J.a, J.b, J.out, J.d2, J.pcs, J.log_n, J.nl, nullptr, gx, gy);
-        } else if constexpr (STAGE == kModupConv) {
+        if constexpr (STAGE == kModupConv) {
             modup_bconv_unit<true, CH>(J.d_coeff, J.ext, J.pcs, J.modup_tab, J.modup_stride, J.log_n, J.nl, J.L, J.K, J.alpha,
                              gx, gy);
-        } else if constexpr (STAGE == kInnerProduct) {
+        } else {
             IpFold f;
             f.pinv = J.pinv;
             f.mode = 1;
             f.a = J.a;
             f.b = J.b;
-            inner_product_unit<1>(J.d2, J.ext, J.evk, J.ip, J.pcs, J.log_n, J.nl, J.L, J.K, J.alpha, gx, gy, f);
-        } else if constexpr (STAGE == kModdownConv) {
-            moddown_bconv_unit(J.ip, J.conv, J.pcs, J.moddown_tab, J.log_n, J.nl, J.L, J.K, gx, gy);
-        } else if constexpr (STAGE == kTail) {
-            const size_t poly = (size_t)J.nl << J.log_n;
-            moddown_tail_unit(J.ip, J.conv, J.out, J.out + poly, J.out, J.pcs, J.pinv, J.log_n, J.nl, J.K, gx, gy);
+            inner_product_unit<1>(nullptr, J.ext, J.evk, J.ip, J.pcs, J.log_n, J.nl, J.L, J.K, J.alpha, gx, gy, f);
         }
     }
 }
@@ -424,6 +416,7 @@ struct rf_batch {
 
 namespace {
 
+// (nl of them spare)
 size_t item_ws_limbs(const rf_ctx *c, uint32_t nl) {
     const ModupLevel &lv = c->modup_levels[nl];
     return (size_t)nl + (size_t)nl + lv.ext_limbs + 2 * (size_t)(nl + c->K) + 2 * (size_t)nl;
@@ -504,15 +497,13 @@ int enqueue(rf_batch *p, hipStream_t s, bool profile) {
         const uint32_t total = p->total[st];
         if (total == 0) continue;
         ProfScope prof(profile ? names[st] : nullptr, s);
-        const bool ntt_step = st != kTensor && st != kModupConv && st != kInnerProduct && st != kModdownConv &&
-                              st != kTail;
+        const bool ntt_step = st != kModupConv && st != kInnerProduct;
         if (!ntt_step) {
             const uint32_t g = p->grid[st] == 0 ? total : std::min(total, p->grid[st]);
             const uint32_t per = (total + g - 1) / g;
             const uint32_t blocks = (total + per - 1) / per;
             const uint32_t nj = p->n_items;
             switch (st) {
-                case kTensor: hipLaunchKernelGGL(ks_batched_kernel<kTensor>, blocks, kEw, 0, s, p->d_jobs, nj, total, per); break;
                 case kModupConv:
                     if (p->modup_chunk == 4)
                         hipLaunchKernelGGL((ks_batched_kernel<kModupConv, 4>), blocks, kEw, 0, s, p->d_jobs, nj, total, per);
@@ -522,8 +513,6 @@ int enqueue(rf_batch *p, hipStream_t s, bool profile) {
                         hipLaunchKernelGGL((ks_batched_kernel<kModupConv, 8>), blocks, kEw, 0, s, p->d_jobs, nj, total, per);
                     break;
                 case kInnerProduct: hipLaunchKernelGGL(ks_batched_kernel<kInnerProduct>, blocks, kEw, 0, s, p->d_jobs, nj, total, per); break;
-                case kModdownConv: hipLaunchKernelGGL(ks_batched_kernel<kModdownConv>, blocks, kEw, 0, s, p->d_jobs, nj, total, per); break;
-                case kTail: hipLaunchKernelGGL(ks_batched_kernel<kTail>, blocks, kEw, 0, s, p->d_jobs, nj, total, per); break;
             }
         } else {
             // one launch per ring degree; the step's workgroups are shared out in
@@ -641,8 +630,7 @@ void build_tables(rf_batch *p, std::vector<KsJob> &jobs, std::vector<NttJob> (&n
         J.b = it.b;
         J.evk = it.rlk;
         J.out = it.out;
-        J.d2 = w;
-        J.d_coeff = J.d2 + (size_t)nl * N;
+        J.d_coeff = w;
         J.ext = J.d_coeff + (size_t)nl * N;
         J.ip = J.ext + (size_t)lv.ext_limbs * N;
         J.conv = J.ip + 2 * (size_t)(nl + c->K) * N;
@@ -650,7 +638,7 @@ void build_tables(rf_batch *p, std::vector<KsJob> &jobs, std::vector<NttJob> (&n
         J.pcs = c->d_pc;
         J.modup_tab = c->d_modup;
         J.modup_stride = c->modup_stride;
-        J.moddown_tab = c->scheme == RF_BGV ? c->d_moddown_t : c->d_moddown;
+        const uint64_t *moddown_tab = c->scheme == RF_BGV ? c->d_moddown_t : c->d_moddown;
         J.pinv = c->d_moddown + moddown_pinv_off(c);
         J.log_n = c->log_n;
         J.nl = nl;
@@ -697,8 +685,8 @@ void build_tables(rf_batch *p, std::vector<KsJob> &jobs, std::vector<NttJob> (&n
             ntt[k][i].ip = J.ip;
             ntt[k][i].out = J.out;
             ntt[k][i].pinv = J.pinv;
-            ntt[k][i].md_cross = J.moddown_tab + moddown_cross_off(c);
-            ntt[k][i].md_negp = J.moddown_tab + moddown_negp_off(c);
+            ntt[k][i].md_cross = moddown_tab + moddown_cross_off(c);
+            ntt[k][i].md_negp = moddown_tab + moddown_negp_off(c);
             ntt[k][i].nl = nl;
             ntt[k][i].K = c->K;
             ntt[k][i].L = c->L;

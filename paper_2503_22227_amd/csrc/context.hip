@@ -577,7 +577,7 @@ extern "C" int rf_ctx_create(const rf_params *p, int device, rf_ctx **out) {
     for (uint32_t nl = 1; nl <= c->L; ++nl) {
         const ModupLevel &lv = c->modup_levels[nl];
         c->modup_units[nl].off = (uint32_t)units.size();
-        for (int narrow = 0; narrow < 2; ++narrow) {
+        for (int narrow = 0; narrow < 2 && modup_fused(c, true); ++narrow) {  // (no other reads them)
             uint32_t at = lv.pmap_off;
             for (uint32_t j = 0; j < lv.dnum; ++j) {
                 const uint32_t sz = std::min(A, nl - j * A), n = nl - sz + c->K;

@@ -34,10 +34,8 @@ __device__ __forceinline__ void tensor_unit(const uint64_t *__restrict__ a, cons
 // targets over several units multiplies the parallelism of the conversion
 // (its inputs are re-read, from L2, and where not pre-scaled re-scaled per
 // chunk, which is cheap next to the chunk's multiply-accumulates) and lets the
-// unrolled target loop prefetch its uniform constants.
-constexpr int kConvChunk = 8;
-// ModUp targets per thread (the conversion's limb grouping; rf_tuning picks
-// 4, 8 or 16 per level).  Measured at N = 2^16, 24 + 4 primes, alpha = 8 (20
+// unrolled target loop prefetch its uniform constants.  ModUp targets per thread
+// (the conversion's limb grouping; rf_tuning picks 4, 8 or 16 per level).  Measured at N = 2^16, 24 + 4 primes, alpha = 8 (20
 // targets per digit): 8 targets 18.4 us, 10 targets 19.1 us, 20 targets 24.8 us
 // per launch (fewer, longer waves hide less latency).
 constexpr int kModupChunk = 8;
@@ -45,7 +43,6 @@ constexpr int kModupChunk = 8;
 __host__ __device__ inline uint32_t modup_chunks(uint32_t nl, uint32_t K, uint32_t chunk) {
     return (nl + K - 1 + chunk - 1) / chunk;
 }
-__host__ __device__ inline uint32_t moddown_chunks(uint32_t nl) { return (nl + kConvChunk - 1) / kConvChunk; }
 
 // ModUp conversion of one chunk of targets for a digit of S primes (S a
 // compile-time constant, so the S multiply-accumulates per target are fully
@@ -271,84 +268,6 @@ __device__ __forceinline__ void inner_product_unit(const uint64_t *__restrict__ 
     }
     store_v<V>(ip + ((size_t)m << log_n) + n, r0);
     store_v<V>(ip + out_poly + ((size_t)m << log_n) + n, r1);
-}
-
-// ModDown conversion of one chunk of Q targets from KP special primes
-// (compile-time), centred digits.
-template <int KP>
-__device__ __forceinline__ void moddown_conv_k(const uint64_t *__restrict__ src, uint64_t *__restrict__ dst,
-                                               const PrimeConst *__restrict__ pcs, const uint64_t *__restrict__ tab,
-                                               uint32_t i0, uint32_t nl, uint32_t L, uint32_t log_n) {
-    const uint64_t *cross = tab + 2 * KP;
-    const uint64_t *negp = tab + 2 * KP + (size_t)KP * L + 2 * (size_t)L;
-    uint32_t yl[KP], yh[KP];
-    uint64_t cnt = 0;
-#pragma unroll
-    for (int a = 0; a < KP; ++a) {
-        const uint64_t p = pcs[L + a].q;
-        const uint64_t y = shoup(src[(size_t)a << log_n], tab[2 * a], tab[2 * a + 1], p);
-        cnt += y > (p >> 1) ? 1u : 0u;
-        yl[a] = (uint32_t)y & 0x3fffffffu;
-        yh[a] = (uint32_t)(y >> 30);
-    }
-#pragma unroll
-    for (int k = 0; k < kConvChunk; ++k) {
-        const uint32_t i = i0 + k;
-        if (i < nl) {
-            const PrimeConst pc = pcs[i];
-            const uint64_t *ci = cross + (size_t)i * KP;
-            MacAcc acc;
-            acc.add(cnt * negp[i]);
-#pragma unroll
-            for (int a = 0; a < KP; ++a) acc.mac_split(yl[a], yh[a], ci[a]);
-            dst[(size_t)i << log_n] = reduce128_lazy(acc.value(), pc.q, pc.r64, pc.r64_p, pc.one_p);
-        }
-    }
-}
-
-// ModDown base conversion P -> Q_l with centred digits, gy = polynomial *
-// moddown_chunks + chunk.  ip = [2][nl + K][N] with the K P-limbs already in
-// the coefficient domain; conv = [2][nl][N] coefficient domain, residues in
-// [0, 4q) (a forward NTT follows).
-__device__ __forceinline__ void moddown_bconv_unit(const uint64_t *__restrict__ ip, uint64_t *__restrict__ conv,
-                                                   const PrimeConst *__restrict__ pcs,
-                                                   const uint64_t *__restrict__ tab, uint32_t log_n,
-                                                   uint32_t nl, uint32_t L, uint32_t K, uint32_t gx, uint32_t gy) {
-    const uint32_t nch = moddown_chunks(nl);
-    const uint32_t c = gy / nch, ch = gy - c * nch;
-    const uint32_t i0 = ch * kConvChunk;
-    const size_t n = (size_t)gx * kEw + threadIdx.x;
-    const uint64_t *src = ip + (((size_t)c * (nl + K) + nl) << log_n) + n;
-    uint64_t *dst = conv + (((size_t)c * nl) << log_n) + n;
-    switch (K) {
-        case 1: moddown_conv_k<1>(src, dst, pcs, tab, i0, nl, L, log_n); break;
-        case 2: moddown_conv_k<2>(src, dst, pcs, tab, i0, nl, L, log_n); break;
-        case 3: moddown_conv_k<3>(src, dst, pcs, tab, i0, nl, L, log_n); break;
-        case 4: moddown_conv_k<4>(src, dst, pcs, tab, i0, nl, L, log_n); break;
-        case 5: moddown_conv_k<5>(src, dst, pcs, tab, i0, nl, L, log_n); break;
-        case 6: moddown_conv_k<6>(src, dst, pcs, tab, i0, nl, L, log_n); break;
-        case 7: moddown_conv_k<7>(src, dst, pcs, tab, i0, nl, L, log_n); break;
-        default: moddown_conv_k<8>(src, dst, pcs, tab, i0, nl, L, log_n); break;
-    }
-}
-
-// out[c][i] = (ip[c][i] - conv[c][i]) * P^-1 mod q_i  (+ add_c[i] when add_c != null).
-// grid.y = c * nl + i.  add_c may alias out (same element is read then written).
-__device__ __forceinline__ void moddown_tail_unit(const uint64_t *__restrict__ ip,
-                                                           const uint64_t *__restrict__ conv, const uint64_t *add0,
-                                                           const uint64_t *add1, uint64_t *out,
-                                                           const PrimeConst *__restrict__ pcs,
-                                                           const uint64_t *__restrict__ pinv, uint32_t log_n,
-                                                           uint32_t nl, uint32_t K, uint32_t gx, uint32_t gy) {
-    const uint32_t c = gy / nl, i = gy - c * nl;
-    const size_t n = (size_t)gx * kEw + threadIdx.x;
-    const PrimeConst pc = pcs[i];
-    const uint64_t x = ip[(((size_t)c * (nl + K) + i) << log_n) + n];
-    const size_t off = (((size_t)c * nl + i) << log_n) + n;
-    uint64_t r = shoup(submod(x, conv[off], pc.q), pinv[2 * i], pinv[2 * i + 1], pc.q);
-    const uint64_t *add = c == 0 ? add0 : add1;
-    if (add) r = addmod(r, add[((size_t)i << log_n) + n], pc.q);
-    out[off] = r;
 }
 
 // sigma_g in the NTT domain: out[k] = in[k'] with 2 brv(k') + 1 = (2 brv(k) + 1) g mod 2N.
