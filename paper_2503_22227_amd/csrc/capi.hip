@@ -13,14 +13,11 @@ namespace {
 // 30.9 us; a launch for every run of one class took 174.
 LimbOrder window_order(const rf_ctx *c, uint32_t first, uint32_t n) {
     const rf_ctx::OrderRef &all = c->all_order;
-    uint32_t before = 0;
-    LimbOrder o;
+    uint32_t before = 0, wide = 0;
     for (uint32_t i = 0; i < first + n; ++i)
-        if (!c->fp_mask.has(i)) ++(i < first ? before : o.n_wide);
-    o.ent = c->d_order + all.off + before;
-    o.gap = (all.n_wide - before) + (first - before) - o.n_wide;
-    o.base = first;
-    return o;
+        if (!c->fp_mask.has(i)) ++(i < first ? before : wide);
+    const uint32_t gap = (all.n_wide - before) + (first - before) - wide;
+    return LimbOrder{c->d_order + all.off + before, (uint16_t)wide, (uint8_t)gap, (uint8_t)first};
 }
 
 // Key-switching workspace at level nl, in limbs of N residues:

@@ -398,7 +398,7 @@ static void launch_two_pass_blk(const rf_ctx *c, Fp fpm, const NttBatch &b, bool
         if (m.o.n_wide == b.per_poly && tiles >= wide_tiles_from(c)) {
             // primes that follow each other need no look at the order, a load ahead of
             // all others (0.4 us of the passes at N = 2^13)
-            if (!b.pmap) m.o = LimbOrder{nullptr, b.per_poly, 0, b.prime_base};
+            if (!b.pmap) m.o = LimbOrder{nullptr, (uint16_t)b.per_poly, 0, (uint8_t)b.prime_base};
             launch_mixed<A, B, false>(c, WideTiles{}, b, m, dim3(tiles), forward, s, pcs);
             return;
         }
