@@ -175,7 +175,12 @@ constexpr int ilog2(int x) { return x <= 1 ? 0 : 1 + ilog2(x >> 1); }
 // them are in flight together with the tile's own loads; kTwCached then takes
 // them from that array.  A pass with few residues per thread (the small-tile
 // passes) otherwise waits one table latency after every round's barrier.
-constexpr int kTwLoad = 0, kTwPrefetch = 1, kTwCached = 2;
+// kTwPrefetchOrdered issues them in the order of the rounds (integer row passes):
+// left to the scheduler, a first round waited for the last one's twiddles behind its
+// own (2 limbs at N = 2^16, inverse rows 7.1 us against 6.6).  The column passes'
+// few twiddles and the FP64 passes' doubles are better left to it (1 to 5 %).
+constexpr int kTwLoad = 0, kTwPrefetch = 1, kTwCached = 2, kTwPrefetchOrdered = 3;
+constexpr bool tw_prefetch(int tw) { return tw == kTwPrefetch || tw == kTwPrefetchOrdered; }
 
 // Register slots of the prefetched twiddles of a pass of S_LOG stages with E
 // residues per thread: round r, group gi, stage c, element e at
@@ -214,10 +219,10 @@ __device__ __forceinline__ void ntt_round(const Lds &lds, int t, uint32_t tw_bas
     constexpr int G = 1 << C;
     constexpr int NG = E / G;
     constexpr int DL = FWD ? (S_LOG - ST0 - C) : ST0;
-    constexpr bool RUN = TW != kTwPrefetch;
+    constexpr bool RUN = !tw_prefetch(TW);
     // twiddle (slot, table index): fetched, loaded or taken from the cache
     auto twiddle = [&](int slot, uint32_t idx) -> Tw {
-        if constexpr (TW == kTwPrefetch) {
+        if constexpr (tw_prefetch(TW)) {
             cache[slot] = tw[idx];
             return Tw{};
         } else if constexpr (TW == kTwCached) {
@@ -295,12 +300,8 @@ __device__ __forceinline__ void ntt_round(const Lds &lds, int t, uint32_t tw_bas
 }
 
 // Rounds of a size-2^S_LOG sub-transform from stage ST0 on: radix-E rounds,
-// the last one shorter when log2(E) does not divide S_LOG.  With kTwPrefetch
-// only the twiddle loads run (no barriers).  The integer passes' are issued in
-// the order of their rounds: left to the scheduler, a first round waited for the
-// last one's twiddles behind its own (2 limbs at N = 2^16, inverse rows 7.1 us
-// against 6.6; the product and modulus switch of 9 limbs of 55 bits at N = 2^15
-// 103.6 against 100.7).  FP64 passes are 1 % slower with it.
+// the last one shorter when log2(E) does not divide S_LOG.  With a prefetch
+// only the twiddle loads run (no barriers).
 template <typename Ar, int S_LOG, int ST0, bool FWD, bool SCALE_LAST, int ROW_A, int E = kElems, int TW = kTwLoad,
           int SLOT0 = 0, typename Lds>
 __device__ __forceinline__ void ntt_rounds_from(const Lds &lds, int t, uint32_t tw_base,
@@ -311,8 +312,8 @@ __device__ __forceinline__ void ntt_rounds_from(const Lds &lds, int t, uint32_t 
     constexpr bool LAST = ST0 + C == S_LOG;
     ntt_round<Ar, S_LOG, ST0, C, FWD, SCALE_LAST && LAST, ROW_A, false, false, E, TW, SLOT0>(
         lds, t, tw_base, tw, ar, nullptr, cache);
-    if constexpr (TW != kTwPrefetch) __syncthreads();
-    else if constexpr (!Ar::kFp) __builtin_amdgcn_sched_barrier(0);
+    if constexpr (!tw_prefetch(TW)) __syncthreads();
+    else if constexpr (TW == kTwPrefetchOrdered) __builtin_amdgcn_sched_barrier(0);
     if constexpr (!LAST)
         ntt_rounds_from<Ar, S_LOG, ST0 + C, FWD, SCALE_LAST, ROW_A, E, TW, SLOT0 + E * C>(lds, t, tw_base, tw, ar,
                                                                                          cache);
@@ -551,7 +552,8 @@ __device__ __forceinline__ void ntt_rows_small_t(uint64_t *lds, const Pro &pro, 
     }
     const int u = threadIdx.x % U;
     typename Ar::Tw twc[tw_slots(B, E)];
-    ntt_rounds<Ar, B, FWD, false, 0, E, kTwPrefetch>(TileLds{lds, LDU, u}, threadIdx.x / U, (1u << A) + row0 + u, tw, ar, twc);
+    ntt_rounds<Ar, B, FWD, false, 0, E, Ar::kFp ? kTwPrefetch : kTwPrefetchOrdered>(TileLds{lds, LDU, u}, threadIdx.x / U,
+                                                                                    (1u << A) + row0 + u, tw, ar, twc);
 #pragma unroll
     for (int r = 0; r < E; ++r) {
         const int idx = threadIdx.x + r * NT;
