@@ -11,7 +11,8 @@ Single operations, per (ring degree, limb count) of a context
   * ntt_small_tile: 1024- or 2048-residue small tiles (0: by launch size);
   * ntt_small_radix: residues per thread of the small tiles, i.e. radix-4 or
     radix-8 LDS rounds (the 4096-residue tiles always run radix-16 rounds);
-  * modup_chunk: ModUp output limbs per thread (the conversion's limb grouping);
+  * modup_chunk: ModUp output limbs per thread (the conversion's limb grouping),
+    where the conversion is a launch of its own (Context.fused_modup);
   * ntt_fused_small_below: the small-tile threshold of the launches that carry
     a fused step (tensor, automorphism, ModDown conversion and tail, rescale
     lift and tail).
@@ -30,7 +31,7 @@ Both searches are coordinate descent from the defaults: each candidate value of
 one knob is timed with HIP events, and a change is kept only if it is faster
 than the best so far by more than ``min_gain`` (a relative margin, so timing
 noise does not move the setting).  Results are cached per device (architecture and
-CU count) and shape in a JSON file (RF_AUTOTUNE_CACHE, default
+CU count), shape and KERNEL_REVISION in a JSON file (RF_AUTOTUNE_CACHE, default
 ~/.cache/rnsfhe_autotune.json).  Every variant computes the same residues, so
 tuning changes speed only.
 """
@@ -41,6 +42,9 @@ import json
 import os
 
 import torch
+
+# Raised when kernels change, so that settings found on older ones are searched again.
+KERNEL_REVISION = 2
 
 # ---------------------------------------------------------------- batches
 CLASSES = {
@@ -77,7 +81,7 @@ def device_key(device=None) -> str:
 
 def shape_key(shape) -> str:
     """Key of a batch: sorted (log_n, limbs) pairs."""
-    s = ",".join("%d:%d" % x for x in sorted(shape))
+    s = "r%d," % KERNEL_REVISION + ",".join("%d:%d" % x for x in sorted(shape))
     return hashlib.sha1(s.encode()).hexdigest()[:16]
 
 
@@ -179,7 +183,7 @@ class _LevelApply:
 
 def level_key(ctx, nlimbs: int, tag: str) -> str:
     h = hashlib.sha1(",".join(str(x) for x in ctx.q + ctx.p).encode()).hexdigest()[:12]
-    return "level:%s:%d:%d:%d:%s:%s" % (ctx.scheme, ctx.log_n, nlimbs, ctx.alpha, h, tag)
+    return "level:r%d:%s:%d:%d:%d:%s:%s" % (KERNEL_REVISION, ctx.scheme, ctx.log_n, nlimbs, ctx.alpha, h, tag)
 
 
 def tune_level(ctx, nlimbs: int, workload, reps: int = 10, min_gain: float = 0.01, use_cache: bool = True,
@@ -198,7 +202,8 @@ def tune_level(ctx, nlimbs: int, workload, reps: int = 10, min_gain: float = 0.0
         return dict(hit, cached=True)
     ap = _LevelApply(ctx, nlimbs)
     ap(DEFAULT_LEVEL)
-    setting, best, trials, default_ms = _descend(LEVEL_CANDIDATES, ap, lambda: time_fn(workload, reps), min_gain,
+    knobs = {k: v for k, v in LEVEL_CANDIDATES.items() if k != "modup_chunk" or not getattr(ctx, "fused_modup", False)}
+    setting, best, trials, default_ms = _descend(knobs, ap, lambda: time_fn(workload, reps), min_gain,
                                                  log)
     res = {"setting": setting, "default": dict(DEFAULT_LEVEL), "default_ms": default_ms, "tuned_ms": best,
            "trials": len(trials)}
@@ -239,7 +244,8 @@ def tune(plan, shape, reps: int = 3, use_cache: bool = True, min_gain: float = 0
         apply(plan, hit["setting"])
         return hit["setting"]
     knobs = {cls: CANDIDATES for cls in CLASSES}
-    knobs["modup_chunk"] = MODUP_CHUNKS
+    if plan.stage_units(CLASSES["bconv"][0]) > 0:
+        knobs["modup_chunk"] = MODUP_CHUNKS
     ap = _BatchApply(plan)
     setting, best, trials, _ = _descend(knobs, ap, lambda: time_fn(lambda: plan.run(graph=True), reps, repeats=2),
                                         min_gain, log, rounds=1)
@@ -285,15 +291,16 @@ def write_table(out: str, workloads=TABLE_WORKLOADS, levels=None, reps: int = 10
     """Tune each level of each workload's chain for one operation at a time: CKKS
     HMult+Relin, rescale and HRotate; BGV HMult+Relin, modulus switch and HRotate;
     BFV HMult+Relin and HRotate (at all L limbs, the only level BFV runs at).
-    Settings that differ from the defaults are merged into this device's entry of
-    ``out``; with ``levels`` given, a level in between takes the setting of the
+    Settings that differ from the defaults take the place of the workload's entries
+    for this device in ``out``; with ``levels`` given, a level in between takes the setting of the
     tuned level below it."""
     import synthetic
     from .fhe import Context
     from .params import chain_for
 
     dkey = device_key()
-    table = {}
+    table, searched = {}, []
+    unused_chunk = set()  # not searched: what is there stays, for chains of wide primes of that shape
     saved = os.environ.get("RF_NO_SHIPPED_TUNING")
     os.environ["RF_NO_SHIPPED_TUNING"] = "1"  # search from the defaults
     for wname, lns in workloads:
@@ -309,6 +316,7 @@ def write_table(out: str, workloads=TABLE_WORKLOADS, levels=None, reps: int = 10
         gen = torch.Generator(device="cuda")
         gen.manual_seed(w["seed"] + 11)
         for ln in lns:
+            searched += [shipped_key(scheme, ln, w["alpha"], len(ch["p"]), nl) for nl in range(1, len(ch["q"]) + 1)]
             ctx = Context(ch["q"], ch["p"], ln, w["alpha"], log_nmax=w["log_nmax"], **kw)
             n = 1 << ln
             key = torch.stack([torch.stack([_residues(qp, n, gen) for _ in range(2)]) for _ in range(ctx.dnum)])
@@ -333,7 +341,10 @@ def write_table(out: str, workloads=TABLE_WORKLOADS, levels=None, reps: int = 10
                     print("tuned %s N=2^%d limbs=%d: %s (%.4f -> %.4f ms)" % (
                         wname, ln, nl, res["setting"], res["default_ms"], res["tuned_ms"]), flush=True)
                 if prev is not None and (levels is not None or nl in tuned_levels):
-                    table[shipped_key(scheme, ln, w["alpha"], len(ch["p"]), nl)] = prev
+                    k = shipped_key(scheme, ln, w["alpha"], len(ch["p"]), nl)
+                    table[k] = prev
+                    if ctx.fused_modup:
+                        unused_chunk.add(k)
             ctx.close()
     if saved is None:
         del os.environ["RF_NO_SHIPPED_TUNING"]
@@ -346,7 +357,12 @@ def write_table(out: str, workloads=TABLE_WORKLOADS, levels=None, reps: int = 10
                 doc = json.load(f)
         except (OSError, ValueError):
             doc = {}
-    doc.setdefault(dkey, {}).update(table)
+    entries = doc.setdefault(dkey, {})
+    for k in searched:  # a level whose default won has no entry
+        prev = entries.pop(k, None)
+        if prev and k in table and k in unused_chunk:
+            table[k] = dict(table[k], modup_chunk=prev["modup_chunk"])
+    entries.update(table)
     with open(out, "w") as f:
         json.dump(doc, f, indent=1, sort_keys=True)
     return table

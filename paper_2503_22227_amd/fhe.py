@@ -111,6 +111,15 @@ class Context:
     # ---------------------------------------------------------------- kernel variants
     TUNING_FIELDS = ("ntt_small_below", "ntt_small_tile", "ntt_small_radix", "modup_chunk", "ntt_fused_small_below")
 
+    @property
+    def fused_modup(self) -> bool:
+        """Whether no key switch of this context launches a ModUp conversion of its own
+        (the N = 2^12 kernels and the transforms' first pass hold it), so that
+        rf_tuning.modup_chunk changes nothing.  BFV products convert from the
+        coefficients and keep the launch; primes below 2^46 are the narrow ones."""
+        narrow = min(self.q + self.p) < 1 << 46
+        return self.log_n == 12 or self.alpha == 1 or (narrow and self.scheme != "bfv")
+
     def set_tuning(self, nlimbs: int, setting: dict) -> None:
         """Kernel variants of level ``nlimbs`` (0: every level); fields not given keep
         their current value (rf_tuning in include/rnsfhe.h)."""
