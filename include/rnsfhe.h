@@ -108,7 +108,10 @@ void rf_ctx_destroy(rf_ctx *ctx);
  *   ntt_small_below  an (I)NTT launch of a two-pass degree (N >= 2^13) with fewer
  *                    4096-residue tiles than this runs the small-tile passes
  *                    (more workgroups, a shorter butterfly chain per thread);
- *                    0 = never.  Default 256 (the CU count).
+ *                    0 = never.  Default 256 (the CU count).  Other launches hold
+ *                    primes below 2^46 in 4096-residue tiles and larger ones in
+ *                    tiles of 1024, or of 4096 in large transforms of larger
+ *                    primes alone.
  *   ntt_small_tile   residues per small tile: 1024 or 2048, or 0 = 2048 when the
  *                    launch has at least half of ntt_small_below tiles, else 1024
  *                    (default 0).
@@ -123,7 +126,9 @@ void rf_ctx_destroy(rf_ctx *ctx);
  *                    fused step (the tensor or automorphism before the first INTT
  *                    pass, the ModDown conversion and tail, the rescale lift and
  *                    tail); their small tiles take ntt_small_tile and 4 residues per
- *                    thread.  Default 0 (always 4096-residue tiles).
+ *                    thread.  Default 0 (never).  With a prime below 2^46 in the
+ *                    context the ModDown conversion has one form, and so has the
+ *                    lift unless most of its targets are larger primes.
  * The settings of every level start at the defaults. */
 typedef struct rf_tuning {
     uint32_t ntt_small_below;
@@ -371,8 +376,8 @@ int rf_batch_create(const rf_batch_item *items, uint32_t n_items, void *workspac
 void rf_batch_destroy(rf_batch *plan);
 /* Tuning knob (the stream-pool size ablation of V-C is the paper's analogue):
  * number of workgroups of launch `stage` (0..12), each walking a contiguous
- * range of work units; 0 = one workgroup per work unit.  Invalidates a
- * captured graph. */
+ * range of work units; 0 = one workgroup per work unit.  A stage whose step
+ * runs inside another's launch has no units.  Invalidates a captured graph. */
 int rf_batch_set_grid(rf_batch *plan, uint32_t stage, uint32_t workgroups);
 /* Limb grouping of the batched ModUp conversion: output limbs per thread,
  * 4, 8 (default) or 16 (modup_chunk of rf_tuning).  Waits for the device to

@@ -46,8 +46,8 @@ struct FpMask {
     }
     bool any() const { return (m[0] | m[1] | m[2] | m[3]) != 0; }
 };
-// The mask of a context with no such prime (the exact schemes' 55-bit chain):
-// its kernels hold the integer code alone.  With both forms in every kernel the
+// The mask of a launch with no such prime (chains of wide primes, and the wide limbs
+// of any other on their own): its kernels hold the integer code alone.  With both forms in every kernel the
 // few-limb passes of that chain took 2.5 % longer (HMult+Relin of 9 limbs at
 // N = 2^15, 115.6 against 112.4 us).
 struct NoFp {
