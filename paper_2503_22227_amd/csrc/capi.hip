@@ -131,7 +131,7 @@ int keyswitch_core(const rf_ctx *c, const uint64_t *d, const uint64_t *evk, uint
     const NttBatch pl = batch(ip + (size_t)nl * N, ip + (size_t)nl * N, ip_stride, ip_stride, c->K, 2, c->L, nullptr,
                               c->order(c->p_order), true);
     if ((rc = launch_inner_product(c, d, ext, evk, ip, nl, s, f))) return rc;
-    if ((rc = launch_intt_cols(c, pl, s, c->d_pc_md, &tn))) return rc;
+    if ((rc = launch_intt_cols(c, pl, s, c->d_pc_md, &tn, c->q_order[nl].n_wide < nl))) return rc;
     return launch_ntt_fwd_moddown(c, conv, ip, out, nl, s, &tn);
 }
 

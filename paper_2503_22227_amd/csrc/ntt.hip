@@ -804,10 +804,11 @@ static int launch_intt_cols_t(const rf_ctx *c, Fp fpm, const NttBatch &b, hipStr
     return RF_OK;
 }
 
-int launch_intt_cols(const rf_ctx *c, const NttBatch &b, hipStream_t s, const PrimeConst *pcs, const rf_tuning *tn) {
+int launch_intt_cols(const rf_ctx *c, const NttBatch &b, hipStream_t s, const PrimeConst *pcs, const rf_tuning *tn,
+                     bool mixed) {
     const rf_tuning &t = tn ? *tn : kDefaultTuning;
     if (!pcs) pcs = c->d_pc;
-    return narrow_in(b) ? launch_intt_cols_t(c, c->fp_mask, b, s, pcs, t)
+    return mixed || narrow_in(b) ? launch_intt_cols_t(c, c->fp_mask, b, s, pcs, t)
                         : launch_intt_cols_t(c, NoFp{}, b, s, pcs, t);
 }
 

@@ -266,8 +266,9 @@ int launch_ntt(const rf_ctx *c, const NttBatch &b, bool forward, hipStream_t s, 
 // First pass alone of the INTT of b's few limbs, into the blocked layout (contexts with narrow primes).
 int launch_intt_rows(const rf_ctx *c, const NttBatch &b, hipStream_t s);
 // Second pass alone of the INTT of b's limbs, in place (two-pass ring degrees).
+// mixed: the kernel of both classes for limbs of wide primes alone too.
 int launch_intt_cols(const rf_ctx *c, const NttBatch &b, hipStream_t s, const PrimeConst *pcs = nullptr,
-                     const rf_tuning *tn = nullptr);
+                     const rf_tuning *tn = nullptr, bool mixed = false);
 // Last pass alone of the forward NTT of b's limbs after launch_modup_cols.
 int launch_ntt_fwd_rows(const rf_ctx *c, const NttBatch &b, hipStream_t s, const rf_tuning *tn);
 // ModUp conversion and the first pass of the extension's NTT in one launch
