@@ -61,11 +61,13 @@ struct WideTiles {};
 // whole chain's order, its wide primes and, gap entries further on, its narrow
 // ones; base is its first limb (both 0 for an order of its own).  A launch has fewer
 // than 65536 limbs, a chain at most kMaxPrimes.  16 bytes: with 24 the kernels'
-// arguments ran into another cache line, 0.3 to 0.9 us a launch.
+// arguments ran into another cache line, 0.3 to 0.9 us a launch.  Bit-fields, not
+// smaller members: scalar loads read whole words, and a batch's kernels, which take
+// this from memory, held a 16-bit n_wide in vector registers (the last row pass of
+// 20 items at N = 2^16 4 spills, 238.6 us against 227.7).
 struct LimbOrder {
-    const uint32_t *ent = nullptr;
-    uint16_t n_wide = 0;
-    uint8_t gap = 0, base = 0;
+    const uint32_t *ent;
+    uint32_t n_wide : 16, gap : 8, base : 8;
 };
 
 // Launch description of a batched (I)NTT over limbs laid out as
@@ -79,7 +81,7 @@ struct NttBatch {
     uint32_t n_polys;
     uint32_t prime_base;
     const uint32_t *pmap;      // device array [per_poly] or nullptr
-    LimbOrder order;           // the same limbs in launch order
+    LimbOrder order{};         // the same limbs in launch order
     bool blocked = false;      // the coefficient side is in the blocked layout (ntt_dev.hpp)
 };
 
