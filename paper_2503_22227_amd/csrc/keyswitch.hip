@@ -95,7 +95,7 @@ constexpr bool kTilePro<IpRowsPro<E>> = true;
 // which come first: (limb, polynomial, tile of 1024 residues) a workgroup; then
 // 256 coefficients of a Q-limb each.  Bound by the keys' and the extension's bytes.
 // At 64 registers the streaming part keeps its 8 waves on a SIMD (the P-limbs' part
-// spills 11), and that pass costs no launch of its own: with it, N = 2^16, 24 + 4
+// spills 6 to 12), and that pass costs no launch of its own: with it, N = 2^16, 24 + 4
 // limbs, alpha = 8: 40.0 us against 35.2 + 6.4; 9 + 4 limbs, alpha = 4: 19.0 against
 // 15.9 + 6.2; N = 2^13, 5 + 4 limbs 5.3 against 3.9 + 4.2.
 template <int A, int B, typename Fp>

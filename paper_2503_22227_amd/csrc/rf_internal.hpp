@@ -47,9 +47,9 @@ struct FpMask {
     bool any() const { return (m[0] | m[1] | m[2] | m[3]) != 0; }
 };
 // The mask of a launch with no such prime (chains of wide primes, and the wide limbs
-// of any other on their own): its kernels hold the integer code alone.  With both forms in every kernel the
-// few-limb passes of that chain took 2.5 % longer (HMult+Relin of 9 limbs at
-// N = 2^15, 115.6 against 112.4 us).
+// of any other on their own): its kernels hold the integer code alone.  With both
+// forms in every kernel the few-limb passes of a chain of 55-bit primes took 2.5 %
+// longer (HMult+Relin of 9 limbs at N = 2^15, 115.6 against 112.4 us).
 struct NoFp {
     __host__ __device__ __forceinline__ static constexpr bool has(uint32_t) { return false; }
 };
@@ -69,6 +69,7 @@ struct LimbOrder {
     const uint32_t *ent;
     uint32_t n_wide : 16, gap : 8, base : 8;
 };
+static_assert(sizeof(LimbOrder) == 16, "a launch's arguments");
 
 // Launch description of a batched (I)NTT over limbs laid out as
 // [n_polys][per_poly][N]; limb i of a polynomial uses prime pmap[i] (or prime_base + i).
